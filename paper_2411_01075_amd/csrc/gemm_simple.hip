@@ -1,6 +1,5 @@
 // Plain LDS-tiled GEMM with fp32 FMA arithmetic, any operand strides, ragged edges allowed.
-// It serves the fp32 workload (whose sizes are launch-bound, not throughput-bound) and
-// shapes the MFMA kernel does not take.  64x64 output tile, 16-deep k-slab, 4x4 per thread.
+// It serves the bf16 shapes the MFMA kernel does not take.  64x64 output tile, 16-deep k-slab, 4x4 per thread.
 #include "kernels.h"
 
 namespace cephalo {
@@ -116,7 +115,6 @@ int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s) {
   return CEPHALO_OK;
 }
 
-template int launch_gemm_simple<float>(const GemmArgs<float>&, hipStream_t);
 template int launch_gemm_simple<bf16>(const GemmArgs<bf16>&, hipStream_t);
 
 }  // namespace cephalo

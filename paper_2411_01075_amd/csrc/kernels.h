@@ -163,7 +163,8 @@ bool gemm_mfma_takes(const GemmArgs<bf16>& a);          // whether launch_gemm_m
 // Number of pieces the weight-gradient GEMM G[M,N] = sum over K tokens would like the token axis cut into (1: none).
 int gemm_grad_splits(int M, int N, int K);
 
-template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);
+template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);   // (bf16 only)
+int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s);  // fp32 operands and arithmetic, any strides
 int launch_gemm_mfma(const GemmArgs<bf16>& a, hipStream_t s);  // bf16 operands, MFMA, fp32 accumulate
 // While one of these is alive on a thread, that thread's GEMM launches choose their tiles for 256 / `kernels` compute
 // units: the caller runs that many kernels side by side on different streams (results do not depend on the choice).

@@ -155,7 +155,7 @@ constexpr float kRopeBase = 10000.0f;   // rotary embedding: angle of pair i at 
 
 // ---- kernel selection ------------------------------------------------------------------
 template <typename T> int gemm(const GemmArgs<T>& a, hipStream_t s);
-template <> int gemm<float>(const GemmArgs<float>& a, hipStream_t s) { return launch_gemm_simple<float>(a, s); }
+template <> int gemm<float>(const GemmArgs<float>& a, hipStream_t s) { return launch_gemm_f32(a, s); }
 template <> int gemm<bf16>(const GemmArgs<bf16>& a, hipStream_t s) { return launch_gemm_mfma(a, s); }
 
 template <typename T> int attn_fwd(const T* qkv, T* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s);

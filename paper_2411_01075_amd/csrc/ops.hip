@@ -65,7 +65,7 @@ extern "C" int cephalo_op_gemm(int32_t dtype, const void* A, int64_t a_rs, int64
   if (dtype == CEPHALO_F32) {
     GemmArgs<float> a = {};
     op_gemm_t<float>(A, a_rs, a_cs, B, b_rs, b_cs, M, N, K, epilogue, C, bias, R, Z, G, scale, accumulate, &a);
-    return launch_gemm_simple<float>(a, s);     // fp32 mode: C and R are fp32 anyway
+    return launch_gemm_f32(a, s);     // fp32 mode: C and R are fp32 anyway
   }
   if (dtype == CEPHALO_BF16) {
     GemmArgs<bf16> a = {};
