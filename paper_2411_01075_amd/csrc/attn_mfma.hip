@@ -156,7 +156,7 @@ struct BlockCoords { int x, y, z; };
 __device__ __forceinline__ BlockCoords block_coords() {
   const int gx = gridDim.x, gy = gridDim.y, n = gx * gy * gridDim.z;
   int l = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  if (n % 8 == 0) l = (l % 8) * (n / 8) + l / 8;
+  l = (l & 7) * (n >> 3) + min(l & 7, n & 7) + (l >> 3);      // (the first n % 8 runs are one longer)
   // (the divisions run on the vector unit; readfirstlane tells the compiler that the results are uniform)
   return {__builtin_amdgcn_readfirstlane(l % gx), __builtin_amdgcn_readfirstlane((l / gx) % gy), __builtin_amdgcn_readfirstlane(l / (gx * gy))};
 }

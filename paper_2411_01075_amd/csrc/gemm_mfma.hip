@@ -130,12 +130,12 @@ struct OperandTile {
 //
 // Everything here is straight-line code.  What the epilogue reads from memory is fetched for a whole staged block at
 // once (`fetch`, into a register set), the bias once per tile; then every row's result is formed, then every row is
-// stored.  All accesses go through buffer descriptors over the wavefront's 64 rows, whose range check drops what lies
+// stored.  All accesses go through buffer descriptors over the wavefront's 32 * BLOCKS rows, whose range check drops what lies
 // past the matrix (rows past M; columns past N get an out-of-range offset), so no row needs a branch.  Written row by
 // row as load, use, store under a bounds test, every row waited for its loads behind the previous row's stores: one
 // memory round trip per row, 16 in a row per tile, 12 000 to 25 000 clocks of epilogue on a tile whose main loop takes
 // 83 000 at K = 2048.  (The compiler counts memory operations in order and gives up at branches.)
-template <int EPI, int WTN>
+template <int EPI, int WTN, int BLOCKS>
 struct StagedRows {
   static constexpr int SP = WTN + 4, LPR = WTN / 8, RPS = 64 / LPR, PASSES = (32 + RPS - 1) / RPS;
   static constexpr bool BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_DERIV || EPI == EPI_BIAS_RESID;
@@ -150,7 +150,7 @@ struct StagedRows {
   __amdgpu_buffer_rsrc_t out16, out32, zed, res;     // C, Cf, Z, R or Rf: the wavefront's rows of each
   unsigned res_es, res_second;                       // residual: bytes per element, offset of its second vector
 
-  // mrow0, ncol0: matrix coordinates of the wavefront tile's corner (64 rows: two staged blocks)
+  // mrow0, ncol0: matrix coordinates of the wavefront tile's corner
   __device__ __forceinline__ void init(const GemmArgs<bf16>& a, int mrow0, int ncol0, int ldc_) {
     mrow0 = __builtin_amdgcn_readfirstlane(mrow0);       // (the same in every lane: the descriptors must be scalars)
     const int lane = threadIdx.x & 63;
@@ -160,7 +160,7 @@ struct StagedRows {
     ldc = ldc_;
     mrow = mrow0;
     col_off = n < a.N ? 0u : kOob;
-    const int rows = max(0, min(a.M - mrow0, 64));
+    const int rows = max(0, min(a.M - mrow0, 32 * BLOCKS));
     const int64_t base = (int64_t)mrow0 * ldc;
     const unsigned elems = (unsigned)rows * (unsigned)ldc;
     out16 = make_rsrc(a.C ? a.C + base : nullptr, a.C ? elems * 2 : 0);
@@ -311,6 +311,56 @@ struct StagedRows {
 // s_waitcnt operand that waits for vmcnt(n) only (6-bit counter split over two fields; the other counters at their maxima)
 constexpr int vmcnt_only(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
+// The epilogue of every output but the fp32 gradient: each wavefront passes its tile through its own LDS region, 32 rows at a
+// time, to turn the accumulator layout into row-major 16-byte vectors; bias, residual and pre-activation are then read, and the
+// results written, as coalesced 16-byte accesses.
+template <int EPI, int WGM, int WGN, int BM, int BN, int MI, int NI>
+__device__ __forceinline__ void finish_tile(const GemmArgs<bf16>& a, f32x4 (&acc)[MI][NI], LDS_AS char* smem, int m0, int n0) {
+  constexpr int NW = WGM * WGN, WTM = BM / WGM, WTN = BN / WGN;
+  static_assert(MI * 16 == WTM && NI * 16 == WTN, "the wavefront's accumulators");
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wm = (wave / WGN) * WTM, wn = (wave % WGN) * WTN;
+  const int ldc = a.ldc ? a.ldc : a.N;
+  constexpr int SP = WTN + 4;
+  static_assert(NW * 32 * SP * 4 <= 160 * 1024, "staging regions must fit in LDS");
+  LDS_AS float* stage = (LDS_AS float*)(smem + wave * (32 * SP * 4));
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0) & 0xF0FF);     // the last (unused) slab loads and fragment reads are over,
+  static_assert(MI == 2 || MI == 4, "one or two staged blocks of 32 rows");
+  typedef StagedRows<EPI, WTN, MI / 2> Rows;
+  Rows rows;
+  rows.init(a, m0 + wm, n0 + wn, ldc);
+  typedef typename Rows::Set Operands;
+  Operands set0, set1;                                    // (named, not indexed: a choice of address keeps them out of registers)
+  rows.fetch(a, set0, 0);                                 // (the first block's operands fly across the barrier)
+  __syncthreads();                                        // in every wavefront, before the stages are overwritten
+  // The second block's operands are asked for before the first block is written where one 16-byte vector per row is
+  // all (two register sets); with two vectors per row the accumulators still held leave room for one set only, and the
+  // second block's loads follow the first block's stores.
+  constexpr bool TWO_SETS = MI == 4 && Rows::NX < 2;
+  auto stage_block = [&](int i2) {
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+        *reinterpret_cast<LDS_AS f32x4*>(stage + (16 * ii + (lane & 15)) * SP + 16 * j + 4 * (lane >> 4)) = acc[2 * i2 + ii][j];
+  };
+  if constexpr (TWO_SETS) rows.fetch(a, set1, 1);
+  stage_block(0);
+  rows.write(a, stage, set0, 0);
+  if constexpr (MI == 4) {
+    if constexpr (!TWO_SETS) rows.fetch(a, set0, 1);
+    stage_block(1);
+    rows.write(a, stage, TWO_SETS ? set1 : set0, 1);
+  }
+}
+
+// Blocks are dealt round-robin to the 8 XCDs: block `pid` of `total` becomes a place in an order in which each XCD has one contiguous
+// run (the first total % 8 of them one longer).
+__device__ __forceinline__ int xcd_run(int pid, int total) {
+  const int x = pid & 7;
+  return x * (total >> 3) + min(x, total & 7) + (pid >> 3);
+}
+
 // The kernel.
 //
 // Operand fragment (16 rows x 32 k): lane l holds row l%16, k-values 8*(l/16) .. +7 -- one 16-byte LDS read of a
@@ -351,7 +401,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
   const int total = tiles_m * tiles_n;
   const int split = blockIdx.x / total;
   int pid = blockIdx.x % total;
-  if (total % 8 == 0) pid = (pid % 8) * (total / 8) + pid / 8;
+  pid = xcd_run(pid, total);
   constexpr int GROUP = 4;
   const int per_group = GROUP * tiles_n;
   const int g0 = (pid / per_group) * GROUP;
@@ -503,7 +553,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
   int next_sum = 0x7fffffff;
   f32x4 rsum = {0.f, 0.f, 0.f, 0.f};
   if constexpr (EPI == EPI_GRAD) {
-    static_assert(EPI != EPI_GRAD || MI == 4, "four row fragments share the accumulator");
+    static_assert(EPI != EPI_GRAD || MI <= 4, "up to four row fragments share the accumulator");
     if (a.rowsum_part) next_sum = ((owner - kb0) % owners + owners) % owners;
   }
   auto ones_for = [&](int i, int row4) -> bf16x8 {         // row4: (this lane's operand row) / 4
@@ -638,10 +688,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
 
   __builtin_amdgcn_s_setprio(0);
   // Epilogue
-  if (EPI == EPI_GRAD) {
+  if constexpr (EPI == EPI_GRAD) {
     if (a.rowsum_part) {
       const int m = m0 + wm + lane;
-      if (m < a.M) a.rowsum_part[((int64_t)split * owners + owner) * a.M + m] = rsum[0];
+      if (lane < 16 * MI && m < a.M) a.rowsum_part[((int64_t)split * owners + owner) * a.M + m] = rsum[0];
     }
     const bool partial = a.splits > 1;
     float* const gbase = partial ? a.part + (int64_t)split * a.M * a.N : a.G;
@@ -661,40 +711,110 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
         *gp = v;
       }
     }
-    return;
+  } else {
+    finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
   }
-  // Other outputs: each wavefront passes its tile through its own LDS region, 32 rows at a time, to turn the
-  // accumulator layout into row-major 16-byte vectors; bias, residual and pre-activation are then read, and the
-  // results written, as coalesced 16-byte accesses.
-  const int ldc = a.ldc ? a.ldc : a.N;
-  constexpr int SP = WTN + 4;
-  static_assert(NW * 32 * SP * 4 <= 160 * 1024, "staging regions must fit in LDS");
-  LDS_AS float* stage = (LDS_AS float*)(smem + wave * (32 * SP * 4));
-  __builtin_amdgcn_s_waitcnt(vmcnt_only(0) & 0xF0FF);     // the last (unused) slab loads and fragment reads are over,
-  StagedRows<EPI, WTN> rows;
-  rows.init(a, m0 + wm, n0 + wn, ldc);
-  typedef typename StagedRows<EPI, WTN>::Set Operands;
-  Operands set0, set1;                                    // (named, not indexed: a choice of address keeps them out of registers)
-  rows.fetch(a, set0, 0);                                 // (the first block's operands fly across the barrier)
-  __syncthreads();                                        // in every wavefront, before the stages are overwritten
-  static_assert(MI == 4, "two staged blocks of 32 rows");
-  // The second block's operands are asked for before the first block is written where one 16-byte vector per row is
-  // all (two register sets); with two vectors per row the accumulators still held leave room for one set only, and the
-  // second block's loads follow the first block's stores.
-  constexpr bool TWO_SETS = StagedRows<EPI, WTN>::NX < 2;
-  auto stage_block = [&](int i2) {
+}
+
+// The k-contiguous kernel for outputs with few tiles (BM x BN up to 256 x 128), same products in the same order.
+//
+// A small tile leaves a wavefront 4 to 16 products per k-step, so the kernel above, which reads the fragments of a k-step during the
+// step before, waits for an LDS round trip twice in every slab, and with one block per compute unit nobody covers the wait
+// (1024 x 1024 x 4096: 64 tiles of 128 x 128, 48 us, 1600 clocks a slab against 512 of products).  Here the fragments of a whole slab
+// are held in registers, and the next slab's are read while this one's are multiplied: a slab costs one barrier and the larger of
+// its reads and its products.  NS stages of LDS, NS slabs of global loads in flight.
+template <int BM, int BN, int WGM, int WGN, int EPI, int NS>
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int) {
+  constexpr int NW = WGM * WGN;
+  typedef OperandTile<BM, true, NW> TA;
+  typedef OperandTile<BN, true, NW> TB;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  constexpr int MI = WTM / 16, NI = WTN / 16;
+  constexpr int STAGE = TA::BYTES + TB::BYTES;
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  LDS_AS char* smem = (LDS_AS char*)smem_raw;
+
+  // tile order: as above
+  const int total = tiles_m * tiles_n;
+  int pid = blockIdx.x;
+  pid = xcd_run(pid, total);
+  constexpr int GROUP = 4;
+  const int per_group = GROUP * tiles_n;
+  const int g0 = (pid / per_group) * GROUP;
+  const int gsz = min(tiles_m - g0, GROUP);
+  const int tile_m = g0 + (pid % per_group) % gsz, tile_n = (pid % per_group) / gsz;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wm = (wave / WGN) * WTM, wn = (wave % WGN) * WTN;
+
+  f32x4 acc[MI][NI];
 #pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
-        *reinterpret_cast<LDS_AS f32x4*>(stage + (16 * ii + (lane & 15)) * SP + 16 * j + 4 * (lane >> 4)) = acc[2 * i2 + ii][j];
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const i32x4 ra_rsrc = make_rsrc_words(a.A, (unsigned)(2 * (int64_t)a.M * a.a_rs)), rb_rsrc = make_rsrc_words(a.B, (unsigned)(2 * (int64_t)a.N * a.b_rs));
+  unsigned offa[TA::PER_WAVE], offb[TB::PER_WAVE];
+  TA::init_offsets(a.a_rs, 1, m0, a.M, a.K, offa);
+  TB::init_offsets(a.b_rs, 1, n0, a.N, a.K, offb);
+  const int nk = (a.K + BK - 1) / BK;
+
+  // fragment addresses of k-contiguous tiles: see above
+  const int fa0 = (wm + (lane & 15)) * TA::PITCH + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
+  const int fb0 = TA::BYTES + (wn + (lane & 15)) * TB::PITCH + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
+  struct Frags { bf16x8 a[2][MI], b[2][NI]; };
+  constexpr int READS = 2 * (MI + NI);
+  auto read_one = [&](Frags& f, const LDS_AS char* stage, int q) {      // the q-th fragment read of a slab, in the order the products want them
+    const int ks = q / (MI + NI), e = q % (MI + NI);
+    if (e < MI) f.a[ks][e] = *reinterpret_cast<const LDS_AS bf16x8*>(stage + (fa0 ^ (ks << 6)) + e * 16 * TA::PITCH);
+    else f.b[ks][e - MI] = *reinterpret_cast<const LDS_AS bf16x8*>(stage + (fb0 ^ (ks << 6)) + (e - MI) * 16 * TB::PITCH);
   };
-  if constexpr (TWO_SETS) rows.fetch(a, set1, 1);
-  stage_block(0);
-  rows.write(a, stage, set0, 0);
-  if constexpr (!TWO_SETS) rows.fetch(a, set0, 1);
-  stage_block(1);
-  rows.write(a, stage, TWO_SETS ? set1 : set0, 1);
+  constexpr int LOADS = TA::PER_WAVE + TB::PER_WAVE;
+  static_assert((NS - 1) * LOADS < 64, "the outstanding loads must fit the counter");
+  auto load_one = [&](int k0, LDS_AS char* stage, int q) {
+    if (q < TA::PER_WAVE) TA::load_one(ra_rsrc, offa, k0, a.K, stage, q);
+    else TB::load_one(rb_rsrc, offb, k0, a.K, stage + TA::BYTES, q - TA::PER_WAVE);
+  };
+#pragma unroll
+  for (int p = 0; p < NS; ++p) {
+    if (p > 0) { TA::advance(offa, 2 * BK); TB::advance(offb, 2 * BK); }
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) load_one(p * BK, smem + p * STAGE, q);
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 1) * LOADS));
+  __syncthreads();
+  Frags f0, f1;
+#pragma unroll
+  for (int q = 0; q < READS; ++q) read_one(f0, smem, q);
+
+  int st = 0;                                             // slab kt's stage
+  auto slab = [&](int kt, Frags& cur, Frags& nxt) {
+    const int st1 = st + 1 == NS ? 0 : st + 1;
+    // this slab's fragments are in registers, so its stage is free behind the barrier; the next slab's loads have landed
+    __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 2) * LOADS) & 0xF0FF);     // ... and lgkmcnt(0)
+    __syncthreads();
+    TA::advance(offa, 2 * BK);
+    TB::advance(offb, 2 * BK);
+    __builtin_amdgcn_sched_barrier(0);
+    // the products in their order, a share of the next slab's reads and of the loads of slab kt + NS between them
+    constexpr int STEPS = 2 * NI;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+      for (int q = s * READS / STEPS; q < (s + 1) * READS / STEPS; ++q) read_one(nxt, smem + st1 * STAGE, q);
+#pragma unroll
+      for (int q = s * LOADS / STEPS; q < (s + 1) * LOADS / STEPS; ++q) load_one((kt + NS) * BK, smem + st * STAGE, q);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) acc[i][s % NI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[s / NI][s % NI], cur.a[s / NI][i], acc[i][s % NI], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    st = st1;
+  };
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) { slab(kt, f0, f1); slab(kt + 1, f1, f0); }
+  if (kt < nk) slab(kt, f0, f1);
+
+  finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
 }
 
 // G = (accumulate ? G : 0) + scale * (part[0] + part[1] + ... ) in split order, 4 floats per thread
@@ -760,10 +880,64 @@ int launch_cfg(const GemmArgs<bf16>& a, hipStream_t s) {
   return launch_kernel<gemm_mfma_kernel<BM, BN, WGM, WGN, AK, BKF, EPI, NS, PF, A3>>(a, BM, BN, WGN, 64 * WGM * WGN, lds, s);
 }
 
+template <int BM, int BN, int WGM, int WGN, int EPI, int NS>
+int launch_ring(const GemmArgs<bf16>& a, hipStream_t s) {
+  constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, staging = (size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4;
+  static_assert(stages <= 160 * 1024 && staging <= 160 * 1024, "the stages and the staged rows must fit in LDS");
+  return launch_kernel<gemm_ring_kernel<BM, BN, WGM, WGN, EPI, NS>>(a, BM, BN, WGN, 64 * WGM * WGN, std::max(stages, staging), s);
+}
+
 thread_local int side_by_side = 1;     // kernels the caller runs at once (GemmSideBySide)
+
+// Tile choice of the k-contiguous products: the tile whose estimated time is least.  Fitted per configuration to 240 measured
+// launches (outputs of 256 x 256 to 4096 x 16384, contractions of 256 to 16384, one launch at a time and two side by side, random
+// data): the time of a slab of 64 k-values with few blocks on the chip (`alone`: latency and LDS), with a block on every compute unit (`one`),
+// and in a launch of several rounds of blocks (`more`: L2 traffic and power), the fixed time of a launch (prologue, epilogue, about 2 us
+// of launch); `blocks`: how many a compute unit holds.  Over those launches the choice is on average 1.1 % slower than the fastest tile.
+// Examples (us, former choice -> this one): 1024 x 1024 x 4096 48.0 (128 x 128, four wavefronts) -> 19.3 (64 x 64); 2048 x 1600 x 6400
+// 73.6 (the same) -> 44.0 (128 x 128); 2048 x 2560 x 10240 134.5 (256 x 128) -> 114.1 (128 x 192); two at a time 4096 x 2048 x 8192 195
+// (256 x 256) as before.  The results do not depend on the choice: every tile adds the products of an output in the same order.
+struct TileCost { int bm, bn, blocks; double alone, one, more, fixed; };
+constexpr TileCost kTiles[] = {
+  {256, 256, 1, 0.56, 1.09, 1.16, 6.7}, {256, 192, 1, 0.46, 0.83, 0.85, 8.3}, {256, 128, 1, 0.39, 0.68, 0.80, 5.3}, {128, 192, 1, 0.42, 0.53, 0.62, 6.0},
+  {128, 128, 1, 0.38, 0.41, 0.47, 4.1}, {128, 64, 2, 0.36, 0.32, 0.31, 4.3},  {64, 64, 2, 0.30, 0.21, 0.195, 3.3},
+};
+double tile_us(const TileCost& t, int M, int N, int K, int kernels) {
+  const double cus = 256.0 / kernels;
+  const double blocks = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), nk = (K + BK - 1) / BK;
+  const double rounds = (double)(int64_t)(blocks / (cus * t.blocks)), rest = blocks - rounds * cus * t.blocks;
+  const double full = blocks > cus * t.blocks ? t.more : t.one;
+  double us = t.fixed + rounds * t.blocks * nk * full + std::max(0.0, rounds - 1) * (t.fixed - 2.0);
+  if (rest > 0) {
+    const double per_cu = rest / cus, most = (double)(int64_t)((rest + cus - 1) / cus);
+    us += nk * std::max(t.alone + (full - t.alone) * std::min(1.0, per_cu), most * full);
+    if (rounds > 0) us += t.fixed - 2.0;
+  }
+  return us;
+}
+
+template <int EPI>
+int launch_rows(const GemmArgs<bf16>& a, hipStream_t s) {
+  int best = 0;
+  double least = 1e30;
+  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+    const double us = tile_us(kTiles[c], a.M, a.N, a.K, side_by_side);
+    if (us < least) { least = us; best = c; }
+  }
+  switch (best) {
+    case 0: return launch_cfg<256, 256, 4, 2, true, true, EPI>(a, s);
+    case 1: return launch_cfg<256, 192, 4, 2, true, true, EPI>(a, s);
+    case 2: return launch_ring<256, 128, 4, 2, EPI, 3>(a, s);
+    case 3: return launch_ring<128, 192, 2, 4, EPI, 3>(a, s);
+    case 4: return launch_ring<128, 128, 4, 2, EPI, 4>(a, s);
+    case 5: return launch_ring<128, 64, 4, 2, EPI, 3>(a, s);
+    default: return launch_ring<64, 64, 2, 2, EPI, 5>(a, s);
+  }
+}
 
 template <bool AK, bool BKF, int EPI>
 int launch_tiles(const GemmArgs<bf16>& a, hipStream_t s) {
+  if constexpr (AK && BKF && EPI != EPI_GRAD) return launch_rows<EPI>(a, s);
   // Tile choice: the score of a configuration is the fraction of the last round of blocks that the 256 compute
   // units fill, times the rate its main loop reaches relative to the 256 x 256 tile (measured: bigger tiles
   // move fewer LDS and L2 bytes per MFMA).
