@@ -855,8 +855,12 @@ int launch_kernel(const GemmArgs<bf16>& a, int BMv, int BNv, int wgn, int thread
   KERN<<<tm * tn * splits, threads, lds, s>>>(k, tm, tn, per);
   CEPHALO_CHECK_LAUNCH("gemm_mfma");
   if (rowsum) {
-    const int rc = launch_reduce_partials(a.rowsum_part, pieces, a.M, a.rowsum, a.scale, a.accumulate, nullptr, 0, s);
-    if (rc != CEPHALO_OK) return rc;
+    if (a.rowsum_pieces) {
+      *a.rowsum_pieces = pieces;
+    } else {
+      const int rc = launch_reduce_partials(a.rowsum_part, pieces, a.M, a.rowsum, a.scale, a.accumulate, s);
+      if (rc != CEPHALO_OK) return rc;
+    }
   }
   if (splits > 1) {
     const int64_t mn4 = (int64_t)a.M * a.N / 4;
@@ -992,9 +996,9 @@ GemmSideBySide::~GemmSideBySide() { side_by_side = before; }
 void GemmSideBySide::now(int kernels) { side_by_side = kernels < 1 ? 1 : kernels; }
 int gemm_set_side_by_side(int kernels) { const int was = side_by_side; side_by_side = kernels < 1 ? 1 : kernels; return was; }
 
-size_t gemm_rowsum_part_bytes(int M, int N) {
-  // the most splits of gemm_grad_splits, the narrowest tile (128 columns) and its two wavefront columns
-  return (size_t)8 * ((N + 127) / 128) * 2 * (size_t)M * sizeof(float);
+size_t gemm_rowsum_part_bytes(int M, int N, int splits) {
+  // (the most splits of gemm_grad_splits,) the narrowest tile (128 columns) and its two wavefront columns
+  return (size_t)splits * ((N + 127) / 128) * 2 * (size_t)M * sizeof(float);
 }
 
 namespace {

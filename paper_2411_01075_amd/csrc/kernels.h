@@ -156,8 +156,9 @@ struct GemmArgs {
   float* rowsum;
   float* rowsum_part;
   size_t rowsum_part_bytes;
+  int* rowsum_pieces;   // if set, the pieces [*rowsum_pieces][M] are left in rowsum_part for the caller to add (with other sums, in one launch)
 };
-size_t gemm_rowsum_part_bytes(int M, int N);            // upper bound over tile shapes and splits
+size_t gemm_rowsum_part_bytes(int M, int N, int splits = 8);   // upper bound over tile shapes (and splits)
 bool gemm_mfma_takes(const GemmArgs<bf16>& a);          // whether launch_gemm_mfma runs this problem on its MFMA kernels
 
 // Number of pieces the weight-gradient GEMM G[M,N] = sum over K tokens would like the token axis cut into (1: none).
@@ -187,7 +188,7 @@ int launch_ln_fwd(const float* x, const T* gamma, const T* beta, T* u, float* me
 // out = resid + LN-backward(du), all fp32 (resid may be null: no residual); out_lowp, if not null, receives the same
 // values in the activation type (the copy a following GEMM reads).  Each block of rows also writes its partial sums
 // of dgamma (du * xhat) and dbeta (du) to part_g / part_b ([ln_bwd_blocks(rows)][H] fp32 each);
-// launch_reduce_partials folds any number of such partial rows into a flat-gradient slice:
+// launch_reduce_partials / _jobs fold any number of such partial rows into a flat-gradient slice:
 //   g = (accumulate ? g : 0) + scale * sum over chunks.
 // part_s, if not null (LayerNorm form only): the blocks' column sums of `out`, laid out like part_g.
 template <typename T>
@@ -204,23 +205,29 @@ int launch_rotary_table(float* tab, int S, int d, float base, hipStream_t s);
 template <typename T> int launch_rotary(T* qkv, const float* tab, int rows, int S, int H, int heads, int inverse, hipStream_t s);
 // Gated SiLU: gu [rows, 2F] = [gate | up], h [rows, F] = silu(gate) * up; backward dgu from dh and gu.
 template <typename T> int launch_swiglu_fwd(const T* gu, T* h, int64_t rows, int F, hipStream_t s);
-// tmp (reduce_tmp_bytes(nchunks, N) bytes, may be null) lets a long reduction run in two parallel stages.
-int launch_reduce_partials(const float* partials, int nchunks, int N, float* g, float scale, int accumulate,
-                           float* tmp, size_t tmp_bytes, hipStream_t s);
-size_t reduce_tmp_bytes(int nchunks, int N);
+int launch_reduce_partials(const float* partials, int nchunks, int N, float* g, float scale, int accumulate, hipStream_t s);
+// several such reductions in one launch: part [nchunks][N], N a multiple of 4, 16-byte aligned pointers
+struct ReduceJob { const float* part; int nchunks; int N; float* out; };
+constexpr int kMaxReduceJobs = 8;
+int launch_reduce_jobs(const ReduceJob* jobs, int n, float scale, int accumulate, hipStream_t s);
 
 // g[n] = (accumulate ? g[n] : 0) + scale * sum_t dY[t][n]   (bias gradient), dY [rows, N]
 template <typename T>
 int launch_colsum(const T* dY, float* partials, size_t partial_bytes, float* g, float scale,
                   int accumulate, int rows, int N, hipStream_t s);
 size_t colsum_partial_bytes(int rows, int N);
+// lowp = bf16(x) for x [rows, N] fp32 and, on the way, the column sums of x in cast_colsum_chunks(rows) partial rows
+int launch_cast_colsum(const float* x, bf16* lowp, float* partials, size_t partial_bytes, int rows, int N, hipStream_t s);
+int cast_colsum_chunks(int rows);
 
 // dst[i] = bf16(src[i]), i in [0, n)
 int launch_cast_bf16(bf16* dst, const float* src, int64_t n, hipStream_t s);
 
-// out[c][r] = in[r][c] for a row-major bf16 matrix [rows, cols]; out has row pitch out_pitch (0: rows) and its
-// columns [rows, out_pitch) are zero-filled; cols and the pitch are multiples of 8
-int launch_transpose_bf16(const bf16* in, bf16* out, int rows, int cols, hipStream_t s, int out_pitch = 0);
+// out[c][r] = in[r][c] for a row-major bf16 matrix [rows, cols]; out has row pitch `pitch` (0: rows) and its
+// columns [rows, pitch) are zero-filled; cols and the pitch are multiples of 8
+struct TransposeJob { const bf16* in; bf16* out; int rows, cols, pitch; };
+constexpr int kMaxTransposes = 4;
+int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s);      // several such matrices in one launch
 
 // ---------------------------------------------------------------------------------------
 // Attention on the packed projection qkv [m*S, 3H] (Q | K | V column blocks, head a in

@@ -228,7 +228,8 @@ GemmArgs<T> linear_wgrad(const T* dY, const T* X, int Tn, int N, int K, float* G
 // `colsums` (optional): where the column sums of dY, the bias gradient of the same projection, are wanted with the same
 // scale / acc.  The bf16 GEMM sums them beside the products when it can (one piece, operands that fit its MFMA kernels)
 // and then sets colsums->done; otherwise the caller runs the column-sum kernel.
-struct ColsumsBeside { float* g; float* part; size_t part_bytes; bool done; };
+// defer: the GEMM leaves its pieces in `part` (`pieces` rows) and the caller adds them.
+struct ColsumsBeside { float* g; float* part; size_t part_bytes; bool done; bool defer; int pieces; };
 template <typename T>
 int wgrad(const T* dY, const T* X, int Tn, int N, int K, float* G, float scale, int acc, float* part, hipStream_t s, int ldy = 0,
           ColsumsBeside* colsums = nullptr);
@@ -254,8 +255,9 @@ int wgrad<bf16>(const bf16* dY, const bf16* X, int Tn, int N, int K, float* G, f
     a.splits = part ? gemm_grad_splits(N, K, tc) : 1;     // `part` was sized with the same rule for the whole token axis
     a.part = part;
     if (tc != Tn) a.splits = 1;
-    if (colsums && tc == Tn && colsums->part && colsums->part_bytes >= gemm_rowsum_part_bytes(N, K) && gemm_mfma_takes(a)) {
+    if (colsums && tc == Tn && colsums->part && colsums->part_bytes >= gemm_rowsum_part_bytes(N, K, a.splits) && gemm_mfma_takes(a)) {
       a.rowsum = colsums->g; a.rowsum_part = colsums->part; a.rowsum_part_bytes = colsums->part_bytes;
+      if (colsums->defer) a.rowsum_pieces = &colsums->pieces;
       colsums->done = true;
     }
     TRY(gemm<bf16>(a, s));
@@ -313,6 +315,11 @@ Work<T> work_at(void* base, const ScratchLayout& W, const cephalo_layer_desc& d,
 }
 
 // ---- forward of one micro-batch ----------------------------------------------------------------
+// (sv.rot of a Llama-style layer holds the rotary table: make_rotary, once for all micro-batches)
+template <typename T>
+int make_rotary(const cephalo_layer_desc& d, const Saved<T>& sv, hipStream_t s) {
+  return is_llama(d) ? launch_rotary_table(sv.rot, d.seq, d.hidden / d.heads, kRopeBase, s) : CEPHALO_OK;
+}
 template <typename T>
 int layer_fwd_t(const cephalo_layer_desc& d, const T* P, const float* x, float* y, int m, const Saved<T>& sv, hipStream_t s) {
   const ParamOffsets o = param_offsets(d);
@@ -321,7 +328,6 @@ int layer_fwd_t(const cephalo_layer_desc& d, const T* P, const float* x, float* 
     // u = RMS1(x); qkv = u Wqkv^T; rotary on q, k; attention; x1 = x + O Wo^T; u2 = RMS2(x1); [g | up] = u2 Wgu^T;
     // h = silu(g) up; y = x1 + h Wdown^T
     TRY(launch_ln_fwd<T>(x, P + o.ln1_g, (const T*)nullptr, sv.u, sv.mean1, sv.rstd1, Tn, H, d.ln_eps, s, true));
-    TRY(launch_rotary_table(sv.rot, d.seq, H / d.heads, kRopeBase, s));   // (every micro-batch writes the same values)
     {
       GemmArgs<T> a = linear_fwd<T>(sv.u, P + o.w_qkv, Tn, 3 * H, H);
       a.epi = EPI_ROPE; a.C = sv.qkv;       // q and k leave the GEMM already rotated (one rounding, of the rotated value)
@@ -380,10 +386,21 @@ template <> inline const float* lowp_of<float>(const float* f, const float*) { r
 template <> inline const bf16* lowp_of<bf16>(const float*, const bf16* l) { return l; }
 template <typename T> T* lowp_out(T* l) { return std::is_same<T, float>::value ? nullptr : l; }   // nothing extra to write in fp32 mode
 
-// dst = T(src) for n elements when T is not float (used where the caller hands dy in fp32)
-template <typename T> int make_lowp(T* dst, const float* src, int64_t n, hipStream_t s);
-template <> inline int make_lowp<float>(float*, const float*, int64_t, hipStream_t) { return CEPHALO_OK; }
-template <> inline int make_lowp<bf16>(bf16* dst, const float* src, int64_t n, hipStream_t s) { return launch_cast_bf16(dst, src, n, s); }
+// The caller's dy [tokens, H], handed over in fp32: its copy in T (when T is not float) and, for a layer with biases, partial rows of
+// its column sums, in `sums` for the parameter pass.
+struct DySums { const float* part; int chunks; };
+template <typename T> int take_dy(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<T>& w, DySums* sums, hipStream_t s);
+template <> inline int take_dy<float>(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<float>&, DySums* sums, hipStream_t) {
+  *sums = {is_llama(d) ? nullptr : dy, is_llama(d) ? 0 : tokens};          // (a row is a partial sum of one token)
+  return CEPHALO_OK;
+}
+template <> inline int take_dy<bf16>(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<bf16>& w, DySums* sums, hipStream_t s) {
+  *sums = {nullptr, 0};
+  if (is_llama(d)) return launch_cast_bf16(w.dyl, dy, (int64_t)tokens * d.hidden, s);
+  TRY(launch_cast_colsum(dy, w.dyl, w.col_part, w.col_part_bytes, tokens, d.hidden, s));
+  *sums = {w.col_part, cast_colsum_chunks(tokens)};
+  return CEPHALO_OK;
+}
 
 // Input-gradient contraction dX = dY W of the linear layer whose weight sits at flat offset `off`.  In bf16 mode it
 // reads the transposed copy made by prepare_dgrad_weights (so both MFMA operands come from 16-byte LDS reads, the
@@ -401,11 +418,9 @@ template <> inline int prepare_dgrad_weights<float>(const cephalo_layer_desc&, c
 template <> inline int prepare_dgrad_weights<bf16>(const cephalo_layer_desc& d, const bf16* P, bf16* wT, hipStream_t s) {
   const ParamOffsets o = param_offsets(d);
   const int H = d.hidden, F = d.mlp;
-  TRY(launch_transpose_bf16(P + o.w_qkv, wT + o.w_qkv, 3 * H, H, s));
-  TRY(launch_transpose_bf16(P + o.w_o, wT + o.w_o, H, H, s));
-  TRY(launch_transpose_bf16(P + o.w_fc1, wT + o.w_fc1, (int)ff1_width(d), H, s));
-  TRY(launch_transpose_bf16(P + o.w_fc2, wT + o.w_fc2, H, F, s));
-  return CEPHALO_OK;
+  const TransposeJob jobs[] = {{P + o.w_qkv, wT + o.w_qkv, 3 * H, H, 0}, {P + o.w_o, wT + o.w_o, H, H, 0},
+                               {P + o.w_fc1, wT + o.w_fc1, (int)ff1_width(d), H, 0}, {P + o.w_fc2, wT + o.w_fc2, H, F, 0}};
+  return launch_transposes(jobs, 4, s);
 }
 
 // ---- backward, data path of one micro-batch: dx and the dY operands (dz, dx1, dqkv) of the weight gradients --------
@@ -474,52 +489,92 @@ int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, co
 // happens inside the fp32 MFMA accumulators and each gradient element is written exactly once.  Bias gradients of the
 // two residual-stream projections are column sums of the fp32 gradients of the stream: of dx1 (out-projection), which
 // the backward of the second LayerNorm has summed block by block as it wrote it, and of dy (second feed-forward
-// projection), summed here unless the caller passes none.  A caller whose dy was the dx of the layer above (a stack)
-// passes null and gives that layer `b_fc2_below` instead: where the sums of its dx go, with the same scale / acc.
+// projection), whose partial rows take_dy has left in dy_sums.  A caller whose dy was the dx of the layer above (a stack)
+// passes none and gives that layer `b_fc2_below` instead: where the sums of its dx go, with the same scale / acc.
+//
+// The sums of partial rows are collected and added in one launch: with a second stream the norms' ones at once, beside
+// the GEMMs, and the GEMMs' own column sums at the end; on one stream all of them at the end.
+struct SumList {
+  ReduceJob job[kMaxReduceJobs];
+  int n = 0;
+  float scale;
+  int acc;
+  void add(const float* part, int chunks, int N, float* out) { job[n++] = ReduceJob{part, chunks, N, out}; }
+  int flush(hipStream_t s) { const int k = n; n = 0; return launch_reduce_jobs(job, k, scale, acc, s); }
+};
+// column sums of X [tokens, N] that no GEMM has formed: a short fp32 matrix is its own partial rows, others take the column-sum kernel
+constexpr int kRowsAsPartials = 4096;
 template <typename T>
-int layer_bwd_params_t(const cephalo_layer_desc& d, const float* dy, const T* dyl, int tokens, int ln_chunks,
+int add_colsum(SumList& list, const T* X, int tokens, int N, float* out, const Work<T>& w, hipStream_t s, hipStream_t s2) {
+  if (std::is_same<T, float>::value && tokens <= kRowsAsPartials) {
+    list.add(reinterpret_cast<const float*>(X), tokens, N, out);
+    return CEPHALO_OK;
+  }
+  if (s2 == s) TRY(list.flush(s));      // (what is in the list may be the work area the kernel writes)
+  return launch_colsum<T>(X, w.col_part, w.col_part_bytes, out, list.scale, list.acc, tokens, N, s2);
+}
+template <typename T>
+int layer_bwd_params_t(const cephalo_layer_desc& d, const DySums& dy_sums, const T* dyl, int tokens, int ln_chunks,
                        const Saved<T>& sv, const Work<T>& w, float* G, float scale, int acc, hipStream_t s, hipStream_t s2 = nullptr,
                        float* b_fc2_below = nullptr) {
   if (!s2) s2 = s;      // s2: where the bandwidth-bound reductions (bias column sums, norm-parameter partials) run, beside the GEMMs on s
   const ParamOffsets o = param_offsets(d);
   const int H = d.hidden, F = d.mlp;
+  SumList sums;
+  sums.scale = scale; sums.acc = acc;
+  sums.add(w.ln2_g, ln_chunks, H, G + o.ln2_g);
+  sums.add(w.ln1_g, ln_chunks, H, G + o.ln1_g);
   if (is_llama(d)) {
+    if (s2 != s) TRY(sums.flush(s2));
     TRY(wgrad<T>(dyl, sv.h, tokens, H, F, G + o.w_fc2, scale, acc, w.wg_part, s));
     TRY(wgrad<T>(w.dz, sv.u2, tokens, 2 * F, H, G + o.w_fc1, scale, acc, w.wg_part, s));
-    TRY(launch_reduce_partials(w.ln2_g, ln_chunks, H, G + o.ln2_g, scale, acc, w.col_part, w.col_part_bytes, s2));
     TRY(wgrad<T>(lowp_of<T>(w.dx1, w.dx1l), sv.O, tokens, H, H, G + o.w_o, scale, acc, w.wg_part, s));
     TRY(wgrad<T>(w.dqkv, sv.u, tokens, 3 * H, H, G + o.w_qkv, scale, acc, w.wg_part, s));
-    TRY(launch_reduce_partials(w.ln1_g, ln_chunks, H, G + o.ln1_g, scale, acc, w.col_part, w.col_part_bytes, s2));
-    return CEPHALO_OK;
+    return sums.flush(s2);
   }
+  sums.add(w.ln2_b, ln_chunks, H, G + o.ln2_b);
+  sums.add(w.ln1_b, ln_chunks, H, G + o.ln1_b);
+  sums.add(w.ln2_s, ln_chunks, H, G + o.b_o);
+  if (b_fc2_below) sums.add(w.ln1_s, ln_chunks, H, b_fc2_below);
+  else if (dy_sums.part) {
+    if constexpr (std::is_same<T, float>::value) TRY(add_colsum<T>(sums, dy_sums.part, dy_sums.chunks, H, G + o.b_fc2, w, s, s2));
+    else sums.add(dy_sums.part, dy_sums.chunks, H, G + o.b_fc2);
+  }
+  if (s2 != s) TRY(sums.flush(s2));
   // (the other two bias gradients are sums of the very bf16 values their weight-gradient GEMMs read, and the GEMMs form
   // them on the way)
-  if (b_fc2_below) TRY(launch_reduce_partials(w.ln1_s, ln_chunks, H, b_fc2_below, scale, acc, w.col_part, w.col_part_bytes, s2));
-  if (dy) TRY(launch_colsum<float>(dy, w.col_part, w.col_part_bytes, G + o.b_fc2, scale, acc, tokens, H, s2));   // (null: the caller has summed it already)
   TRY(wgrad<T>(dyl, sv.h, tokens, H, F, G + o.w_fc2, scale, acc, w.wg_part, s));
-  {
-    ColsumsBeside cb = {G + o.b_fc1, w.rs_part, w.rs_part_bytes, false};
-    TRY(wgrad<T>(w.dz, sv.u2, tokens, F, H, G + o.w_fc1, scale, acc, w.wg_part, s, 0, &cb));
-    if (!cb.done) TRY(launch_colsum<T>(w.dz, w.col_part, w.col_part_bytes, G + o.b_fc1, scale, acc, tokens, F, s2));
+  float* pieces = w.rs_part;
+  size_t room = w.rs_part_bytes;
+  struct { const T* dY; const T* X; int N; float *g, *gb; } two[] = {{w.dz, sv.u2, F, G + o.w_fc1, G + o.b_fc1}, {w.dqkv, sv.u, 3 * H, G + o.w_qkv, G + o.b_qkv}};
+  for (int i = 0; i < 2; ++i) {
+    auto& p = two[i];
+    if (i == 1) TRY(wgrad<T>(lowp_of<T>(w.dx1, w.dx1l), sv.O, tokens, H, H, G + o.w_o, scale, acc, w.wg_part, s));
+    // the second GEMM's pieces go behind the first's where both fit; otherwise the first's are added now and make room
+    if (i == 1 && std::is_same<T, bf16>::value && room < gemm_rowsum_part_bytes(p.N, H, w.wg_part ? gemm_grad_splits(p.N, H, tokens) : 1)) {
+      TRY(sums.flush(s));
+      pieces = w.rs_part; room = w.rs_part_bytes;
+    }
+    ColsumsBeside cb = {p.gb, pieces, room, false, true, 0};
+    TRY(wgrad<T>(p.dY, p.X, tokens, p.N, H, p.g, scale, acc, w.wg_part, s, 0, &cb));
+    if (cb.done) {
+      sums.add(pieces, cb.pieces, p.N, p.gb);
+      const size_t used = align_up((size_t)cb.pieces * p.N * sizeof(float));
+      pieces += used / sizeof(float);
+      room = room > used ? room - used : 0;
+    } else {
+      TRY(add_colsum<T>(sums, p.dY, tokens, p.N, p.gb, w, s, s2));
+    }
   }
-  TRY(launch_reduce_partials(w.ln2_g, ln_chunks, H, G + o.ln2_g, scale, acc, w.col_part, w.col_part_bytes, s2));
-  TRY(launch_reduce_partials(w.ln2_b, ln_chunks, H, G + o.ln2_b, scale, acc, w.col_part, w.col_part_bytes, s2));
-  TRY(launch_reduce_partials(w.ln2_s, ln_chunks, H, G + o.b_o, scale, acc, w.col_part, w.col_part_bytes, s2));
-  TRY(wgrad<T>(lowp_of<T>(w.dx1, w.dx1l), sv.O, tokens, H, H, G + o.w_o, scale, acc, w.wg_part, s));
-  {
-    ColsumsBeside cb = {G + o.b_qkv, w.rs_part, w.rs_part_bytes, false};
-    TRY(wgrad<T>(w.dqkv, sv.u, tokens, 3 * H, H, G + o.w_qkv, scale, acc, w.wg_part, s, 0, &cb));
-    if (!cb.done) TRY(launch_colsum<T>(w.dqkv, w.col_part, w.col_part_bytes, G + o.b_qkv, scale, acc, tokens, 3 * H, s2));
-  }
-  TRY(launch_reduce_partials(w.ln1_g, ln_chunks, H, G + o.ln1_g, scale, acc, w.col_part, w.col_part_bytes, s2));
-  TRY(launch_reduce_partials(w.ln1_b, ln_chunks, H, G + o.ln1_b, scale, acc, w.col_part, w.col_part_bytes, s2));
-  return CEPHALO_OK;
+  return sums.flush(s);
 }
 
 template <typename T>
 int run_fwd(const cephalo_layer_desc& d, const void* P, const float* x, float* y, int m, void* save, hipStream_t s) {
   const SaveLayout L = save_layout(d, m);
-  return layer_fwd_t<T>(d, static_cast<const T*>(P), x, y, m, saved_at<T>(save, L, d, 0), s);
+  const Saved<T> sv = saved_at<T>(save, L, d, 0);
+  TRY(make_rotary<T>(d, sv, s));
+  return layer_fwd_t<T>(d, static_cast<const T*>(P), x, y, m, sv, s);
 }
 
 template <typename T>
@@ -529,12 +584,12 @@ int run_bwd(const cephalo_layer_desc& d, const void* P, const float* x, const fl
   const ScratchLayout W = scratch_layout(d, m, m);
   const Saved<T> sv = saved_at<T>(save, L, d, 0);
   const Work<T> w = work_at<T>(scratch, W, d, 0, 0, m);
-  const int64_t act = (int64_t)m * d.seq * d.hidden;
-  TRY(make_lowp<T>(w.dyl, dy, act, s));
+  DySums dy_sums;
+  TRY(take_dy<T>(d, dy, m * d.seq, w, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w.dyl);
   TRY(prepare_dgrad_weights<T>(d, static_cast<const T*>(P), w.wT, s));
   TRY(layer_bwd_data_t<T>(d, static_cast<const T*>(P), x, dy, dyl, dx, (T*)nullptr, m, sv, w, s));
-  return layer_bwd_params_t<T>(d, dy, dyl, m * d.seq, ln_bwd_blocks(m * d.seq), sv, w, G, scale, acc, s);
+  return layer_bwd_params_t<T>(d, dy_sums, dyl, m * d.seq, ln_bwd_blocks(m * d.seq), sv, w, G, scale, acc, s);
 }
 
 // The two compute streams of an interleaved step.  fork: the side stream continues from where the main stream is;
@@ -590,9 +645,11 @@ int run_share(const cephalo_layer_desc& d, const void* Pv, const float* x, float
   TRY(J.open());
   struct JCloser { Streams& j; bool done = false; ~JCloser() { if (!done) (void)j.close(); } } jcloser{J};   // early exits still join
   const Work<T> w0 = work_at<T>(scratch, W, d, 0, 0, m);
-  TRY(make_lowp<T>(w0.dyl, dy, (int64_t)l * act, s));
+  DySums dy_sums;
+  TRY(take_dy<T>(d, dy, b * d.seq, w0, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w0.dyl);
   TRY(prepare_dgrad_weights<T>(d, P, w0.wT, s));
+  TRY(make_rotary<T>(d, saved_at<T>(save, L, d, 0), s));
   J.fork();
   {
     GemmSideBySide hint(nst);
@@ -604,7 +661,7 @@ int run_share(const cephalo_layer_desc& d, const void* Pv, const float* x, float
   }
   J.join();
   J.fork();      // the parameter pass's reductions beside its GEMMs
-  TRY(layer_bwd_params_t<T>(d, dy, dyl, b * d.seq, l * ln_bwd_blocks(m * d.seq), saved_at<T>(save, L, d, 0), w0, G, scale, 0, s, st[1]));
+  TRY(layer_bwd_params_t<T>(d, dy_sums, dyl, b * d.seq, l * ln_bwd_blocks(m * d.seq), saved_at<T>(save, L, d, 0), w0, G, scale, 0, s, st[1]));
   jcloser.done = true;
   return J.close();      // joins the streams; an error of the join or of the event release is the call's result
 }

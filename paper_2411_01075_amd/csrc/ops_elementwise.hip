@@ -19,6 +19,11 @@ bool all_aligned(std::initializer_list<const void*> ptrs) {
   return true;
 }
 size_t norm_bwd_part_floats(int rows, int H) { return (size_t)ln_bwd_blocks(rows) * H; }
+// (part of the reported sizes since the reduction ran in two stages; not used any more)
+size_t norm_bwd_spare(int rows, int H) {
+  const size_t chunks = ln_bwd_blocks(rows);
+  return chunks > 64 ? (chunks + 31) / 32 * H * sizeof(float) : 0;
+}
 }  // namespace
 
 extern "C" int cephalo_op_norm_fwd(int32_t dtype, int32_t rms, const float* x, const void* gamma, const void* beta, void* u,
@@ -35,7 +40,7 @@ extern "C" int cephalo_op_norm_fwd(int32_t dtype, int32_t rms, const float* x, c
 
 extern "C" size_t cephalo_op_norm_bwd_workspace(int32_t rows, int32_t H) {
   if (rows <= 0 || H <= 0) return 0;
-  return (2 * norm_bwd_part_floats(rows, H)) * sizeof(float) + reduce_tmp_bytes(ln_bwd_blocks(rows), H) + 256;
+  return (2 * norm_bwd_part_floats(rows, H)) * sizeof(float) + norm_bwd_spare(rows, H) + 256;
 }
 
 extern "C" int cephalo_op_norm_bwd(int32_t dtype, int32_t rms, const float* du, const float* x, const float* mean, const float* rstd,
@@ -50,21 +55,18 @@ extern "C" int cephalo_op_norm_bwd(int32_t dtype, int32_t rms, const float* du, 
   const int nb = ln_bwd_blocks(rows);
   float* part_g = static_cast<float*>(workspace);
   float* part_b = part_g + norm_bwd_part_floats(rows, H);
-  float* tmp = part_b + norm_bwd_part_floats(rows, H);
-  const size_t tmp_bytes = reduce_tmp_bytes(nb, H);
   if (dtype == CEPHALO_F32)
     TRY(launch_ln_bwd<float>(du, x, mean, rstd, static_cast<const float*>(gamma), resid, dx, static_cast<float*>(nullptr), part_g, part_b, rows, H, s, rms != 0));
   else
     TRY(launch_ln_bwd<bf16>(du, x, mean, rstd, static_cast<const bf16*>(gamma), resid, dx, static_cast<bf16*>(dx_lowp), part_g, part_b, rows, H, s, rms != 0));
-  TRY(launch_reduce_partials(part_g, nb, H, dgamma, 1.0f, 0, tmp, tmp_bytes, s));
-  if (!rms) TRY(launch_reduce_partials(part_b, nb, H, dbeta, 1.0f, 0, tmp, tmp_bytes, s));
-  return CEPHALO_OK;
+  const ReduceJob jobs[] = {{part_g, nb, H, dgamma}, {part_b, nb, H, dbeta}};
+  return launch_reduce_jobs(jobs, rms ? 1 : 2, 1.0f, 0, s);
 }
 
 // norm_bwd in the LayerNorm form with the column sums of its result as a third reduction
 extern "C" size_t cephalo_op_norm_bwd_sums_workspace(int32_t rows, int32_t H) {
   if (rows <= 0 || H <= 0) return 0;
-  return (3 * norm_bwd_part_floats(rows, H)) * sizeof(float) + reduce_tmp_bytes(ln_bwd_blocks(rows), H) + 256;
+  return (3 * norm_bwd_part_floats(rows, H)) * sizeof(float) + norm_bwd_spare(rows, H) + 256;
 }
 
 extern "C" int cephalo_op_norm_bwd_sums(int32_t dtype, const float* du, const float* x, const float* mean, const float* rstd,
@@ -81,16 +83,12 @@ extern "C" int cephalo_op_norm_bwd_sums(int32_t dtype, const float* du, const fl
   float* part_g = static_cast<float*>(workspace);
   float* part_b = part_g + each;
   float* part_s = part_b + each;
-  float* tmp = part_s + each;
-  const size_t tmp_bytes = reduce_tmp_bytes(nb, H);
   if (dtype == CEPHALO_F32)
     TRY(launch_ln_bwd<float>(du, x, mean, rstd, static_cast<const float*>(gamma), resid, dx, static_cast<float*>(nullptr), part_g, part_b, rows, H, s, false, part_s));
   else
     TRY(launch_ln_bwd<bf16>(du, x, mean, rstd, static_cast<const bf16*>(gamma), resid, dx, static_cast<bf16*>(dx_lowp), part_g, part_b, rows, H, s, false, part_s));
-  TRY(launch_reduce_partials(part_g, nb, H, dgamma, 1.0f, 0, tmp, tmp_bytes, s));
-  TRY(launch_reduce_partials(part_b, nb, H, dbeta, 1.0f, 0, tmp, tmp_bytes, s));
-  TRY(launch_reduce_partials(part_s, nb, H, dx_colsum, 1.0f, 0, tmp, tmp_bytes, s));
-  return CEPHALO_OK;
+  const ReduceJob jobs[] = {{part_g, nb, H, dgamma}, {part_b, nb, H, dbeta}, {part_s, nb, H, dx_colsum}};
+  return launch_reduce_jobs(jobs, 3, 1.0f, 0, s);
 }
 
 extern "C" size_t cephalo_op_colsum_workspace(int32_t rows, int32_t N) {

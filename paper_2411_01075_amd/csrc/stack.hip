@@ -360,7 +360,8 @@ template <> GemmArgs<bf16> head_dgrad_args<bf16>(const bf16* dlg, const bf16*, c
 template <typename T> int prepare_head_weights(const T* wte, T* wteT, int V, int H, int ldv, hipStream_t s);
 template <> int prepare_head_weights<float>(const float*, float*, int, int, int, hipStream_t) { return CEPHALO_OK; }
 template <> int prepare_head_weights<bf16>(const bf16* wte, bf16* wteT, int V, int H, int ldv, hipStream_t s) {
-  return launch_transpose_bf16(wte, wteT, V, H, s, ldv);
+  const TransposeJob job = {wte, wteT, V, H, ldv};
+  return launch_transposes(&job, 1, s);
 }
 
 __global__ void __launch_bounds__(kThreads) zero_kernel(float* __restrict__ p, int64_t n4) {
@@ -570,6 +571,10 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   struct GCloser { Boundary& x; bool done = false; ~GCloser() { if (!done) (void)x.close(); } } gcloser{Gx};
 
   // ---- forward
+  // the layers' rotary table: one of them, in the first layer's save area, for all (the same positions and head width)
+  float* rot = saved_at<T>(at<char>(ws, L.saves), SL, ld, 0).rot;
+  auto saved_of = [&](void* save, int sample0) { Saved<T> v = saved_at<T>(save, SL, ld, sample0); v.rot = rot; return v; };
+  TRY(make_rotary<T>(ld, saved_of(at<char>(ws, L.saves), 0), s));
   TRY(prepare_head_weights<T>(P + o_head, at<T>(ws, L.wteT), V, H, L.ldv, s));
   J.fork();
   GemmSideBySide hint(nst);     // until the join: two kernels share the device
@@ -586,7 +591,7 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
       const float* xi = X.in(li, j, l);
       X.prefetch(li, j + 1, l);
       float* xo = X.out(li + 1, j);
-      TRY(layer_fwd_t<T>(ld, P + o_layers + li * PL, xi, xo, m, saved_at<T>(save, SL, ld, j * m), st[j % nst]));
+      TRY(layer_fwd_t<T>(ld, P + o_layers + li * PL, xi, xo, m, saved_of(save, j * m), st[j % nst]));
       X.in_done();
       X.out_done(li + 1, j);
     }
@@ -633,14 +638,13 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   mean_kernel<<<1, kThreads, 0, s>>>(at<float>(ws, L.loss), n, loss_out);
   CEPHALO_CHECK_LAUNCH("mean_loss");
   {
-    Work<T> w = work_at<T>(scratch, WL, ld, 0, 0, m);
     TRY(wgrad<T>(dlogits, uf, n, V, H, G + o_head, 1.0f, 0, (float*)nullptr, s, L.ldv));       // the head's gradient (tied: the head's part of d wte), whole share
-    TRY(launch_reduce_partials(lnf_g, l * nb, H, G + o_lnf, 1.0f, 0, w.col_part, w.col_part_bytes, s));
-    if (!rms) TRY(launch_reduce_partials(lnf_b, l * nb, H, G + o_lnf + H, 1.0f, 0, w.col_part, w.col_part_bytes, s));
     // The bias gradient of a layer's second feed-forward projection is the column sum of the gradient arriving at the
     // layer's output.  Whoever produces that gradient (the final norm's backward here, the layer above further down)
     // sums it block by block as it writes it.
-    if (!rms) TRY(launch_reduce_partials(lnf_s, l * nb, H, G + o_layers + (size_t)(NL - 1) * PL + param_offsets(ld).b_fc2, 1.0f, 0, w.col_part, w.col_part_bytes, s));
+    const ReduceJob jobs[] = {{lnf_g, l * nb, H, G + o_lnf}, {lnf_b, l * nb, H, G + o_lnf + H},
+                              {lnf_s, l * nb, H, G + o_layers + (size_t)(NL - 1) * PL + param_offsets(ld).b_fc2}};
+    TRY(launch_reduce_jobs(jobs, rms ? 1 : 3, 1.0f, 0, s));
   }
   // ---- backward through the layers
   for (int li = NL - 1; li >= 0; --li) {
@@ -657,14 +661,14 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
     for (int j = 0; j < l; ++j) {
       const float* xi = X.in(li, j, l);
       X.prefetch(li, j + 1, l);
-      if (recompute) TRY(layer_fwd_t<T>(ld, Pl, xi, at<float>(ws, L.xdump) + (size_t)(j % nst) * act, m, saved_at<T>(save, SL, ld, j * m), st[j % nst]));
+      if (recompute) TRY(layer_fwd_t<T>(ld, Pl, xi, at<float>(ws, L.xdump) + (size_t)(j % nst) * act, m, saved_of(save, j * m), st[j % nst]));
       // the fp32 gradient arriving at this layer's output and the one leaving at its input: resident buffers, or (offload = 2)
       // a slot just fetched from the host and a slot about to leave for it; layer 0's result stays on the device for the embeddings
       const float* dyj = Gx.offload ? Gx.in((li + 1) % 2, j, l) : dx_cur + j * act;
       Gx.prefetch((li + 1) % 2, j + 1, l);
       float* dxj = !Gx.offload ? dx_nxt + j * act : (li == 0 ? at<float>(ws, L.dxa) + j * act : Gx.out(li % 2, j));
       TRY(layer_bwd_data_t<T>(ld, Pl, xi, dyj, dxl_cur + j * act, dxj,
-                              dxl_nxt + j * act, m, saved_at<T>(save, SL, ld, j * m), work_at<T>(scratch, WL, ld, j * m, j, m, j % nst), st[j % nst]));
+                              dxl_nxt + j * act, m, saved_of(save, j * m), work_at<T>(scratch, WL, ld, j * m, j, m, j % nst), st[j % nst]));
       Gx.in_done();
       if (Gx.offload && li > 0) Gx.out_done(li % 2, j);
       X.in_done();
@@ -672,8 +676,8 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
     J.join();
     hint.now(1);
     J.fork();        // the parameter pass: weight-gradient GEMMs on the main stream, the bandwidth-bound reductions beside them
-    TRY(layer_bwd_params_t<T>(ld, (const float*)nullptr, Gx.offload ? dxl_cur : lowp_of<T>(dx_cur, dxl_cur), n, l * nb,
-                              saved_at<T>(save, SL, ld, 0), work_at<T>(scratch, WL, ld, 0, 0, m), G + o_layers + li * PL, 1.0f, 0, s, st[1],
+    TRY(layer_bwd_params_t<T>(ld, DySums{nullptr, 0}, Gx.offload ? dxl_cur : lowp_of<T>(dx_cur, dxl_cur), n, l * nb,
+                              saved_of(save, 0), work_at<T>(scratch, WL, ld, 0, 0, m), G + o_layers + li * PL, 1.0f, 0, s, st[1],
                               (!rms && li > 0) ? G + o_layers + (size_t)(li - 1) * PL + param_offsets(ld).b_fc2 : (float*)nullptr));
     J.join();
     { float* t = dx_cur; dx_cur = dx_nxt; dx_nxt = t; }

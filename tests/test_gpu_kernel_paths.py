@@ -78,3 +78,55 @@ def test_gemm_tiles_give_the_same_bits(M, N, K):
     assert (np.abs(first["plain"].double().cpu().numpy() - acc) <= bound).all()
     ref = acc + b.double().cpu().numpy() + R.double().cpu().numpy()
     assert (np.abs(first["resid"].double().cpu().numpy() - ref) <= bound + 3 * 2.0 ** -24 * (np.abs(acc) + np.abs(ref) + 4)).all()
+
+
+@pytest.mark.parametrize("rows", [1, 7, 64, 65, 200, 4099])
+@pytest.mark.parametrize("N", [8, 72, 264, 1032])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_column_sums_edges(rows, N, bf16):
+    """Chunks of 64 rows, 64 vectors of 16 bytes per block; the reduction over 1 to 65 chunks."""
+    g = torch.Generator(device="cuda").manual_seed(rows * 31 + N)
+    X = torch.randn(rows, N, device="cuda", generator=g)
+    X = X.bfloat16() if bf16 else X
+    dt = C.BF16 if bf16 else C.F32
+    ws = torch.empty(C.cephalo_op_colsum_workspace(rows, N), dtype=torch.uint8, device="cuda").fill_(255)
+    out = torch.full((N,), float("nan"), device="cuda")
+    C.cephalo_op_colsum(dt, X, rows, N, out, 0.5, 0, ws)
+    x = X.double().cpu().numpy()
+    bound = (rows + 4) * 2.0 ** -24 * np.abs(x).sum(0)
+    assert (np.abs(out.double().cpu().numpy() - 0.5 * x.sum(0)) <= 0.5 * bound).all()
+    C.cephalo_op_colsum(dt, X, rows, N, out, 1.0, 1, ws)
+    assert (np.abs(out.double().cpu().numpy() - 1.5 * x.sum(0)) <= 1.5 * bound + 2.0 ** -23 * np.abs(x.sum(0))).all()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("m,S", [(8, 512), (8, 513), (1, 9), (3, 43)])
+def test_bias_gradient_of_the_last_projection_is_the_column_sum_of_dy(m, S, bf16):
+    """fp32: up to 4096 rows are their own partial sums, more go through the column-sum kernel; bf16: summed in the copy kernel, 32 rows
+    per block."""
+    H, F = 64, 72
+    desc = C.layer_desc(H, 1, F, S, True, C.BF16 if bf16 else C.F32)
+    g = torch.Generator(device="cuda").manual_seed(m * S)
+    flat = (torch.randn(C.cephalo_layer_param_count(desc), device="cuda", generator=g) * 0.02).to(torch.bfloat16 if bf16 else torch.float32)
+    x, dy = torch.randn(m, S, H, device="cuda", generator=g), torch.randn(m, S, H, device="cuda", generator=g)
+    y, dx, G = torch.empty_like(x), torch.empty_like(x), torch.full((flat.numel(),), float("nan"), device="cuda")
+    sv, sc = C.cephalo_layer_workspace_bytes(desc, m)
+    save, scratch = torch.empty(sv, dtype=torch.uint8, device="cuda"), torch.empty(sc, dtype=torch.uint8, device="cuda").fill_(255)
+    C.cephalo_layer_fwd(desc, flat, x, y, m, save, scratch)
+    C.cephalo_layer_bwd(desc, flat, x, dy, dx, m, save, G, 0.25, 0, scratch)
+    off = C.cephalo_layer_param_offsets(desc)[11]
+    d = dy.double().cpu().numpy().reshape(-1, H)
+    got = G[off:off + H].double().cpu().numpy()
+    assert (np.abs(got - 0.25 * d.sum(0)) <= 0.25 * (m * S + 4) * 2.0 ** -24 * np.abs(d).sum(0)).all()
+    assert torch.isfinite(G).all() and torch.isfinite(dx).all()
+
+
+def test_bias_sums_of_two_projections_that_do_not_fit_the_work_area_together():
+    """256 wide over 8192 tokens: the first GEMM's pieces fill the area, so they are added before the second GEMM runs."""
+    import dataclasses
+    from tests import harness as Hn
+    from workloads import CONFIGS, draw_activations, draw_layer_params
+    cfg = dataclasses.replace(CONFIGS["c2"], hidden=256, heads=4, mlp=1024, seq=512, micro_batch=8, n_micro=2)
+    tensors = draw_layer_params(cfg, perturbed=True)
+    x, dy = draw_activations(cfg)
+    Hn.compare_share(cfg, Hn.gpu_share_step(cfg, tensors, x, dy), Hn.oracle_share_step(cfg, tensors, x, dy))
