@@ -122,6 +122,33 @@ struct OperandTile {
     for (int j = 0; j < PER_WAVE; ++j) off[j] += slab_bytes;    // the mark stays out of range (extents are < 2^31)
   }
 
+  // Fragment addresses (per lane, for block 0 and k-step 0 of the wavefront tile that starts at tile row w0).
+  //  k-contiguous tile [row][64 k]: row l%16, chunk l/16; k-step 1 is chunk + 4, under the XOR swizzle the same
+  //   address with bit 6 flipped; block b is 16 rows further.
+  //  row-contiguous tile [k][rows]: within a group of 16 lanes, lane i addresses 4 consecutive rows (8 bytes) of
+  //   k-row 8*(l/16) + i/4 and receives the 4 k-values of row i; a second read 4 k-rows further completes the 8.
+  //   The swizzle term of those k-rows is the same for both reads and both k-steps; block b is two chunks further,
+  //   which under the XOR is the address with b << 5 flipped (the wavefront's first chunk is a multiple of 8 or 16,
+  //   so the block bits are free).
+  __device__ static int frag_base(int w0) {
+    const int lane = threadIdx.x & 63;
+    if (KFAST) return (w0 + (lane & 15)) * PITCH + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
+    const int g = lane >> 4, i = lane & 15;
+    const int krow = 8 * g + (i >> 2);
+    const int sw = ((krow & 3) << 2) | ((g & 1) << 1);
+    return krow * PITCH + ((((w0 >> 3) | ((i & 3) >> 1)) ^ sw) << 4) + 8 * (i & 1);
+  }
+  __device__ static bf16x8 frag(const LDS_AS char* tile, int base, int blk, int kstep) {
+    if constexpr (KFAST) {
+      return *reinterpret_cast<const LDS_AS bf16x8*>(tile + (base ^ (kstep << 6)) + blk * 16 * PITCH);
+    } else {
+      const LDS_AS char* p0 = tile + (base ^ (blk << 5)) + kstep * 32 * PITCH;
+      union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+      u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0));
+      u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 4 * PITCH));
+      return u.v;
+    }
+  }
 };
 
 // Second half of the bf16/fp32-output epilogue: 32 rows x WTN columns of fp32 results staged row-major in LDS (pitch
@@ -311,6 +338,42 @@ struct StagedRows {
 // s_waitcnt operand that waits for vmcnt(n) only (6-bit counter split over two fields; the other counters at their maxima)
 constexpr int vmcnt_only(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
+// The fp32 gradient's epilogue (a piece of a split contraction goes to its partial image), and the wavefront's row sums.
+// mw, nw: matrix coordinates of the wavefront tile's corner.
+template <int MI, int NI>
+__device__ __forceinline__ void finish_grad(const GemmArgs<bf16>& a, f32x4 (&acc)[MI][NI], f32x4 rsum, int split, int owners, int owner, int mw, int nw) {
+  const int lane = threadIdx.x & 63;
+  if (a.rowsum_part) {
+    const int m = mw + lane;
+    if (lane < 16 * MI && m < a.M) a.rowsum_part[((int64_t)split * owners + owner) * a.M + m] = rsum[0];
+  }
+  const bool partial = a.splits > 1;
+  float* const gbase = partial ? a.part + (int64_t)split * a.M * a.N : a.G;
+  const float scale = partial ? 1.0f : a.scale;
+  const bool accumulate = !partial && a.accumulate;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int m = mw + 16 * i + (lane & 15);
+    if (m >= a.M) continue;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int n = nw + 16 * j + 4 * (lane >> 4);
+      if (n >= a.N) continue;                           // N is a multiple of 8: the group of 4 is inside or outside
+      f32x4* gp = reinterpret_cast<f32x4*>(gbase + (int64_t)m * a.N + n);
+      f32x4 v = scale * acc[i][j];
+      if (accumulate) v += *gp;
+      *gp = v;
+    }
+  }
+}
+// Left operand of the row sums: rows 4i..4i+3 are ones, the others zero; row4 = (this lane's operand row) / 4.
+__device__ __forceinline__ bf16x8 ones_for(int i, int row4) {
+  union { unsigned u[4]; bf16x8 v; } sel;
+  const unsigned w = (row4 == i) ? 0x3F803F80u : 0u;      // two bf16 ones
+  sel.u[0] = w; sel.u[1] = w; sel.u[2] = w; sel.u[3] = w;
+  return sel.v;
+}
+
 // The epilogue of every output but the fp32 gradient: each wavefront passes its tile through its own LDS region, 32 rows at a
 // time, to turn the accumulator layout into row-major 16-byte vectors; bias, residual and pre-activation are then read, and the
 // results written, as coalesced 16-byte accesses.
@@ -432,44 +495,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
     TA::advance(offa, (unsigned)kb0 * a_step);
     TB::advance(offb, (unsigned)kb0 * b_step);
   }
-  // Fragment addresses (per lane, for block 0 and k-step 0 of the wavefront tile).
-  //  k-contiguous tile [row][64 k]: row l%16, chunk l/16; k-step 1 is chunk + 4, under the XOR swizzle the same
-  //   address with bit 6 flipped; block b is 16 rows further.
-  //  row-contiguous tile [k][rows]: within a group of 16 lanes, lane i addresses 4 consecutive rows (8 bytes) of
-  //   k-row 8*(l/16) + i/4 and receives the 4 k-values of row i; a second read 4 k-rows further completes the 8.
-  //   The swizzle term of those k-rows is the same for both reads and both k-steps; block b is two chunks further,
-  //   which under the XOR is the address with b << 5 flipped (the wavefront's first chunk is a multiple of 8 or 16,
-  //   so the block bits are free).
-  auto frag_base = [&](bool kfast, int w0, int pitch) {
-    if (kfast) return (w0 + (lane & 15)) * pitch + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
-    const int g = lane >> 4, i = lane & 15;
-    const int krow = 8 * g + (i >> 2);
-    const int sw = ((krow & 3) << 2) | ((g & 1) << 1);
-    return krow * pitch + ((((w0 >> 3) | ((i & 3) >> 1)) ^ sw) << 4) + 8 * (i & 1);
-  };
-  const int fa0 = frag_base(AK, wm, TA::PITCH), fb0 = frag_base(BKF, wn, TB::PITCH);
-  auto frag_a = [&](const LDS_AS char* tile, int blk, int kstep) -> bf16x8 {
-    if constexpr (AK) {
-      return *reinterpret_cast<const LDS_AS bf16x8*>(tile + (fa0 ^ (kstep << 6)) + blk * 16 * TA::PITCH);
-    } else {
-      const LDS_AS char* p0 = tile + (fa0 ^ (blk << 5)) + kstep * 32 * TA::PITCH;
-      union { struct { s16x4 a, b; } s; bf16x8 v; } u;
-      u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0));
-      u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 4 * TA::PITCH));
-      return u.v;
-    }
-  };
-  auto frag_b = [&](const LDS_AS char* tile, int blk, int kstep) -> bf16x8 {
-    if constexpr (BKF) {
-      return *reinterpret_cast<const LDS_AS bf16x8*>(tile + (fb0 ^ (kstep << 6)) + blk * 16 * TB::PITCH);
-    } else {
-      const LDS_AS char* p0 = tile + (fb0 ^ (blk << 5)) + kstep * 32 * TB::PITCH;
-      union { struct { s16x4 a, b; } s; bf16x8 v; } u;
-      u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0));
-      u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 4 * TB::PITCH));
-      return u.v;
-    }
-  };
+  const int fa0 = TA::frag_base(wm), fb0 = TB::frag_base(wn);
+  auto frag_a = [&](const LDS_AS char* tile, int blk, int kstep) -> bf16x8 { return TA::frag(tile, fa0, blk, kstep); };
+  auto frag_b = [&](const LDS_AS char* tile, int blk, int kstep) -> bf16x8 { return TB::frag(tile, fb0, blk, kstep); };
   constexpr int RA = AK ? 1 : 2, RB = BKF ? 1 : 2;       // LDS reads per fragment
   static_assert(AK || WTM % 64 == 0, "block bits of a row-contiguous A tile");
   static_assert(BKF || WTN % 64 == 0, "block bits of a row-contiguous B tile");
@@ -556,12 +584,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
     static_assert(EPI != EPI_GRAD || MI <= 4, "up to four row fragments share the accumulator");
     if (a.rowsum_part) next_sum = ((owner - kb0) % owners + owners) % owners;
   }
-  auto ones_for = [&](int i, int row4) -> bf16x8 {         // row4: (this lane's operand row) / 4
-    union { unsigned u[4]; bf16x8 v; } sel;
-    const unsigned w = (row4 == i) ? 0x3F803F80u : 0u;      // two bf16 ones
-    sel.u[0] = w; sel.u[1] = w; sel.u[2] = w; sel.u[3] = w;
-    return sel.v;
-  };
 
   constexpr int JB = 1;                                    // column blocks of k-step 1 multiplied before the barrier
   if constexpr (A3) TA::advance(offa, a_step);             // (the prologue left the offsets at slab 1; A's next load is slab 2)
@@ -689,28 +711,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
   __builtin_amdgcn_s_setprio(0);
   // Epilogue
   if constexpr (EPI == EPI_GRAD) {
-    if (a.rowsum_part) {
-      const int m = m0 + wm + lane;
-      if (lane < 16 * MI && m < a.M) a.rowsum_part[((int64_t)split * owners + owner) * a.M + m] = rsum[0];
-    }
-    const bool partial = a.splits > 1;
-    float* const gbase = partial ? a.part + (int64_t)split * a.M * a.N : a.G;
-    const float scale = partial ? 1.0f : a.scale;
-    const bool accumulate = !partial && a.accumulate;
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = m0 + wm + 16 * i + (lane & 15);
-      if (m >= a.M) continue;
-#pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        const int n = n0 + wn + 16 * j + 4 * (lane >> 4);
-        if (n >= a.N) continue;                           // N is a multiple of 8: the group of 4 is inside or outside
-        f32x4* gp = reinterpret_cast<f32x4*>(gbase + (int64_t)m * a.N + n);
-        f32x4 v = scale * acc[i][j];
-        if (accumulate) v += *gp;
-        *gp = v;
-      }
-    }
+    finish_grad(a, acc, rsum, split, owners, owner, m0 + wm, n0 + wn);
   } else {
     finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
   }
@@ -723,11 +724,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
 // (1024 x 1024 x 4096: 64 tiles of 128 x 128, 48 us, 1600 clocks a slab against 512 of products).  Here the fragments of a whole slab
 // are held in registers, and the next slab's are read while this one's are multiplied: a slab costs one barrier and the larger of
 // its reads and its products.  NS stages of LDS, NS slabs of global loads in flight.
-template <int BM, int BN, int WGM, int WGN, int EPI, int NS>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int) {
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS>
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int slabs_per_split) {
   constexpr int NW = WGM * WGN;
-  typedef OperandTile<BM, true, NW> TA;
-  typedef OperandTile<BN, true, NW> TB;
+  typedef OperandTile<BM, AK, NW> TA;
+  typedef OperandTile<BN, BKF, NW> TB;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int MI = WTM / 16, NI = WTN / 16;
   constexpr int STAGE = TA::BYTES + TB::BYTES;
@@ -736,7 +737,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
 
   // tile order: as above
   const int total = tiles_m * tiles_n;
-  int pid = blockIdx.x;
+  const int split = blockIdx.x / total;
+  int pid = blockIdx.x % total;
   pid = xcd_run(pid, total);
   constexpr int GROUP = 4;
   const int per_group = GROUP * tiles_n;
@@ -753,21 +755,25 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const i32x4 ra_rsrc = make_rsrc_words(a.A, (unsigned)(2 * (int64_t)a.M * a.a_rs)), rb_rsrc = make_rsrc_words(a.B, (unsigned)(2 * (int64_t)a.N * a.b_rs));
+  const i32x4 ra_rsrc = make_rsrc_words(a.A, (unsigned)(2 * (AK ? (int64_t)a.M * a.a_rs : (int64_t)a.K * a.a_cs)));
+  const i32x4 rb_rsrc = make_rsrc_words(a.B, (unsigned)(2 * (BKF ? (int64_t)a.N * a.b_rs : (int64_t)a.K * a.b_cs)));
   unsigned offa[TA::PER_WAVE], offb[TB::PER_WAVE];
-  TA::init_offsets(a.a_rs, 1, m0, a.M, a.K, offa);
-  TB::init_offsets(a.b_rs, 1, n0, a.N, a.K, offb);
-  const int nk = (a.K + BK - 1) / BK;
-
-  // fragment addresses of k-contiguous tiles: see above
-  const int fa0 = (wm + (lane & 15)) * TA::PITCH + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
-  const int fb0 = TA::BYTES + (wn + (lane & 15)) * TB::PITCH + (((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
+  TA::init_offsets(a.a_rs, a.a_cs, m0, a.M, a.K, offa);
+  TB::init_offsets(a.b_rs, a.b_cs, n0, a.N, a.K, offb);
+  const unsigned a_step = (unsigned)(2 * BK * a.a_cs), b_step = (unsigned)(2 * BK * a.b_cs);   // bytes per k-slab
+  const int kb0 = split * slabs_per_split, nk = min((a.K + BK - 1) / BK - kb0, slabs_per_split);
+  if (kb0 > 0) {
+    TA::advance(offa, (unsigned)kb0 * a_step);
+    TB::advance(offb, (unsigned)kb0 * b_step);
+  }
+  const int fa0 = TA::frag_base(wm), fb0 = TB::frag_base(wn);
+  static_assert((AK || WTM % 64 == 0) && (BKF || WTN % 64 == 0), "block bits of a row-contiguous tile");
   struct Frags { bf16x8 a[2][MI], b[2][NI]; };
   constexpr int READS = 2 * (MI + NI);
   auto read_one = [&](Frags& f, const LDS_AS char* stage, int q) {      // the q-th fragment read of a slab, in the order the products want them
     const int ks = q / (MI + NI), e = q % (MI + NI);
-    if (e < MI) f.a[ks][e] = *reinterpret_cast<const LDS_AS bf16x8*>(stage + (fa0 ^ (ks << 6)) + e * 16 * TA::PITCH);
-    else f.b[ks][e - MI] = *reinterpret_cast<const LDS_AS bf16x8*>(stage + (fb0 ^ (ks << 6)) + (e - MI) * 16 * TB::PITCH);
+    if (e < MI) f.a[ks][e] = TA::frag(stage, fa0, e, ks);
+    else f.b[ks][e - MI] = TB::frag(stage + TA::BYTES, fb0, e - MI, ks);
   };
   constexpr int LOADS = TA::PER_WAVE + TB::PER_WAVE;
   static_assert((NS - 1) * LOADS < 64, "the outstanding loads must fit the counter");
@@ -777,9 +783,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
   };
 #pragma unroll
   for (int p = 0; p < NS; ++p) {
-    if (p > 0) { TA::advance(offa, 2 * BK); TB::advance(offb, 2 * BK); }
+    if (p > 0) { TA::advance(offa, a_step); TB::advance(offb, b_step); }
 #pragma unroll
-    for (int q = 0; q < LOADS; ++q) load_one(p * BK, smem + p * STAGE, q);
+    for (int q = 0; q < LOADS; ++q) load_one((kb0 + p) * BK, smem + p * STAGE, q);
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 1) * LOADS));
   __syncthreads();
@@ -787,15 +793,37 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
 #pragma unroll
   for (int q = 0; q < READS; ++q) read_one(f0, smem, q);
 
+  // row sums of A: as in the kernel above
+  const int owners = tiles_n * WGN, owner = tile_n * WGN + wave % WGN;
+  int next_sum = 0x7fffffff;
+  f32x4 rsum = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (EPI == EPI_GRAD) {
+    if (a.rowsum_part) next_sum = ((owner - kb0) % owners + owners) % owners;
+  }
+
   int st = 0;                                             // slab kt's stage
   auto slab = [&](int kt, Frags& cur, Frags& nxt) {
     const int st1 = st + 1 == NS ? 0 : st + 1;
     // this slab's fragments are in registers, so its stage is free behind the barrier; the next slab's loads have landed
     __builtin_amdgcn_s_waitcnt(vmcnt_only((NS - 2) * LOADS) & 0xF0FF);     // ... and lgkmcnt(0)
     __syncthreads();
-    TA::advance(offa, 2 * BK);
-    TB::advance(offb, 2 * BK);
+    TA::advance(offa, a_step);
+    TB::advance(offb, b_step);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EPI == EPI_GRAD) {
+      if (kt == next_sum) {
+        next_sum += owners;
+        int row4 = (lane & 15) >> 2;
+        asm volatile("" : "+v"(row4));
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          const bf16x8 sel = ones_for(i, row4);
+          rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, cur.a[0][i], rsum, 0, 0, 0);
+          rsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, cur.a[1][i], rsum, 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // the products in their order, a share of the next slab's reads and of the loads of slab kt + NS between them
     constexpr int STEPS = 2 * NI;
 #pragma unroll
@@ -803,7 +831,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
 #pragma unroll
       for (int q = s * READS / STEPS; q < (s + 1) * READS / STEPS; ++q) read_one(nxt, smem + st1 * STAGE, q);
 #pragma unroll
-      for (int q = s * LOADS / STEPS; q < (s + 1) * LOADS / STEPS; ++q) load_one((kt + NS) * BK, smem + st * STAGE, q);
+      for (int q = s * LOADS / STEPS; q < (s + 1) * LOADS / STEPS; ++q) load_one((kb0 + kt + NS) * BK, smem + st * STAGE, q);
 #pragma unroll
       for (int i = 0; i < MI; ++i) acc[i][s % NI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.b[s / NI][s % NI], cur.a[s / NI][i], acc[i][s % NI], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
@@ -814,7 +842,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
   for (; kt + 1 < nk; kt += 2) { slab(kt, f0, f1); slab(kt + 1, f1, f0); }
   if (kt < nk) slab(kt, f0, f1);
 
-  finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
+  if constexpr (EPI == EPI_GRAD) finish_grad(a, acc, rsum, split, owners, owner, m0 + wm, n0 + wn);
+  else finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
 }
 
 // G = (accumulate ? G : 0) + scale * (part[0] + part[1] + ... ) in split order, 4 floats per thread
@@ -884,11 +913,11 @@ int launch_cfg(const GemmArgs<bf16>& a, hipStream_t s) {
   return launch_kernel<gemm_mfma_kernel<BM, BN, WGM, WGN, AK, BKF, EPI, NS, PF, A3>>(a, BM, BN, WGN, 64 * WGM * WGN, lds, s);
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int NS>
+template <int BM, int BN, int WGM, int WGN, int EPI, int NS, bool AK = true, bool BKF = true>
 int launch_ring(const GemmArgs<bf16>& a, hipStream_t s) {
   constexpr size_t stages = (size_t)NS * (BM + BN) * BK * 2, staging = (size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4;
   static_assert(stages <= 160 * 1024 && staging <= 160 * 1024, "the stages and the staged rows must fit in LDS");
-  return launch_kernel<gemm_ring_kernel<BM, BN, WGM, WGN, EPI, NS>>(a, BM, BN, WGN, 64 * WGM * WGN, std::max(stages, staging), s);
+  return launch_kernel<gemm_ring_kernel<BM, BN, WGM, WGN, AK, BKF, EPI, NS>>(a, BM, BN, WGN, 64 * WGM * WGN, EPI == EPI_GRAD ? stages : std::max(stages, staging), s);
 }
 
 thread_local int side_by_side = 1;     // kernels the caller runs at once (GemmSideBySide)
@@ -906,9 +935,11 @@ constexpr TileCost kTiles[] = {
   {256, 256, 1, 0.56, 1.09, 1.16, 6.7}, {256, 192, 1, 0.46, 0.83, 0.85, 8.3}, {256, 128, 1, 0.39, 0.68, 0.80, 5.3}, {128, 192, 1, 0.42, 0.53, 0.62, 6.0},
   {128, 128, 1, 0.38, 0.41, 0.47, 4.1}, {128, 64, 2, 0.36, 0.32, 0.31, 4.3},  {64, 64, 2, 0.30, 0.21, 0.195, 3.3},
 };
-double tile_us(const TileCost& t, int M, int N, int K, int kernels) {
+// splits: pieces the contraction is cut into, one block each
+double tile_us(const TileCost& t, int M, int N, int K, int kernels, int splits = 1) {
   const double cus = 256.0 / kernels;
-  const double blocks = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), nk = (K + BK - 1) / BK;
+  const int slabs = (K + BK - 1) / BK, nk = (slabs + splits - 1) / splits;
+  const double blocks = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * ((slabs + nk - 1) / nk);
   const double rounds = (double)(int64_t)(blocks / (cus * t.blocks)), rest = blocks - rounds * cus * t.blocks;
   const double full = blocks > cus * t.blocks ? t.more : t.one;
   double us = t.fixed + rounds * t.blocks * nk * full + std::max(0.0, rounds - 1) * (t.fixed - 2.0);
@@ -939,9 +970,38 @@ int launch_rows(const GemmArgs<bf16>& a, hipStream_t s) {
   }
 }
 
+// Weight gradients, both operands token-major: the same estimate over tile and pieces of the token axis, fitted to 190 launches (outputs
+// of 256 x 256 to 22016 x 4096, 256 to 16000 tokens, 1 to 8 pieces).  A piece costs a fp32 image of the output written and read
+// back (4.5 TB/s) and the pass that adds the images about 3 us, which is more than idle compute units in a last round of blocks cost: the former
+// rule (fill the last round) cut 6144 tokens x 6400 x 1600 into 4 pieces (174 us, in one 133), 8192 x 6144 x 2048 into 4 (233, 180).  The
+// 128 x 128 tile of the ring kernel runs with four stages, or with two so that a compute unit holds two blocks (2048 x 7680 x
+// 2560: 256 x 256 in 3 pieces 138 us, this 92).  Within 0.2 % of the fastest tile and cut over those launches, 18 % faster than the former rule.
+constexpr TileCost kGradTiles[] = {
+  {256, 256, 1, 1.08, 1.24, 1.42, 9.3}, {256, 128, 1, 0.18, 0.70, 0.80, 7.0}, {128, 128, 1, 0.29, 0.47, 0.50, 4.9}, {128, 128, 2, 0.72, 0.475, 0.50, 5.0},
+};
+struct GradPlan { int tile; double us; };
+GradPlan grad_plan(int M, int N, int K, int kernels, int splits) {
+  GradPlan best = {0, 1e30};
+  for (int c = 0; c < (int)(sizeof(kGradTiles) / sizeof(kGradTiles[0])); ++c) {
+    const double us = tile_us(kGradTiles[c], M, N, K, kernels, splits);
+    if (us < best.us) best = {c, us};
+  }
+  if (splits > 1) best.us += 3.0 + (splits + 1) * 4e-6 / 4.5 * (double)M * N;
+  return best;
+}
+int launch_grad(const GemmArgs<bf16>& a, hipStream_t s) {
+  const int splits = (a.splits > 1 && a.part) ? a.splits : 1;
+  switch (grad_plan(a.M, a.N, a.K, side_by_side, splits).tile) {
+    case 0: return launch_cfg<256, 256, 4, 2, false, false, EPI_GRAD>(a, s);
+    case 1: return launch_ring<256, 128, 4, 2, EPI_GRAD, 3, false, false>(a, s);
+    case 2: return launch_ring<128, 128, 2, 2, EPI_GRAD, 4, false, false>(a, s);
+    default: return launch_ring<128, 128, 2, 2, EPI_GRAD, 2, false, false>(a, s);
+  }
+}
+
+// The layouts that no layer produces (cephalo_op_gemm alone does).
 template <bool AK, bool BKF, int EPI>
 int launch_tiles(const GemmArgs<bf16>& a, hipStream_t s) {
-  if constexpr (AK && BKF && EPI != EPI_GRAD) return launch_rows<EPI>(a, s);
   // Tile choice: the score of a configuration is the fraction of the last round of blocks that the 256 compute
   // units fill, times the rate its main loop reaches relative to the 256 x 256 tile (measured: bigger tiles
   // move fewer LDS and L2 bytes per MFMA).
@@ -970,7 +1030,7 @@ int launch_tiles(const GemmArgs<bf16>& a, hipStream_t s) {
 
 }  // namespace
 
-int gemm_grad_splits(int M, int N, int K) {
+int gemm_grad_splits_most(int M, int N, int K) {
   const double tiles = (double)((M + 255) / 256) * ((N + 255) / 256);
   int best = 1;
   double best_score = 0.0;
@@ -979,6 +1039,17 @@ int gemm_grad_splits(int M, int N, int K) {
     const double t = tiles * sp;
     const double score = t / (256.0 * (double)(int64_t)((t + 255) / 256)) * (1.0 - 0.03 * (sp - 1));   // fill, minus the second pass
     if (score > best_score + 1e-9) { best_score = score; best = sp; }
+  }
+  return best;
+}
+int gemm_grad_splits(int M, int N, int K) {
+  const int most = gemm_grad_splits_most(M, N, K);
+  int best = 1;
+  double least = 1e30;
+  for (int sp : {1, 2, 3, 4, 6, 8}) {
+    if (sp > most) break;
+    const double us = grad_plan(M, N, K, 1, sp).us;       // (not of the side-by-side hint: the pieces decide the order of the sums)
+    if (us < least) { least = us; best = sp; }
   }
   return best;
 }
@@ -1034,16 +1105,16 @@ int launch_gemm_mfma(const GemmArgs<bf16>& a, hipStream_t s) {
   // Only the layout/epilogue pairs a linear layer produces are instantiated.
   if (ak && bk) {          // forward: Y = X W^T
     switch (a.epi) {
-      case EPI_NONE: return launch_tiles<true, true, EPI_NONE>(a, s);
-      case EPI_NONE_HEAD: return launch_tiles<true, true, EPI_NONE_HEAD>(a, s);
-      case EPI_ROPE: if (a.rot_cols % 8 == 0 && a.rot_d % 8 == 0 && aligned16(a.rot)) return launch_tiles<true, true, EPI_ROPE>(a, s); break;
-      case EPI_BIAS: return launch_tiles<true, true, EPI_BIAS>(a, s);
-      case EPI_BIAS_RESID: return launch_tiles<true, true, EPI_BIAS_RESID>(a, s);
-      case EPI_BIAS_GELU: return launch_tiles<true, true, EPI_BIAS_GELU>(a, s);
-      case EPI_DGELU: return launch_tiles<true, true, EPI_DGELU>(a, s);
-      case EPI_BIAS_GELU_DERIV: return launch_tiles<true, true, EPI_BIAS_GELU_DERIV>(a, s);
-      case EPI_MUL: return launch_tiles<true, true, EPI_MUL>(a, s);
-      case EPI_DSWIGLU: if (a.N % 8 == 0) return launch_tiles<true, true, EPI_DSWIGLU>(a, s); break;
+      case EPI_NONE: return launch_rows<EPI_NONE>(a, s);
+      case EPI_NONE_HEAD: return launch_rows<EPI_NONE_HEAD>(a, s);
+      case EPI_ROPE: if (a.rot_cols % 8 == 0 && a.rot_d % 8 == 0 && aligned16(a.rot)) return launch_rows<EPI_ROPE>(a, s); break;
+      case EPI_BIAS: return launch_rows<EPI_BIAS>(a, s);
+      case EPI_BIAS_RESID: return launch_rows<EPI_BIAS_RESID>(a, s);
+      case EPI_BIAS_GELU: return launch_rows<EPI_BIAS_GELU>(a, s);
+      case EPI_DGELU: return launch_rows<EPI_DGELU>(a, s);
+      case EPI_BIAS_GELU_DERIV: return launch_rows<EPI_BIAS_GELU_DERIV>(a, s);
+      case EPI_MUL: return launch_rows<EPI_MUL>(a, s);
+      case EPI_DSWIGLU: if (a.N % 8 == 0) return launch_rows<EPI_DSWIGLU>(a, s); break;
       case EPI_GRAD: return launch_tiles<true, true, EPI_GRAD>(a, s);
     }
   } else if (ak && !bk) {  // dgrad: dX = dY W
@@ -1054,7 +1125,7 @@ int launch_gemm_mfma(const GemmArgs<bf16>& a, hipStream_t s) {
     }
     if (a.epi == EPI_GRAD) return launch_tiles<true, false, EPI_GRAD>(a, s);   // wgrad with dY pre-transposed
   } else if (!ak && !bk) {  // wgrad: dW = dY^T X
-    if (a.epi == EPI_GRAD) return launch_tiles<false, false, EPI_GRAD>(a, s);
+    if (a.epi == EPI_GRAD) return launch_grad(a, s);
   } else {                  // wgrad with X pre-transposed
     if (a.epi == EPI_GRAD) return launch_tiles<false, true, EPI_GRAD>(a, s);
   }

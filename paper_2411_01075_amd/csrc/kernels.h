@@ -161,8 +161,10 @@ struct GemmArgs {
 size_t gemm_rowsum_part_bytes(int M, int N, int splits = 8);   // upper bound over tile shapes (and splits)
 bool gemm_mfma_takes(const GemmArgs<bf16>& a);          // whether launch_gemm_mfma runs this problem on its MFMA kernels
 
-// Number of pieces the weight-gradient GEMM G[M,N] = sum over K tokens would like the token axis cut into (1: none).
+// Number of pieces the weight-gradient GEMM G[M,N] = sum over K tokens would like the token axis cut into (1: none), and the most it
+// may ask for (work areas are sized by the latter).
 int gemm_grad_splits(int M, int N, int K);
+int gemm_grad_splits_most(int M, int N, int K);
 
 template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);   // (bf16 only)
 int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s);  // fp32 operands and arithmetic, any strides

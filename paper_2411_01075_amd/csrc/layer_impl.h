@@ -134,7 +134,7 @@ ScratchLayout scratch_layout(const cephalo_layer_desc& d, int m, int span, int s
     size_t need = 0;
     const int dims[4][2] = {{(int)(3 * H), (int)H}, {(int)H, (int)H}, {(int)F1, (int)H}, {(int)H, (int)F}};
     for (auto& nk : dims) {
-      const int sp = gemm_grad_splits(nk[0], nk[1], (int)Ts);
+      const int sp = gemm_grad_splits_most(nk[0], nk[1], (int)Ts);
       if (sp > 1) need = std::max(need, (size_t)sp * nk[0] * nk[1] * sizeof(float));
     }
     take(need);
@@ -224,7 +224,7 @@ GemmArgs<T> linear_wgrad(const T* dY, const T* X, int Tn, int N, int K, float* G
 // Parameter gradient of a linear layer over Tn tokens: G[N, K] (+)= scale * dY^T X, dY [Tn, ldy >= N], X [Tn, K].
 // Both operands are read as they lie, token-major (the contraction runs over their rows: the GEMM reads such
 // operands with transposing LDS reads at the rate of k-contiguous ones, so no transposed copy is made).
-// `part`: room for the pieces of a split contraction (sized by gemm_grad_splits for the whole token axis), or null.
+// `part`: room for the pieces of a split contraction (sized by gemm_grad_splits_most for the whole token axis), or null.
 // `colsums` (optional): where the column sums of dY, the bias gradient of the same projection, are wanted with the same
 // scale / acc.  The bf16 GEMM sums them beside the products when it can (one piece, operands that fit its MFMA kernels)
 // and then sets colsums->done; otherwise the caller runs the column-sum kernel.
@@ -252,7 +252,7 @@ int wgrad<bf16>(const bf16* dY, const bf16* X, int Tn, int N, int K, float* G, f
     const int tc = (int)(Tn - t0 < piece ? Tn - t0 : piece);
     GemmArgs<bf16> a = linear_wgrad<bf16>(dY + t0 * ldy, X + t0 * K, tc, N, K, G, scale, t0 > 0 ? 1 : acc);
     a.a_cs = ldy;
-    a.splits = part ? gemm_grad_splits(N, K, tc) : 1;     // `part` was sized with the same rule for the whole token axis
+    a.splits = part ? gemm_grad_splits(N, K, tc) : 1;     // `part` holds the most pieces of the whole token axis
     a.part = part;
     if (tc != Tn) a.splits = 1;
     if (colsums && tc == Tn && colsums->part && colsums->part_bytes >= gemm_rowsum_part_bytes(N, K, a.splits) && gemm_mfma_takes(a)) {

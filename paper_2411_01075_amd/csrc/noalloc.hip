@@ -45,10 +45,10 @@ extern "C" int cephalo_op_linear_wgrad_static(int32_t dtype, const void* dY, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == CEPHALO_F32)      // the fp32 kernel does not split the contraction: no scratch at all
     return wgrad<float>(static_cast<const float*>(dY), static_cast<const float*>(X), T, N, K, G, scale, accumulate, nullptr, s);
-  const int splits = gemm_grad_splits(N, K, T);
+  const int splits = gemm_grad_splits_most(N, K, T);
   const size_t need = splits > 1 ? (size_t)splits * N * K * sizeof(float) : 0;
   if (need > (size_t)CEPHALO_NOALLOC_SCRATCH_BYTES)
-    return fail(CEPHALO_EWORKSPACE, "linear_wgrad_static: a %d x %d gradient over %d tokens is summed in %d pieces and needs %zu B of partial "
+    return fail(CEPHALO_EWORKSPACE, "linear_wgrad_static: a %d x %d gradient over %d tokens is summed in up to %d pieces and needs %zu B of partial "
                 "sums; the fixed area holds %zu B (use cephalo_op_linear_wgrad with a work area of its own)",
                 N, K, T, splits, need, (size_t)CEPHALO_NOALLOC_SCRATCH_BYTES);
   void* part = nullptr;

@@ -80,7 +80,7 @@ namespace {
 // workspace of linear_wgrad: the partial sums of a split token axis
 size_t wgrad_part_bytes(int dtype, int T, int N, int K) {
   if (dtype != CEPHALO_BF16) return 0;
-  const int sp = gemm_grad_splits(N, K, T);
+  const int sp = gemm_grad_splits_most(N, K, T);
   return sp > 1 ? (size_t)sp * N * K * sizeof(float) : 0;
 }
 }  // namespace

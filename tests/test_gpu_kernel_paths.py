@@ -130,3 +130,32 @@ def test_bias_sums_of_two_projections_that_do_not_fit_the_work_area_together():
     tensors = draw_layer_params(cfg, perturbed=True)
     x, dy = draw_activations(cfg)
     Hn.compare_share(cfg, Hn.gpu_share_step(cfg, tensors, x, dy), Hn.oracle_share_step(cfg, tensors, x, dy))
+
+
+# tokens, out features, in features: every tile of the weight gradient (128 x 128 with four and with two stages, 256 x 128, 256 x 256), ragged
+# edges, one slab and less, a token axis in 1, 2, 4 and 8 pieces
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (65, 136, 72), (200, 264, 392), (300, 1544, 1032), (130, 3080, 2056), (4100, 264, 136), (9000, 520, 264), (2100, 1032, 520)])
+def test_weight_gradient_tiles(T, N, K):
+    print("wgrad tiles", T, N, K, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    dY, X = torch.randn(T, N, device="cuda", generator=g).bfloat16(), torch.randn(T, K, device="cuda", generator=g).bfloat16()
+    a, b = dY.double().cpu().numpy(), X.double().cpu().numpy()
+    ref, bound = a.T @ b, _sum_bound(a.T, b, T, 12)
+    gref, gbound = a.sum(0), (T + 12) * 2.0 ** -24 * np.abs(a).sum(0)
+    ws = torch.empty(C.binding.cephalo_op_linear_wgrad_bias_workspace(C.BF16, T, N, K), dtype=torch.uint8, device="cuda").fill_(255)
+    first = None
+    before = C.binding.cephalo_gemm_side_by_side(1)
+    try:
+        for kernels in (1, 2, 3, 5, 8, 16, 256):      # (steers the tile, not the pieces: same bits)
+            C.binding.cephalo_gemm_side_by_side(kernels)
+            G, gb = torch.full((N, K), float("nan"), device="cuda"), torch.full((N,), float("nan"), device="cuda")
+            C.binding.cephalo_op_linear_wgrad_bias(C.BF16, dY, X, T, N, K, G, gb, 1.0, 0, ws)
+            assert (np.abs(gb.double().cpu().numpy() - gref) <= gbound).all()
+            G2 = torch.full((N, K), float("nan"), device="cuda")
+            C.binding.cephalo_op_linear_wgrad(C.BF16, dY, X, T, N, K, G2, 1.0, 0, ws)
+            assert torch.equal(G, G2)
+            assert first is None or torch.equal(first, G), kernels
+            first = G
+    finally:
+        C.binding.cephalo_gemm_side_by_side(before)
+    assert (np.abs(first.double().cpu().numpy() - ref) <= bound).all()
