@@ -42,50 +42,39 @@ __device__ __forceinline__ i32x4 make_rsrc_words(const void* p, unsigned bytes) 
   return i32x4{(int)(unsigned)addr, (int)(unsigned)((addr >> 32) & 0xffffu), (int)bytes, 0x00020000};
 }
 
-// ROWS tokens by D values of one operand in LDS, staged by THREADS threads (through registers, or straight from
-// global memory).
+// ROWS tokens by D values (D = 32, 64 or 128) of one operand in LDS, staged by THREADS threads straight from global memory.
 //
-// Two layouts.  D = 64: rows padded to 72 elements (pitch 36 banks: a 16-byte fragment read has 16 lanes on 16
-// consecutive rows, a transposing read has each group of 16 lanes on 4 consecutive rows; both fall on distinct banks).
-// D = 128: rows of exactly 256 bytes (all 64 banks) with the 16-byte chunks of a row permuted,
-//     chunk c of row r lives at chunk  c ^ swz(r),   swz(r) = ((r & 7) << 1) | ((r >> 3) & 1),
-// so that 16 consecutive rows put the same chunk on 16 different places (fragment reads) and 4 consecutive rows put a
-// pair of neighbouring chunks on 4 different pairs (transposing reads).  Without padding a direct-to-LDS load of 16
-// bytes per lane fills 1 KiB = 4 whole rows at once; the permutation is applied by the address each lane fetches.
-// (With padded rows only 4-byte-per-lane loads fit a row, and those run at a quarter of the rate: at 64 KB per key
-// tile the forward pass spent more time staging than multiplying.)
+// Rows are 2 D bytes without padding, so that a direct-to-LDS load of 16 bytes per lane fills 1 KiB = 512 / D whole rows at once; bank
+// conflicts are avoided by permuting the 16-byte chunks of a row, chunk c of row r lives at chunk  c ^ swz(r);  the permutation is
+// applied by the address each lane fetches.  16 consecutive rows put the same chunk on 16 different places of the 64 banks (fragment
+// reads: 1, 2 or 4 rows share a line of all banks), and 4 consecutive rows put four neighbouring chunks on disjoint places
+// (transposing reads):
+//     D = 128   swz(r) = ((r & 7) << 1) | ((r >> 3) & 1)
+//     D =  64   swz(r) = (((r >> 1) & 1) << 2) | ((r >> 2) & 3)
+//     D =  32   swz(r) = (r >> 2) & 3
+// (With padded rows only 4-byte-per-lane loads fit a row, and those run at a quarter of the rate; through registers, as the
+// 64-wide tiles used to be staged, the loads cost 16 registers and an LDS write each.)
 template <int D, int ROWS = TILE, int THREADS = kThreads> struct Tile {
-  static constexpr bool DIRECT = D == 128;
-  static constexpr int LD = DIRECT ? D : D + 8;
+  static constexpr int LD = D;
   static constexpr int ELEMS = ROWS * LD;
-  static constexpr int PER_THREAD = ROWS * D / 8 / THREADS;
-  __device__ static constexpr int swz(int r) { return ((r & 7) << 1) | ((r >> 3) & 1); }
-
-  // rows [row0, row0+ROWS) of a [*, ld] matrix, columns [0, D); rows >= nrows and columns >= d (the head's own width,
-  // a multiple of 8, when it is narrower than the tile) read as zero
-  __device__ static void load_global(const bf16* __restrict__ g, int64_t ld, int row0, int nrows, bf16x8 (&reg)[PER_THREAD], int d) {
-#pragma unroll
-    for (int p = 0; p < PER_THREAD; ++p) {
-      const int v = threadIdx.x + THREADS * p;
-      const int row = v / (D / 8), c = (v % (D / 8)) * 8;
-      bf16x8 val = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (row0 + row < nrows && c < d) val = *reinterpret_cast<const bf16x8*>(g + (int64_t)(row0 + row) * ld + c);
-      reg[p] = val;
-    }
+  __device__ static constexpr int swz(int r) {
+    return D == 128 ? ((r & 7) << 1) | ((r >> 3) & 1) : D == 64 ? (((r >> 1) & 1) << 2) | ((r >> 2) & 3) : (r >> 2) & 3;
   }
-  // The same rows straight from global memory into LDS, no registers in between (D = 128): 16 bytes per lane, a load
-  // instruction fills 4 rows.  rsrc covers exactly one sample of the [*, ld_bytes/2] matrix, col_bytes is the head's
+  static constexpr int FLIP8 = D == 128 ? 1 : 2;          // swz(r + 8) = swz(r) ^ FLIP8 for r < 8
+
+  // rsrc covers exactly one sample of the [*, ld_bytes/2] matrix, col_bytes is the head's
   // column offset.  Rows past the sample's end and chunks past the head's own width d are beyond the buffer's range
   // (every part of the address is in the range-checked offset): the hardware makes them zeros; callers mask such keys.
   // The loads are asynchronous: wait for vmcnt(0) and a workgroup barrier before reading the tile.
-  static constexpr int NW = THREADS / 64, LOADS = ROWS / 4, PER_WAVE = LOADS / NW;
+  static constexpr int NW = THREADS / 64, RPL = 512 / D, LOADS = ROWS / RPL, PER_WAVE = LOADS >= NW ? LOADS / NW : 1;      // RPL: rows per load
+  static_assert(LOADS % NW == 0 || NW % LOADS == 0, "loads split evenly over the wavefronts");
   // the part of the offset that belongs to the lane (the same for every tile: the compiler keeps it out of the loops)
   // (wave: this wavefront's place among the THREADS / 64 that stage the tile; by default its place in the block)
   __device__ static unsigned stage_lane(int j, unsigned ld_bytes, int d, int wave = -1) {
     if (wave < 0) wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int row = (wave * PER_WAVE + j) * 4 + (lane >> 4);
-    const int c = (lane & 15) ^ swz(row);
+    const int row = (wave * PER_WAVE + j) * RPL + lane / (D / 8);
+    const int c = (lane % (D / 8)) ^ swz(row);
     return c * 8 < d ? (unsigned)row * ld_bytes + (unsigned)c * 16 : 0x80000000u;
   }
   // The loads are issued behind the compiler's back: it tracks loads that write LDS, cannot tell one buffer from
@@ -93,34 +82,22 @@ template <int D, int ROWS = TILE, int THREADS = kThreads> struct Tile {
   // tile).  Callers wait (vmcnt(0)) and synchronise before they read what was staged.
   __device__ static void stage_one(i32x4 rsrc, int j, unsigned tile_bytes, unsigned ld_bytes, lds_bf16* lds, int d) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned dst = (unsigned)(uintptr_t)(lds + (wave * PER_WAVE + j) * 4 * LD);
+    if (LOADS < NW && wave >= LOADS) return;               // (a tile with fewer loads than wavefronts)
+    const unsigned dst = (unsigned)(uintptr_t)(lds + (wave * PER_WAVE + j) * RPL * LD);
     const unsigned off = stage_lane(j, ld_bytes, d) + tile_bytes;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(off), "s"(rsrc) : "m0");
   }
   __device__ static void stage(i32x4 rsrc, unsigned col_bytes, unsigned ld_bytes, int row0, lds_bf16* lds, int d) {
-    static_assert(DIRECT && LOADS % NW == 0, "rows of 256 bytes, loads split evenly over the wavefronts");
 #pragma unroll
     for (int j = 0; j < PER_WAVE; ++j) stage_one(rsrc, j, (unsigned)row0 * ld_bytes + col_bytes, ld_bytes, lds, d);
-  }
-  __device__ static void store_lds(lds_bf16* lds, const bf16x8 (&reg)[PER_THREAD]) {
-#pragma unroll
-    for (int p = 0; p < PER_THREAD; ++p) {
-      const int v = threadIdx.x + THREADS * p;
-      const int row = v / (D / 8), c = v % (D / 8);
-      *reinterpret_cast<LDS_AS bf16x8*>(lds + row * LD + (DIRECT ? c ^ swz(row) : c) * 8) = reg[p];
-    }
   }
   // operand with MFMA rows = tile rows [rb, rb+32), contraction over d in [kk, kk+16)   (rb: a multiple of 16 rows from
   // the tile's first row, so that a row's place in its group of 16 is the lane's)
   __device__ static bf16x8 frag_rows(const lds_bf16* lds, int rb, int kk) {
     const int lane = threadIdx.x & 63;
-    if constexpr (DIRECT) {
-      // chunk (kk/8 + h) ^ swz = (kk/8) ^ (h ^ swz): the lane's part once, the fragment's part as an XOR of the byte address
-      const unsigned own = (unsigned)(lane & 31) * (LD * 2) + (unsigned)(((lane >> 5) ^ swz(lane & 15)) << 4);
-      return *reinterpret_cast<const LDS_AS bf16x8*>((const LDS_AS char*)lds + rb * (LD * 2) + (own ^ (unsigned)(kk * 2)));
-    } else {
-      return *reinterpret_cast<const LDS_AS bf16x8*>(lds + (rb + (lane & 31)) * LD + kk + (lane >> 5) * 8);
-    }
+    // chunk (kk/8 + h) ^ swz = (kk/8) ^ (h ^ swz): the lane's part once, the fragment's part as an XOR of the byte address
+    const unsigned own = (unsigned)(lane & 31) * (LD * 2) + (unsigned)(((lane >> 5) ^ swz(lane & 15)) << 4);
+    return *reinterpret_cast<const LDS_AS bf16x8*>((const LDS_AS char*)lds + rb * (LD * 2) + (own ^ (unsigned)(kk * 2)));
   }
   // operand with MFMA rows = d in [db, db+32), contraction over 16 tile rows in the order the
   // accumulator of a preceding 32x32 product holds them: slot 4c+i of half-wave h is tile row
@@ -128,19 +105,12 @@ template <int D, int ROWS = TILE, int THREADS = kThreads> struct Tile {
   __device__ static bf16x8 frag_cols(const lds_bf16* lds, int db, int tb) {
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4, i = lane & 15;
-    s16x4 lo, hi;
-    if constexpr (DIRECT) {
-      // rows r and r + 8 (r < 8): swz(r + 8) = swz(r) | 1, so the second read is the first with chunk bit 0 flipped
-      const int r = 4 * (g >> 1) + (i >> 2);
-      const unsigned own = (unsigned)r * (LD * 2) + (unsigned)(((2 * (g & 1) + ((i & 3) >> 1)) ^ swz(r)) << 4) + 8u * (i & 1);
-      const LDS_AS char* p0 = (const LDS_AS char*)lds + tb * (LD * 2);
-      lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + (own ^ (unsigned)(db * 2))));
-      hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 8 * (LD * 2) + ((own ^ 16u) ^ (unsigned)(db * 2))));
-    } else {
-      const lds_bf16* p0 = lds + (tb + 4 * (g >> 1) + (i >> 2)) * LD + db + 16 * (g & 1) + 4 * (i & 3);
-      lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0));
-      hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 8 * LD));
-    }
+    // rows r and r + 8 (r < 8): the second read is the first with a chunk bit flipped
+    const int r = 4 * (g >> 1) + (i >> 2);
+    const unsigned own = (unsigned)r * (LD * 2) + (unsigned)(((2 * (g & 1) + ((i & 3) >> 1)) ^ swz(r)) << 4) + 8u * (i & 1);
+    const LDS_AS char* p0 = (const LDS_AS char*)lds + tb * (LD * 2);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + (own ^ (unsigned)(db * 2))));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(p0 + 8 * (LD * 2) + ((own ^ (16u * FLIP8)) ^ (unsigned)(db * 2))));
     union { struct { s16x4 a, b; } s; bf16x8 v; } u;
     u.s.a = lo; u.s.b = hi;
     return u.v;
@@ -179,10 +149,9 @@ __device__ void load_row_frags(const bf16* __restrict__ g, int64_t ld, int row0,
 // with R2 reads each: the fragments of the first kAhead products are requested before the first product, then each
 // product is followed by the request for the product kAhead places later.  (Left alone, the compiler waits for each
 // fragment right before the product that uses it, and the matrix core idles for an LDS round trip every time.)
-template <int N1, int R1, int N2 = 0, int R2 = 0, int kAhead = 4>
+template <int N1, int R1, int N2 = 0, int R2 = 0>
 __device__ __forceinline__ void lds_ahead_schedule() {
-  constexpr int N = N1 + N2;
-  static_assert(N1 >= kAhead, "the first run covers the look-ahead");
+  constexpr int N = N1 + N2, kAhead = N1 < 4 ? N1 : 4;
   __builtin_amdgcn_sched_group_barrier(0x100, kAhead * R1, 0);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -258,6 +227,8 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int64_t ld = 3 * (int64_t)H;
   const bf16* base = qkv + (int64_t)n * S * ld + a * d;
+  const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
+  const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
   // Under a causal mask the work of a query tile grows with its index, and a launch has about as many blocks as the
   // chip has slots, so nothing would even the load out: each block takes tile x and then tile ntq-1-x, whose key
@@ -281,18 +252,16 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
 
   const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
   const int ntiles = (kv_end + TILE - 1) / TILE;
-  bf16x8 rk[TL::PER_THREAD], rv[TL::PER_THREAD];
-  TL::load_global(base + H, ld, 0, S, rk, d);
-  TL::load_global(base + 2 * H, ld, 0, S, rv, d);
-  TL::store_lds(Ks(0), rk);
-  TL::store_lds(Vs(0), rv);
+  TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
+  TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
   __syncthreads();
 
   for (int kt = 0; kt < ntiles; ++kt) {
     const int cur = kt & 1, t0 = kt * TILE;
     if (kt + 1 < ntiles) {
-      TL::load_global(base + H, ld, t0 + TILE, S, rk, d);
-      TL::load_global(base + 2 * H, ld, t0 + TILE, S, rv, d);
+      TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, t0 + TILE, Ks(cur ^ 1), d);
+      TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, t0 + TILE, Vs(cur ^ 1), d);
     }
     if (!CAUSAL || t0 <= q0 + 31) {
       // All K fragments of the tile are read before the first MFMA needs one, and the two 32-key blocks accumulate
@@ -365,10 +334,7 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
             o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[dt], pf, o[dt], 0, 0, 0);
         }
     }
-    if (kt + 1 < ntiles) {
-      TL::store_lds(Ks(cur ^ 1), rk);
-      TL::store_lds(Vs(cur ^ 1), rv);
-    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
   }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -385,10 +351,16 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
 // (o = o0 2^(m0-m) + o1 2^(m1-m), likewise the sums).  While one wavefront of a SIMD runs its softmax on the vector
 // unit the other's MFMAs keep the matrix core busy.
 constexpr int kThreads8 = 512;
+// Wavefronts per SIMD the eight-wavefront kernels are compiled for.  A head of 64 or less is bound by the softmax arithmetic (about
+// 40 clocks of the vector unit per score against 8 to 16 of the matrix core) and by waits; within 128 registers two blocks share a
+// compute unit and cover each other's (32 heads of 64, 2 x 2048 tokens, causal: forward 59 -> 51 us).  The backward keeps too much at
+// 64 (within 128 registers it spills: 173 -> 359 us); at 128 the accumulators alone rule it out.
+template <int D> constexpr int kFwdWaves = D == 128 ? 2 : 4;
+template <int D> constexpr int kBwdWaves = D == 32 ? 4 : 2;
 
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(kThreads8)
-attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale) {
+__global__ void __launch_bounds__(kThreads8, kFwdWaves<D>)
+attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale, int paired) {
   typedef Tile<D, 128, kThreads8> TL;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
@@ -406,9 +378,9 @@ attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __re
   const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
   const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
-  const int ntq = (S + 127) / 128;                  // causal: query tile x, then its mirror tile (equal work per block)
-  for (int pass = 0; pass < (CAUSAL ? 2 : 1); ++pass) {
-    const int qt = pass == 0 ? blk.x : ntq - 1 - blk.x;
+  const int ntq = (S + 127) / 128;                  // causal, paired: query tile x, then its mirror tile (equal work per block)
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
+    const int qt = pass == 0 && (paired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
     if (pass == 1 && qt == blk.x) break;
     const int q0 = qt * 128 + qsub * 32;
     const int q = q0 + (lane & 31);
@@ -424,29 +396,16 @@ attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __re
 
     const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
     const int ntiles = (kv_end + 127) / 128;
-    bf16x8 rk[TL::DIRECT ? 1 : TL::PER_THREAD], rv[TL::DIRECT ? 1 : TL::PER_THREAD];   // register staging (D = 64)
-    if constexpr (TL::DIRECT) {
-      TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
-      TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
-    } else {
-      TL::load_global(base + H, ld, 0, S, rk, d);
-      TL::load_global(base + 2 * H, ld, 0, S, rv, d);
-      TL::store_lds(Ks(0), rk);
-      TL::store_lds(Vs(0), rv);
-    }
+    TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
+    TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wavefront's rows have landed
     __syncthreads();
 
     for (int kt = 0; kt < ntiles; ++kt) {
       const int cur = kt & 1;
       if (kt + 1 < ntiles) {                           // the next stage flies meanwhile
-        if constexpr (TL::DIRECT) {
-          TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * 128, Ks(cur ^ 1), d);
-          TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * 128, Vs(cur ^ 1), d);
-        } else {
-          TL::load_global(base + H, ld, (kt + 1) * 128, S, rk, d);
-          TL::load_global(base + 2 * H, ld, (kt + 1) * 128, S, rv, d);
-        }
+        TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * 128, Ks(cur ^ 1), d);
+        TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * 128, Vs(cur ^ 1), d);
       }
       const int t0 = kt * 128 + kh * 64;            // this wavefront's 64 keys
       const lds_bf16* Kt = Ks(cur) + kh * 64 * TL::LD;
@@ -509,12 +468,6 @@ attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __re
               o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_cols(Vt, dt * 32, tb * 32 + 16 * jj), pf, o[dt], 0, 0, 0);
           }
         lds_ahead_schedule<D / 8, 2>();
-      }
-      if constexpr (!TL::DIRECT) {
-        if (kt + 1 < ntiles) {
-          TL::store_lds(Ks(cur ^ 1), rk);
-          TL::store_lds(Vs(cur ^ 1), rv);
-        }
       }
       __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
       __syncthreads();
@@ -603,9 +556,8 @@ __device__ __forceinline__ void turn_products(const lds_bf16* Vt, const lds_bf16
 // loads are issued behind the compiler's back (it would make the next transposing LDS read wait for them).
 template <int D, bool CAUSAL>
 __global__ void __launch_bounds__(kThreads8)
-attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale) {
+attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale, int paired) {
   typedef Tile<D, 128, kThreads8> TL;
-  static_assert(TL::DIRECT, "rows of 256 bytes");
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Ks = [&](int st) { return smem + st * 2 * TL::ELEMS; };
@@ -635,8 +587,8 @@ attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float*
   };
   const float c2 = scale * kLog2e;
   const int ntq = (S + 127) / 128;
-  for (int pass = 0; pass < (CAUSAL ? 2 : 1); ++pass) {
-    const int qt = pass == 0 ? blk.x : ntq - 1 - blk.x;
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
+    const int qt = pass == 0 && (paired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;
     if (pass == 1 && qt == blk.x) break;
     const int q0 = qt * 128 + qsub * 32;
     const int q = q0 + (lane & 31);
@@ -792,46 +744,6 @@ attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float*
   }
 }
 
-// ------------------------------------------------------------------------------------ rowsum(dO * O)
-// dvec[n, a, s] = sum_d dO[s, a*D + d] * O[s, a*D + d]; a head's D values sit in D/8 consecutive lanes
-template <int D>
-__global__ void __launch_bounds__(kThreads)
-attn_dvec_kernel(const bf16* __restrict__ O, const bf16* __restrict__ dO, float* __restrict__ dvec, int rows, int S, int H, int A) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + wave;
-  if (row >= rows) return;
-  const int n = row / S, s = row % S;
-  for (int v = lane; v < H / 8; v += 64) {
-    float a8[8], b8[8];
-    load_vec<bf16>(O + (int64_t)row * H + v * 8, a8);
-    load_vec<bf16>(dO + (int64_t)row * H + v * 8, b8);
-    float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc += a8[i] * b8[i];
-#pragma unroll
-    for (int o = 1; o < D / 8; o <<= 1) acc += __shfl_xor(acc, o, 64);
-    if ((lane & (D / 8 - 1)) == 0) dvec[((int64_t)n * A + (v * 8) / D) * S + s] = acc;
-  }
-}
-
-// the same for a head width d that is not a power of two: one thread per (token, head), d/8 vectors each
-__global__ void __launch_bounds__(kThreads)
-attn_dvec_any_kernel(const bf16* __restrict__ O, const bf16* __restrict__ dO, float* __restrict__ dvec, int rows, int S, int H, int A) {
-  const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (idx >= (int64_t)rows * A) return;
-  const int row = (int)(idx / A), a = (int)(idx % A), d = H / A;
-  const int n = row / S, s = row % S;
-  float acc = 0.f;
-  for (int v = 0; v < d / 8; ++v) {
-    float a8[8], b8[8];
-    load_vec<bf16>(O + (int64_t)row * H + a * d + v * 8, a8);
-    load_vec<bf16>(dO + (int64_t)row * H + a * d + v * 8, b8);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc += a8[i] * b8[i];
-  }
-  dvec[((int64_t)n * A + a) * S + s] = acc;
-}
-
 // ------------------------------------------------------------------------------------ dQ
 // A block owns 128 queries (causal: tile x, then its mirror tile) and walks the keys they see in stages of 128.  Eight
 // wavefronts, as in the forward kernel: wavefront w takes the 32 queries of block w & 3 and the 64 keys of half w >> 2
@@ -839,10 +751,10 @@ attn_dvec_any_kernel(const bf16* __restrict__ O, const bf16* __restrict__ dO, fl
 // The products are taken transposed (S^T = K Q^T, dP^T = V dO^T), so that a lane's 16 values belong to one query and
 // its statistics are two scalars, and dS^T is at once the operand of dQ^T += K^T dS^T.
 template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads8)
-attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
-               const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
-                const float* __restrict__ rot) {
+__global__ void __launch_bounds__(kThreads8, kBwdWaves<D>)
+attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
+               float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+               const float* __restrict__ rot, int paired) {
   typedef Tile<D, 128, kThreads8> TL;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
@@ -860,9 +772,9 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const 
   const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
   const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
-  const int ntq = (S + 127) / 128;                 // causal: query tiles x and ntq-1-x in turn (equal work per block)
-  for (int pass = 0; pass < (CAUSAL ? 2 : 1); ++pass) {
-  const int qt = pass == 0 ? blk.x : ntq - 1 - blk.x;
+  const int ntq = (S + 127) / 128;                 // causal, paired: query tiles x and ntq-1-x in turn (equal work per block)
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
+  const int qt = pass == 0 && (paired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
   if (pass == 1 && qt == blk.x) break;
   const int q0 = qt * 128 + qsub * 32;
   const int q = q0 + (lane & 31);
@@ -872,7 +784,19 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const 
   load_row_frags<D>(dO + (int64_t)n * S * H + a * d, H, q0, S, dof, d);
   const int64_t stat = ((int64_t)n * A + a) * S + q;
   const float lse2 = (q < S) ? lse[stat] * kLog2e : 0.f;
-  const float dv = (q < S) ? dvec[stat] : 0.f;
+  // dvec = rowsum(dO * O) of this lane's query, formed here (dO's row is in registers) and left for the dK/dV kernel, which runs next;
+  // a kernel of its own took 2.5 to 11 us
+  float dv = 0.f;
+  {
+    bf16x8 of[D / 16];
+    load_row_frags<D>(O + (int64_t)n * S * H + a * d, H, q0, S, of, d);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dv += (float)of[kk][e] * (float)dof[kk][e];
+    dv += __shfl_xor(dv, 32, 64);
+  }
+  if (kh == 0 && h == 0 && q < S) dvec[stat] = dv;
 
   f32x16 dq[D / 32];
 #pragma unroll
@@ -882,29 +806,16 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const 
 
   const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
   const int ntiles = (kv_end + 127) / 128;
-  bf16x8 rk[TL::DIRECT ? 1 : TL::PER_THREAD], rv[TL::DIRECT ? 1 : TL::PER_THREAD];   // register staging (D = 64)
-  if constexpr (TL::DIRECT) {
-    TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
-    TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
-  } else {
-    TL::load_global(base + H, ld, 0, S, rk, d);
-    TL::load_global(base + 2 * H, ld, 0, S, rv, d);
-    TL::store_lds(Ks(0), rk);
-    TL::store_lds(Vs(0), rv);
-  }
+  TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
+  TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
   __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
   __syncthreads();
 
   for (int kt = 0; kt < ntiles; ++kt) {
     const int cur = kt & 1;
     if (kt + 1 < ntiles) {                             // the next stage flies meanwhile
-      if constexpr (TL::DIRECT) {
-        TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * 128, Ks(cur ^ 1), d);
-        TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * 128, Vs(cur ^ 1), d);
-      } else {
-        TL::load_global(base + H, ld, (kt + 1) * 128, S, rk, d);
-        TL::load_global(base + 2 * H, ld, (kt + 1) * 128, S, rv, d);
-      }
+      TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * 128, Ks(cur ^ 1), d);
+      TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * 128, Vs(cur ^ 1), d);
     }
     const int t0 = kt * 128 + kh * 64;                 // this wavefront's 64 keys
     const lds_bf16* Kt = Ks(cur) + kh * 64 * TL::LD;
@@ -946,12 +857,6 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const 
         if (tb == 1) lds_ahead_schedule<D / 16, 2>();
       }
     }
-    if constexpr (!TL::DIRECT) {
-      if (kt + 1 < ntiles) {
-        TL::store_lds(Ks(cur ^ 1), rk);
-        TL::store_lds(Vs(cur ^ 1), rv);
-      }
-    }
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
   }
@@ -987,10 +892,10 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const 
 // kernel past 256 registers, where the accumulators move to the second register file and every score has to be copied
 // back for the vector unit.  Query and dO tiles are double-buffered; at D = 128 they come straight from global memory.
 template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads8)
+__global__ void __launch_bounds__(kThreads8, kBwdWaves<D>)
 attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
                 const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
-                const float* __restrict__ rot) {
+                const float* __restrict__ rot, int paired) {
   typedef Tile<D, TILE, kThreads8> TL;
   typedef Tile<D, 128, kThreads8> TKV;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -1016,23 +921,15 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
   const float* lse_base = lse + ((int64_t)n * A + a) * S;
   const float* dv_base = dvec + ((int64_t)n * A + a) * S;
   const float c2 = scale * kLog2e;
-  const int ntk = (S + 127) / 128;                 // causal: key tiles x and ntk-1-x in turn (early key tiles see the most queries)
-  for (int pass = 0; pass < (CAUSAL ? 2 : 1); ++pass) {
+  const int ntk = (S + 127) / 128;                 // causal, paired: key tiles x and ntk-1-x in turn (early key tiles see the most queries)
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
   const int tt = pass == 0 ? blk.x : ntk - 1 - blk.x;
   if (pass == 1 && tt == blk.x) break;
   const int t0 = tt * 128 + kg * 32;               // this wavefront's 32 keys
   const int t = t0 + (lane & 31);
 
-  if constexpr (TL::DIRECT) {
-    TKV::stage(rs_qkv, (unsigned)H * 2 + col_bytes, (unsigned)ld * 2, tt * 128, Ks, d);
-    TKV::stage(rs_qkv, (unsigned)H * 4 + col_bytes, (unsigned)ld * 2, tt * 128, Vs, d);
-  } else {
-    bf16x8 rkv[TKV::PER_THREAD];
-    TKV::load_global(base + H, ld, tt * 128, S, rkv, d);
-    TKV::store_lds(Ks, rkv);
-    TKV::load_global(base + 2 * H, ld, tt * 128, S, rkv, d);
-    TKV::store_lds(Vs, rkv);
-  }
+  TKV::stage(rs_qkv, (unsigned)H * 2 + col_bytes, (unsigned)ld * 2, tt * 128, Ks, d);
+  TKV::stage(rs_qkv, (unsigned)H * 4 + col_bytes, (unsigned)ld * 2, tt * 128, Vs, d);
 
   f32x16 dk[D / 32], dvv[D / 32];
 #pragma unroll
@@ -1050,16 +947,8 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
       if (r < S) rstat = threadIdx.x < 64 ? lse_base[r] * kLog2e : dv_base[r];
     }
   };
-  bf16x8 rq[TL::DIRECT ? 1 : TL::PER_THREAD], rdo[TL::DIRECT ? 1 : TL::PER_THREAD];   // register staging (D = 64)
-  if constexpr (TL::DIRECT) {
-    TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, first * TILE, Qs(0), d);
-    TL::stage(rs_do, col_bytes, (unsigned)H * 2, first * TILE, dOs(0), d);
-  } else {
-    TL::load_global(base, ld, first * TILE, S, rq, d);
-    TL::load_global(dObase, H, first * TILE, S, rdo, d);
-    TL::store_lds(Qs(0), rq);
-    TL::store_lds(dOs(0), rdo);
-  }
+  TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, first * TILE, Qs(0), d);
+  TL::stage(rs_do, col_bytes, (unsigned)H * 2, first * TILE, dOs(0), d);
   load_stats(first * TILE);
   if (threadIdx.x < 128) stats[threadIdx.x] = rstat;
   __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
@@ -1068,13 +957,8 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
   for (int it = first; it < ntiles; ++it) {
     const int cur = (it - first) & 1, qb0 = it * TILE;
     if (it + 1 < ntiles) {                             // the next tile flies into the other stage meanwhile
-      if constexpr (TL::DIRECT) {
-        TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, qb0 + TILE, Qs(cur ^ 1), d);
-        TL::stage(rs_do, col_bytes, (unsigned)H * 2, qb0 + TILE, dOs(cur ^ 1), d);
-      } else {
-        TL::load_global(base, ld, qb0 + TILE, S, rq, d);
-        TL::load_global(dObase, H, qb0 + TILE, S, rdo, d);
-      }
+      TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, qb0 + TILE, Qs(cur ^ 1), d);
+      TL::stage(rs_do, col_bytes, (unsigned)H * 2, qb0 + TILE, dOs(cur ^ 1), d);
       load_stats(qb0 + TILE);
     }
     const LDS_AS float* st = stats + cur * 128;
@@ -1127,12 +1011,6 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
       }
       lds_ahead_schedule<NP, 2>();
     }
-    if constexpr (!TL::DIRECT) {
-      if (it + 1 < ntiles) {
-        TL::store_lds(Qs(cur ^ 1), rq);
-        TL::store_lds(dOs(cur ^ 1), rdo);
-      }
-    }
     if (it + 1 < ntiles && threadIdx.x < 128) stats[(cur ^ 1) * 128 + threadIdx.x] = rstat;
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
@@ -1179,33 +1057,35 @@ int reserve_lds(K kern, size_t bytes) {
   return CEPHALO_OK;
 }
 
+// Causal launches: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute unit of their own at
+// once: then the launch lasts as long as the longest tile, not as the longest and the shortest (8 heads of 80, 700 tokens, 48 tiles: forward 22 ->
+// 15 us, backward 61 -> 44).  Beyond that single tiles, longest first, lose (25 heads of 64, 2 x 1024 tokens, 400 tiles: backward 56 paired, 78).
+inline bool pair_tiles(int nt, int A, int m) { return (int64_t)nt * A * m > 256; }
+
 template <int D, bool CAUSAL>
 int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hipStream_t s) {
   const int nt = (S + 127) / 128;
-  dim3 grid(CAUSAL ? (nt + 1) / 2 : nt, A, m);     // causal: a block takes a tile and its mirror image
+  const float scale = 1.0f / sqrtf((float)(H / A));
   if constexpr (CAUSAL) {
-    // one paired block per compute unit: eight wavefronts, the staged keys split between two groups
-    const size_t lds = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16);
-    if constexpr (Tile<D, 128, kThreads8>::DIRECT) {
-      // (tiles staged straight into LDS: the two groups take turns on the matrix core and the vector unit)
-      auto kern = attn_fwd_turns_kernel<D, CAUSAL>;
-      int rc = reserve_lds(kern, lds);
-      if (rc != CEPHALO_OK) return rc;
-      kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, 1.0f / sqrtf((float)(H / A)));
-    } else {
-      auto kern = attn_fwd8_kernel<D, CAUSAL>;
-      int rc = reserve_lds(kern, lds);
-      if (rc != CEPHALO_OK) return rc;
-      kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, 1.0f / sqrtf((float)(H / A)));
-    }
+    // eight wavefronts, the staged keys split between two groups; at D = 128 the two groups take turns on the matrix core and the
+    // vector unit
+    const bool paired = pair_tiles(nt, A, m);
+    dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
+    const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16 + 2) * 64 * sizeof(float);
+    const size_t lds = staging > merge ? staging : merge;
+    auto kern = [] { if constexpr (D == 128) return attn_fwd_turns_kernel<D, CAUSAL>; else return attn_fwd8_kernel<D, CAUSAL>; }();
+    int rc = reserve_lds(kern, lds);
+    if (rc != CEPHALO_OK) return rc;
+    kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, scale, paired);
   } else {
     // uniform tiles: two independent four-wavefront blocks per compute unit run out of phase with each other
     // (measured 12 % faster than the eight-wavefront form, whose wavefronts move in step between barriers)
+    dim3 grid(nt, A, m);
     const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);
     auto kern = attn_fwd_kernel<D, CAUSAL>;
     int rc = reserve_lds(kern, lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads, lds, s>>>(qkv, O, lse, S, H, A, 1.0f / sqrtf((float)(H / A)));
+    kern<<<grid, kThreads, lds, s>>>(qkv, O, lse, S, H, A, scale);
   }
   CEPHALO_CHECK_LAUNCH("attn_fwd_mfma");
   return CEPHALO_OK;
@@ -1214,20 +1094,18 @@ int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hi
 template <int D, bool CAUSAL, bool ROT>
 int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, float* dvec, bf16* dqkv,
             int m, int S, int H, int A, const float* rot, hipStream_t s) {
-  const int d = H / A;
-  const float scale = 1.0f / sqrtf((float)d);
-  const int rows = m * S;
-  if (d == D) attn_dvec_kernel<D><<<(rows + 3) / 4, kThreads, 0, s>>>(O, dO, dvec, rows, S, H, A);
-  else if (d == 32) attn_dvec_kernel<32><<<(rows + 3) / 4, kThreads, 0, s>>>(O, dO, dvec, rows, S, H, A);
-  else attn_dvec_any_kernel<<<(int)(((int64_t)rows * A + kThreads - 1) / kThreads), kThreads, 0, s>>>(O, dO, dvec, rows, S, H, A);
+  const float scale = 1.0f / sqrtf((float)(H / A));
   const int nt = (S + 127) / 128;
-  dim3 grid(CAUSAL ? (nt + 1) / 2 : nt, A, m);     // causal: a block takes a tile and its mirror image
+  const bool paired = CAUSAL && pair_tiles(nt, A, m);
+  dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
   {
-    const size_t lds = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16);   // two stages of 128 keys and values
+    // two stages of 128 keys and values or, at the end, the merge of the halves
+    const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16) * 64 * sizeof(float);
+    const size_t lds = staging > merge ? staging : merge;
     auto kern = attn_dq_kernel<D, CAUSAL, ROT>;
     int rc = reserve_lds(kern, lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot);
+    kern<<<grid, kThreads8, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
   }
   {
     // staging (2 stages of Q and dO, the keys, the values, the row statistics) or, at the end, the merge of the halves
@@ -1237,7 +1115,7 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
     auto kern = attn_dkv_kernel<D, CAUSAL, ROT>;
     int rc = reserve_lds(kern, lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot);
+    kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
   }
   CEPHALO_CHECK_LAUNCH("attn_bwd_mfma");
   return CEPHALO_OK;
@@ -1259,9 +1137,10 @@ int launch_attn_fwd_mfma(const bf16* qkv, bf16* O, float* lse, int m, int S, int
   if (H % 8 != 0 || !aligned16(qkv) || !aligned16(O)) return fail(CEPHALO_EINVAL, "attention: rows must be 16-byte aligned");
   if ((int64_t)S * 3 * H * 2 >= (int64_t)1 << 31)
     return fail(CEPHALO_EUNSUPPORTED, "attention: one sample of qkv (%lld bytes) exceeds the 2 GiB a buffer offset reaches", (long long)S * 3 * H * 2);
-  // a head narrower than the 64- or 128-wide tile runs on that tile with its further columns held at zero
+  // a head that is not 32, 64 or 128 wide runs on the next of these tiles with the further columns held at zero
   if (A <= 0 || H % A != 0 || D % 8 != 0 || D > 128)
     return fail(CEPHALO_EUNSUPPORTED, "attention (matrix-core kernel): head dim %d is not a multiple of 8 up to 128", A > 0 ? D : 0);
+  if (D <= 32) return causal ? fwd_cfg<32, true>(qkv, O, lse, m, S, H, A, s) : fwd_cfg<32, false>(qkv, O, lse, m, S, H, A, s);
   if (D <= 64) return causal ? fwd_cfg<64, true>(qkv, O, lse, m, S, H, A, s) : fwd_cfg<64, false>(qkv, O, lse, m, S, H, A, s);
   return causal ? fwd_cfg<128, true>(qkv, O, lse, m, S, H, A, s) : fwd_cfg<128, false>(qkv, O, lse, m, S, H, A, s);
 }
@@ -1275,6 +1154,7 @@ int launch_attn_bwd_mfma(const bf16* qkv, const bf16* O, const bf16* dO, const f
     return fail(CEPHALO_EUNSUPPORTED, "attention: one sample of qkv (%lld bytes) exceeds the 2 GiB a buffer offset reaches", (long long)S * 3 * H * 2);
   if (A <= 0 || H % A != 0 || D % 8 != 0 || D > 128)
     return fail(CEPHALO_EUNSUPPORTED, "attention (matrix-core kernel): head dim %d is not a multiple of 8 up to 128", A > 0 ? D : 0);
+  if (D <= 32) return bwd_pick<32>(qkv, O, dO, lse, dvec, dqkv, m, S, H, A, causal, rot, s);
   if (D <= 64) return bwd_pick<64>(qkv, O, dO, lse, dvec, dqkv, m, S, H, A, causal, rot, s);
   return bwd_pick<128>(qkv, O, dO, lse, dvec, dqkv, m, S, H, A, causal, rot, s);
 }

@@ -159,3 +159,46 @@ def test_weight_gradient_tiles(T, N, K):
     finally:
         C.binding.cephalo_gemm_side_by_side(before)
     assert (np.abs(first.double().cpu().numpy() - ref) <= bound).all()
+
+
+def _attention64(qkv, dO, m, S, A, d, causal):
+    q, k, v = [t.reshape(m, S, A, d).transpose(1, 2).contiguous().requires_grad_(True) for t in qkv.double().view(m * S, 3, A * d).unbind(1)]
+    z = torch.matmul(q, k.transpose(-1, -2).contiguous()) / d ** 0.5
+    if causal:
+        z = z.masked_fill(torch.ones(S, S, dtype=torch.bool, device=z.device).triu(1), float("-inf"))
+    o = torch.matmul(torch.softmax(z, -1), v)
+    o.backward(dO.double().view(m, S, A, d).transpose(1, 2).contiguous())
+    flat = lambda t: t.transpose(1, 2).reshape(m * S, A * d)
+    return flat(o.detach()), torch.cat([flat(q.grad), flat(k.grad), flat(v.grad)], 1), torch.logsumexp(z, -1).detach()
+
+
+# head widths: the 32-, 64- and 128-wide tiles, full and narrower; tokens around the 32-, 64- and 128-token pieces; the last column: few tiles
+# (one per block) or more than 256 of them (a tile and its mirror image per block under the causal mask, with an odd and an even count)
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("m,S,A", [(1, 1, 1), (3, 31, 2), (1, 65, 3), (2, 129, 2), (1, 300, 90), (2, 450, 34)])
+def test_attention_tiles(m, S, A, d, causal):
+    print("attention tiles", m, S, A, d, causal, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m * S + d)
+    H = A * d
+    qkv, dO = torch.randn(m * S, 3 * H, device="cuda", generator=g).bfloat16(), torch.randn(m * S, H, device="cuda", generator=g).bfloat16()
+    ro, rg, rl = _attention64(qkv, dO, m, S, A, d, causal)
+    desc = C.layer_desc(H, A, 4 * H, S, causal, C.BF16)
+    O = torch.full((m * S, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    lse, dvec = torch.full((m, A, S), float("nan"), device="cuda"), torch.full((m, A, S), float("nan"), device="cuda")
+    dqkv = torch.full((m * S, 3 * H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    C.cephalo_op_attention_fwd(desc, qkv, O, lse, m)
+    C.cephalo_op_attention_bwd(desc, qkv, O, dO, lse, dvec, dqkv, m)
+
+    def near(got, ref, what):
+        e = (got.double() - ref).abs()
+        # bf16 operands, probabilities and results: the bound the layer tests use, relative to the tensor (a causal single token has
+        # gradients of exactly zero for queries and keys: products of rounded values that cancel, 2^-8 of their size)
+        assert e.max() <= 2e-2 * ref.abs().max() + 1e-2, (what, e.max().item(), ref.abs().max().item())
+        assert e.mean() <= 5e-3 * ref.abs().mean() + 1e-3, (what, e.mean().item(), ref.abs().mean().item())
+    near(O, ro, "O")
+    assert (lse.double() - rl).abs().max() < 2e-3
+    for i, name in enumerate(("dQ", "dK", "dV")):
+        near(dqkv[:, i * H:(i + 1) * H], rg[:, i * H:(i + 1) * H], name)
+    dv = (dO.double() * O.double()).view(m, S, A, d).sum(-1).transpose(1, 2)
+    assert (dvec.double() - dv).abs().max() <= (d + 4) * 2.0 ** -24 * (dO.double() * O.double()).abs().view(m, S, A, d).sum(-1).max()
