@@ -225,6 +225,46 @@ __global__ void __launch_bounds__(kThreads) bitonic_pass_kernel(u64* __restrict_
   if ((a > b) == ascending) { keys[i] = b; keys[l] = a; }
 }
 
+// Up to kRankMost tokens: a token's place is the number of smaller keys, counted outright.  A block ranks 64 tokens, one per lane; its 16
+// wavefronts count over a sixteenth of all tokens each.  The token compared with is the same for the whole wavefront (a scalar load), and
+// outside the block's own 64 the order of equal ids is known, so a token costs one compare and one add: 64 n / 16 of them per wavefront
+// against the network's (log2 n)^2 / 2 dependent LDS round trips (544 tokens: 18 -> 4.8 us; 8192: 50 -> 25).  The work grows with n^2,
+// so long inputs keep the network.
+constexpr int kRankMost = 16384;
+__global__ void __launch_bounds__(1024) rank_tokens_kernel(const int* __restrict__ ids, u64* __restrict__ sorted, int n, int V) {
+  __shared__ int part[16][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = blockIdx.x * 64, i = i0 + lane;
+  const int mine = clamp_id(ids[min(i, n - 1)], V);
+  const int chunk = (n + 15) / 16, j0 = min(n, wave * chunk), j1 = min(n, j0 + chunk);
+  int count = 0, j = j0;
+  auto sixteen = [&](auto smaller) {                        // (asked for together: one at a time, each compare waits for its load)
+    int id[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) id[u] = ids[j + u];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) count += smaller(clamp_id(id[u], V));
+    j += 16;
+  };
+  const int before = min(j1, i0);
+  while (j + 16 <= before) sixteen([&](int id) { return id <= mine; });      // earlier tokens: an equal id comes first
+  for (; j < before; ++j) count += clamp_id(ids[j], V) <= mine;
+  for (const int to = min(j1, i0 + 64); j < to; ++j) {
+    const int id = clamp_id(ids[j], V);
+    count += id < mine || (id == mine && j < i);
+  }
+  while (j + 16 <= j1) sixteen([&](int id) { return id < mine; });
+  for (; j < j1; ++j) count += clamp_id(ids[j], V) < mine;
+  part[wave][lane] = count;
+  __syncthreads();
+  if (wave == 0 && i < n) {
+    int place = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) place += part[w][lane];
+    sorted[place] = ((u64)(unsigned)mine << 32) | (unsigned)i;
+  }
+}
+
 int sort_pad(int n) {
   int p = kSortTile;
   while (p < n) p <<= 1;
@@ -232,6 +272,11 @@ int sort_pad(int n) {
 }
 
 int launch_sort_tokens(const int* ids, u64* keys, int n, int V, hipStream_t s) {
+  if (n <= kRankMost) {
+    rank_tokens_kernel<<<(n + 63) / 64, 1024, 0, s>>>(ids, keys, n, V);
+    CEPHALO_CHECK_LAUNCH("rank_tokens");
+    return CEPHALO_OK;
+  }
   const int npad = sort_pad(n);
   sort_keys_kernel<<<(npad + kThreads - 1) / kThreads, kThreads, 0, s>>>(ids, keys, n, npad, V);
   CEPHALO_CHECK_LAUNCH("sort_keys");
@@ -260,35 +305,56 @@ constexpr int kEmbedSeg = 32;
 
 __device__ __forceinline__ unsigned key_id(u64 k) { return (unsigned)(k >> 32); }
 
+//
+// In pass 1 a wavefront takes 256 columns of a segment (a row is H / 256 wavefronts), the segment's keys in its lanes, and asks for
+// eight positions' rows of dx0 and of the gradient at once.  (One wavefront per segment, walking the columns and waiting for each
+// position's loads in turn, took 469 us for 8192 tokens at H 2048, and 52 for 544 at 256.)
 __global__ void __launch_bounds__(kThreads)
-embed_bwd_segments_kernel(const u64* __restrict__ sorted, const float* __restrict__ dx0, float* __restrict__ g_wte,
+embed_bwd_segments_kernel(const u64* __restrict__ sorted, const float* __restrict__ dx0, float* g_wte,
                           float* __restrict__ part, int n, int H) {
-  constexpr int VN = 4;
-  const int seg = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int per_row = (H + 255) / 256;
+  const int seg = wv / per_row, col = (wv % per_row) * 256 + lane * 4;
   const int p0 = seg * kEmbedSeg;
   if (p0 >= n) return;
-  const int p1 = min(n, p0 + kEmbedSeg);
-  int i = p0;
-  while (i < p1) {
-    const unsigned id = key_id(sorted[i]);
-    int e = i + 1;
-    while (e < p1 && key_id(sorted[e]) == id) ++e;
-    const bool from_before = i == p0 && p0 > 0 && key_id(sorted[p0 - 1]) == id;
-    const bool goes_on = e == p1 && p1 < n && key_id(sorted[p1]) == id;
-    float* dst = from_before ? part + ((size_t)seg * 2 + 0) * H : (goes_on ? part + ((size_t)seg * 2 + 1) * H : g_wte + (size_t)id * H);
-    const bool add = !from_before && !goes_on;      // a whole run: onto the row; a piece: stored
-    for (int v = lane; v < H / VN; v += 64) {
-      float acc[VN] = {0.f, 0.f, 0.f, 0.f};
-      for (int j = i; j < e; ++j) {
-        float a[VN];
-        load_vec<float>(dx0 + (int64_t)(unsigned)sorted[j] * H + v * VN, a);
+  const int cnt = min(n - p0, kEmbedSeg);
+  const bool in = col < H;
+  const int c = in ? col : 0;
+  const u64 mine = sorted[p0 + min(lane, cnt - 1)];
+  const unsigned my_id = key_id(mine), my_token = (unsigned)mine;
+  const bool before = p0 > 0, after = p0 + cnt < n;
+  const unsigned id_before = before ? key_id(sorted[p0 - 1]) : 0u, id_after = after ? key_id(sorted[p0 + cnt]) : 0u;
+  auto id_at = [&](int i) { return (unsigned)__builtin_amdgcn_readlane((int)my_id, i); };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  bool from_before = before && id_before == id_at(0);       // the run being summed came in from the previous segment
+  constexpr int AT_ONCE = 8;
+  for (int g = 0; g < cnt; g += AT_ONCE) {
+    f32x4 row[AT_ONCE], old[AT_ONCE];
 #pragma unroll
-        for (int c = 0; c < VN; ++c) acc[c] += a[c];
-      }
-#pragma unroll
-      for (int c = 0; c < VN; ++c) dst[v * VN + c] = add ? dst[v * VN + c] + acc[c] : acc[c];
+    for (int u = 0; u < AT_ONCE; ++u) {
+      const int i = min(g + u, cnt - 1);
+      row[u] = *reinterpret_cast<const f32x4*>(dx0 + (int64_t)(unsigned)__builtin_amdgcn_readlane((int)my_token, i) * H + c);
+      old[u] = *reinterpret_cast<const f32x4*>(g_wte + (size_t)id_at(i) * H + c);
     }
-    i = e;
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) {
+      const int i = g + u;
+      if (i >= cnt) break;
+      acc += row[u];
+      const unsigned id = id_at(i);
+      const bool last = i == cnt - 1;
+      if (!last && id_at(min(i + 1, cnt - 1)) == id) continue;
+      const bool goes_on = last && after && id_after == id;
+      if (in) {
+        if (from_before) *reinterpret_cast<f32x4*>(part + ((size_t)seg * 2 + 0) * H + c) = acc;
+        else if (goes_on) *reinterpret_cast<f32x4*>(part + ((size_t)seg * 2 + 1) * H + c) = acc;
+        else *reinterpret_cast<f32x4*>(g_wte + (size_t)id * H + c) = old[u] + acc;       // a whole run: onto the row
+      }
+      acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      from_before = false;
+    }
   }
 }
 
@@ -697,7 +763,8 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   u64* keys = at<u64>(ws, L.keys);
   TRY(launch_sort_tokens(ids, keys, n, V, s));
   const int nseg = embed_segments(n);
-  embed_bwd_segments_kernel<<<(nseg + 3) / 4, kThreads, 0, s>>>(keys, dx_cur, G + o_wte, at<float>(ws, L.embed_part), n, H);
+  const int64_t waves = (int64_t)nseg * ((H + 255) / 256);
+  embed_bwd_segments_kernel<<<(int)((waves + 3) / 4), kThreads, 0, s>>>(keys, dx_cur, G + o_wte, at<float>(ws, L.embed_part), n, H);
   CEPHALO_CHECK_LAUNCH("embed_bwd_segments");
   embed_bwd_joins_kernel<<<(nseg + 3) / 4, kThreads, 0, s>>>(keys, G + o_wte, at<float>(ws, L.embed_part), n, H);
   CEPHALO_CHECK_LAUNCH("embed_bwd_joins");

@@ -202,3 +202,33 @@ def test_attention_tiles(m, S, A, d, causal):
         near(dqkv[:, i * H:(i + 1) * H], rg[:, i * H:(i + 1) * H], name)
     dv = (dO.double() * O.double()).view(m, S, A, d).sum(-1).transpose(1, 2)
     assert (dvec.double() - dv).abs().max() <= (d + 4) * 2.0 ** -24 * (dO.double() * O.double()).abs().view(m, S, A, d).sum(-1).max()
+
+
+@pytest.mark.parametrize("H,heads,S,b", [(320, 5, 150, 4), (64, 1, 1, 1), (256, 4, 33, 1), (264, 3, 700, 4), (8, 1, 33, 1000)])
+@pytest.mark.parametrize("spread", ["few", "many", "one"])
+def test_token_embedding_gradient(H, heads, S, b, spread):
+    """Rows of 1 to 2 wavefronts; runs of equal ids inside a segment of 32, across several, and of all tokens; 1 to 2800 tokens ranked by
+    counting, 33000 sorted by the network."""
+    V = {"few": 13, "many": 4096, "one": 5}[spread]
+    desc = C.layer_desc(H, heads, 72, S, True, C.BF16, kind=C.LAYER_LLAMA)
+    sd = C.StackDesc(desc, 1, V, 0, 0, 0)
+    g = torch.Generator(device="cuda").manual_seed(H + S)
+    P = C.cephalo_stack_param_count(sd)
+    flat = (torch.randn(P, device="cuda", generator=g) * 0.02).bfloat16()
+    ids = torch.randint(0, V, (b, S), device="cuda", generator=g, dtype=torch.int32)
+    if spread == "one":
+        ids.fill_(3)
+    targets = torch.randint(0, V, (b, S), device="cuda", generator=g, dtype=torch.int32)
+    G, loss = torch.full((P,), float("nan"), device="cuda"), torch.empty(1, device="cuda")
+    m = 500 if b == 1000 else 1
+    ws = torch.empty(C.cephalo_stack_workspace_bytes(sd, b, m), dtype=torch.uint8, device="cuda")
+    C.cephalo_stack_step(sd, flat, ids, targets, b, m, G, 64.0, loss, ws)
+    at = C.binding.cephalo_stack_workspace_regions(sd, b, m)[1]
+    n = b * S
+    dx0 = ws[at:at + 4 * n * H].view(torch.float32).view(n, H).double()
+    rows = ids.view(-1).long()
+    ref = torch.zeros(V, H, dtype=torch.float64, device="cuda").index_add_(0, rows, dx0)
+    size = torch.zeros(V, H, dtype=torch.float64, device="cuda").index_add_(0, rows, dx0.abs())
+    got = G[:V * H].view(V, H).double()
+    assert torch.isfinite(G).all() and dx0.abs().max() > 0
+    assert ((got - ref).abs() <= n * 2.0 ** -24 * size).all()
