@@ -71,14 +71,13 @@ __device__ __forceinline__ void store_share(float* lds, bool kfast, f32x4 v) {
 }
 
 template <bool VEC>
-__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmArgs<float> a) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs<float>& a, int tile_m, int tile_n) {
   __shared__ __attribute__((aligned(16))) float As[2][TB * PITCH];
   __shared__ __attribute__((aligned(16))) float Bs[2][TB * PITCH];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int group = wave >> 2;                           // which 32 k-values of a slab
   const int wm = (wave >> 1 & 1) * 16, wn = (wave & 1) * 16;
-  const int m0 = (blockIdx.z * gridDim.y + blockIdx.y) * TB, n0 = blockIdx.x * TB;
-  if (m0 >= a.M) return;
+  const int m0 = tile_m * TB, n0 = tile_n * TB;
   const bool ak = a.a_cs == 1, bk = a.b_cs == 1;
 
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -164,6 +163,23 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmArgs<float> a) {
   }
 }
 
+template <bool VEC>
+__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmArgs<float> a) {
+  const int tile_m = blockIdx.z * gridDim.y + blockIdx.y;
+  if (tile_m * TB < a.M) gemm_f32_tile<VEC>(a, tile_m, blockIdx.x);
+}
+
+// Several products in one launch (a layer's weight gradients: four launches of 8 us each, most of it waiting, are one of 11).
+struct F32Batch { int n; int first[kMaxGradGroup + 1]; int tiles_n[kMaxGradGroup]; GemmArgs<float> a[kMaxGradGroup]; };
+template <bool VEC>
+__global__ void __launch_bounds__(kThreads) gemm_f32_group_kernel(F32Batch b) {
+  int q = 0;
+  while (q + 1 < b.n && (int)blockIdx.x >= b.first[q + 1]) ++q;
+  const GemmArgs<float> a = b.a[q];
+  const int block = (int)blockIdx.x - b.first[q];
+  gemm_f32_tile<VEC>(a, block / b.tiles_n[q], block % b.tiles_n[q]);
+}
+
 // 16-byte loads of an operand: base, pitch and extent along the contiguous axis are multiples of four floats
 bool vec_ok(const float* p, int64_t rs, int64_t cs, int rows, int K) {
   if (!aligned16(p)) return false;
@@ -179,6 +195,31 @@ int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s) {
   if (vec_ok(a.A, a.a_rs, a.a_cs, a.M, a.K) && vec_ok(a.B, a.b_rs, a.b_cs, a.N, a.K)) gemm_f32_kernel<true><<<grid, kThreads, 0, s>>>(a);
   else gemm_f32_kernel<false><<<grid, kThreads, 0, s>>>(a);
   CEPHALO_CHECK_LAUNCH("gemm_f32");
+  return CEPHALO_OK;
+}
+
+int launch_gemm_f32_group(const GemmArgs<float>* a, int n, hipStream_t s) {
+  if (n <= 0 || n > kMaxGradGroup) return fail(CEPHALO_EINVAL, "gemm: %d products in one launch", n);
+  F32Batch b = {};
+  b.n = n;
+  bool vec = true;
+  int64_t blocks = 0;
+  for (int q = 0; q < n; ++q) {
+    if (a[q].M <= 0 || a[q].N <= 0 || a[q].K <= 0) return fail(CEPHALO_EINVAL, "gemm: empty problem %dx%dx%d", a[q].M, a[q].N, a[q].K);
+    b.a[q] = a[q];
+    b.tiles_n[q] = (a[q].N + TB - 1) / TB;
+    blocks += (int64_t)((a[q].M + TB - 1) / TB) * b.tiles_n[q];
+    b.first[q + 1] = (int)blocks;
+    vec = vec && vec_ok(a[q].A, a[q].a_rs, a[q].a_cs, a[q].M, a[q].K) && vec_ok(a[q].B, a[q].b_rs, a[q].b_cs, a[q].N, a[q].K);
+  }
+  if (blocks > (1 << 21)) {      // (a grid ends at 2^32 threads)
+    for (int q = 0; q < n; ++q)
+      if (const int rc = launch_gemm_f32(a[q], s); rc != CEPHALO_OK) return rc;
+    return CEPHALO_OK;
+  }
+  if (vec) gemm_f32_group_kernel<true><<<(int)blocks, kThreads, 0, s>>>(b);
+  else gemm_f32_group_kernel<false><<<(int)blocks, kThreads, 0, s>>>(b);
+  CEPHALO_CHECK_LAUNCH("gemm_f32_group");
   return CEPHALO_OK;
 }
 

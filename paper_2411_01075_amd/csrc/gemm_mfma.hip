@@ -446,8 +446,8 @@ __device__ __forceinline__ int xcd_run(int pid, int total) {
 // load, is saturated in that window while it idles in the other half.  A third buffer for A alone still fits (5 x 32 KB
 // at 256 x 256): the A tile of slab kt+2 goes into the buffer that slab kt-1 left at the previous barrier and is loaded
 // during k-step 0 of slab kt, with a whole slab to land; only the B tile is loaded after the barrier.
-template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS, int PF, bool A3 = false>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int slabs_per_split) {
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS, int PF, bool A3>
+__device__ __forceinline__ void gemm_mfma_tile(const GemmArgs<bf16>& a, int tiles_m, int tiles_n, int slabs_per_split, int block) {
   constexpr int NW = WGM * WGN;
   typedef OperandTile<BM, AK, NW> TA;
   typedef OperandTile<BN, BKF, NW> TB;
@@ -462,8 +462,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
   // column, so that the tiles an XCD works on at the same time form a compact patch sharing A row-panels and B
   // column-panels in its L2.
   const int total = tiles_m * tiles_n;
-  const int split = blockIdx.x / total;
-  int pid = blockIdx.x % total;
+  const int split = block / total;
+  int pid = block % total;
   pid = xcd_run(pid, total);
   constexpr int GROUP = 4;
   const int per_group = GROUP * tiles_n;
@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16
 // are held in registers, and the next slab's are read while this one's are multiplied: a slab costs one barrier and the larger of
 // its reads and its products.  NS stages of LDS, NS slabs of global loads in flight.
 template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int slabs_per_split) {
+__device__ __forceinline__ void gemm_ring_tile(const GemmArgs<bf16>& a, int tiles_m, int tiles_n, int slabs_per_split, int block) {
   constexpr int NW = WGM * WGN;
   typedef OperandTile<BM, AK, NW> TA;
   typedef OperandTile<BN, BKF, NW> TB;
@@ -737,8 +737,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
 
   // tile order: as above
   const int total = tiles_m * tiles_n;
-  const int split = blockIdx.x / total;
-  int pid = blockIdx.x % total;
+  const int split = block / total;
+  int pid = block % total;
   pid = xcd_run(pid, total);
   constexpr int GROUP = 4;
   const int per_group = GROUP * tiles_n;
@@ -846,6 +846,28 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16
   else finish_tile<EPI, WGM, WGN, BM, BN>(a, acc, smem, m0, n0);
 }
 
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS, int PF, bool A3 = false>
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_mfma_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int slabs_per_split) {
+  gemm_mfma_tile<BM, BN, WGM, WGN, AK, BKF, EPI, NS, PF, A3>(a, tiles_m, tiles_n, slabs_per_split, blockIdx.x);
+}
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BKF, int EPI, int NS>
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_ring_kernel(GemmArgs<bf16> a, int tiles_m, int tiles_n, int slabs_per_split) {
+  gemm_ring_tile<BM, BN, WGM, WGN, AK, BKF, EPI, NS>(a, tiles_m, tiles_n, slabs_per_split, blockIdx.x);
+}
+
+// Several weight gradients over the same tokens in one launch: problem q owns blocks first[q] .. first[q + 1] - 1.  (A problem's runs per
+// XCD come out right wherever its first block lies: blocks 8 apart share an XCD.)
+struct GradBatch { int n; int first[kMaxGradGroup + 1]; int tiles_m[kMaxGradGroup], tiles_n[kMaxGradGroup]; GemmArgs<bf16> a[kMaxGradGroup]; };
+template <int BM, int BN, int WGM, int WGN, int NS, int PF, bool RING>
+__global__ void __launch_bounds__(64 * WGM * WGN) grad_group_kernel(GradBatch b) {
+  int q = 0;
+  while (q + 1 < b.n && (int)blockIdx.x >= b.first[q + 1]) ++q;
+  const GemmArgs<bf16> a = b.a[q];
+  const int block = (int)blockIdx.x - b.first[q], slabs = (a.K + BK - 1) / BK;
+  if constexpr (RING) gemm_ring_tile<BM, BN, WGM, WGN, false, false, EPI_GRAD, NS>(a, b.tiles_m[q], b.tiles_n[q], slabs, block);
+  else gemm_mfma_tile<BM, BN, WGM, WGN, false, false, EPI_GRAD, NS, PF, false>(a, b.tiles_m[q], b.tiles_n[q], slabs, block);
+}
+
 // G = (accumulate ? G : 0) + scale * (part[0] + part[1] + ... ) in split order, 4 floats per thread
 __global__ void __launch_bounds__(256)
 splitk_reduce_kernel(const float* __restrict__ part, int splits, int64_t mn4, float* __restrict__ G, float scale, int accumulate) {
@@ -858,10 +880,8 @@ splitk_reduce_kernel(const float* __restrict__ part, int splits, int64_t mn4, fl
   reinterpret_cast<f32x4*>(G)[i] = out;
 }
 
-// Launch of one instantiation: LDS reservation (once), the split of the contracted axis, the reduction of the pieces.
 template <auto KERN>
-int launch_kernel(const GemmArgs<bf16>& a, int BMv, int BNv, int wgn, int threads, size_t lds, hipStream_t s) {
-  const int tm = (a.M + BMv - 1) / BMv, tn = (a.N + BNv - 1) / BNv;
+int reserve_lds(size_t lds) {
   // per instantiation; setting the attribute again with the same value is harmless, so two threads that both find the
   // flag clear may both set it
   static std::atomic<bool> attr_set{false};
@@ -870,6 +890,14 @@ int launch_kernel(const GemmArgs<bf16>& a, int BMv, int BNv, int wgn, int thread
       return fail(CEPHALO_EHIP, "gemm_mfma: cannot reserve %zu B of LDS", lds);
     attr_set.store(true, std::memory_order_release);
   }
+  return CEPHALO_OK;
+}
+
+// Launch of one instantiation: LDS reservation (once), the split of the contracted axis, the reduction of the pieces.
+template <auto KERN>
+int launch_kernel(const GemmArgs<bf16>& a, int BMv, int BNv, int wgn, int threads, size_t lds, hipStream_t s) {
+  const int tm = (a.M + BMv - 1) / BMv, tn = (a.N + BNv - 1) / BNv;
+  if (const int rc = reserve_lds<KERN>(lds); rc != CEPHALO_OK) return rc;
   const int slabs = (a.K + BK - 1) / BK;
   int splits = (a.epi == EPI_GRAD && a.splits > 1 && a.part) ? a.splits : 1;
   int per = (slabs + splits - 1) / splits;
@@ -936,10 +964,15 @@ constexpr TileCost kTiles[] = {
   {128, 128, 1, 0.38, 0.41, 0.47, 4.1}, {128, 64, 2, 0.36, 0.32, 0.31, 4.3},  {64, 64, 2, 0.30, 0.21, 0.195, 3.3},
 };
 // splits: pieces the contraction is cut into, one block each
+double tiles_of(const TileCost& t, int M, int N) { return (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+double blocks_us(const TileCost& t, double blocks, int nk, int kernels);
 double tile_us(const TileCost& t, int M, int N, int K, int kernels, int splits = 1) {
-  const double cus = 256.0 / kernels;
   const int slabs = (K + BK - 1) / BK, nk = (slabs + splits - 1) / splits;
-  const double blocks = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * ((slabs + nk - 1) / nk);
+  return blocks_us(t, tiles_of(t, M, N) * ((slabs + nk - 1) / nk), nk, kernels);
+}
+// a launch of `blocks` blocks that walk nk slabs each
+double blocks_us(const TileCost& t, double blocks, int nk, int kernels) {
+  const double cus = 256.0 / kernels;
   const double rounds = (double)(int64_t)(blocks / (cus * t.blocks)), rest = blocks - rounds * cus * t.blocks;
   const double full = blocks > cus * t.blocks ? t.more : t.one;
   double us = t.fixed + rounds * t.blocks * nk * full + std::max(0.0, rounds - 1) * (t.fixed - 2.0);
@@ -988,6 +1021,27 @@ GradPlan grad_plan(int M, int N, int K, int kernels, int splits) {
   }
   if (splits > 1) best.us += 3.0 + (splits + 1) * 4e-6 / 4.5 * (double)M * N;
   return best;
+}
+// one launch of a group
+template <auto KERN>
+int launch_group(const GemmArgs<bf16>* a, int n, int bm, int bn, int wgn, int threads, size_t lds, hipStream_t s) {
+  if (const int rc = reserve_lds<KERN>(lds); rc != CEPHALO_OK) return rc;
+  GradBatch b = {};
+  b.n = n;
+  for (int q = 0; q < n; ++q) {
+    GemmArgs<bf16>& k = b.a[q] = a[q];
+    b.tiles_m[q] = (k.M + bm - 1) / bm; b.tiles_n[q] = (k.N + bn - 1) / bn;
+    b.first[q + 1] = b.first[q] + b.tiles_m[q] * b.tiles_n[q];
+    k.splits = 1;
+    if (!k.rowsum) { k.rowsum_part = nullptr; continue; }
+    const int pieces = b.tiles_n[q] * wgn;
+    if (!k.rowsum_part || !k.rowsum_pieces || k.rowsum_part_bytes < (size_t)pieces * k.M * sizeof(float))
+      return fail(CEPHALO_EWORKSPACE, "gemm_mfma: %zu B for the %d pieces of %d row sums", k.rowsum_part_bytes, pieces, k.M);
+    *k.rowsum_pieces = pieces;
+  }
+  KERN<<<b.first[n], threads, lds, s>>>(b);
+  CEPHALO_CHECK_LAUNCH("grad_group");
+  return CEPHALO_OK;
 }
 int launch_grad(const GemmArgs<bf16>& a, hipStream_t s) {
   const int splits = (a.splits > 1 && a.part) ? a.splits : 1;
@@ -1066,6 +1120,37 @@ GemmSideBySide::GemmSideBySide(int kernels) : before(side_by_side) { side_by_sid
 GemmSideBySide::~GemmSideBySide() { side_by_side = before; }
 void GemmSideBySide::now(int kernels) { side_by_side = kernels < 1 ? 1 : kernels; }
 int gemm_set_side_by_side(int kernels) { const int was = side_by_side; side_by_side = kernels < 1 ? 1 : kernels; return was; }
+
+// The group runs as one launch where that is estimated to be faster than one launch each (with pieces): it saves the fixed time of the
+// others and the idle compute units of their last rounds.  All blocks of a group take the same time (the token axis is theirs in
+// common), so no order of them is better than another.  256 x 1024 .. 256 tokens (a tiny layer's four): 31 -> 9 us; 4096 tokens at
+// width 1024: 132 -> 101.
+int grad_group_tile(const GemmArgs<bf16>* a, int n) {
+  if (n < 2 || n > kMaxGradGroup) return -1;
+  double apart = 0, least = 1e30;
+  int tile = 0;
+  for (int q = 0; q < n; ++q) {
+    if (!gemm_mfma_takes(a[q]) || a[q].a_cs == 1 || a[q].b_cs == 1 || a[q].K != a[0].K) return -1;
+    apart += grad_plan(a[q].M, a[q].N, a[q].K, 1, (a[q].splits > 1 && a[q].part) ? a[q].splits : 1).us;
+  }
+  for (int c = 0; c < (int)(sizeof(kGradTiles) / sizeof(kGradTiles[0])); ++c) {
+    double blocks = 0;
+    for (int q = 0; q < n; ++q) blocks += tiles_of(kGradTiles[c], a[q].M, a[q].N);
+    const double us = blocks_us(kGradTiles[c], blocks, (a[0].K + BK - 1) / BK, 1);
+    if (us < least) { least = us; tile = c; }
+  }
+  return least < apart ? tile : -1;
+}
+int launch_grad_group(const GemmArgs<bf16>* a, int n, int tile, hipStream_t s) {
+  if (n < 1 || n > kMaxGradGroup) return fail(CEPHALO_EINVAL, "gemm: %d products in one launch", n);
+  constexpr size_t KB = 1024;
+  switch (tile) {
+    case 0: return launch_group<grad_group_kernel<256, 256, 4, 2, 2, 2, false>>(a, n, 256, 256, 2, 512, 2 * 64 * KB + 256, s);
+    case 1: return launch_group<grad_group_kernel<256, 128, 4, 2, 3, 0, true>>(a, n, 256, 128, 2, 512, 3 * 48 * KB, s);
+    case 2: return launch_group<grad_group_kernel<128, 128, 2, 2, 4, 0, true>>(a, n, 128, 128, 2, 256, 4 * 32 * KB, s);
+    default: return launch_group<grad_group_kernel<128, 128, 2, 2, 2, 0, true>>(a, n, 128, 128, 2, 256, 2 * 32 * KB, s);
+  }
+}
 
 size_t gemm_rowsum_part_bytes(int M, int N, int splits) {
   // (the most splits of gemm_grad_splits,) the narrowest tile (128 columns) and its two wavefront columns

@@ -169,6 +169,12 @@ int gemm_grad_splits_most(int M, int N, int K);
 template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);   // (bf16 only)
 int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s);  // fp32 operands and arithmetic, any strides
 int launch_gemm_mfma(const GemmArgs<bf16>& a, hipStream_t s);  // bf16 operands, MFMA, fp32 accumulate
+// Weight gradients over the same tokens in one launch, each in one piece (row sums: rowsum_pieces must be set).  grad_group_tile: which tile
+// to hand to the launch, or -1 if one launch each (with pieces) is estimated to be faster or a kernel does not take one of them.
+constexpr int kMaxGradGroup = 4;
+int grad_group_tile(const GemmArgs<bf16>* a, int n);
+int launch_grad_group(const GemmArgs<bf16>* a, int n, int tile, hipStream_t s);
+int launch_gemm_f32_group(const GemmArgs<float>* a, int n, hipStream_t s);      // any fp32 products, one launch
 // While one of these is alive on a thread, that thread's GEMM launches choose their tiles for 256 / `kernels` compute
 // units: the caller runs that many kernels side by side on different streams (results do not depend on the choice).
 struct GemmSideBySide {

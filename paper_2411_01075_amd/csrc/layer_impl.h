@@ -513,6 +513,49 @@ int add_colsum(SumList& list, const T* X, int tokens, int N, float* out, const W
   if (s2 == s) TRY(list.flush(s));      // (what is in the list may be the work area the kernel writes)
   return launch_colsum<T>(X, w.col_part, w.col_part_bytes, out, list.scale, list.acc, tokens, N, s2);
 }
+// A projection's weight gradient g [N, K] = dY^T X and, where it has a bias whose gradient is the sum of the same values, gb [N].
+template <typename T> struct GradJob { const T* dY; const T* X; int N, K; float *g, *gb; };
+
+// The weight gradients of a layer's projections in one launch, where that is faster (done; otherwise nothing has run and the caller
+// launches them one by one).  The pieces of the bias sums lie one behind the other in the work area.
+template <typename T> int wgrad_group(const GradJob<T>* jobs, int n, int tokens, SumList& sums, const Work<T>& w, hipStream_t s, bool* done);
+template <> inline int wgrad_group<float>(const GradJob<float>* jobs, int n, int tokens, SumList& sums, const Work<float>&, hipStream_t s, bool* done) {
+  GemmArgs<float> a[kMaxGradGroup];
+  for (int i = 0; i < n; ++i) a[i] = linear_wgrad<float>(jobs[i].dY, jobs[i].X, tokens, jobs[i].N, jobs[i].K, jobs[i].g, sums.scale, sums.acc);
+  *done = true;
+  for (int i = 0; i < n; ++i) if (jobs[i].gb && tokens > kRowsAsPartials) *done = false;
+  if (!*done) return CEPHALO_OK;
+  for (int i = 0; i < n; ++i) if (jobs[i].gb) sums.add(jobs[i].dY, tokens, jobs[i].N, jobs[i].gb);
+  return launch_gemm_f32_group(a, n, s);
+}
+template <> inline int wgrad_group<bf16>(const GradJob<bf16>* jobs, int n, int tokens, SumList& sums, const Work<bf16>& w, hipStream_t s, bool* done) {
+  GemmArgs<bf16> a[kMaxGradGroup];
+  int pieces[kMaxGradGroup];
+  *done = false;
+  for (int i = 0; i < n; ++i) {
+    const GradJob<bf16>& q = jobs[i];
+    a[i] = linear_wgrad<bf16>(q.dY, q.X, tokens, q.N, q.K, q.g, sums.scale, sums.acc);
+    a[i].splits = w.wg_part ? gemm_grad_splits(q.N, q.K, tokens) : 1;
+    a[i].part = w.wg_part;
+  }
+  const int tile = grad_group_tile(a, n);
+  if (tile < 0) return CEPHALO_OK;
+  size_t used = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!jobs[i].gb) continue;
+    a[i].rowsum = jobs[i].gb;
+    a[i].rowsum_part = w.rs_part + used / sizeof(float);
+    a[i].rowsum_part_bytes = gemm_rowsum_part_bytes(jobs[i].N, jobs[i].K, 1);
+    a[i].rowsum_pieces = &pieces[i];
+    used += align_up(a[i].rowsum_part_bytes);
+  }
+  if (used > w.rs_part_bytes) return CEPHALO_OK;
+  TRY(launch_grad_group(a, n, tile, s));
+  for (int i = 0; i < n; ++i) if (jobs[i].gb) sums.add(a[i].rowsum_part, pieces[i], jobs[i].N, jobs[i].gb);
+  *done = true;
+  return CEPHALO_OK;
+}
+
 template <typename T>
 int layer_bwd_params_t(const cephalo_layer_desc& d, const DySums& dy_sums, const T* dyl, int tokens, int ln_chunks,
                        const Saved<T>& sv, const Work<T>& w, float* G, float scale, int acc, hipStream_t s, hipStream_t s2 = nullptr,
@@ -520,50 +563,52 @@ int layer_bwd_params_t(const cephalo_layer_desc& d, const DySums& dy_sums, const
   if (!s2) s2 = s;      // s2: where the bandwidth-bound reductions (bias column sums, norm-parameter partials) run, beside the GEMMs on s
   const ParamOffsets o = param_offsets(d);
   const int H = d.hidden, F = d.mlp;
+  const bool biases = !is_llama(d);
   SumList sums;
   sums.scale = scale; sums.acc = acc;
   sums.add(w.ln2_g, ln_chunks, H, G + o.ln2_g);
   sums.add(w.ln1_g, ln_chunks, H, G + o.ln1_g);
-  if (is_llama(d)) {
-    if (s2 != s) TRY(sums.flush(s2));
-    TRY(wgrad<T>(dyl, sv.h, tokens, H, F, G + o.w_fc2, scale, acc, w.wg_part, s));
-    TRY(wgrad<T>(w.dz, sv.u2, tokens, 2 * F, H, G + o.w_fc1, scale, acc, w.wg_part, s));
-    TRY(wgrad<T>(lowp_of<T>(w.dx1, w.dx1l), sv.O, tokens, H, H, G + o.w_o, scale, acc, w.wg_part, s));
-    TRY(wgrad<T>(w.dqkv, sv.u, tokens, 3 * H, H, G + o.w_qkv, scale, acc, w.wg_part, s));
-    return sums.flush(s2);
-  }
-  sums.add(w.ln2_b, ln_chunks, H, G + o.ln2_b);
-  sums.add(w.ln1_b, ln_chunks, H, G + o.ln1_b);
-  sums.add(w.ln2_s, ln_chunks, H, G + o.b_o);
-  if (b_fc2_below) sums.add(w.ln1_s, ln_chunks, H, b_fc2_below);
-  else if (dy_sums.part) {
-    if constexpr (std::is_same<T, float>::value) TRY(add_colsum<T>(sums, dy_sums.part, dy_sums.chunks, H, G + o.b_fc2, w, s, s2));
-    else sums.add(dy_sums.part, dy_sums.chunks, H, G + o.b_fc2);
+  if (biases) {
+    sums.add(w.ln2_b, ln_chunks, H, G + o.ln2_b);
+    sums.add(w.ln1_b, ln_chunks, H, G + o.ln1_b);
+    sums.add(w.ln2_s, ln_chunks, H, G + o.b_o);
+    if (b_fc2_below) sums.add(w.ln1_s, ln_chunks, H, b_fc2_below);
+    else if (dy_sums.part) {
+      if constexpr (std::is_same<T, float>::value) TRY(add_colsum<T>(sums, dy_sums.part, dy_sums.chunks, H, G + o.b_fc2, w, s, s2));
+      else sums.add(dy_sums.part, dy_sums.chunks, H, G + o.b_fc2);
+    }
   }
   if (s2 != s) TRY(sums.flush(s2));
   // (the other two bias gradients are sums of the very bf16 values their weight-gradient GEMMs read, and the GEMMs form
   // them on the way)
-  TRY(wgrad<T>(dyl, sv.h, tokens, H, F, G + o.w_fc2, scale, acc, w.wg_part, s));
+  const GradJob<T> jobs[] = {{dyl, sv.h, H, F, G + o.w_fc2, nullptr},
+                             {w.dz, sv.u2, (int)ff1_width(d), H, G + o.w_fc1, biases ? G + o.b_fc1 : nullptr},
+                             {lowp_of<T>(w.dx1, w.dx1l), sv.O, H, H, G + o.w_o, nullptr},
+                             {w.dqkv, sv.u, 3 * H, H, G + o.w_qkv, biases ? G + o.b_qkv : nullptr}};
+  bool done = false;
+  TRY(wgrad_group<T>(jobs, 4, tokens, sums, w, s, &done));
+  if (done) return sums.flush(s);
   float* pieces = w.rs_part;
   size_t room = w.rs_part_bytes;
-  struct { const T* dY; const T* X; int N; float *g, *gb; } two[] = {{w.dz, sv.u2, F, G + o.w_fc1, G + o.b_fc1}, {w.dqkv, sv.u, 3 * H, G + o.w_qkv, G + o.b_qkv}};
-  for (int i = 0; i < 2; ++i) {
-    auto& p = two[i];
-    if (i == 1) TRY(wgrad<T>(lowp_of<T>(w.dx1, w.dx1l), sv.O, tokens, H, H, G + o.w_o, scale, acc, w.wg_part, s));
-    // the second GEMM's pieces go behind the first's where both fit; otherwise the first's are added now and make room
-    if (i == 1 && std::is_same<T, bf16>::value && room < gemm_rowsum_part_bytes(p.N, H, w.wg_part ? gemm_grad_splits(p.N, H, tokens) : 1)) {
+  for (const GradJob<T>& q : jobs) {
+    if (!q.gb) {
+      TRY(wgrad<T>(q.dY, q.X, tokens, q.N, q.K, q.g, scale, acc, w.wg_part, s));
+      continue;
+    }
+    // the second bias's pieces go behind the first's where both fit; otherwise the first's are added now and make room
+    if (pieces != w.rs_part && room < gemm_rowsum_part_bytes(q.N, q.K, w.wg_part ? gemm_grad_splits(q.N, q.K, tokens) : 1)) {
       TRY(sums.flush(s));
       pieces = w.rs_part; room = w.rs_part_bytes;
     }
-    ColsumsBeside cb = {p.gb, pieces, room, false, true, 0};
-    TRY(wgrad<T>(p.dY, p.X, tokens, p.N, H, p.g, scale, acc, w.wg_part, s, 0, &cb));
+    ColsumsBeside cb = {q.gb, pieces, room, false, true, 0};
+    TRY(wgrad<T>(q.dY, q.X, tokens, q.N, q.K, q.g, scale, acc, w.wg_part, s, 0, &cb));
     if (cb.done) {
-      sums.add(pieces, cb.pieces, p.N, p.gb);
-      const size_t used = align_up((size_t)cb.pieces * p.N * sizeof(float));
+      sums.add(pieces, cb.pieces, q.N, q.gb);
+      const size_t used = align_up((size_t)cb.pieces * q.N * sizeof(float));
       pieces += used / sizeof(float);
       room = room > used ? room - used : 0;
     } else {
-      TRY(add_colsum<T>(sums, p.dY, tokens, p.N, p.gb, w, s, s2));
+      TRY(add_colsum<T>(sums, q.dY, tokens, q.N, q.gb, w, s, s2));
     }
   }
   return sums.flush(s);
