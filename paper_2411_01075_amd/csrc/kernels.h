@@ -241,12 +241,10 @@ int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s);      // s
 // Attention on the packed projection qkv [m*S, 3H] (Q | K | V column blocks, head a in
 // columns [a*d,(a+1)*d) of each block).  O [m*S, H], lse [m, A, S] fp32 (log-sum-exp of the
 // scaled, masked scores of each query row).
-template <typename T>
-int launch_attn_fwd_simple(const T* qkv, T* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s);
+int launch_attn_fwd_f32(const float* qkv, float* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s);
 // dqkv [m*S, 3H]; dvec [m, A, S] fp32 scratch for rowsum(dO*O)
-template <typename T>
-int launch_attn_bwd_simple(const T* qkv, const T* O, const T* dO, const float* lse, float* dvec, T* dqkv,
-                           int m, int S, int H, int A, int causal, hipStream_t s);
+int launch_attn_bwd_f32(const float* qkv, const float* O, const float* dO, const float* lse, float* dvec, float* dqkv,
+                        int m, int S, int H, int A, int causal, hipStream_t s);
 
 int launch_attn_fwd_mfma(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s);
 // rot: if not null, a rotary table [S, d/2, 2] by which the stored dq and dk are turned back (q and k were rotated)

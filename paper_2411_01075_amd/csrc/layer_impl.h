@@ -160,7 +160,7 @@ template <> int gemm<bf16>(const GemmArgs<bf16>& a, hipStream_t s) { return laun
 
 template <typename T> int attn_fwd(const T* qkv, T* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s);
 template <> int attn_fwd<float>(const float* qkv, float* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s) {
-  return launch_attn_fwd_simple<float>(qkv, O, lse, m, S, H, A, causal, s);
+  return launch_attn_fwd_f32(qkv, O, lse, m, S, H, A, causal, s);
 }
 template <> int attn_fwd<bf16>(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, int causal, hipStream_t s) {
   return launch_attn_fwd_mfma(qkv, O, lse, m, S, H, A, causal, s);
@@ -171,7 +171,7 @@ int attn_bwd(const T* qkv, const T* O, const T* dO, const float* lse, float* dve
              const float* rot = nullptr);
 template <> int attn_bwd<float>(const float* qkv, const float* O, const float* dO, const float* lse, float* dvec, float* dqkv,
                                 int m, int S, int H, int A, int causal, hipStream_t s, const float* rot) {
-  int rc = launch_attn_bwd_simple<float>(qkv, O, dO, lse, dvec, dqkv, m, S, H, A, causal, s);
+  int rc = launch_attn_bwd_f32(qkv, O, dO, lse, dvec, dqkv, m, S, H, A, causal, s);
   if (rc == CEPHALO_OK && rot) rc = launch_rotary<float>(dqkv, rot, m * S, S, H, A, 1, s);
   return rc;
 }

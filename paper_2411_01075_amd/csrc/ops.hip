@@ -147,7 +147,7 @@ extern "C" int cephalo_op_attention_fwd(const cephalo_layer_desc* d, const void*
   if (!qkv || !O || !lse) return fail(CEPHALO_EINVAL, "attention_fwd: null buffer");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (d->dtype == CEPHALO_F32)
-    return launch_attn_fwd_simple<float>(static_cast<const float*>(qkv), static_cast<float*>(O), lse, m, d->seq, d->hidden, d->heads, d->causal, s);
+    return launch_attn_fwd_f32(static_cast<const float*>(qkv), static_cast<float*>(O), lse, m, d->seq, d->hidden, d->heads, d->causal, s);
   return launch_attn_fwd_mfma(static_cast<const bf16*>(qkv), static_cast<bf16*>(O), lse, m, d->seq, d->hidden, d->heads, d->causal, s);
 }
 
@@ -158,7 +158,7 @@ extern "C" int cephalo_op_attention_bwd(const cephalo_layer_desc* d, const void*
   if (!qkv || !O || !dO || !lse || !dvec || !dqkv) return fail(CEPHALO_EINVAL, "attention_bwd: null buffer");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (d->dtype == CEPHALO_F32)
-    return launch_attn_bwd_simple<float>(static_cast<const float*>(qkv), static_cast<const float*>(O), static_cast<const float*>(dO),
+    return launch_attn_bwd_f32(static_cast<const float*>(qkv), static_cast<const float*>(O), static_cast<const float*>(dO),
                                          lse, dvec, static_cast<float*>(dqkv), m, d->seq, d->hidden, d->heads, d->causal, s);
   return launch_attn_bwd_mfma(static_cast<const bf16*>(qkv), static_cast<const bf16*>(O), static_cast<const bf16*>(dO),
                               lse, dvec, static_cast<bf16*>(dqkv), m, d->seq, d->hidden, d->heads, d->causal, s);

@@ -232,3 +232,43 @@ def test_token_embedding_gradient(H, heads, S, b, spread):
     got = G[:V * H].view(V, H).double()
     assert torch.isfinite(G).all() and dx0.abs().max() > 0
     assert ((got - ref).abs() <= n * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("d", [4, 20, 30, 32, 64, 100, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("m,S,A", [(1, 1, 2), (2, 15, 4), (1, 17, 2), (2, 64, 2), (1, 150, 4)])
+def test_fp32_attention_edges(m, S, A, d, causal):
+    """Blocks of 16 queries and keys over four wavefronts, head widths between the 32-, 64- and 128-wide forms, a width that takes scalar loads."""
+    print("attention f32", m, S, A, d, causal, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m * S + d)
+    H = A * d
+    qkv, dO = torch.randn(m * S, 3 * H, device="cuda", generator=g), torch.randn(m * S, H, device="cuda", generator=g)
+    ro, rg, rl = _attention64(qkv, dO, m, S, A, d, causal)
+    desc = C.layer_desc(H, A, 4 * H, S, causal, C.F32)
+    O, lse, dvec = torch.full((m * S, H), float("nan"), device="cuda"), torch.full((m, A, S), float("nan"), device="cuda"), torch.full((m, A, S), float("nan"), device="cuda")
+    dqkv = torch.full((m * S, 3 * H), float("nan"), device="cuda")
+    C.cephalo_op_attention_fwd(desc, qkv, O, lse, m)
+    C.cephalo_op_attention_bwd(desc, qkv, O, dO, lse, dvec, dqkv, m)
+    # fp32 sums over up to S + d terms of size about 1, scores of size sqrt(d): 2^-24 (S + d) sqrt(d) with a margin of 4
+    tol = 4 * 2.0 ** -24 * (S + d) * d ** 0.5
+    for got, ref in ((O, ro), (lse, rl), (dqkv, rg)):
+        assert (got.double() - ref).abs().max() <= tol * max(1.0, ref.abs().max().item())
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_fp32_attention_masked_tokens_stay_out(bad):
+    """Under the causal mask a token's values reach no earlier token's output, whatever they are."""
+    m, S, A, d = 1, 37, 2, 64
+    H = A * d
+    g = torch.Generator(device="cuda").manual_seed(5)
+    qkv = torch.randn(m * S, 3 * H, device="cuda", generator=g)
+    desc = C.layer_desc(H, A, 4 * H, S, True, C.F32)
+    clean, lse = torch.empty(m * S, H, device="cuda"), torch.empty(m, A, S, device="cuda")
+    C.cephalo_op_attention_fwd(desc, qkv, clean, lse, m)
+    for at in (36, 20, 16):
+        dirty = qkv.clone()
+        dirty[at, 2 * H + 3] = bad
+        out = torch.empty_like(clean)
+        C.cephalo_op_attention_fwd(desc, dirty, out, lse, m)
+        assert torch.isfinite(out[:at]).all() and (out[:at] - clean[:at]).abs().max() < 1e-5
+        assert not torch.isfinite(out[at:, 3]).any()
