@@ -111,36 +111,42 @@ constexpr int kLnBwdRowsPerBlock = 8;
 // RMS: backward of the root-mean-square norm, out = resid + rstd * (g - xhat * mean(g*xhat)) with xhat = x * rstd
 // (part_b is still written, and not used).
 //
-// A block of four wavefronts works on its 8 rows together, two rows at a time: a thread owns the same MV 16-byte
-// column groups of every row, so the column sums of the parameter gradients stay in its registers from the first row to
-// the last (no reduction across wavefronts at the end) and a row costs it 3 x MV vectors.  With so few registers per
-// row the loads of the next two rows are in flight while these two are reduced and written.  (One wavefront per row,
-// the row in registers, needed 234 registers at H = 2048 and left two wavefronts per SIMD taking turns between a burst
-// of loads and a burst of stores: 0.50-0.57 of the memory's rate.)  The two row sums go through LDS: one barrier per
-// pair of rows, the slots alternate so that a second one is not needed.
+// A block works on 8 rows.  TEAM threads (64, 128 or 256, the fewest that cover a row with MV 16-byte column groups each) share a
+// row.  A thread owns the same column groups of every row of its team, so the column sums of the parameter gradients stay in its
+// registers to the end and a row costs it three vectors; the two row sums of a team of several wavefronts go through LDS, one barrier per
+// step, the slots alternate so that a second one is not needed.  (One wavefront per row, the row in registers, needed 234 registers at
+// H = 2048.)  Wide rows (TEAM 256): one team per block, two rows a step and the next two in flight.  Narrow rows: 512 threads, so 4 or 8
+// teams with 2 rows or 1 each, all asked for at once, and the teams' sums are added through LDS in team order; with one team of 256 half of
+// it was idle at H = 1024 and seven eighths at 256 (1024 x 1024: 9.1 -> 7.9 us, 256 x 256: 7.8 -> 5.7).  Two teams of 256 lose (2048 x 1600:
+// 14.0 -> 14.7; 2048 x 2560: 21 -> 26, spills).
 // SUMS: the block's column sums of `out` go to part_s as well (the bias gradient of a projection that writes into the
 // residual stream is the column sum of the stream's gradient, which is this kernel's result).
 // RESID: there is a residual to add (otherwise `resid` is not read).
-template <typename T, int MV, bool RMS, bool SUMS, bool RESID>
-__global__ void __launch_bounds__(kThreads)
+constexpr int ln_bwd_threads(int team) { return team == 256 ? 256 : 512; }
+template <typename T, int TEAM, int MV, bool RMS, bool SUMS, bool RESID>
+__global__ void __launch_bounds__(ln_bwd_threads(TEAM))
 ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const float* __restrict__ mean,
               const float* __restrict__ rstd, const T* __restrict__ gamma, const float* __restrict__ resid,
               float* __restrict__ out, T* __restrict__ out_lowp, float* __restrict__ part_g, float* __restrict__ part_b,
               float* __restrict__ part_s, int rows, int H) {
   constexpr int VN = Vec<T>::N;
-  constexpr int R = 2;                                   // rows per step
-  constexpr int STEPS = kLnBwdRowsPerBlock / R;
-  constexpr bool AHEAD = MV <= 2;                        // wide rows: no room for the next step's rows
-  __shared__ float red[2][R][2][kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int TEAMS = ln_bwd_threads(TEAM) / TEAM, TW = TEAM / 64;                 // teams per block, wavefronts per team
+  constexpr int PER_TEAM = kLnBwdRowsPerBlock / TEAMS;                        // rows of a team
+  constexpr int R = PER_TEAM < 2 ? 1 : 2;                                     // ... per step
+  constexpr int STEPS = PER_TEAM / R;
+  constexpr bool AHEAD = MV <= 2 && STEPS % 2 == 0;                           // the next step's rows fly under this one's
+  constexpr int NS = SUMS ? 3 : 2;                                            // column sums
+  __shared__ float red[2][TEAMS][R][2][TW];
+  __shared__ __attribute__((aligned(16))) float cols[TEAM * VN];              // a team's sums on their way to the first team's
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % TW, team = threadIdx.x / TEAM, tt = threadIdx.x % TEAM;
   const int nv = H / VN;
   const float inv_h = 1.0f / (float)H;
-  const int row0 = blockIdx.x * kLnBwdRowsPerBlock;
+  const int row0 = blockIdx.x * kLnBwdRowsPerBlock + team * PER_TEAM;
 
-  float gm[MV][VN], dg[MV][VN], db[MV][VN], ds[SUMS ? MV : 1][VN];
+  float gm[MV][VN], sum[NS][MV][VN];                                          // sums: d gamma, d beta, the result's
 #pragma unroll
   for (int j = 0; j < MV; ++j) {
-    const int v = threadIdx.x + kThreads * j;
+    const int v = tt + TEAM * j;
     if (v < nv) {
       load_vec<T>(gamma + v * VN, gm[j]);
     } else {
@@ -148,11 +154,9 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
       for (int i = 0; i < VN; ++i) gm[j][i] = 0.f;
     }
 #pragma unroll
-    for (int i = 0; i < VN; ++i) { dg[j][i] = 0.f; db[j][i] = 0.f; }
-    if (SUMS) {
+    for (int k = 0; k < NS; ++k)
 #pragma unroll
-      for (int i = 0; i < VN; ++i) ds[j][i] = 0.f;
-    }
+      for (int i = 0; i < VN; ++i) sum[k][j][i] = 0.f;
   }
 
   struct Rows { float d[R][MV][VN], xv[R][MV][VN], rr[R][MV][VN]; };
@@ -165,7 +169,7 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
         // (no branch around the loads: a group past the last row or the row's end reads a valid one instead and is
         // replaced by zeros -- it contributes nothing and is not stored; with the loads under bounds branches the
         // compiler waits for all of them at once and the rows asked for ahead do not overlap the arithmetic)
-        const int v = threadIdx.x + kThreads * j;
+        const int v = tt + TEAM * j;
         const bool ok = row < rows && v < nv;
         const int64_t o = (int64_t)min(row, rows - 1) * H + (v < nv ? v : 0) * VN;
         load_f32<VN>(du + o, b.d[r][j]);
@@ -183,13 +187,13 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
     }
   };
   auto reduce_and_store = [&](Rows& b, int step) {
-    float rs[R];
+    float rs[R], s1[R], s2[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = min(row0 + step * R + r, rows - 1);
       const float mu = RMS ? 0.f : mean[row];
       rs[r] = rstd[row];
-      float s1 = 0.f, s2 = 0.f;
+      s1[r] = s2[r] = 0.f;
 #pragma unroll
       for (int j = 0; j < MV; ++j)
 #pragma unroll
@@ -197,37 +201,40 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
           const float d = b.d[r][j][i];
           const float xh = (b.xv[r][j][i] - mu) * rs[r];
           const float g = d * gm[j][i];
-          s1 += g;
-          s2 += g * xh;
-          dg[j][i] += d * xh;
-          db[j][i] += d;
+          s1[r] += g;
+          s2[r] += g * xh;
+          sum[0][j][i] += d * xh;
+          sum[1][j][i] += d;
           b.xv[r][j][i] = xh;
           b.d[r][j][i] = g;
         }
-      s1 = wave_sum(s1);
-      s2 = wave_sum(s2);
-      if (lane == 0) { red[step & 1][r][0][wave] = s1; red[step & 1][r][1][wave] = s2; }
+      s1[r] = wave_sum(s1[r]);
+      s2[r] = wave_sum(s2[r]);
+      if (TW > 1 && lane == 0) { red[step & 1][team][r][0][wave] = s1[r]; red[step & 1][team][r][1][wave] = s2[r]; }
     }
-    __syncthreads();
+    if (TW > 1) __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = row0 + step * R + r;
-      float c1 = 0.f, c2 = 0.f;
+      float c1 = s1[r], c2 = s2[r];
+      if (TW > 1) {
+        c1 = c2 = 0.f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) { c1 += red[step & 1][r][0][w]; c2 += red[step & 1][r][1][w]; }
+        for (int w = 0; w < TW; ++w) { c1 += red[step & 1][team][r][0][w]; c2 += red[step & 1][team][r][1][w]; }
+      }
       c1 = RMS ? 0.f : c1 * inv_h;
       c2 *= inv_h;
       if (row < rows) {
 #pragma unroll
         for (int j = 0; j < MV; ++j) {
-          const int v = threadIdx.x + kThreads * j;
+          const int v = tt + TEAM * j;
           if (v < nv) {
             float o[VN];
 #pragma unroll
             for (int i = 0; i < VN; ++i) o[i] = b.rr[r][j][i] + rs[r] * (b.d[r][j][i] - c1 - b.xv[r][j][i] * c2);
             if (SUMS) {
 #pragma unroll
-              for (int i = 0; i < VN; ++i) ds[j][i] += o[i];
+              for (int i = 0; i < VN; ++i) sum[NS - 1][j][i] += o[i];
             }
             store_f32<VN>(out + (int64_t)row * H + v * VN, o);
             if (out_lowp) store_vec<T>(out_lowp + (int64_t)row * H + v * VN, o);
@@ -254,15 +261,23 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
       reduce_and_store(b0, step);
     }
   }
-  float* pg = part_g + (int64_t)blockIdx.x * H;
-  float* pb = part_b + (int64_t)blockIdx.x * H;
+  // add the teams' column sums, in team order, one sum and column group at a time
 #pragma unroll
-  for (int j = 0; j < MV; ++j) {
-    const int v = threadIdx.x + kThreads * j;
-    if (v < nv) {
-      store_f32<VN>(pg + v * VN, dg[j]);
-      store_f32<VN>(pb + v * VN, db[j]);
-      if (SUMS) store_f32<VN>(part_s + (int64_t)blockIdx.x * H + v * VN, ds[j]);
+  for (int k = 0; k < NS; ++k) {
+    float* const part = (k == 0 ? part_g : k == 1 ? part_b : part_s) + (int64_t)blockIdx.x * H;
+#pragma unroll
+    for (int j = 0; j < MV; ++j) {
+      for (int t = 1; t < TEAMS; ++t) {
+        __syncthreads();
+        if (team == t) store_f32<VN>(cols + tt * VN, sum[k][j]);
+        __syncthreads();
+        if (team == 0) {
+#pragma unroll
+          for (int i = 0; i < VN; ++i) sum[k][j][i] += cols[tt * VN + i];
+        }
+      }
+      const int v = tt + TEAM * j;
+      if (team == 0 && v < nv) store_f32<VN>(part + v * VN, sum[k][j]);
     }
   }
 }
@@ -443,21 +458,18 @@ int launch_ln_bwd(const float* du, const float* x, const float* mean, const floa
                   float* part_s) {
   if (rms && part_s) return fail(CEPHALO_EINVAL, "norm backward: column sums of the result go with the LayerNorm form only");
   const int nblocks = ln_bwd_blocks(rows);
-  const int nv = H / Vec<T>::N;
-  int mv = 1;
-  while (mv * kThreads < nv) mv *= 2;          // 16-byte column groups per thread
-#define LN_BWD_FORMS(MV, RESID)                                                                                      \
-    { if (rms) ln_bwd_kernel<T, MV, true, false, RESID><<<nblocks, kThreads, 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); \
-      else if (part_s) ln_bwd_kernel<T, MV, false, true, RESID><<<nblocks, kThreads, 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, part_s, rows, H); \
-      else ln_bwd_kernel<T, MV, false, false, RESID><<<nblocks, kThreads, 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); }
-#define LN_BWD_CASE(MV)                                                                                               \
-  case MV:                                                                                                            \
-    if (resid) LN_BWD_FORMS(MV, true) else LN_BWD_FORMS(MV, false)                                                    \
-    break;
-  switch (mv) {
-    LN_BWD_CASE(1) LN_BWD_CASE(2) LN_BWD_CASE(4)
-    default: return fail(CEPHALO_EUNSUPPORTED, "layer norm: hidden width %d too large", H);
-  }
+  const int nv = H / Vec<T>::N;                // 16-byte column groups of a row
+#define LN_BWD_FORMS(TEAM, MV, RESID)                                                                                \
+    { if (rms) ln_bwd_kernel<T, TEAM, MV, true, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); \
+      else if (part_s) ln_bwd_kernel<T, TEAM, MV, false, true, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, part_s, rows, H); \
+      else ln_bwd_kernel<T, TEAM, MV, false, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); }
+#define LN_BWD_CASE(TEAM, MV) { if (resid) LN_BWD_FORMS(TEAM, MV, true) else LN_BWD_FORMS(TEAM, MV, false) }
+  if (nv <= 64) LN_BWD_CASE(64, 1)
+  else if (nv <= 128) LN_BWD_CASE(128, 1)
+  else if (nv <= 256) LN_BWD_CASE(256, 1)
+  else if (nv <= 512) LN_BWD_CASE(256, 2)
+  else if (nv <= 1024) LN_BWD_CASE(256, 4)
+  else return fail(CEPHALO_EUNSUPPORTED, "layer norm: hidden width %d too large", H);
 #undef LN_BWD_CASE
 #undef LN_BWD_FORMS
   CEPHALO_CHECK_LAUNCH("ln_bwd");

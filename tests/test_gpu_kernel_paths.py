@@ -272,3 +272,39 @@ def test_fp32_attention_masked_tokens_stay_out(bad):
         C.cephalo_op_attention_fwd(desc, dirty, out, lse, m)
         assert torch.isfinite(out[:at]).all() and (out[:at] - clean[:at]).abs().max() < 1e-5
         assert not torch.isfinite(out[at:, 3]).any()
+
+
+@pytest.mark.parametrize("H", [8, 256, 512, 520, 1024, 1032, 2048, 2056, 4096])
+@pytest.mark.parametrize("rows", [1, 8, 13, 100])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("rms", [False, True])
+def test_norm_backward_teams(rows, H, bf16, rms):
+    """Teams of 64, 128 and 256 threads per row with 1, 2 and 4 vectors each, around the widths where they change; blocks of 8 rows, partly filled."""
+    g = torch.Generator(device="cuda").manual_seed(rows + H)
+    du, x, res = (torch.randn(rows, H, device="cuda", generator=g) for _ in range(3))
+    dt = torch.bfloat16 if bf16 else torch.float32
+    gam = (1 + 0.1 * torch.randn(H, device="cuda", generator=g)).to(dt)
+    x64, d64, g64 = x.double(), du.double(), gam.double()
+    mean = torch.zeros(rows, device="cuda", dtype=torch.float64) if rms else x64.mean(1)
+    rstd = 1 / torch.sqrt(((x64 - mean[:, None]) ** 2).mean(1) + 1e-5)
+    mean, rstd = mean.float(), rstd.float()
+    xh = (x64 - mean.double()[:, None]) * rstd.double()[:, None]
+    gg = d64 * g64
+    ref = res.double() + rstd.double()[:, None] * (gg - (0 if rms else gg.mean(1, keepdim=True)) - xh * (gg * xh).mean(1, keepdim=True))
+    dx, dg, db = torch.full_like(x, float("nan")), torch.full((H,), float("nan"), device="cuda"), torch.full((H,), float("nan"), device="cuda")
+    low = torch.full((rows, H), float("nan"), device="cuda", dtype=dt) if bf16 else None
+    ws = torch.empty(max(C.cephalo_op_norm_bwd_workspace(rows, H), C.binding.cephalo_op_norm_bwd_sums_workspace(rows, H)), dtype=torch.uint8, device="cuda").fill_(255)
+    C.cephalo_op_norm_bwd(C.BF16 if bf16 else C.F32, rms, du, x, mean, rstd, gam, res, dx, low, dg, None if rms else db, rows, H, ws)
+    eps = 2.0 ** -24
+    # sums over H terms of size |g| and |g xhat|, then a handful of roundings of values up to the largest of the row
+    size = res.abs().double() + rstd.double()[:, None] * (gg.abs() + gg.abs().mean(1, keepdim=True) + xh.abs() * (gg * xh).abs().mean(1, keepdim=True))
+    assert ((dx.double() - ref).abs() <= (H + 16) * eps * size).all()
+    if bf16:
+        assert torch.equal(low, dx.bfloat16())
+    assert ((dg.double() - (d64 * xh).sum(0)).abs() <= (rows + 8) * eps * (d64 * xh).abs().sum(0) + 1e-30).all()
+    if not rms:
+        assert ((db.double() - d64.sum(0)).abs() <= (rows + 8) * eps * d64.abs().sum(0)).all()
+        ds, dx2, dg2, db2 = torch.full((H,), float("nan"), device="cuda"), torch.empty_like(dx), torch.empty_like(dg), torch.empty_like(db)
+        C.binding.cephalo_op_norm_bwd_sums(C.BF16 if bf16 else C.F32, du, x, mean, rstd, gam, res, dx2, low, dg2, db2, ds, rows, H, ws)
+        assert torch.equal(dx, dx2) and torch.equal(dg, dg2) and torch.equal(db, db2)
+        assert ((ds.double() - dx.double().sum(0)).abs() <= (rows + 8) * eps * dx.double().abs().sum(0)).all()
