@@ -263,7 +263,7 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
       TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, t0 + TILE, Ks(cur ^ 1), d);
       TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, t0 + TILE, Vs(cur ^ 1), d);
     }
-    if (!CAUSAL || t0 <= q0 + 31) {
+    if (q0 < S && (!CAUSAL || t0 <= q0 + 31)) {          // (a wavefront whose queries all lie past the end only stages)
       // All K fragments of the tile are read before the first MFMA needs one, and the two 32-key blocks accumulate
       // in turn, so neither an LDS round trip nor a dependent accumulator sits between consecutive MFMAs.
       bf16x8 kfr[2][D / 16];
@@ -410,7 +410,7 @@ attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __re
       const int t0 = kt * 128 + kh * 64;            // this wavefront's 64 keys
       const lds_bf16* Kt = Ks(cur) + kh * 64 * TL::LD;
       const lds_bf16* Vt = Vs(cur) + kh * 64 * TL::LD;
-      if (t0 < S && (!CAUSAL || t0 <= q0 + 31)) {
+      if (t0 < S && q0 < S && (!CAUSAL || t0 <= q0 + 31)) {
         f32x16 s[2];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
@@ -820,7 +820,7 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
     const int t0 = kt * 128 + kh * 64;                 // this wavefront's 64 keys
     const lds_bf16* Kt = Ks(cur) + kh * 64 * TL::LD;
     const lds_bf16* Vt = Vs(cur) + kh * 64 * TL::LD;
-    if (t0 < S && (!CAUSAL || t0 <= q0 + 31)) {
+    if (t0 < S && q0 < S && (!CAUSAL || t0 <= q0 + 31)) {      // (a wavefront whose queries or keys all lie past the end only stages)
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         f32x16 s, dp;       // S^T and dP^T accumulate in turn: no dependent accumulator between consecutive MFMAs
@@ -963,7 +963,7 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
     }
     const LDS_AS float* st = stats + cur * 128;
     const int q0 = qb0 + qh * 32;                      // this wavefront's 32 queries
-    if (!CAUSAL || q0 + 31 >= t0) {
+    if (q0 < S && t0 < S && (!CAUSAL || q0 + 31 >= t0)) {      // (a wavefront whose queries or keys all lie past the end only stages)
       constexpr int NP = D / 8;                        // products per phase
       // S and dP of the 32 queries x 32 keys
       f32x16 sc, dp;
