@@ -1,19 +1,20 @@
 // bf16 GEMM on the gfx950 matrix cores:  C[M,N] = sum_k A(m,k) B(n,k), fp32 accumulate, fused epilogue.
 //
-// One kernel template covers the contractions of a linear layer; each operand is either k-contiguous or
-// row-contiguous (strided along k):
+// Each operand is either k-contiguous or row-contiguous (strided along k):
 //   forward          Y  = X W^T        both k-contiguous
 //   input gradient   dX = dY (W^T)^T   both k-contiguous (the layer keeps a transposed copy of its weights)
-//   weight gradient  dW = dY^T X       tokens are k: one operand is transposed beforehand by the caller, the other
-//                                      is read row-contiguous
+//   weight gradient  dW = dY^T X       tokens are k: both row-contiguous, read as they lie
+// Two main loops share the staging, the matrix instruction and the epilogues: gemm_mfma_tile for the large tiles (256 x 256 and
+// 256 x 192: as many products per byte as the accumulators allow) and gemm_ring_tile for the small ones, down to 64 x 64, where the
+// output has few tiles.  Tile and number of pieces are chosen per launch by estimated time (kTiles, kGradTiles below).
 //
 // Matrix instruction: v_mfma_f32_16x16x32_bf16.  On this chip a stream of 16x16x32 products sustains an eighth
 // more than a stream of 32x32x16 products on the same data (measured with operands held in registers, the same
 // 64 x 128 wavefront tile either way: 2.06 against 1.82 PFLOP/s; the chip is power-limited long before its nominal
 // 2.5), and the LDS bytes per flop depend on the wavefront tile only, not on the MFMA shape.
 //
-// Data path.  The tile is as large as the accumulators allow (256 x 256 per block of 8 wavefronts, 64 x 128 per
-// wavefront: every byte brought into LDS and every LDS byte read feeds the most MFMAs) and operand slabs of 64
+// Data path.  The largest tile is what the accumulators allow (256 x 256 per block of 8 wavefronts, 64 x 128 per
+// wavefront: every byte brought into LDS and every LDS byte read feeds the most MFMAs).  Operand slabs of 64
 // k-values go from global memory straight into LDS (buffer_load ... lds, 16 bytes per lane) without passing through
 // registers.  Those loads write 64 lanes x 16 B = 1 KiB of consecutive LDS per instruction, so rows cannot be padded;
 // bank conflicts are avoided by an XOR swizzle of the 16-byte chunk index, applied to the global address each lane
@@ -28,7 +29,7 @@
 // Rows or k-values outside the matrix are never read: their buffer offsets are out of the descriptor's range and the
 // hardware returns zeros.
 //
-// Pipeline: two or three LDS stages; the loads of the following slab(s) are in flight while a slab is multiplied;
+// Pipeline: two to four LDS stages; the loads of the following slab(s) are in flight while a slab is multiplied;
 // one barrier per slab.  The loads are issued through inline assembly (see load_slab_untracked).
 #include "kernels.h"
 #include <atomic>
@@ -58,6 +59,13 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4 make_rsrc_words(const void* p, unsigned bytes) {
   const uint64_t addr = (uint64_t)(uintptr_t)p;
   return i32x4{(int)(unsigned)addr, (int)(unsigned)((addr >> 32) & 0xffffu), (int)bytes, 0x00020000};
+}
+
+// Extent of an operand of `rows` rows and K k-values, for its descriptor.  Row-contiguous: to the end of the last k-value's rows and not of
+// its pitch (the operand may be some of a matrix's rows, with the others between its k-values); k-values past K lie beyond it.
+template <bool KFAST>
+__device__ __forceinline__ unsigned operand_bytes(int rows, int64_t rs, int64_t cs, int K) {
+  return (unsigned)(2 * (KFAST ? (int64_t)rows * rs : (int64_t)(K - 1) * cs + (rows + 7) / 8 * 8));
 }
 
 // One operand's tile: ROWS matrix rows (m or n) by BK k-values, ROWS*BK*2 bytes of LDS, unpadded.
@@ -481,8 +489,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs<bf16>& a, int tile
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const unsigned a_bytes = (unsigned)(2 * (AK ? (int64_t)a.M * a.a_rs : (int64_t)a.K * a.a_cs));
-  const unsigned b_bytes = (unsigned)(2 * (BKF ? (int64_t)a.N * a.b_rs : (int64_t)a.K * a.b_cs));
+  const unsigned a_bytes = operand_bytes<AK>(a.M, a.a_rs, a.a_cs, a.K), b_bytes = operand_bytes<BKF>(a.N, a.b_rs, a.b_cs, a.K);
   const i32x4 ra_rsrc = make_rsrc_words(a.A, a_bytes), rb_rsrc = make_rsrc_words(a.B, b_bytes);
   unsigned offa[TA::PER_WAVE], offb[TB::PER_WAVE];
   TA::init_offsets(a.a_rs, a.a_cs, m0, a.M, a.K, offa);
@@ -755,8 +762,8 @@ __device__ __forceinline__ void gemm_ring_tile(const GemmArgs<bf16>& a, int tile
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const i32x4 ra_rsrc = make_rsrc_words(a.A, (unsigned)(2 * (AK ? (int64_t)a.M * a.a_rs : (int64_t)a.K * a.a_cs)));
-  const i32x4 rb_rsrc = make_rsrc_words(a.B, (unsigned)(2 * (BKF ? (int64_t)a.N * a.b_rs : (int64_t)a.K * a.b_cs)));
+  const i32x4 ra_rsrc = make_rsrc_words(a.A, operand_bytes<AK>(a.M, a.a_rs, a.a_cs, a.K));
+  const i32x4 rb_rsrc = make_rsrc_words(a.B, operand_bytes<BKF>(a.N, a.b_rs, a.b_cs, a.K));
   unsigned offa[TA::PER_WAVE], offb[TB::PER_WAVE];
   TA::init_offsets(a.a_rs, a.a_cs, m0, a.M, a.K, offa);
   TB::init_offsets(a.b_rs, a.b_cs, n0, a.N, a.K, offb);
@@ -1012,12 +1019,32 @@ int launch_rows(const GemmArgs<bf16>& a, hipStream_t s) {
 constexpr TileCost kGradTiles[] = {
   {256, 256, 1, 1.08, 1.24, 1.42, 9.3}, {256, 128, 1, 0.18, 0.70, 0.80, 7.0}, {128, 128, 1, 0.29, 0.47, 0.50, 4.9}, {128, 128, 2, 0.72, 0.475, 0.50, 5.0},
 };
-struct GradPlan { int tile; double us; };
-GradPlan grad_plan(int M, int N, int K, int kernels, int splits) {
-  GradPlan best = {0, 1e30};
+// Without pieces, the rows of the output may be computed in two launches: as many tile rows as make whole rounds of blocks, and the rest on
+// the tile that is fastest for it.  A last round takes nearly as long as a full one however few blocks it has: 22016 x 4096 has 1376 tiles of
+// 256 x 256, 5.4 rounds, and the 96 tiles left over are 192 of 256 x 128, which one round of half the length holds.  8192 tokens: 22016 x 4096
+// 1269 -> 1142 us, 50264 x 2048 1567 -> 1411.  Where the line lies (200 measured shapes, 300 to 16384 tokens, 1 to 7 rounds): only where the tile
+// columns divide a round, so that the first launch ends on a full one (with 10, 20 or 43 of them it is 4 % slower to 12 % faster, without a
+// pattern that the estimate knows); from 1024 tokens (300 and 512: the writes of the output bound both, up to 11 % slower); for an estimated
+// gain of 6 %, or 15 % if the first launch is a single round (below that up to 5 % slower).  Within it 0.2 % slower to 28 % faster, 9 % on average.
+struct GradPlan { int tile; double us; int rows; };      // rows: those of the first launch, 0: all
+GradPlan grad_plan(int M, int N, int K, int kernels, int splits, bool two_launches) {
+  constexpr int kCount = (int)(sizeof(kGradTiles) / sizeof(kGradTiles[0]));
+  GradPlan best = {0, 1e30, 0};
   for (int c = 0; c < (int)(sizeof(kGradTiles) / sizeof(kGradTiles[0])); ++c) {
     const double us = tile_us(kGradTiles[c], M, N, K, kernels, splits);
-    if (us < best.us) best = {c, us};
+    if (us < best.us) best = {c, us, 0};
+  }
+  if (splits == 1 && two_launches && K >= 1024) {
+    const double whole = best.us;
+    for (int c = 0; c < kCount; ++c) {
+      const TileCost& t = kGradTiles[c];
+      const int64_t tm = (M + t.bm - 1) / t.bm, tn = (N + t.bn - 1) / t.bn, round = std::max(1, 256 / kernels) * t.blocks;
+      if (round % tn != 0) continue;
+      const int64_t rows = tm * tn / round * (round / tn) * t.bm;
+      if (rows <= 0 || rows >= M) continue;
+      const double us = tile_us(t, (int)rows, N, K, kernels) + grad_plan(M - (int)rows, N, K, kernels, 1, false).us;
+      if (us < best.us && us < (rows * tn >= 2 * round * t.bm ? 0.94 : 0.87) * whole) best = {c, us, (int)rows};
+    }
   }
   if (splits > 1) best.us += 3.0 + (splits + 1) * 4e-6 / 4.5 * (double)M * N;
   return best;
@@ -1043,14 +1070,26 @@ int launch_group(const GemmArgs<bf16>* a, int n, int bm, int bn, int wgn, int th
   CEPHALO_CHECK_LAUNCH("grad_group");
   return CEPHALO_OK;
 }
-int launch_grad(const GemmArgs<bf16>& a, hipStream_t s) {
-  const int splits = (a.splits > 1 && a.part) ? a.splits : 1;
-  switch (grad_plan(a.M, a.N, a.K, side_by_side, splits).tile) {
+int launch_grad_tile(const GemmArgs<bf16>& a, int tile, hipStream_t s) {
+  switch (tile) {
     case 0: return launch_cfg<256, 256, 4, 2, false, false, EPI_GRAD>(a, s);
     case 1: return launch_ring<256, 128, 4, 2, EPI_GRAD, 3, false, false>(a, s);
     case 2: return launch_ring<128, 128, 2, 2, EPI_GRAD, 4, false, false>(a, s);
     default: return launch_ring<128, 128, 2, 2, EPI_GRAD, 2, false, false>(a, s);
   }
+}
+// (row sums come in one piece per owner of a tile row, and the tiles of two launches differ in those: with them, one launch)
+bool grad_in_two(const GemmArgs<bf16>& a) { return !a.rowsum; }
+int launch_grad(const GemmArgs<bf16>& a, hipStream_t s) {
+  const GradPlan p = grad_plan(a.M, a.N, a.K, side_by_side, (a.splits > 1 && a.part) ? a.splits : 1, grad_in_two(a));
+  if (!p.rows) return launch_grad_tile(a, p.tile, s);
+  GemmArgs<bf16> first = a, rest = a;
+  first.M = p.rows;
+  rest.M = a.M - p.rows;
+  rest.A += p.rows * a.a_rs;
+  rest.G += (int64_t)p.rows * a.N;
+  if (const int rc = launch_grad_tile(first, p.tile, s); rc != CEPHALO_OK) return rc;
+  return launch_grad_tile(rest, grad_plan(rest.M, rest.N, rest.K, side_by_side, 1, false).tile, s);
 }
 
 // The layouts that no layer produces (cephalo_op_gemm alone does).
@@ -1102,7 +1141,7 @@ int gemm_grad_splits(int M, int N, int K) {
   double least = 1e30;
   for (int sp : {1, 2, 3, 4, 6, 8}) {
     if (sp > most) break;
-    const double us = grad_plan(M, N, K, 1, sp).us;       // (not of the side-by-side hint: the pieces decide the order of the sums)
+    const double us = grad_plan(M, N, K, 1, sp, false).us;       // (not of the side-by-side hint: the pieces decide the order of the sums)
     if (us < least) { least = us; best = sp; }
   }
   return best;
@@ -1124,14 +1163,14 @@ int gemm_set_side_by_side(int kernels) { const int was = side_by_side; side_by_s
 // The group runs as one launch where that is estimated to be faster than one launch each (with pieces): it saves the fixed time of the
 // others and the idle compute units of their last rounds.  All blocks of a group take the same time (the token axis is theirs in
 // common), so no order of them is better than another.  256 x 1024 .. 256 tokens (a tiny layer's four): 31 -> 9 us; 4096 tokens at
-// width 1024: 132 -> 101.
+// width 1024: 132 -> 105.
 int grad_group_tile(const GemmArgs<bf16>* a, int n) {
   if (n < 2 || n > kMaxGradGroup) return -1;
   double apart = 0, least = 1e30;
   int tile = 0;
   for (int q = 0; q < n; ++q) {
     if (!gemm_mfma_takes(a[q]) || a[q].a_cs == 1 || a[q].b_cs == 1 || a[q].K != a[0].K) return -1;
-    apart += grad_plan(a[q].M, a[q].N, a[q].K, 1, (a[q].splits > 1 && a[q].part) ? a[q].splits : 1).us;
+    apart += grad_plan(a[q].M, a[q].N, a[q].K, 1, (a[q].splits > 1 && a[q].part) ? a[q].splits : 1, grad_in_two(a[q])).us;
   }
   for (int c = 0; c < (int)(sizeof(kGradTiles) / sizeof(kGradTiles[0])); ++c) {
     double blocks = 0;

@@ -133,8 +133,9 @@ def test_bias_sums_of_two_projections_that_do_not_fit_the_work_area_together():
 
 
 # tokens, out features, in features: every tile of the weight gradient (128 x 128 with four and with two stages, 256 x 128, 256 x 256), ragged
-# edges, one slab and less, a token axis in 1, 2, 4 and 8 pieces
-@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (65, 136, 72), (200, 264, 392), (300, 1544, 1032), (130, 3080, 2056), (4100, 264, 136), (9000, 520, 264), (2100, 1032, 520)])
+# edges, one slab and less, a token axis in 1, 2, 4 and 8 pieces; the last: on an eighth of the chip and less, 2048 and 136
+# of its rows in two launches where no bias gradient comes along, which has the same bits
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (65, 136, 72), (200, 264, 392), (300, 1544, 1032), (130, 3080, 2056), (4100, 264, 136), (9000, 520, 264), (2100, 1032, 520), (1100, 2184, 1000)])
 def test_weight_gradient_tiles(T, N, K):
     print("wgrad tiles", T, N, K, flush=True)
     g = torch.Generator(device="cuda").manual_seed(T + N + K)
