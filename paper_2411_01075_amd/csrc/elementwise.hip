@@ -1,7 +1,7 @@
 // LayerNorm forward/backward and column sums (bias gradients): HBM-bound row kernels.
 // Forward: one 64-lane wavefront owns a row; its lanes hold the row in registers as 16-byte
 // vectors, and row statistics are wavefront reductions (no LDS, no block barrier).
-// Backward: a block of four wavefronts shares each row (see ln_bwd_kernel).
+// Backward: a team of one, two or four wavefronts shares each row (see ln_bwd_kernel).
 // The residual stream (x, x1, y and their gradients) and the gradients entering LayerNorm's
 // backward are fp32; LayerNorm outputs are in the activation type T.
 #include "kernels.h"
