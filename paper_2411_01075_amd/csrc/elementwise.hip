@@ -118,7 +118,8 @@ constexpr int kLnBwdRowsPerBlock = 8;
 // H = 2048.)  Wide rows (TEAM 256): one team per block, two rows a step and the next two in flight.  Narrow rows: 512 threads, so 4 or 8
 // teams with 2 rows or 1 each, all asked for at once, and the teams' sums are added through LDS in team order; with one team of 256 half of
 // it was idle at H = 1024 and seven eighths at 256 (1024 x 1024: 9.1 -> 7.9 us, 256 x 256: 7.8 -> 5.7).  Two teams of 256 lose (2048 x 1600:
-// 14.0 -> 14.7; 2048 x 2560: 21 -> 26, spills).
+// 14.0 -> 14.7; 2048 x 2560: 21 -> 26, spills).  Inside a layer's backward, tensors from memory: 8192 x 2048 52.7 us, 4096 x 4096 59, 2048 x 1600
+13.4, 2048 x 8192 67; 55.5, 61, 15.3 and 70 with the rows' statistics in vector loads.
 // SUMS: the block's column sums of `out` go to part_s as well (the bias gradient of a projection that writes into the
 // residual stream is the column sum of the stream's gradient, which is this kernel's result).
 // RESID: there is a residual to add (otherwise `resid` is not read).
@@ -138,7 +139,10 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
   constexpr int NS = SUMS ? 3 : 2;                                            // column sums
   __shared__ float red[2][TEAMS][R][2][TW];
   __shared__ __attribute__((aligned(16))) float cols[TEAM * VN];              // a team's sums on their way to the first team's
-  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % TW, team = threadIdx.x / TEAM, tt = threadIdx.x % TEAM;
+  // (the team is the same in every lane of a wavefront, and said so: a row's mean and rstd are then scalar loads, with a counter of their
+  // own.  As vector loads they are the youngest when they are needed, and waiting for them drains the rows asked for ahead)
+  const int lane = threadIdx.x & 63, of_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = of_block % TW, team = TEAMS == 1 ? 0 : of_block / TW, tt = threadIdx.x % TEAM;
   const int nv = H / VN;
   const float inv_h = 1.0f / (float)H;
   const int row0 = blockIdx.x * kLnBwdRowsPerBlock + team * PER_TEAM;

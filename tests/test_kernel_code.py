@@ -1,0 +1,14 @@
+"""Properties of the compiled kernels that no result shows."""
+import pytest
+
+from tests import kernel_code
+
+
+@pytest.mark.parametrize("form", ["IDF16bLi256ELi1", "IDF16bLi256ELi2", "IfLi256ELi1", "IfLi256ELi2"])
+def test_norm_backward_reads_the_statistics_through_the_scalar_unit(form):
+    """A row's mean and rstd are single floats.  As vector loads they are younger than the next rows' loads, and waiting for them waits
+    for those too (memory operations are counted in order)."""
+    for name in kernel_code.kernels("ln_bwd_kernel" + form):
+        code = kernel_code.instructions(name)
+        assert any(i.startswith("global_load_dwordx4") for i in code), name
+        assert not [i for i in code if i.split()[0] in ("global_load_dword", "flat_load_dword", "buffer_load_dword")], name
