@@ -119,7 +119,7 @@ constexpr int kLnBwdRowsPerBlock = 8;
 // teams with 2 rows or 1 each, all asked for at once, and the teams' sums are added through LDS in team order; with one team of 256 half of
 // it was idle at H = 1024 and seven eighths at 256 (1024 x 1024: 9.1 -> 7.9 us, 256 x 256: 7.8 -> 5.7).  Two teams of 256 lose (2048 x 1600:
 // 14.0 -> 14.7; 2048 x 2560: 21 -> 26, spills).  Inside a layer's backward, tensors from memory: 8192 x 2048 52.7 us, 4096 x 4096 59, 2048 x 1600
-13.4, 2048 x 8192 67; 55.5, 61, 15.3 and 70 with the rows' statistics in vector loads.
+// 13.4, 2048 x 8192 67; 55.5, 61, 15.3 and 70 with the rows' statistics in vector loads.
 // SUMS: the block's column sums of `out` go to part_s as well (the bias gradient of a projection that writes into the
 // residual stream is the column sum of the stream's gradient, which is this kernel's result).
 // RESID: there is a residual to add (otherwise `resid` is not read).
