@@ -337,20 +337,27 @@ reduce_jobs_kernel(ReduceBatch b, float scale, int accumulate) {
 }
 
 // Column sums of ROWS rows by 64 vectors of 16 bytes per block: the four wavefronts take every fourth row, all of them in flight, and
-// their sums are added in wavefront order.  LOWP (T = float): the rows are written in bf16 as well.  The blocks of the same rows are
-// neighbours in the launch (neighbours in the column instead read lines 64 rows apart: 24576 x 8192 in bf16 74 -> 83 us).  (One row at a time
-// per thread, as it used to be: the 4096 x 1024 gradient of a BERT-Large-shaped share took 38 to 68 us inside the step, with the copy into
-// bf16 beside it 6; 24576 x 8192 in bf16, alone 78, now 73.)
+// their sums are added in wavefront order.  LOWP (T = float): the rows are written in bf16 as well.  (One row at a time per thread, as it
+// used to be: the 4096 x 1024 gradient of a BERT-Large-shaped share took 38 to 68 us inside the step, with the copy into bf16 beside it 6.)
+// Order of the blocks, whose sums do not depend on it: those of the same rows are neighbours (in order of the columns instead, neighbours read
+// lines 64 rows apart: 24576 x 8192 in bf16 74 -> 83 us).  runs: each XCD has one contiguous run of that order, so that it reads whole rows; with
+// neighbours on neighbouring XCDs each reads an eighth of every row and, at widths of a power of two, through a part of its L2's
+// channels.  Memory by itself is faster with all XCDs at the same place.  So: runs where the matrix fits the 256 MB cache.  Both orders and the kernel
+// of one row at a time, with the reduction, us: 24576 x 2048 fp32 38.4, runs 33.8, former 33.1; 24576 x 4096 bf16 37.2, 34.3, 34.5; 24576 x 2048 bf16 26.1,
+// 20.6, 28.7; 8192 x 16384 bf16 48.3, 43.7, 48.9; beyond 256 MB 24576 x 8192 bf16 72.5, 76.6, 80.7; 24576 x 4096 fp32 72.5, 73.2, 76.7.  The
+// copying form inside a layer, which also writes, keeps the plain order: 8192 x 2048 19.2, runs 20.1.  What is still behind
+// the former kernel: 8192 x 10240 fp32 57.3 (55.8) and, for its reduction in one stage, 100000 x 256 fp32 25.8 (25.1).
 constexpr int kColsumRowsPerChunk = 64;
 template <typename T, bool LOWP, int ROWS>
 __global__ void __launch_bounds__(kThreads)
-colsum_kernel(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restrict__ partials, int rows, int N) {
+colsum_kernel(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restrict__ partials, int rows, int N, int runs) {
   constexpr int VN = Vec<T>::N;
   typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
   __shared__ float red[kWaves][64][VN + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col_blocks = (N / VN + 63) / 64, chunk = blockIdx.x / col_blocks;
-  const int col = (blockIdx.x % col_blocks * 64 + lane) * VN;
+  const int col_blocks = (N / VN + 63) / 64, total = gridDim.x, xcd = blockIdx.x & 7;
+  const int at = runs ? xcd * (total >> 3) + min(xcd, total & 7) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int chunk = at / col_blocks, col = (at % col_blocks * 64 + lane) * VN;
   const int r0 = chunk * ROWS + wave;
   const bool in = col < N;
   float acc[VN];
@@ -511,7 +518,7 @@ int launch_colsum(const T* dY, float* partials, size_t partial_bytes, float* g, 
   const int nchunks = (rows + kColsumRowsPerChunk - 1) / kColsumRowsPerChunk;
   const int nvec = N / Vec<T>::N;
   const int64_t grid = (int64_t)nchunks * ((nvec + 63) / 64);      // (one axis: the blocks of a chunk of rows are neighbours)
-  colsum_kernel<T, false, kColsumRowsPerChunk><<<(unsigned)grid, kThreads, 0, s>>>(dY, nullptr, partials, rows, N);
+  colsum_kernel<T, false, kColsumRowsPerChunk><<<(unsigned)grid, kThreads, 0, s>>>(dY, nullptr, partials, rows, N, (size_t)rows * N * sizeof(T) <= (size_t)256 << 20);
   CEPHALO_CHECK_LAUNCH("colsum");
   return launch_reduce_partials(partials, nchunks, N, g, scale, accumulate, s);
 }
@@ -522,7 +529,7 @@ int cast_colsum_chunks(int rows) { return (rows + kCastColsumRows - 1) / kCastCo
 int launch_cast_colsum(const float* x, bf16* lowp, float* partials, size_t partial_bytes, int rows, int N, hipStream_t s) {
   const int nchunks = cast_colsum_chunks(rows);
   if (partial_bytes < (size_t)nchunks * N * sizeof(float)) return fail(CEPHALO_EWORKSPACE, "cast_colsum: partial buffer too small");
-  colsum_kernel<float, true, kCastColsumRows><<<(unsigned)((int64_t)nchunks * ((N / 4 + 63) / 64)), kThreads, 0, s>>>(x, lowp, partials, rows, N);
+  colsum_kernel<float, true, kCastColsumRows><<<(unsigned)((int64_t)nchunks * ((N / 4 + 63) / 64)), kThreads, 0, s>>>(x, lowp, partials, rows, N, 0);
   CEPHALO_CHECK_LAUNCH("cast_colsum");
   return CEPHALO_OK;
 }

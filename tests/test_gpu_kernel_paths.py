@@ -99,6 +99,19 @@ def test_column_sums_edges(rows, N, bf16):
     assert (np.abs(out.double().cpu().numpy() - 1.5 * x.sum(0)) <= 1.5 * bound + 2.0 ** -23 * np.abs(x.sum(0))).all()
 
 
+@pytest.mark.parametrize("rows,N,bf16", [(4096, 32768, True), (4097, 32776, True), (2048, 32768, False), (3001, 32776, False), (40001, 2048, False)])
+def test_column_sums_around_the_size_of_the_cache(rows, N, bf16):
+    """The blocks' order changes at 256 MB; odd numbers of blocks leave the eight runs of different lengths."""
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    X = torch.randn(rows, N, device="cuda", generator=g)
+    X = X.bfloat16() if bf16 else X
+    ws = torch.empty(C.cephalo_op_colsum_workspace(rows, N), dtype=torch.uint8, device="cuda").fill_(255)
+    out = torch.full((N,), float("nan"), device="cuda")
+    C.cephalo_op_colsum(C.BF16 if bf16 else C.F32, X, rows, N, out, 1.0, 0, ws)
+    ref, size = X.sum(0, dtype=torch.float64), X.abs().sum(0, dtype=torch.float64)
+    assert ((out.double() - ref).abs() <= (rows + 4) * 2.0 ** -24 * size).all()
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("m,S", [(8, 512), (8, 513), (1, 9), (3, 43)])
 def test_bias_gradient_of_the_last_projection_is_the_column_sum_of_dy(m, S, bf16):
