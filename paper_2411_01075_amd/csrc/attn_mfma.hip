@@ -14,6 +14,7 @@
 // [token][d] tiles) is fetched from LDS with the transposing read ds_read_b64_tr_b16.
 #include <type_traits>
 #include "kernels.h"
+#include "reserve_lds.h"
 #include <cstdlib>
 
 namespace cephalo {
@@ -1051,16 +1052,6 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
   }   // pass
 }
 
-template <typename K>
-int reserve_lds(K kern, size_t bytes) {
-  static bool done = false;       // one flag per kernel instantiation
-  if (done) return CEPHALO_OK;
-  done = true;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
-    return fail(CEPHALO_EHIP, "attention: cannot reserve %zu B of LDS", bytes);
-  return CEPHALO_OK;
-}
-
 // Causal launches: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute unit of their own at
 // once: then the launch lasts as long as the longest tile, not as the longest and the shortest (8 heads of 80, 700 tokens, 48 tiles: forward 22 ->
 // 15 us, backward 61 -> 44).  Beyond that single tiles, longest first, lose (25 heads of 64, 2 x 1024 tokens, 400 tiles: backward 56 paired, 78).
@@ -1077,8 +1068,8 @@ int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hi
     dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
     const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16 + 2) * 64 * sizeof(float);
     const size_t lds = staging > merge ? staging : merge;
-    auto kern = [] { if constexpr (D == 128) return attn_fwd_turns_kernel<D, CAUSAL>; else return attn_fwd8_kernel<D, CAUSAL>; }();
-    int rc = reserve_lds(kern, lds);
+    constexpr auto kern = [] { if constexpr (D == 128) return attn_fwd_turns_kernel<D, CAUSAL>; else return attn_fwd8_kernel<D, CAUSAL>; }();
+    int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
     kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, scale, paired);
   } else {
@@ -1086,8 +1077,8 @@ int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hi
     // (measured 12 % faster than the eight-wavefront form, whose wavefronts move in step between barriers)
     dim3 grid(nt, A, m);
     const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);
-    auto kern = attn_fwd_kernel<D, CAUSAL>;
-    int rc = reserve_lds(kern, lds);
+    constexpr auto kern = attn_fwd_kernel<D, CAUSAL>;
+    int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
     kern<<<grid, kThreads, lds, s>>>(qkv, O, lse, S, H, A, scale);
   }
@@ -1106,8 +1097,8 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
     // two stages of 128 keys and values or, at the end, the merge of the halves
     const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16) * 64 * sizeof(float);
     const size_t lds = staging > merge ? staging : merge;
-    auto kern = attn_dq_kernel<D, CAUSAL, ROT>;
-    int rc = reserve_lds(kern, lds);
+    constexpr auto kern = attn_dq_kernel<D, CAUSAL, ROT>;
+    int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
     kern<<<grid, kThreads8, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
   }
@@ -1116,8 +1107,8 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
     const size_t staging = (4 * (size_t)Tile<D>::ELEMS + 2 * (size_t)Tile<D, 128>::ELEMS) * sizeof(bf16) + 2 * 128 * sizeof(float);
     const size_t merge = (size_t)4 * (D / 32 * 16 * 2) * 64 * sizeof(float);
     const size_t lds = staging > merge ? staging : merge;
-    auto kern = attn_dkv_kernel<D, CAUSAL, ROT>;
-    int rc = reserve_lds(kern, lds);
+    constexpr auto kern = attn_dkv_kernel<D, CAUSAL, ROT>;
+    int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
     kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
   }

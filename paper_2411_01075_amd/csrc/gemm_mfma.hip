@@ -32,6 +32,7 @@
 // Pipeline: two to four LDS stages; the loads of the following slab(s) are in flight while a slab is multiplied;
 // one barrier per slab.  The loads are issued through inline assembly (see load_slab_untracked).
 #include "kernels.h"
+#include "reserve_lds.h"
 #include <atomic>
 #include <cstdlib>
 #include <cstdint>
@@ -887,24 +888,11 @@ splitk_reduce_kernel(const float* __restrict__ part, int splits, int64_t mn4, fl
   reinterpret_cast<f32x4*>(G)[i] = out;
 }
 
-template <auto KERN>
-int reserve_lds(size_t lds) {
-  // per instantiation; setting the attribute again with the same value is harmless, so two threads that both find the
-  // flag clear may both set it
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return fail(CEPHALO_EHIP, "gemm_mfma: cannot reserve %zu B of LDS", lds);
-    attr_set.store(true, std::memory_order_release);
-  }
-  return CEPHALO_OK;
-}
-
 // Launch of one instantiation: LDS reservation (once), the split of the contracted axis, the reduction of the pieces.
 template <auto KERN>
 int launch_kernel(const GemmArgs<bf16>& a, int BMv, int BNv, int wgn, int threads, size_t lds, hipStream_t s) {
   const int tm = (a.M + BMv - 1) / BMv, tn = (a.N + BNv - 1) / BNv;
-  if (const int rc = reserve_lds<KERN>(lds); rc != CEPHALO_OK) return rc;
+  if (const int rc = reserve_lds<KERN>("gemm_mfma", lds); rc != CEPHALO_OK) return rc;
   const int slabs = (a.K + BK - 1) / BK;
   int splits = (a.epi == EPI_GRAD && a.splits > 1 && a.part) ? a.splits : 1;
   int per = (slabs + splits - 1) / splits;
@@ -1052,7 +1040,7 @@ GradPlan grad_plan(int M, int N, int K, int kernels, int splits, bool two_launch
 // one launch of a group
 template <auto KERN>
 int launch_group(const GemmArgs<bf16>* a, int n, int bm, int bn, int wgn, int threads, size_t lds, hipStream_t s) {
-  if (const int rc = reserve_lds<KERN>(lds); rc != CEPHALO_OK) return rc;
+  if (const int rc = reserve_lds<KERN>("gemm_mfma", lds); rc != CEPHALO_OK) return rc;
   GradBatch b = {};
   b.n = n;
   for (int q = 0; q < n; ++q) {
