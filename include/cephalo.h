@@ -253,6 +253,21 @@ int cephalo_op_linear_wgrad_bias(int32_t dtype, const void* dY, const void* X, i
                                  float* G, float* gb, float scale, int32_t accumulate, void* workspace,
                                  size_t workspace_bytes, void* stream);
 
+/* Up to four bf16 weight gradients over the same T tokens in one launch, as a layer's backward runs its projections' where
+ * that is faster: G[i] [N[i],K[i]] and, where gb[i] is not NULL, gb[i] [N[i]] as in cephalo_op_linear_wgrad_bias.  Every product
+ * is one piece.  tile: 0 is 256 x 256, 1 is 256 x 128, 2 is 128 x 128 with four stages, 3 is 128 x 128 with two; G does not depend on
+ * it, gb's order of additions does.  N and K are multiples of 8; buffers 16-byte aligned, on the device; the arrays are host
+ * memory.  workspace: at least cephalo_op_linear_wgrad_group_workspace(count, N, K) bytes.
+ * cephalo_wgrad_group_tile tells the tile on which a layer runs such products in one launch, -1 where it launches them one by one
+ * (bias[i]: product i has a bias gradient), and in pieces[i], unless pieces is NULL, how many pieces of the token axis product
+ * i takes by itself. */
+int cephalo_wgrad_group_tile(int32_t count, int32_t T, const int32_t* N, const int32_t* K, const int32_t* bias, int32_t* tile,
+                             int32_t* pieces);
+size_t cephalo_op_linear_wgrad_group_workspace(int32_t count, const int32_t* N, const int32_t* K);
+int cephalo_op_linear_wgrad_group(int32_t count, const void* const* dY, const void* const* X, int32_t T, const int32_t* N, const int32_t* K,
+                                  float* const* G, float* const* gb, float scale, int32_t accumulate, int32_t tile, void* workspace,
+                                  size_t workspace_bytes, void* stream);
+
 /* For callers that cannot allocate device memory and have no work area to hand over (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): cephalo_op_linear_wgrad with the partial sums of a split
  * token axis kept in a fixed device array of CEPHALO_NOALLOC_SCRATCH_BYTES that the library's code object carries

@@ -96,6 +96,11 @@ SIGNATURES = {
     "cephalo_op_linear_wgrad": (ctypes.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _f32, _i32, _vp, _sz, _vp]),
     "cephalo_op_linear_wgrad_bias_workspace": (_sz, [_i32, _i32, _i32, _i32]),
     "cephalo_op_linear_wgrad_bias": (ctypes.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _f32, _i32, _vp, _sz, _vp]),
+    "cephalo_wgrad_group_tile": (ctypes.c_int, [_i32, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32), ctypes.POINTER(_i32), ctypes.POINTER(_i32),
+                                                ctypes.POINTER(_i32)]),
+    "cephalo_op_linear_wgrad_group_workspace": (_sz, [_i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
+    "cephalo_op_linear_wgrad_group": (ctypes.c_int, [_i32, ctypes.POINTER(_vp), ctypes.POINTER(_vp), _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32),
+                                                     ctypes.POINTER(_vp), ctypes.POINTER(_vp), _f32, _i32, _i32, _vp, _sz, _vp]),
     "cephalo_op_linear_wgrad_static": (ctypes.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _f32, _i32, _vp]),
     "cephalo_op_norm_fwd": (ctypes.c_int, [_i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _i32, _f32, _vp]),
     "cephalo_op_norm_bwd_workspace": (_sz, [_i32, _i32]),
@@ -326,6 +331,30 @@ def cephalo_op_linear_wgrad_bias_workspace(dtype, T, N, K):
 def cephalo_op_linear_wgrad_bias(dtype, dY, X, T, N, K, G, gb, scale, accumulate, workspace, stream=None):
     _check(lib().cephalo_op_linear_wgrad_bias(dtype, _ptr(dY), _ptr(X), T, N, K, _ptr(G), _ptr(gb), scale, int(accumulate),
                                               _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+
+
+def _ints(values):
+    return (_i32 * len(values))(*values)
+
+
+def _ptrs(tensors):
+    return (_vp * len(tensors))(*[_ptr(t) for t in tensors])
+
+
+def cephalo_wgrad_group_tile(T, N, K, bias):
+    """(tile or -1, pieces of each product by itself)"""
+    tile, pieces = _i32(0), _ints([0] * len(N))
+    _check(lib().cephalo_wgrad_group_tile(len(N), T, _ints(N), _ints(K), _ints([int(b) for b in bias]), ctypes.byref(tile), pieces))
+    return tile.value, list(pieces)
+
+
+def cephalo_op_linear_wgrad_group_workspace(N, K):
+    return int(lib().cephalo_op_linear_wgrad_group_workspace(len(N), _ints(N), _ints(K)))
+
+
+def cephalo_op_linear_wgrad_group(dY, X, T, N, K, G, gb, scale, accumulate, tile, workspace, stream=None):
+    _check(lib().cephalo_op_linear_wgrad_group(len(N), _ptrs(dY), _ptrs(X), T, _ints(N), _ints(K), _ptrs(G), _ptrs(gb), scale, int(accumulate), tile,
+                                               _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def cephalo_op_attention_fwd(desc, qkv, O, lse, micro_batch, stream=None):

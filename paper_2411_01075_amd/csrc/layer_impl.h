@@ -528,32 +528,39 @@ template <> inline int wgrad_group<float>(const GradJob<float>* jobs, int n, int
   for (int i = 0; i < n; ++i) if (jobs[i].gb) sums.add(jobs[i].dY, tokens, jobs[i].N, jobs[i].gb);
   return launch_gemm_f32_group(a, n, s);
 }
-template <> inline int wgrad_group<bf16>(const GradJob<bf16>* jobs, int n, int tokens, SumList& sums, const Work<bf16>& w, hipStream_t s, bool* done) {
-  GemmArgs<bf16> a[kMaxGradGroup];
-  int pieces[kMaxGradGroup];
-  *done = false;
+// the products as they would run apart: in pieces where that is faster
+inline void group_products(const GradJob<bf16>* jobs, int n, int tokens, float scale, int acc, float* part, GemmArgs<bf16>* a) {
   for (int i = 0; i < n; ++i) {
     const GradJob<bf16>& q = jobs[i];
-    a[i] = linear_wgrad<bf16>(q.dY, q.X, tokens, q.N, q.K, q.g, sums.scale, sums.acc);
-    a[i].splits = w.wg_part ? gemm_grad_splits(q.N, q.K, tokens) : 1;
-    a[i].part = w.wg_part;
+    a[i] = linear_wgrad<bf16>(q.dY, q.X, tokens, q.N, q.K, q.g, scale, acc);
+    a[i].splits = part ? gemm_grad_splits(q.N, q.K, tokens) : 1;
+    a[i].part = part;
   }
-  const int tile = grad_group_tile(a, n);
-  if (tile < 0) return CEPHALO_OK;
+}
+// ... and in one launch on `tile`, the pieces of the bias sums in rs_part and listed in `sums` (done: there was room for them)
+inline int group_launch(const GradJob<bf16>* jobs, int n, int tile, GemmArgs<bf16>* a, float* rs_part, size_t rs_part_bytes, SumList& sums, hipStream_t s, bool* done) {
+  int pieces[kMaxGradGroup];
   size_t used = 0;
   for (int i = 0; i < n; ++i) {
     if (!jobs[i].gb) continue;
     a[i].rowsum = jobs[i].gb;
-    a[i].rowsum_part = w.rs_part + used / sizeof(float);
+    a[i].rowsum_part = rs_part + used / sizeof(float);
     a[i].rowsum_part_bytes = gemm_rowsum_part_bytes(jobs[i].N, jobs[i].K, 1);
     a[i].rowsum_pieces = &pieces[i];
     used += align_up(a[i].rowsum_part_bytes);
   }
-  if (used > w.rs_part_bytes) return CEPHALO_OK;
+  *done = used <= rs_part_bytes;
+  if (!*done) return CEPHALO_OK;
   TRY(launch_grad_group(a, n, tile, s));
   for (int i = 0; i < n; ++i) if (jobs[i].gb) sums.add(a[i].rowsum_part, pieces[i], jobs[i].N, jobs[i].gb);
-  *done = true;
   return CEPHALO_OK;
+}
+template <> inline int wgrad_group<bf16>(const GradJob<bf16>* jobs, int n, int tokens, SumList& sums, const Work<bf16>& w, hipStream_t s, bool* done) {
+  GemmArgs<bf16> a[kMaxGradGroup];
+  *done = false;
+  group_products(jobs, n, tokens, sums.scale, sums.acc, w.wg_part, a);
+  const int tile = grad_group_tile(a, n);
+  return tile < 0 ? CEPHALO_OK : group_launch(jobs, n, tile, a, w.rs_part, w.rs_part_bytes, sums, s, done);
 }
 
 template <typename T>

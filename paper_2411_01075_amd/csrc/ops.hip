@@ -140,6 +140,68 @@ extern "C" int cephalo_op_linear_wgrad_bias(int32_t dtype, const void* dY, const
   return launch_colsum<bf16>(static_cast<const bf16*>(dY), col_part, col_bytes, gb, scale, accumulate, T, N, s);
 }
 
+namespace {
+// the jobs of a group entry (checked); a query has no buffers and takes any aligned address
+int group_jobs(const char* who, int count, int T, const int32_t* N, const int32_t* K, GradJob<bf16>* jobs) {
+  if (count < 1 || count > kMaxGradGroup) return fail(CEPHALO_EINVAL, "%s: %d products, 1 to %d go in one launch", who, count, kMaxGradGroup);
+  if (T <= 0 || !N || !K) return fail(CEPHALO_EINVAL, "%s: no tokens or no sizes", who);
+  for (int i = 0; i < count; ++i) {
+    if (N[i] <= 0 || K[i] <= 0) return fail(CEPHALO_EINVAL, "%s: sizes %d x %d must be positive", who, N[i], K[i]);
+    if (N[i] % 8 != 0 || K[i] % 8 != 0) return fail(CEPHALO_EUNSUPPORTED, "%s: the widths %d x %d must be multiples of 8", who, N[i], K[i]);
+    jobs[i] = GradJob<bf16>{nullptr, nullptr, N[i], K[i], nullptr, nullptr};
+  }
+  return CEPHALO_OK;
+}
+}  // namespace
+
+extern "C" int cephalo_wgrad_group_tile(int32_t count, int32_t T, const int32_t* N, const int32_t* K, const int32_t* bias, int32_t* tile,
+                                        int32_t* pieces) {
+  GradJob<bf16> jobs[kMaxGradGroup];
+  GemmArgs<bf16> a[kMaxGradGroup];
+  TRY(group_jobs("wgrad_group_tile", count, T, N, K, jobs));
+  if (!bias || !tile) return fail(CEPHALO_EINVAL, "wgrad_group_tile: null pointer argument");
+  static float somewhere;
+  for (int i = 0; i < count; ++i) jobs[i].gb = bias[i] ? &somewhere : nullptr;
+  group_products(jobs, count, T, 1.0f, 0, &somewhere, a);
+  *tile = grad_group_tile(a, count);
+  for (int i = 0; pieces && i < count; ++i) pieces[i] = a[i].splits;
+  return CEPHALO_OK;
+}
+
+extern "C" size_t cephalo_op_linear_wgrad_group_workspace(int32_t count, const int32_t* N, const int32_t* K) {
+  size_t bytes = 256;
+  for (int i = 0; N && K && i < count; ++i) bytes += align_up(gemm_rowsum_part_bytes(N[i], K[i], 1));
+  return bytes;
+}
+
+extern "C" int cephalo_op_linear_wgrad_group(int32_t count, const void* const* dY, const void* const* X, int32_t T, const int32_t* N, const int32_t* K,
+                                             float* const* G, float* const* gb, float scale, int32_t accumulate, int32_t tile, void* workspace,
+                                             size_t workspace_bytes, void* stream) {
+  GradJob<bf16> jobs[kMaxGradGroup];
+  GemmArgs<bf16> a[kMaxGradGroup];
+  TRY(group_jobs("linear_wgrad_group", count, T, N, K, jobs));
+  if (!dY || !X || !G || !gb || !workspace) return fail(CEPHALO_EINVAL, "linear_wgrad_group: null pointer argument");
+  if (accumulate != 0 && accumulate != 1) return fail(CEPHALO_EINVAL, "linear_wgrad_group: accumulate must be 0 or 1");
+  if (tile < 0 || tile > 3) return fail(CEPHALO_EINVAL, "linear_wgrad_group: tile %d, there are 0 to 3", tile);
+  if (workspace_bytes < cephalo_op_linear_wgrad_group_workspace(count, N, K) || !aligned16(workspace))
+    return fail(CEPHALO_EWORKSPACE, "linear_wgrad_group: workspace %zu B < %zu B, or not 16-byte aligned", workspace_bytes, cephalo_op_linear_wgrad_group_workspace(count, N, K));
+  for (int i = 0; i < count; ++i) {
+    if (!dY[i] || !X[i] || !G[i]) return fail(CEPHALO_EINVAL, "linear_wgrad_group: null buffer");
+    if (!aligned16(gb[i])) return fail(CEPHALO_EINVAL, "linear_wgrad_group: buffers must be 16-byte aligned");
+    jobs[i].dY = static_cast<const bf16*>(dY[i]); jobs[i].X = static_cast<const bf16*>(X[i]);
+    jobs[i].g = G[i]; jobs[i].gb = gb[i];
+  }
+  group_products(jobs, count, T, scale, accumulate, nullptr, a);
+  for (int i = 0; i < count; ++i)
+    if (!gemm_mfma_takes(a[i])) return fail(CEPHALO_EUNSUPPORTED, "linear_wgrad_group: operands beyond 2 GiB or buffers that are not 16-byte aligned");
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  SumList sums;
+  sums.scale = scale; sums.acc = accumulate;
+  bool done = false;
+  TRY(group_launch(jobs, count, tile, a, static_cast<float*>(workspace), workspace_bytes, sums, s, &done));
+  return sums.flush(s);
+}
+
 extern "C" int cephalo_op_attention_fwd(const cephalo_layer_desc* d, const void* qkv, void* O, float* lse,
                                         int32_t m, void* stream) {
   int rc = check_attn(d, m);

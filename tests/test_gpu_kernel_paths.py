@@ -135,11 +135,15 @@ def test_bias_gradient_of_the_last_projection_is_the_column_sum_of_dy(m, S, bf16
 
 
 def test_bias_sums_of_two_projections_that_do_not_fit_the_work_area_together():
-    """256 wide over 8192 tokens: the first GEMM's pieces fill the area, so they are added before the second GEMM runs."""
+    """256 wide over 12288 tokens: the weight gradients run one by one in 8 pieces each, and the first bias's pieces leave no room for the
+    second's, so they are added before the second GEMM runs."""
     import dataclasses
     from tests import harness as Hn
+    from tests.test_wgrad_group import layer_choice
     from workloads import CONFIGS, draw_activations, draw_layer_params
-    cfg = dataclasses.replace(CONFIGS["c2"], hidden=256, heads=4, mlp=1024, seq=512, micro_batch=8, n_micro=2)
+    cfg = dataclasses.replace(CONFIGS["c2"], hidden=256, heads=4, mlp=1024, seq=512, micro_batch=8, n_micro=3)
+    tile, pieces = layer_choice(cfg.hidden, cfg.mlp, cfg.batch_share * cfg.seq)
+    assert tile == -1 and pieces[1] == 8 and pieces[3] == 8
     tensors = draw_layer_params(cfg, perturbed=True)
     x, dy = draw_activations(cfg)
     Hn.compare_share(cfg, Hn.gpu_share_step(cfg, tensors, x, dy), Hn.oracle_share_step(cfg, tensors, x, dy))
