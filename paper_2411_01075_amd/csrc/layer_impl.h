@@ -528,13 +528,14 @@ template <> inline int wgrad_group<float>(const GradJob<float>* jobs, int n, int
   for (int i = 0; i < n; ++i) if (jobs[i].gb) sums.add(jobs[i].dY, tokens, jobs[i].N, jobs[i].gb);
   return launch_gemm_f32_group(a, n, s);
 }
-// the products as they would run apart: in pieces where that is faster
+// the products as they would run apart: in pieces where that is faster, and with the column sums that a bias's brings along
 inline void group_products(const GradJob<bf16>* jobs, int n, int tokens, float scale, int acc, float* part, GemmArgs<bf16>* a) {
   for (int i = 0; i < n; ++i) {
     const GradJob<bf16>& q = jobs[i];
     a[i] = linear_wgrad<bf16>(q.dY, q.X, tokens, q.N, q.K, q.g, scale, acc);
     a[i].splits = part ? gemm_grad_splits(q.N, q.K, tokens) : 1;
     a[i].part = part;
+    a[i].rowsum = q.gb;
   }
 }
 // ... and in one launch on `tile`, the pieces of the bias sums in rs_part and listed in `sums` (done: there was room for them)
@@ -543,7 +544,6 @@ inline int group_launch(const GradJob<bf16>* jobs, int n, int tile, GemmArgs<bf1
   size_t used = 0;
   for (int i = 0; i < n; ++i) {
     if (!jobs[i].gb) continue;
-    a[i].rowsum = jobs[i].gb;
     a[i].rowsum_part = rs_part + used / sizeof(float);
     a[i].rowsum_part_bytes = gemm_rowsum_part_bytes(jobs[i].N, jobs[i].K, 1);
     a[i].rowsum_pieces = &pieces[i];

@@ -28,6 +28,14 @@ def test_the_layers_below_reach_every_tile():
     assert {c[0] for c in LAYERS} == {0, 1, 2, 3}
 
 
+@pytest.mark.parametrize("H,F,tokens", [(3968, 4784, 4096), (4040, 5080, 1500), (4000, 4872, 2048)])
+def test_a_product_with_a_bias_gradient_is_not_priced_at_two_launches(H, F, tokens):
+    """With its column sums a weight gradient is one launch.  At these sizes two of them would be faster than the group, one is not."""
+    N, K, bias = layer_products(H, F)
+    assert binding.cephalo_wgrad_group_tile(tokens, N, K, [0] * 4)[0] == -1
+    assert layer_choice(H, F, tokens)[0] == 0
+
+
 def test_group_entries_refuse_what_they_do_not_take():
     with pytest.raises(binding.CephaloError):
         binding.cephalo_wgrad_group_tile(64, [8] * 5, [8] * 5, [0] * 5)
