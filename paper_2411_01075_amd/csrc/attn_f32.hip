@@ -17,6 +17,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxHeadDim = 128;
+constexpr int kMaxSeq = 7500;          // what the fp32 mode takes (nothing here grows with it; longer samples are the bf16 mode's)
 constexpr int kWaves = 4;
 
 // rows of a row-major [*, ld] matrix as an operand over the head's dimensions: row r0 + l % 16, dimensions 16 p + 4 g .. + 3 of piece p
@@ -312,7 +313,7 @@ attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ dO,
 
 int check_f32(int S, int H, int A) {
   if (H / A > kMaxHeadDim) return fail(CEPHALO_EUNSUPPORTED, "attention: head dim %d > %d", H / A, kMaxHeadDim);
-  if ((size_t)S * 2 * sizeof(float) > 60000) return fail(CEPHALO_EUNSUPPORTED, "attention (plain kernel): seq %d too long", S);
+  if (S > kMaxSeq) return fail(CEPHALO_EUNSUPPORTED, "attention (fp32): %d tokens a sample > %d", S, kMaxSeq);
   return CEPHALO_OK;
 }
 

@@ -508,7 +508,7 @@ int launch_reduce_partials(const float* partials, int nchunks, int N, float* g, 
 
 size_t colsum_partial_bytes(int rows, int N) {
   const size_t nchunks = (rows + kColsumRowsPerChunk - 1) / kColsumRowsPerChunk;
-  return (nchunks + (nchunks > 64 ? (nchunks + 31) / 32 : 0)) * (size_t)N * sizeof(float);
+  return (nchunks + (nchunks > 64 ? (nchunks + 31) / 32 : 0)) * (size_t)N * sizeof(float);      // (the second term is not used any more and stays, so that sizes reported and refused are what they were)
 }
 
 template <typename T>

@@ -29,7 +29,7 @@
 // Rows or k-values outside the matrix are never read: their buffer offsets are out of the descriptor's range and the
 // hardware returns zeros.
 //
-// Pipeline: two to four LDS stages; the loads of the following slab(s) are in flight while a slab is multiplied;
+// Pipeline: two to five LDS stages; the loads of the following slab(s) are in flight while a slab is multiplied;
 // one barrier per slab.  The loads are issued through inline assembly (see load_slab_untracked).
 #include "kernels.h"
 #include "reserve_lds.h"
@@ -725,7 +725,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const GemmArgs<bf16>& a, int tile
   }
 }
 
-// The k-contiguous kernel for outputs with few tiles (BM x BN up to 256 x 128), same products in the same order.
+// The kernel for small tiles (BM x BN up to 256 x 128, for outputs with few of the large ones), k-contiguous products and weight gradients alike;
+// same products in the same order.
 //
 // A small tile leaves a wavefront 4 to 16 products per k-step, so the kernel above, which reads the fragments of a k-step during the
 // step before, waits for an LDS round trip twice in every slab, and with one block per compute unit nobody covers the wait
@@ -952,7 +953,7 @@ thread_local int side_by_side = 1;     // kernels the caller runs at once (GemmS
 // of launch); `blocks`: how many a compute unit holds.  Over those launches the choice is on average 1.1 % slower than the fastest tile.
 // Examples (us, former choice -> this one): 1024 x 1024 x 4096 48.0 (128 x 128, four wavefronts) -> 19.3 (64 x 64); 2048 x 1600 x 6400
 // 73.6 (the same) -> 44.0 (128 x 128); 2048 x 2560 x 10240 134.5 (256 x 128) -> 114.1 (128 x 192); two at a time 4096 x 2048 x 8192 195
-// (256 x 256) as before.  The results do not depend on the choice: every tile adds the products of an output in the same order.
+// (256 x 256) as before.  The products do not depend on the choice: every tile adds those of an output in the same order.
 struct TileCost { int bm, bn, blocks; double alone, one, more, fixed; };
 constexpr TileCost kTiles[] = {
   {256, 256, 1, 0.56, 1.09, 1.16, 6.7}, {256, 192, 1, 0.46, 0.83, 0.85, 8.3}, {256, 128, 1, 0.39, 0.68, 0.80, 5.3}, {128, 192, 1, 0.42, 0.53, 0.62, 6.0},
@@ -1092,15 +1093,13 @@ int launch_tiles(const GemmArgs<bf16>& a, hipStream_t s) {
     const double t = (double)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * nsplit;
     return t / (cus * (double)(int64_t)((t + cus - 1) / cus));
   };
-  int cfg = 0;
   // 256 x 128 tiles run three LDS stages (they fit, and long contractions over few tiles gain a quarter from the
   // deeper prefetch; short ones lose nothing).
-  if (cfg == 0) {
-    double best = fill(256, 256); cfg = 1;
-    if (BKF) { const double v = 0.95 * fill(256, 192); if (v > best) { best = v; cfg = 2; } }
-    { const double v = 0.83 * fill(256, 128); if (v > best) { best = v; cfg = 3; } }
-    { const double v = 0.60 * fill(128, 128); if (v > best) { best = v; cfg = 4; } }
-  }
+  int cfg = 1;
+  double best = fill(256, 256);
+  if (BKF) { const double v = 0.95 * fill(256, 192); if (v > best) { best = v; cfg = 2; } }
+  { const double v = 0.83 * fill(256, 128); if (v > best) { best = v; cfg = 3; } }
+  { const double v = 0.60 * fill(128, 128); if (v > best) { best = v; cfg = 4; } }
   switch (cfg) {
     case 1: return launch_cfg<256, 256, 4, 2, AK, BKF, EPI>(a, s);
     case 2: if constexpr (BKF) return launch_cfg<256, 192, 4, 2, AK, BKF, EPI>(a, s); else return launch_cfg<256, 256, 4, 2, AK, BKF, EPI>(a, s);

@@ -176,7 +176,8 @@ int grad_group_tile(const GemmArgs<bf16>* a, int n);
 int launch_grad_group(const GemmArgs<bf16>* a, int n, int tile, hipStream_t s);
 int launch_gemm_f32_group(const GemmArgs<float>* a, int n, hipStream_t s);      // any fp32 products, one launch
 // While one of these is alive on a thread, that thread's GEMM launches choose their tiles for 256 / `kernels` compute
-// units: the caller runs that many kernels side by side on different streams (results do not depend on the choice).
+// units: the caller runs that many kernels side by side on different streams.  The products do not depend on the choice; row sums formed on
+// the way (GemmArgs::rowsum) are added in an order that depends on the tile.
 struct GemmSideBySide {
   explicit GemmSideBySide(int kernels);
   ~GemmSideBySide();

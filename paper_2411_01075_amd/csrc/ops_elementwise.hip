@@ -19,7 +19,8 @@ bool all_aligned(std::initializer_list<const void*> ptrs) {
   return true;
 }
 size_t norm_bwd_part_floats(int rows, int H) { return (size_t)ln_bwd_blocks(rows) * H; }
-// (part of the reported sizes since the reduction ran in two stages; not used any more)
+// (not used any more: the reduction once ran in two stages.  It stays a part of the reported sizes, so that the areas a call takes and
+// refuses are what they were)
 size_t norm_bwd_spare(int rows, int H) {
   const size_t chunks = ln_bwd_blocks(rows);
   return chunks > 64 ? (chunks + 31) / 32 * H * sizeof(float) : 0;
