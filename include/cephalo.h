@@ -149,7 +149,8 @@ int cephalo_layer_bwd(const cephalo_layer_desc* desc, const void* flat_param,
  * before anything else runs): forward of every micro-batch, backward data path of every
  * micro-batch, then one parameter-gradient pass over all b*S tokens, in which the sum over
  * micro-batches is formed in the fp32 accumulators of the weight-gradient GEMMs and every element
- * of flat_grad is written exactly once:  flat_grad <- grad_scale * sum_j g_j.
+ * of flat_grad is written exactly once:  flat_grad <- grad_scale * sum_j g_j.  One launch takes several micro-batches
+ * where the work area (its size depends on m, not on that) has room for what they need at once.
  * Equal to l calls of layer_fwd and layer_bwd up to the order of the fp32 additions.
  * Fails with CEPHALO_EINVAL unless batch_share = l * micro_batch for a positive integer l.
  *   x, y, dy, dx  device, [b, S, H] fp32;  save, scratch: sizes from cephalo_share_workspace_bytes */
@@ -160,11 +161,10 @@ int cephalo_share_layer_step(const cephalo_layer_desc* desc, const void* flat_pa
                              float* flat_grad, float grad_scale,
                              void* scratch, size_t scratch_bytes, void* stream);
 
-/* The same with two micro-batches in flight: micro-batch j runs on stream j mod 2 (`stream` and `side_stream`, another
- * stream of the same device at the default priority), so that the bandwidth-bound kernels of one run under the
- * matrix-core kernels of the other and GEMMs with few output tiles share the compute units.  Every micro-batch's own
- * kernel order and every reduction order are those of cephalo_share_layer_step: same results bit for bit, same work
- * areas.  The call joins the streams before it returns: work enqueued on `stream` afterwards runs after the whole step. */
+/* The same with a second stream to use (`side_stream`, another stream of the same device at the default priority): of a large share half
+ * of the micro-batches run on each, so that the bandwidth-bound kernels of one half run under the matrix-core kernels of the other; a small
+ * one stays on `stream`.  Same results bit for bit as cephalo_share_layer_step, same work areas.  The call joins the streams before it
+ * returns: work enqueued on `stream` afterwards runs after the whole step. */
 int cephalo_share_layer_step_interleaved(const cephalo_layer_desc* desc, const void* flat_param,
                                          const void* x, void* y, const void* dy, void* dx,
                                          int32_t batch_share, int32_t micro_batch,
@@ -348,7 +348,8 @@ typedef struct cephalo_stack_desc {
                           288 GB device).  1: activation checkpointing at layer boundaries (Sec. 3.2 "Activation
                           Checkpointing and Offloading"): only the layer-boundary activations are kept, and the backward
                           of a layer first runs that layer's forward again for all micro-batches.  Same results bit for
-                          bit; the work area holds one layer's internals instead of L; costs one extra forward. */
+                          bit; the work area holds one layer's internals instead of L; costs one extra forward but for its
+                          last projection, whose result the backward does not read. */
   int32_t offload;     /* 0, or 1 (needs checkpoint = 1): the layer-boundary activations live in pinned host memory instead
                           of the work area (the same section, and the supplementary figure on activation offloading): a
                           micro-batch's boundary activation is copied out on a second stream while the next micro-batch
@@ -356,12 +357,11 @@ typedef struct cephalo_stack_desc {
                           backward for the recomputation; the device holds four micro-batches of them.  Same results bit
                           for bit.  (The gradient of the residual stream, two [b*S, H] buffers, stays on the device; the
                           paper moves that to the host too.)  Goes with cephalo_stack_step_offload. */
-  int32_t interleave;  /* 0, or 1 (not with offload): two micro-batches are in flight at once, micro-batch j on stream j mod 2
-                          (the caller's compute stream and a side stream), so that the bandwidth-bound kernels of one
+  int32_t interleave;  /* 0, or 1 (not with offload): a large share runs half of its micro-batches on the caller's compute stream
+                          and half on a side stream, so that the bandwidth-bound kernels of one half
                           overlap the matrix-core kernels of the other and GEMMs with few output tiles share the compute
-                          units.  The order of a micro-batch's own kernels, and every reduction order, are unchanged: same
-                          results bit for bit.  The work area holds the per-micro-batch buffers twice.  Goes with
-                          cephalo_stack_step_interleaved. */
+                          units.  Same results bit for bit.  The work area holds the per-micro-batch buffers twice.  Goes
+                          with cephalo_stack_step_interleaved. */
 } cephalo_stack_desc;
 
 /* V*H + S*H + L*P_layer + 2H (GPT-style) or 2*V*H + L*P_layer + H (Llama-style); negative on a bad desc. */
@@ -418,7 +418,7 @@ int cephalo_stack_step_offload(const cephalo_stack_desc* desc, const void* flat_
                                void* stream, void* copy_in_stream, void* copy_out_stream);
 
 /* The same step for a desc with interleave = 1 (Sec. 3.2's layered order leaves the micro-batches of a layer independent
- * of each other; here two of them run side by side).  side_stream: a second stream of the same device, other than
+ * of each other; of a large share half run on a stream of their own).  side_stream: a second stream of the same device, other than
  * `stream`, at the default priority.  The call joins the streams before it returns: work enqueued on `stream`
  * afterwards runs after the whole step; the side stream may be reused at once.  Arguments otherwise as for
  * cephalo_stack_step; workspace size from cephalo_stack_workspace_bytes with the same desc. */

@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(ln_bwd_threads(TEAM))
 ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const float* __restrict__ mean,
               const float* __restrict__ rstd, const T* __restrict__ gamma, const float* __restrict__ resid,
               float* __restrict__ out, T* __restrict__ out_lowp, float* __restrict__ part_g, float* __restrict__ part_b,
-              float* __restrict__ part_s, int rows, int H) {
+              float* __restrict__ part_s, int seg, int seg_blocks, int H) {
   constexpr int VN = Vec<T>::N;
   constexpr int TEAMS = ln_bwd_threads(TEAM) / TEAM, TW = TEAM / 64;                 // teams per block, wavefronts per team
   constexpr int PER_TEAM = kLnBwdRowsPerBlock / TEAMS;                        // rows of a team
@@ -145,7 +145,9 @@ ln_bwd_kernel(const float* __restrict__ du, const float* __restrict__ x, const f
   const int wave = of_block % TW, team = TEAMS == 1 ? 0 : of_block / TW, tt = threadIdx.x % TEAM;
   const int nv = H / VN;
   const float inv_h = 1.0f / (float)H;
-  const int row0 = blockIdx.x * kLnBwdRowsPerBlock + team * PER_TEAM;
+  // rows [first, rows) are the block's matrix of seg rows
+  const int of_seg = (int)blockIdx.x / seg_blocks, first = of_seg * seg, rows = first + seg;
+  const int row0 = first + ((int)blockIdx.x - of_seg * seg_blocks) * kLnBwdRowsPerBlock + team * PER_TEAM;
 
   float gm[MV][VN], sum[NS][MV][VN];                                          // sums: d gamma, d beta, the result's
 #pragma unroll
@@ -465,14 +467,16 @@ int ln_bwd_blocks(int rows) { return (rows + kLnBwdRowsPerBlock - 1) / kLnBwdRow
 template <typename T>
 int launch_ln_bwd(const float* du, const float* x, const float* mean, const float* rstd, const T* gamma,
                   const float* resid, float* out, T* out_lowp, float* part_g, float* part_b, int rows, int H, hipStream_t s, bool rms,
-                  float* part_s) {
+                  float* part_s, int seg) {
   if (rms && part_s) return fail(CEPHALO_EINVAL, "norm backward: column sums of the result go with the LayerNorm form only");
-  const int nblocks = ln_bwd_blocks(rows);
+  if (seg <= 0 || seg % kLnBwdRowsPerBlock == 0) seg = rows;          // (blocks end with the matrices anyway)
+  if (rows % seg != 0) return fail(CEPHALO_EINVAL, "norm backward: %d rows are not whole matrices of %d", rows, seg);
+  const int seg_blocks = ln_bwd_blocks(seg), nblocks = rows / seg * seg_blocks;
   const int nv = H / Vec<T>::N;                // 16-byte column groups of a row
 #define LN_BWD_FORMS(TEAM, MV, RESID)                                                                                \
-    { if (rms) ln_bwd_kernel<T, TEAM, MV, true, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); \
-      else if (part_s) ln_bwd_kernel<T, TEAM, MV, false, true, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, part_s, rows, H); \
-      else ln_bwd_kernel<T, TEAM, MV, false, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, rows, H); }
+    { if (rms) ln_bwd_kernel<T, TEAM, MV, true, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, seg, seg_blocks, H); \
+      else if (part_s) ln_bwd_kernel<T, TEAM, MV, false, true, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, part_s, seg, seg_blocks, H); \
+      else ln_bwd_kernel<T, TEAM, MV, false, false, RESID><<<nblocks, ln_bwd_threads(TEAM), 0, s>>>(du, x, mean, rstd, gamma, resid, out, out_lowp, part_g, part_b, nullptr, seg, seg_blocks, H); }
 #define LN_BWD_CASE(TEAM, MV) { if (resid) LN_BWD_FORMS(TEAM, MV, true) else LN_BWD_FORMS(TEAM, MV, false) }
   if (nv <= 64) LN_BWD_CASE(64, 1)
   else if (nv <= 128) LN_BWD_CASE(128, 1)
@@ -638,7 +642,7 @@ int launch_swiglu_fwd(const T* gu, T* h, int64_t rows, int F, hipStream_t s) {
 #define INSTANTIATE(T)                                                                                          \
   template int launch_ln_fwd<T>(const float*, const T*, const T*, T*, float*, float*, int, int, float, hipStream_t, bool); \
   template int launch_ln_bwd<T>(const float*, const float*, const float*, const float*, const T*, const float*, float*, \
-                                T*, float*, float*, int, int, hipStream_t, bool, float*);                         \
+                                T*, float*, float*, int, int, hipStream_t, bool, float*, int);                    \
   template int launch_rotary<T>(T*, const float*, int, int, int, int, int, hipStream_t);                          \
   template int launch_swiglu_fwd<T>(const T*, T*, int64_t, int, hipStream_t);                                     \
   template int launch_colsum<T>(const T*, float*, size_t, float*, float, int, int, int, hipStream_t);

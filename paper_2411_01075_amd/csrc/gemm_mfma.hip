@@ -980,15 +980,19 @@ double blocks_us(const TileCost& t, double blocks, int nk, int kernels) {
   return us;
 }
 
+int best_tile(int M, int N, int K, int kernels, double* us) {
+  int best = 0;
+  *us = 1e30;
+  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+    const double t = tile_us(kTiles[c], M, N, K, kernels);
+    if (t < *us) { *us = t; best = c; }
+  }
+  return best;
+}
 template <int EPI>
 int launch_rows(const GemmArgs<bf16>& a, hipStream_t s) {
-  int best = 0;
-  double least = 1e30;
-  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
-    const double us = tile_us(kTiles[c], a.M, a.N, a.K, side_by_side);
-    if (us < least) { least = us; best = c; }
-  }
-  switch (best) {
+  double us;
+  switch (best_tile(a.M, a.N, a.K, side_by_side, &us)) {
     case 0: return launch_cfg<256, 256, 4, 2, true, true, EPI>(a, s);
     case 1: return launch_cfg<256, 192, 4, 2, true, true, EPI>(a, s);
     case 2: return launch_ring<256, 128, 4, 2, EPI, 3>(a, s);
@@ -1109,6 +1113,12 @@ int launch_tiles(const GemmArgs<bf16>& a, hipStream_t s) {
 }
 
 }  // namespace
+
+double gemm_rows_us(int M, int N, int K, int kernels) {
+  double us;
+  (void)best_tile(M, N, K, kernels, &us);
+  return us;
+}
 
 int gemm_grad_splits_most(int M, int N, int K) {
   const double tiles = (double)((M + 255) / 256) * ((N + 255) / 256);

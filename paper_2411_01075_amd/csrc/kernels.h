@@ -166,6 +166,9 @@ bool gemm_mfma_takes(const GemmArgs<bf16>& a);          // whether launch_gemm_m
 int gemm_grad_splits(int M, int N, int K);
 int gemm_grad_splits_most(int M, int N, int K);
 
+// Estimated time in us of a k-contiguous bf16 product (a projection's forward or input gradient) with `kernels` of them side by side.
+double gemm_rows_us(int M, int N, int K, int kernels);
+
 template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);   // (bf16 only)
 int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s);  // fp32 operands and arithmetic, any strides
 int launch_gemm_mfma(const GemmArgs<bf16>& a, hipStream_t s);  // bf16 operands, MFMA, fp32 accumulate
@@ -200,10 +203,12 @@ int launch_ln_fwd(const float* x, const T* gamma, const T* beta, T* u, float* me
 // launch_reduce_partials / _jobs fold any number of such partial rows into a flat-gradient slice:
 //   g = (accumulate ? g : 0) + scale * sum over chunks.
 // part_s, if not null (LayerNorm form only): the blocks' column sums of `out`, laid out like part_g.
+// seg > 0: the rows are `rows / seg` matrices of seg rows, one behind the other, and a block's rows belong to one of them, so that the partial
+// sums are those of as many calls: [rows / seg * ln_bwd_blocks(seg)][H].
 template <typename T>
 int launch_ln_bwd(const float* du, const float* x, const float* mean, const float* rstd, const T* gamma,
                   const float* resid, float* out, T* out_lowp, float* part_g, float* part_b, int rows, int H, hipStream_t s,
-                  bool rms = false, float* part_s = nullptr);
+                  bool rms = false, float* part_s = nullptr, int seg = 0);
 int ln_bwd_blocks(int rows);
 
 // Rotary position embedding in place on the Q and K thirds of qkv [rows, 3H] (row % S = position, pairs (2i, 2i+1) of

@@ -6,6 +6,7 @@
 #include <initializer_list>
 #include <type_traits>
 #include <algorithm>
+#include <utility>
 
 #define TRY(expr) do { int rc__ = (expr); if (rc__ != CEPHALO_OK) return rc__; } while (0)
 
@@ -81,10 +82,9 @@ struct SaveLayout {
   size_t mean1, rstd1, u, qkv, lse, O, x1, mean2, rstd2, u2, z, h, rot, total;
 };
 // Backward work area.  dz, dx1 and dqkv (the dY operands of the weight gradients) and the copy of dy in the
-// activation type are kept for `span` samples; the rest is per micro-batch of m samples.
+// activation type are kept for `span` samples; what only the data path needs passes through the pool (see work_at).
 struct ScratchLayout {
-  size_t dz, dx1, dx1l, dyl, dqkv, du2, dO, du, dvec, wT, wg_part, rs_part, rs_part_bytes, ln_part, col_part, col_part_bytes, total;
-  size_t slot_each; // bytes of one slot's du2, dO, du, dvec (slot k's copies lie k * slot_each further on)
+  size_t dz, dx1, dx1l, dyl, dqkv, pool, pool_bytes, wT, wg_part, rs_part, rs_part_bytes, ln_part, col_part, col_part_bytes, total;
   size_t ln_rows;   // rows of each of the four LayerNorm partial arrays (ln2.gamma, ln2.beta, ln1.gamma, ln1.beta)
 };
 
@@ -109,7 +109,8 @@ SaveLayout save_layout(const cephalo_layer_desc& d, int n) {
   return L;
 }
 
-// slots: how many micro-batches may be in their backward at once (each needs its own per-micro-batch buffers)
+// slots: the pool holds what as many micro-batches need at once (two fp32 gradients of the norms' outputs, dO and its row sums each; a run
+// of micro-batches packs them closer than that, see run_bytes)
 ScratchLayout scratch_layout(const cephalo_layer_desc& d, int m, int span, int slots = 1) {
   const size_t es = d.dtype == CEPHALO_F32 ? 4 : 2;
   const size_t Tm = (size_t)m * d.seq, Ts = (size_t)span * d.seq, H = d.hidden, F = d.mlp;
@@ -122,12 +123,8 @@ ScratchLayout scratch_layout(const cephalo_layer_desc& d, int m, int span, int s
   L.dx1l = es == 4 ? L.dx1 : take(Ts * H * es);
   L.dyl = es == 4 ? 0 : take(Ts * H * es);
   L.dqkv = take(Ts * 3 * H * es);
-  L.slot_each = align_up(Tm * H * 4) + align_up(Tm * H * es) + align_up(Tm * H * 4) + align_up((size_t)m * d.heads * d.seq * 4);
-  L.du2 = take(Tm * H * 4);        // gradients entering the LayerNorm backward: fp32
-  L.dO = take(Tm * H * es);
-  L.du = take(Tm * H * 4);
-  L.dvec = take((size_t)m * d.heads * d.seq * 4);
-  if (slots > 1) take((size_t)(slots - 1) * L.slot_each);      // the same four again per further slot
+  L.pool_bytes = (size_t)slots * (2 * align_up(Tm * H * 4) + align_up(Tm * H * es) + align_up((size_t)m * d.heads * d.seq * 4));
+  L.pool = take(L.pool_bytes);
   L.wT = es == 4 ? 0 : take((size_t)param_offsets(d).total * es);   // the four weight matrices transposed, at their flat-layout offsets
   L.wg_part = p;                    // partial weight gradients of a split token axis (largest of the four projections)
   if (es != 4) {
@@ -295,15 +292,26 @@ template <typename T> struct Work {
   float *wg_part;
   float *rs_part; size_t rs_part_bytes;
 };
+// Where the data path of a run keeps what lives for a few launches only: the fp32 gradients that enter the two norms' backwards, dO and the
+// attention's row sums.  The second norm's (du2) lies where dqkv will be: three times as wide, and written by the attention's backward, by
+// which time the norm's has consumed it.  The first norm's (du) takes the place of dO and the row sums, which the attention's backward is the
+// last to read.  So a run needs run_bytes of the pool; two streams have half of it each.
+struct Pool { char* base; size_t bytes; };
+inline size_t run_bytes(const cephalo_layer_desc& d, int64_t samples) {
+  const size_t es = d.dtype == CEPHALO_F32 ? 4 : 2, T = (size_t)samples * d.seq, H = d.hidden;
+  return std::max(align_up(T * H * 4), align_up(T * H * es) + align_up(T * d.heads * 4));
+}
+// Work area of the run of `samples` samples from sample0 on (whole micro-batches of m, the first of them mb_index).
 template <typename T>
-Work<T> work_at(void* base, const ScratchLayout& W, const cephalo_layer_desc& d, int sample0, int mb_index, int m, int slot = 0) {
+Work<T> work_at(void* base, const ScratchLayout& W, const cephalo_layer_desc& d, int sample0, int mb_index, int m, char* pool, int samples) {
   const size_t t0 = (size_t)sample0 * d.seq, H = d.hidden, F = d.mlp;
   Work<T> w;
   w.dz = at<T>(base, W.dz) + t0 * (size_t)ff1_width(d); w.dx1 = at<float>(base, W.dx1) + t0 * H; w.dx1l = at<T>(base, W.dx1l) + t0 * H;
   w.dyl = at<T>(base, W.dyl) + t0 * H; w.dqkv = at<T>(base, W.dqkv) + t0 * 3 * H;
-  const size_t so = (size_t)slot * W.slot_each;
-  w.du2 = at<float>(base, W.du2 + so); w.dO = at<T>(base, W.dO + so); w.du = at<float>(base, W.du + so); w.wT = at<T>(base, W.wT);
-  w.dvec = at<float>(base, W.dvec + so);
+  w.du2 = reinterpret_cast<float*>(w.dqkv);
+  w.du = at<float>(pool, 0);
+  w.dO = at<T>(pool, 0); w.dvec = at<float>(pool, align_up((size_t)samples * d.seq * H * sizeof(T)));
+  w.wT = at<T>(base, W.wT);
   float* ln = at<float>(base, W.ln_part);
   const size_t r0 = (size_t)mb_index * ln_bwd_blocks(m * d.seq) * H, arr = W.ln_rows * H;
   w.ln2_g = ln + r0; w.ln2_b = ln + arr + r0; w.ln1_g = ln + 2 * arr + r0; w.ln1_b = ln + 3 * arr + r0;
@@ -314,7 +322,77 @@ Work<T> work_at(void* base, const ScratchLayout& W, const cephalo_layer_desc& d,
   return w;
 }
 
-// ---- forward of one micro-batch ----------------------------------------------------------------
+// ---- runs of micro-batches
+// The micro-batches of a layer do not depend on each other and their rows are contiguous in every saved tensor, so one launch can take
+// several of them: a run.  Results do not depend on the runs: every product is summed in the same order, and the norms' partial sums are those
+// of single micro-batches.
+//
+// How many runs.  A launch of few rows does not fill the chip and pays its fixed time per micro-batch; a launch of many may end in a nearly empty
+// round of blocks.  So: the number of runs with the least estimated time of their eight products (gemm_rows_us) plus 50 us a run for the other
+// launches, each run short enough that the widest tensor between two launches (8 bytes x tokens x hidden) stays in the 256 MB cache; over 24 shapes
+// (hidden 512 to 4096, 2 to 6 micro-batches of 512 to 4096 tokens) that is the fastest number or within 2 % of it.
+// Share on one stream, one micro-batch at a time -> these runs, us: 2 x 512 tokens, width 256, 4 of them 534 -> 188; 1024 x 1024 wide, 4 851 -> 493; 2048 x
+// 1600, 3 1706 -> 1427; 2048 x 4096, 3 6874 -> 6573 (runs of 1 and 2: 6144 rows are 1.5 rounds of blocks); 4096 x 2048, 6 7885 -> 7467.
+//
+// Two streams.  With two runs in flight a kernel's last round and the bandwidth-bound kernels run beside the other stream's, but each run has half
+// the micro-batches, and where the device's few hardware queues put both streams on one, the two take turns (4 x 512 tokens of width 1024, two
+// micro-batches: 500 us side by side, 689 in turns, 490 in one run on one stream).  So the side stream is used for shares of more than 16384 tokens (24
+// layers of width 2048, 6 micro-batches of 4096: 192.7 ms against 196.0 on one stream) and where the pool does not take the share in one run (6 of
+// 2048 tokens, width 768: 937 us against 1040); below that the two are within 5 % of each other, and small shares lose to the events alone (4 x 128
+// tokens of width 256: 135 us, 105 without).
+struct Run { int first, count, lane; };       // micro-batches [first, first + count), on stream `lane`
+struct Runs {
+  int lanes, per_lane[2], n;                  // micro-batches and runs of a stream (the second's may be one run fewer)
+  int runs() const { return n * lanes; }
+  Run run(int i) const {                      // in the order they are enqueued, the streams in turn (count 0: the stream has run out)
+    const int lane = i % lanes;
+    const int64_t k = i / lanes, c = per_lane[lane];
+    const int from = (int)(k * c / n), to = (int)((k + 1) * c / n);
+    return Run{lane * per_lane[0] + from, to - from, lane};
+  }
+};
+
+inline Runs plan_runs(const cephalo_layer_desc& d, int m, int l, bool two_streams, size_t pool_bytes) {
+  const int64_t Tm = (int64_t)m * d.seq, es = d.dtype == CEPHALO_F32 ? 4 : 2;
+  const int H = d.hidden, F = d.mlp, F1 = (int)ff1_width(d);
+  constexpr int64_t kShort = 4096;                          // tokens up to which the fewest runs are always the fastest
+  constexpr int64_t kCached = 22 << 20;                     // tokens x hidden
+  const int64_t row = std::max<int64_t>(3 * (int64_t)H, F1) * es;
+  // whether `g` micro-batches can be one run on one of `lanes` streams: the pool, the GEMM's 32-bit offsets, the attention's grid
+  auto fits = [&](int64_t g, int lanes) {
+    return g == 1 || (run_bytes(d, g * m) <= pool_bytes / lanes / 256 * 256 && g * Tm * row < 0x7fffffff && g * m <= 65535);
+  };
+  auto fewest = [&](int count, int lanes) {
+    int g = 1;
+    while (g < count && fits(g + 1, lanes) && (g + 1) * Tm * H <= kCached) ++g;
+    return (count + g - 1) / g;
+  };
+  auto run_us = [&](int count, int lanes) {
+    double us = 50.0;
+    const int T = (int)(count * Tm);
+    for (const auto& nk : {std::pair<int, int>{3 * H, H}, {H, H}, {F1, H}, {H, F}, {F, H}, {H, F1}, {H, H}, {H, 3 * H}}) us += gemm_rows_us(T, nk.first, nk.second, lanes);
+    return us;
+  };
+  auto best = [&](int count, int lanes) {
+    const int from = fewest(count, lanes);
+    if (es == 4 || count * Tm <= kShort) return from;
+    int n = from;
+    double least = 1e30;
+    for (int k = from; k <= std::min(count, from + 3); ++k) {
+      const int more = count % k;                            // runs of one micro-batch more
+      const double us = more * (more ? run_us(count / k + 1, lanes) : 0.0) + (k - more) * run_us(count / k, lanes);
+      if (us < least) { least = us; n = k; }
+    }
+    return n;
+  };
+  Runs r = {1, {l, 0}, 1};
+  if (two_streams && l > 1 && (l * Tm > 16384 || (l * Tm >= 8192 && !fits(l, 1)))) r = {2, {(l + 1) / 2, l / 2}, 1};
+  r.n = best(r.per_lane[0], r.lanes);
+  return r;
+}
+inline char* pool_of(const Pool& p, int lane, int lanes) { return p.base + p.bytes / lanes / 256 * 256 * lane; }
+
+// ---- forward of one run of micro-batches, m samples in all ----------------------------------------------------------------
 // (sv.rot of a Llama-style layer holds the rotary table: make_rotary, once for all micro-batches)
 template <typename T>
 int make_rotary(const cephalo_layer_desc& d, const Saved<T>& sv, hipStream_t s) {
@@ -347,7 +425,7 @@ int layer_fwd_t(const cephalo_layer_desc& d, const T* P, const float* x, float* 
       TRY(gemm<T>(a, s));
     }
     TRY(launch_swiglu_fwd<T>(sv.z, sv.h, Tn, F, s));
-    {
+    if (y) {
       GemmArgs<T> a = linear_fwd<T>(sv.h, P + o.w_fc2, Tn, H, F);
       a.epi = EPI_BIAS_RESID; a.bias = nullptr; a.Rf = sv.x1; a.Cf = y;
       TRY(gemm<T>(a, s));
@@ -372,7 +450,7 @@ int layer_fwd_t(const cephalo_layer_desc& d, const T* P, const float* x, float* 
     a.epi = EPI_BIAS_GELU_DERIV; a.bias = P + o.b_fc1; a.Z = sv.z; a.C = sv.h;      // saved: gelu'(z), the factor the backward needs
     TRY(gemm<T>(a, s));
   }
-  {
+  if (y) {
     GemmArgs<T> a = linear_fwd<T>(sv.h, P + o.w_fc2, Tn, H, F);
     a.epi = EPI_BIAS_RESID; a.bias = P + o.b_fc2; a.Rf = sv.x1; a.Cf = y;
     TRY(gemm<T>(a, s));
@@ -423,13 +501,13 @@ template <> inline int prepare_dgrad_weights<bf16>(const cephalo_layer_desc& d, 
   return launch_transposes(jobs, 4, s);
 }
 
-// ---- backward, data path of one micro-batch: dx and the dY operands (dz, dx1, dqkv) of the weight gradients --------
+// ---- backward, data path of one run of `samples` samples in micro-batches of m: dx and the dY operands (dz, dx1, dqkv) of the weight gradients ----
 // dyl is dy in the activation type (same rows); dxl, if not null, receives dx in the activation type as well.
 template <typename T>
-int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, const float* dy, const T* dyl, float* dx, T* dxl, int m,
+int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, const float* dy, const T* dyl, float* dx, T* dxl, int m, int samples,
                      const Saved<T>& sv, const Work<T>& w, hipStream_t s) {
   const ParamOffsets o = param_offsets(d);
-  const int Tn = m * d.seq, H = d.hidden, F = d.mlp;
+  const int Tn = samples * d.seq, H = d.hidden, F = d.mlp, Tm = m * d.seq;
   if (is_llama(d)) {
     {
       GemmArgs<T> a = dgrad_args<T>(dyl, P, w.wT, o.w_fc2, Tn, H, F);   // dh = dy Wdown, then d[gate | up] from the fp32 products
@@ -441,19 +519,19 @@ int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, co
       a.epi = EPI_NONE; a.Cf = w.du2;
       TRY(gemm<T>(a, s));
     }
-    TRY(launch_ln_bwd<T>(w.du2, sv.x1, sv.mean2, sv.rstd2, P + o.ln2_g, dy, w.dx1, lowp_out<T>(w.dx1l), w.ln2_g, w.ln2_b, Tn, H, s, true));
+    TRY(launch_ln_bwd<T>(w.du2, sv.x1, sv.mean2, sv.rstd2, P + o.ln2_g, dy, w.dx1, lowp_out<T>(w.dx1l), w.ln2_g, w.ln2_b, Tn, H, s, true, nullptr, Tm));
     {
       GemmArgs<T> a = dgrad_args<T>(lowp_of<T>(w.dx1, w.dx1l), P, w.wT, o.w_o, Tn, H, H);
       a.epi = EPI_NONE; a.C = w.dO;
       TRY(gemm<T>(a, s));
     }
-    TRY(attn_bwd<T>(sv.qkv, sv.O, w.dO, sv.lse, w.dvec, w.dqkv, m, d.seq, H, d.heads, d.causal, s, sv.rot));   // dq, dk: turned back by the angle
+    TRY(attn_bwd<T>(sv.qkv, sv.O, w.dO, sv.lse, w.dvec, w.dqkv, samples, d.seq, H, d.heads, d.causal, s, sv.rot));   // dq, dk: turned back by the angle
     {
       GemmArgs<T> a = dgrad_args<T>(w.dqkv, P, w.wT, o.w_qkv, Tn, 3 * H, H);
       a.epi = EPI_NONE; a.Cf = w.du;
       TRY(gemm<T>(a, s));
     }
-    TRY(launch_ln_bwd<T>(w.du, x, sv.mean1, sv.rstd1, P + o.ln1_g, w.dx1, dx, lowp_out<T>(dxl), w.ln1_g, w.ln1_b, Tn, H, s, true));
+    TRY(launch_ln_bwd<T>(w.du, x, sv.mean1, sv.rstd1, P + o.ln1_g, w.dx1, dx, lowp_out<T>(dxl), w.ln1_g, w.ln1_b, Tn, H, s, true, nullptr, Tm));
     return CEPHALO_OK;
   }
   {
@@ -467,20 +545,20 @@ int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, co
     TRY(gemm<T>(a, s));
   }
   // u2 = LN2(x1); dx1 = dy + LN2-backward(du2)
-  TRY(launch_ln_bwd<T>(w.du2, sv.x1, sv.mean2, sv.rstd2, P + o.ln2_g, dy, w.dx1, lowp_out<T>(w.dx1l), w.ln2_g, w.ln2_b, Tn, H, s, false, w.ln2_s));
+  TRY(launch_ln_bwd<T>(w.du2, sv.x1, sv.mean2, sv.rstd2, P + o.ln2_g, dy, w.dx1, lowp_out<T>(w.dx1l), w.ln2_g, w.ln2_b, Tn, H, s, false, w.ln2_s, Tm));
   {
     GemmArgs<T> a = dgrad_args<T>(lowp_of<T>(w.dx1, w.dx1l), P, w.wT, o.w_o, Tn, H, H);
     a.epi = EPI_NONE; a.C = w.dO;
     TRY(gemm<T>(a, s));
   }
-  TRY(attn_bwd<T>(sv.qkv, sv.O, w.dO, sv.lse, w.dvec, w.dqkv, m, d.seq, H, d.heads, d.causal, s));
+  TRY(attn_bwd<T>(sv.qkv, sv.O, w.dO, sv.lse, w.dvec, w.dqkv, samples, d.seq, H, d.heads, d.causal, s));
   {
     GemmArgs<T> a = dgrad_args<T>(w.dqkv, P, w.wT, o.w_qkv, Tn, 3 * H, H);
     a.epi = EPI_NONE; a.Cf = w.du;
     TRY(gemm<T>(a, s));
   }
   // u = LN1(x); dx = dx1 + LN1-backward(du)
-  TRY(launch_ln_bwd<T>(w.du, x, sv.mean1, sv.rstd1, P + o.ln1_g, w.dx1, dx, lowp_out<T>(dxl), w.ln1_g, w.ln1_b, Tn, H, s, false, w.ln1_s));
+  TRY(launch_ln_bwd<T>(w.du, x, sv.mean1, sv.rstd1, P + o.ln1_g, w.dx1, dx, lowp_out<T>(dxl), w.ln1_g, w.ln1_b, Tn, H, s, false, w.ln1_s, Tm));
   return CEPHALO_OK;
 }
 
@@ -638,12 +716,12 @@ int run_bwd(const cephalo_layer_desc& d, const void* P, const float* x, const fl
   const SaveLayout L = save_layout(d, m);
   const ScratchLayout W = scratch_layout(d, m, m);
   const Saved<T> sv = saved_at<T>(save, L, d, 0);
-  const Work<T> w = work_at<T>(scratch, W, d, 0, 0, m);
+  const Work<T> w = work_at<T>(scratch, W, d, 0, 0, m, at<char>(scratch, W.pool), m);
   DySums dy_sums;
   TRY(take_dy<T>(d, dy, m * d.seq, w, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w.dyl);
   TRY(prepare_dgrad_weights<T>(d, static_cast<const T*>(P), w.wT, s));
-  TRY(layer_bwd_data_t<T>(d, static_cast<const T*>(P), x, dy, dyl, dx, (T*)nullptr, m, sv, w, s));
+  TRY(layer_bwd_data_t<T>(d, static_cast<const T*>(P), x, dy, dyl, dx, (T*)nullptr, m, m, sv, w, s));
   return layer_bwd_params_t<T>(d, dy_sums, dyl, m * d.seq, ln_bwd_blocks(m * d.seq), sv, w, G, scale, acc, s);
 }
 
@@ -692,14 +770,16 @@ int run_share(const cephalo_layer_desc& d, const void* Pv, const float* x, float
   const ScratchLayout W = scratch_layout(d, m, b, 2);
   const int l = b / m;
   const size_t act = (size_t)m * d.seq * d.hidden;   // elements of one micro-batch of x / y / dy / dx
-  // side: micro-batch j runs on stream j % 2 (two in flight, see Streams); what the micro-batches share is made first
-  const int nst = side ? 2 : 1;
+  // two runs may be in flight, one per stream (see Streams); what the runs share is made first
+  const Pool pool = {at<char>(scratch, W.pool), W.pool_bytes};
+  const Runs runs = plan_runs(d, m, l, side != nullptr, pool.bytes);
+  if (runs.lanes == 1) side = nullptr;      // (beside one run of kernels that fill the chip, the two events cost more than the reductions on a stream of their own save)
   hipStream_t st[2] = {s, side ? side : s};
   Streams J;
   J.main = s; J.side = side; J.on = side != nullptr;
   TRY(J.open());
   struct JCloser { Streams& j; bool done = false; ~JCloser() { if (!done) (void)j.close(); } } jcloser{J};   // early exits still join
-  const Work<T> w0 = work_at<T>(scratch, W, d, 0, 0, m);
+  const Work<T> w0 = work_at<T>(scratch, W, d, 0, 0, m, pool.base, m);
   DySums dy_sums;
   TRY(take_dy<T>(d, dy, b * d.seq, w0, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w0.dyl);
@@ -707,12 +787,18 @@ int run_share(const cephalo_layer_desc& d, const void* Pv, const float* x, float
   TRY(make_rotary<T>(d, saved_at<T>(save, L, d, 0), s));
   J.fork();
   {
-    GemmSideBySide hint(nst);
-    for (int j = 0; j < l; ++j)
-      TRY(layer_fwd_t<T>(d, P, x + j * act, y + j * act, m, saved_at<T>(save, L, d, j * m), st[j % nst]));
-    for (int j = 0; j < l; ++j)
-      TRY(layer_bwd_data_t<T>(d, P, x + j * act, dy + j * act, dyl + j * act, dx + j * act, (T*)nullptr, m,
-                              saved_at<T>(save, L, d, j * m), work_at<T>(scratch, W, d, j * m, j, m, j % nst), st[j % nst]));
+    GemmSideBySide hint(runs.lanes);
+    for (int i = 0; i < runs.runs(); ++i) {
+      const Run q = runs.run(i);
+      if (!q.count) continue;
+      TRY(layer_fwd_t<T>(d, P, x + q.first * act, y + q.first * act, q.count * m, saved_at<T>(save, L, d, q.first * m), st[q.lane]));
+    }
+    for (int i = 0; i < runs.runs(); ++i) {
+      const Run q = runs.run(i);
+      if (!q.count) continue;
+      TRY(layer_bwd_data_t<T>(d, P, x + q.first * act, dy + q.first * act, dyl + q.first * act, dx + q.first * act, (T*)nullptr, m, q.count * m,
+                              saved_at<T>(save, L, d, q.first * m), work_at<T>(scratch, W, d, q.first * m, q.first, m, pool_of(pool, q.lane, runs.lanes), q.count * m), st[q.lane]));
+    }
   }
   J.join();
   J.fork();      // the parameter pass's reductions beside its GEMMs

@@ -470,7 +470,7 @@ int check_stack(const cephalo_stack_desc* d) {
 }
 
 struct StackLayout {
-  size_t xs, xdump, saves, save_each, scratch, dxa, dxb, dxal, dxbl, uf, meanf, rstdf, duf, logits, dlogits, wteT, loss, lnf_part, keys, embed_part, total;
+  size_t xs, saves, save_each, scratch, dxa, dxb, dxal, dxbl, uf, meanf, rstdf, duf, logits, dlogits, wteT, loss, lnf_part, keys, embed_part, logits_bytes, total;
   int ldv;            // padded pitch of the logits
   size_t lnf_rows;
 };
@@ -485,9 +485,9 @@ StackLayout stack_layout(const cephalo_stack_desc& d, int b, int m) {
   size_t p = 0;
   auto take = [&](size_t bytes) { size_t at = p; p += align_up(bytes); return at; };
   // layer-boundary activations, the fp32 residual stream: all of them, or (offload) two micro-batches coming in from the
-  // host and two going out; with checkpointing also one micro-batch where the recomputed layer output is dropped
+  // host and two going out
   L.xs = take(d.offload ? 4 * Tm * H * 4 : (size_t)(d.layers + 1) * n * H * 4);
-  L.xdump = d.checkpoint ? take((d.interleave ? 2 : 1) * Tm * H * 4) : 0;
+  if (d.checkpoint) take((d.interleave ? 2 : 1) * Tm * H * 4);         // (not used any more; what is reported and refused stays what it was)
   L.save_each = align_up(save_layout(ld, b).total);
   L.saves = take((size_t)(d.checkpoint ? 1 : d.layers) * L.save_each);   // checkpointing: one layer's internals at a time
   L.scratch = take(scratch_layout(ld, m, b, d.interleave ? 2 : 1).total);
@@ -497,7 +497,8 @@ StackLayout stack_layout(const cephalo_stack_desc& d, int b, int m) {
   L.dxal = es == 4 ? L.dxa : take(n * H * es); L.dxbl = es == 4 ? L.dxb : take(n * H * es);   // and its copy in the activation type
   L.uf = take(n * H * es); L.meanf = take(n * 4); L.rstdf = take(n * 4);
   L.duf = take((d.interleave ? 2 : 1) * Tm * H * 4);
-  L.logits = take((d.interleave ? 2 : 1) * Tm * (size_t)L.ldv * 4);   // one micro-batch of fp32 logits, reused (interleave: one per stream)
+  L.logits_bytes = (d.interleave ? 2 : 1) * Tm * (size_t)L.ldv * 4;   // one micro-batch of fp32 logits, reused (interleave: one per stream)
+  L.logits = take(L.logits_bytes);
   L.dlogits = take(n * (size_t)L.ldv * es);       // their gradient for the whole share (an operand of the weight gradient)
   L.wteT = es == 4 ? 0 : take(H * (size_t)L.ldv * es);   // wte^T [H, ldv] for the input gradient of the LM head
   L.loss = take(n * 4);
@@ -598,16 +599,22 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   const bool rms = is_llama(ld);
   const StackLayout L = stack_layout(d, b, m);
   const SaveLayout SL = save_layout(ld, b);
-  const int nst = d.interleave ? 2 : 1;
-  const ScratchLayout WL = scratch_layout(ld, m, b, nst);
+  const ScratchLayout WL = scratch_layout(ld, m, b, d.interleave ? 2 : 1);
   void* scratch = at<char>(ws, L.scratch);
-  // Interleave: micro-batch j runs on stream j % 2, so that the bandwidth-bound kernels of one micro-batch overlap the
-  // matrix-core kernels of the other and GEMMs with few output tiles share the compute units.  A micro-batch's whole
+  // What runs together: runs of micro-batches (plan_runs), or, where the boundary activations pass through slots for one micro-batch, each
+  // by itself.  Interleave: half of the micro-batches on each stream, so that the bandwidth-bound kernels of one run overlap the
+  // matrix-core kernels of the other and GEMMs with few output tiles share the compute units.  A run's whole
   // chain through the layers stays on its stream; the streams meet where the share is handled as one (weight
   // gradients, shared weight transposes, the embeddings), through fork / join events.
-  hipStream_t st[2] = {s, d.interleave ? side : s};
+  // (the logits' area is free while the layers run backward, and usually the larger pool)
+  Pool pool = {at<char>(scratch, WL.pool), WL.pool_bytes};
+  if (L.logits_bytes > pool.bytes) pool = {at<char>(ws, L.logits), L.logits_bytes};
+  const Runs runs = plan_runs(ld, m, l, d.interleave != 0, d.offload ? 0 : pool.bytes);
+  if (runs.lanes == 1) side = nullptr;
+  const int nst = runs.lanes;
+  hipStream_t st[2] = {s, side ? side : s};
   Streams J;
-  J.main = s; J.side = side; J.on = d.interleave != 0;
+  J.main = s; J.side = side; J.on = side != nullptr;
   TRY(J.open());
   struct JCloser { Streams& j; bool done = false; ~JCloser() { if (!done) (void)j.close(); } } jcloser{J};   // early exits still join
   const size_t act = (size_t)Tm * H;
@@ -644,8 +651,11 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   TRY(prepare_head_weights<T>(P + o_head, at<T>(ws, L.wteT), V, H, L.ldv, s));
   J.fork();
   GemmSideBySide hint(nst);     // until the join: two kernels share the device
-  for (int j = 0; j < l; ++j) {
-    embed_fwd_kernel<T><<<(Tm + 3) / 4, kThreads, 0, st[j % nst]>>>(ids + (size_t)j * Tm, P + o_wte, SO.positions ? P + o_wpe : (const T*)nullptr, X.out(0, j), Tm, S, H, V);
+  for (int i = 0; i < runs.runs(); ++i) {
+    const Run q = runs.run(i);
+    if (!q.count) continue;
+    const int j = q.first, Tr = q.count * Tm;
+    embed_fwd_kernel<T><<<(Tr + 3) / 4, kThreads, 0, st[q.lane]>>>(ids + (size_t)j * Tm, P + o_wte, SO.positions ? P + o_wpe : (const T*)nullptr, X.out(0, j), Tr, S, H, V);
     CEPHALO_CHECK_LAUNCH("embed_fwd");
     X.out_done(0, j);
   }
@@ -653,49 +663,66 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   for (int li = 0; li < NL; ++li) {
     void* save = save_of(li);
     X.prefetch(li, 0, l);
-    for (int j = 0; j < l; ++j) {
+    for (int i = 0; i < runs.runs(); ++i) {
+      const Run q = runs.run(i);
+      if (!q.count) continue;
+      const int j = q.first;
       const float* xi = X.in(li, j, l);
       X.prefetch(li, j + 1, l);
       float* xo = X.out(li + 1, j);
-      TRY(layer_fwd_t<T>(ld, P + o_layers + li * PL, xi, xo, m, saved_of(save, j * m), st[j % nst]));
+      TRY(layer_fwd_t<T>(ld, P + o_layers + li * PL, xi, xo, q.count * m, saved_of(save, j * m), st[q.lane]));
       X.in_done();
       X.out_done(li + 1, j);
     }
   }
   // ---- head: final LN, tied logits (fp32, one micro-batch at a time), cross-entropy and its gradient, back to the last layer's output
-  T* uf = at<T>(ws, L.uf); float* logits = at<float>(ws, L.logits); T* dlogits = at<T>(ws, L.dlogits); float* duf = at<float>(ws, L.duf);
+  T* uf = at<T>(ws, L.uf); T* dlogits = at<T>(ws, L.dlogits); float* duf = at<float>(ws, L.duf);
   float* meanf = at<float>(ws, L.meanf); float* rstdf = at<float>(ws, L.rstdf);
   float* lnf_g = at<float>(ws, L.lnf_part); float* lnf_b = lnf_g + L.lnf_rows * H; float* lnf_s = lnf_b + L.lnf_rows * H;
   float* dx_cur = at<float>(ws, L.dxa); float* dx_nxt = at<float>(ws, L.dxb);
   T* dxl_cur = at<T>(ws, L.dxal); T* dxl_nxt = at<T>(ws, L.dxbl);
   const float coef = scale / (float)n;
   const int nb = ln_bwd_blocks(Tm);
+  // The fp32 logits and the gradient of the final norm's output: a run's micro-batches together where there is room, the logits in the work area
+  // of the layers' backward (not in use yet) if it is the larger, the gradient in the buffer of the next layer's; otherwise one after the other.
+  const size_t mb_logits = (size_t)Tm * L.ldv * sizeof(float);
+  const bool roomy = WL.total > L.logits_bytes && !d.offload;
+  char* const lg_area = roomy ? at<char>(ws, L.scratch) : at<char>(ws, L.logits);
+  const size_t lg_lane = (roomy ? WL.total : L.logits_bytes) / nst / 256 * 256;
+  const int at_once = std::max<int>(1, (int)std::min<size_t>(l, lg_lane / mb_logits));
+  const int dgrad_at_once = std::max<int>(1, (int)std::min<size_t>(l, 0x7fffffff / ((size_t)Tm * L.ldv * sizeof(T))));     // (the GEMM's 32-bit offsets)
   X.prefetch(NL, 0, l);
-  for (int j = 0; j < l; ++j) {
+  for (int i = 0; i < runs.runs(); ++i) {
+    const Run q = runs.run(i);
+    if (!q.count) continue;
+    const int j = q.first, Tr = q.count * Tm;
     const size_t t0 = (size_t)j * Tm;
-    hipStream_t sj = st[j % nst];
-    float* logits_j = logits + (size_t)(j % nst) * Tm * L.ldv;
-    float* duf_j = duf + (size_t)(j % nst) * Tm * H;
+    hipStream_t sj = st[q.lane];
+    float* logits_q = reinterpret_cast<float*>(lg_area + q.lane * lg_lane);
+    float* duf_q = d.offload ? duf : dx_nxt + t0 * H;
     const float* xL = X.in(NL, j, l);
     X.prefetch(NL, j + 1, l);
-    TRY(launch_ln_fwd<T>(xL, P + o_lnf, rms ? (const T*)nullptr : P + o_lnf + H, uf + t0 * H, meanf + t0, rstdf + t0, Tm, H, ld.ln_eps, sj, rms));
+    TRY(launch_ln_fwd<T>(xL, P + o_lnf, rms ? (const T*)nullptr : P + o_lnf + H, uf + t0 * H, meanf + t0, rstdf + t0, Tr, H, ld.ln_eps, sj, rms));
     T* dlg = dlogits + t0 * L.ldv;
-    {
-      GemmArgs<T> a = linear_fwd<T>(uf + t0 * H, P + o_head, Tm, V, H);
-      a.epi = EPI_NONE_HEAD; a.Cf = logits_j; a.ldc = L.ldv;
+    for (int k = 0; k < q.count; k += at_once) {
+      const int Tk = std::min(at_once, q.count - k) * Tm;
+      const size_t r0 = (size_t)k * Tm;
+      GemmArgs<T> a = linear_fwd<T>(uf + (t0 + r0) * H, P + o_head, Tk, V, H);
+      a.epi = EPI_NONE_HEAD; a.Cf = logits_q; a.ldc = L.ldv;
       TRY(gemm<T>(a, sj));
+      launch_cross_entropy<T>(logits_q, dlg + r0 * L.ldv, targets + t0 + r0, at<float>(ws, L.loss) + t0 + r0, Tk, V, L.ldv, coef, sj);
+      CEPHALO_CHECK_LAUNCH("cross_entropy");
     }
-    launch_cross_entropy<T>(logits_j, dlg, targets + t0, at<float>(ws, L.loss) + t0, Tm, V, L.ldv, coef, sj);
-    CEPHALO_CHECK_LAUNCH("cross_entropy");
-    {
-      GemmArgs<T> a = head_dgrad_args<T>(dlg, P + o_head, at<T>(ws, L.wteT), Tm, V, H, L.ldv);   // duf = dlogits W_head
-      a.epi = EPI_NONE_HEAD; a.Cf = duf_j;
+    for (int k = 0; k < q.count; k += dgrad_at_once) {
+      const size_t r0 = (size_t)k * Tm;
+      GemmArgs<T> a = head_dgrad_args<T>(dlg + r0 * L.ldv, P + o_head, at<T>(ws, L.wteT), std::min(dgrad_at_once, q.count - k) * Tm, V, H, L.ldv);   // duf = dlogits W_head
+      a.epi = EPI_NONE_HEAD; a.Cf = duf_q + r0 * H;
       TRY(gemm<T>(a, sj));
     }
     float* dxo = Gx.offload ? Gx.out(NL % 2, j) : dx_cur + t0 * H;
-    TRY(launch_ln_bwd<T>(duf_j, xL, meanf + t0, rstdf + t0, P + o_lnf, (const float*)nullptr, dxo,
-                         lowp_out<T>(dxl_cur + t0 * H), lnf_g + (size_t)j * nb * H, lnf_b + (size_t)j * nb * H, Tm, H, sj, rms,
-                         rms ? (float*)nullptr : lnf_s + (size_t)j * nb * H));
+    TRY(launch_ln_bwd<T>(duf_q, xL, meanf + t0, rstdf + t0, P + o_lnf, (const float*)nullptr, dxo,
+                         lowp_out<T>(dxl_cur + t0 * H), lnf_g + (size_t)j * nb * H, lnf_b + (size_t)j * nb * H, Tr, H, sj, rms,
+                         rms ? (float*)nullptr : lnf_s + (size_t)j * nb * H, Tm));
     Gx.out_done(NL % 2, j);
     X.in_done();
   }
@@ -716,25 +743,28 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   for (int li = NL - 1; li >= 0; --li) {
     void* save = save_of(li);
     const T* Pl = P + o_layers + li * PL;
-    TRY(prepare_dgrad_weights<T>(ld, Pl, work_at<T>(scratch, WL, ld, 0, 0, m).wT, s));
+    TRY(prepare_dgrad_weights<T>(ld, Pl, work_at<T>(scratch, WL, ld, 0, 0, m, pool.base, m).wT, s));
     J.fork();        // (after the previous layer's weight gradients too: they read what this layer's data pass overwrites)
     hint.now(nst);
     // Checkpointing: a micro-batch's internals are recomputed from its boundary input right before its backward (the
-    // last layer's are still there from the forward); the recomputed output, the same values again, is dropped.
+    // last layer's are still there from the forward).  The layer's output is not among them and is not formed again.
     const bool recompute = d.checkpoint && li != NL - 1;
     X.prefetch(li, 0, l);
     Gx.prefetch((li + 1) % 2, 0, l);
-    for (int j = 0; j < l; ++j) {
+    for (int i = 0; i < runs.runs(); ++i) {
+      const Run q = runs.run(i);
+      if (!q.count) continue;
+      const int j = q.first;
       const float* xi = X.in(li, j, l);
       X.prefetch(li, j + 1, l);
-      if (recompute) TRY(layer_fwd_t<T>(ld, Pl, xi, at<float>(ws, L.xdump) + (size_t)(j % nst) * act, m, saved_of(save, j * m), st[j % nst]));
+      if (recompute) TRY(layer_fwd_t<T>(ld, Pl, xi, (float*)nullptr, q.count * m, saved_of(save, j * m), st[q.lane]));
       // the fp32 gradient arriving at this layer's output and the one leaving at its input: resident buffers, or (offload = 2)
       // a slot just fetched from the host and a slot about to leave for it; layer 0's result stays on the device for the embeddings
       const float* dyj = Gx.offload ? Gx.in((li + 1) % 2, j, l) : dx_cur + j * act;
       Gx.prefetch((li + 1) % 2, j + 1, l);
       float* dxj = !Gx.offload ? dx_nxt + j * act : (li == 0 ? at<float>(ws, L.dxa) + j * act : Gx.out(li % 2, j));
-      TRY(layer_bwd_data_t<T>(ld, Pl, xi, dyj, dxl_cur + j * act, dxj,
-                              dxl_nxt + j * act, m, saved_of(save, j * m), work_at<T>(scratch, WL, ld, j * m, j, m, j % nst), st[j % nst]));
+      TRY(layer_bwd_data_t<T>(ld, Pl, xi, dyj, dxl_cur + j * act, dxj, dxl_nxt + j * act, m, q.count * m, saved_of(save, j * m),
+                              work_at<T>(scratch, WL, ld, j * m, j, m, pool_of(pool, q.lane, nst), q.count * m), st[q.lane]));
       Gx.in_done();
       if (Gx.offload && li > 0) Gx.out_done(li % 2, j);
       X.in_done();
@@ -743,7 +773,7 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
     hint.now(1);
     J.fork();        // the parameter pass: weight-gradient GEMMs on the main stream, the bandwidth-bound reductions beside them
     TRY(layer_bwd_params_t<T>(ld, DySums{nullptr, 0}, Gx.offload ? dxl_cur : lowp_of<T>(dx_cur, dxl_cur), n, l * nb,
-                              saved_of(save, 0), work_at<T>(scratch, WL, ld, 0, 0, m), G + o_layers + li * PL, 1.0f, 0, s, st[1],
+                              saved_of(save, 0), work_at<T>(scratch, WL, ld, 0, 0, m, pool.base, m), G + o_layers + li * PL, 1.0f, 0, s, st[1],
                               (!rms && li > 0) ? G + o_layers + (size_t)(li - 1) * PL + param_offsets(ld).b_fc2 : (float*)nullptr));
     J.join();
     { float* t = dx_cur; dx_cur = dx_nxt; dx_nxt = t; }

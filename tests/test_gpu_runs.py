@@ -1,0 +1,85 @@
+"""Several micro-batches per launch: the share and stack calls give the results of single micro-batches bit for bit, however many
+of them a launch takes and whichever stream it runs on."""
+import pytest
+import torch
+
+import paper_2411_01075_amd as C
+
+pytestmark = pytest.mark.gpu
+
+
+def _bytes(n):
+    return torch.empty(max(1, n), dtype=torch.uint8, device="cuda").fill_(255)      # (work areas start as NaNs)
+
+
+def _flat(n, dtype):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    return (torch.randn(n, device="cuda", generator=g) * 0.05).to(torch.float32 if dtype == C.F32 else torch.bfloat16)
+
+
+def _share(desc, b, m, side=False):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, dy = (torch.randn(b, desc.seq, desc.hidden, device="cuda", generator=g) for _ in range(2))
+    flat = _flat(C.cephalo_layer_param_count(desc), desc.dtype)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    G = torch.full((flat.numel(),), float("nan"), device="cuda")
+    save, scratch = (_bytes(n) for n in C.cephalo_share_workspace_bytes(desc, b, m))
+    if side:
+        C.cephalo_share_layer_step_interleaved(desc, flat, x, y, dy, dx, b, m, save, G, 0.5, scratch, torch.cuda.Stream())
+    else:
+        C.cephalo_share_layer_step(desc, flat, x, y, dy, dx, b, m, save, G, 0.5, scratch)
+    torch.cuda.synchronize()
+    return flat, x, dy, y, dx, G
+
+
+@pytest.mark.parametrize("kind,dtype", [("gpt", "bf16"), ("llama", "bf16"), ("gpt", "f32"), ("llama", "f32")])
+@pytest.mark.parametrize("S,m,l", [(37, 1, 3), (197, 1, 5), (64, 3, 2), (9, 5, 9)])      # (micro-batches that are no multiple of a norm block's 8 rows)
+def test_share_is_its_micro_batches_bit_for_bit(kind, dtype, S, m, l):
+    print(kind, dtype, S, m, l, flush=True)
+    desc = C.layer_desc(128, 4, 344, S, True, C.F32 if dtype == "f32" else C.BF16, 1e-5, C.LAYER_LLAMA if kind == "llama" else C.LAYER_GPT)
+    flat, x, dy, y, dx, G = _share(desc, m * l, m)
+    assert not torch.isnan(G).any()
+    Gm = torch.full_like(G, float("nan"))
+    save, scratch = (_bytes(n) for n in C.cephalo_layer_workspace_bytes(desc, m))
+    for j in range(l):
+        sl = slice(j * m, (j + 1) * m)
+        yj, dxj = torch.empty_like(x[sl]), torch.empty_like(x[sl])
+        C.cephalo_layer_fwd(desc, flat, x[sl], yj, m, save, scratch)
+        C.cephalo_layer_bwd(desc, flat, x[sl], dy[sl], dxj, m, save, Gm, 0.5, j > 0, scratch)
+        assert torch.equal(yj, y[sl]) and torch.equal(dxj, dx[sl]), j
+    # the gradient: the same fp32 products, the micro-batches added in the accumulators instead of one after the other
+    assert float((G - Gm).norm() / Gm.norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("S,m,l", [(512, 3, 12), (509, 3, 11), (512, 2, 9)])             # (more than 16384 tokens: both streams; odd counts; 9216 tokens that the pool does not take at once)
+def test_two_streams_take_a_large_share_to_the_same_bits(S, m, l):
+    print(S, m, l, flush=True)
+    desc = C.layer_desc(64, 1, 256, S, True, C.BF16, 1e-5, C.LAYER_GPT)
+    one, two = _share(desc, m * l, m), _share(desc, m * l, m, side=True)
+    assert all(torch.equal(a, b) for a, b in zip(one, two))
+
+
+@pytest.mark.parametrize("kind", [C.LAYER_GPT, C.LAYER_LLAMA], ids=["gpt", "llama"])
+@pytest.mark.parametrize("S,m,l,V", [(37, 1, 5, 77), (512, 3, 12, 1031), (64, 2, 4, 30011)])      # (small logits; two streams; one micro-batch of logits at a time)
+def test_stack_forms_agree_bit_for_bit(kind, S, m, l, V):
+    print(kind, S, m, l, V, flush=True)
+    layer = C.layer_desc(64, 2, 256, S, True, C.BF16, 1e-5, kind)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    ids, tgt = (torch.randint(0, V, (m * l, S), device="cuda", generator=g, dtype=torch.int32) for _ in range(2))
+    got = []
+    for checkpoint, interleave, mb in ((0, 0, m), (0, 1, m), (1, 0, m), (1, 1, m), (0, 0, m * l)):
+        sd = C.StackDesc(layer, 2, V, checkpoint, 0, interleave)
+        flat = _flat(C.cephalo_stack_param_count(sd), C.BF16)
+        G, loss = torch.full((flat.numel(),), float("nan"), device="cuda"), torch.full((1,), float("nan"), device="cuda")
+        ws = _bytes(C.cephalo_stack_workspace_bytes(sd, m * l, mb))
+        if interleave:
+            C.cephalo_stack_step_interleaved(sd, flat, ids, tgt, m * l, mb, G, 1.0, loss, ws, torch.cuda.Stream())
+        else:
+            C.cephalo_stack_step(sd, flat, ids, tgt, m * l, mb, G, 1.0, loss, ws)
+        torch.cuda.synchronize()
+        assert not torch.isnan(G).any()
+        got.append((loss, G))
+    for loss, G in got[1:4]:
+        assert torch.equal(loss, got[0][0]) and torch.equal(G, got[0][1])
+    # one micro-batch instead of l: the norms' partial sums differ where a micro-batch is no multiple of 8 rows, in the order of fp32 additions
+    assert torch.equal(got[4][0], got[0][0]) and float((got[4][1] - got[0][1]).norm() / got[0][1].norm()) <= 1e-5
