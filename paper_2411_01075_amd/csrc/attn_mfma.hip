@@ -13,6 +13,7 @@
 // The other operand of those second products (V^T, K^T, dO^T, Q^T: d-major views of row-major
 // [token][d] tiles) is fetched from LDS with the transposing read ds_read_b64_tr_b16.
 #include <type_traits>
+#include <utility>
 #include "kernels.h"
 #include "reserve_lds.h"
 #include <cstdlib>
@@ -132,6 +133,65 @@ __device__ __forceinline__ BlockCoords block_coords() {
   return {__builtin_amdgcn_readfirstlane(l % gx), __builtin_amdgcn_readfirstlane((l / gx) % gy), __builtin_amdgcn_readfirstlane(l / (gx * gy))};
 }
 
+// The order in which a causal launch of the four-wavefront kernels takes its tiles (the work of a tile grows with the keys its queries see):
+//   kSingle  one tile per block, the longest of a head first
+//   kPaired  a block takes a tile and then its mirror image, so that every block does the same work
+//   kByHead  one tile per block; each XCD has `per` heads and takes the longest tiles of all of them first (grid 8 * per * tiles; the last XCDs
+//            have fewer heads, y < 0: nothing to do)
+// With several blocks on a compute unit pairs leave it idle at the end (600 pairs are 2.3 per compute unit); single tiles, the longest first, even
+// out.  6 x 1024 tokens, 25 heads of 64, kPaired -> kByHead, us: forward 42.5 -> 36.3, dQ 52 -> 46, dK/dV 75 -> 61; 2048 tokens, 80 heads of
+// 32: 48.1 -> 42.3, and 124 -> 112 for the two.  Below 64 heads that are no multiple of 8 the XCDs' shares differ too much (3 x 777 tokens, 12 heads of
+// 80: backward 48.7 -> 50.5).
+struct TileOrder { int kind, per, heads; };
+enum { kSingle = 0, kPaired = 1, kByHead = 2 };
+__device__ __forceinline__ BlockCoords ordered_coords(const TileOrder& order, int A) {
+  if (order.kind != kByHead) return block_coords();
+  const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3, head = xcd * order.per + i % order.per;
+  return {__builtin_amdgcn_readfirstlane(i / order.per), __builtin_amdgcn_readfirstlane(head < order.heads ? head % A : -1), __builtin_amdgcn_readfirstlane(head / A)};
+}
+
+// The LDS addresses of one lane's fragment reads (Tile::frag_rows / frag_cols) for two double-buffered tiles A and B that lie [A | B][A | B]: a register
+// per constant that the permutation XORs in, everything else in the instruction's offset, and one XOR each to turn to the other buffer.
+// (Left to itself the compiler keeps an address per constant and buffer, or forms one per read, an instruction beside every product.)
+template <int D> struct FragAddr {
+  typedef Tile<D> TL;
+  static constexpr unsigned TILE_BYTES = TL::ELEMS * 2, STAGE = 2 * TILE_BYTES;
+  unsigned r[D / 16], lo[D / 32], hi[D / 32];
+  __device__ __forceinline__ explicit FragAddr(const lds_bf16* first) {
+    const unsigned base = (unsigned)(uintptr_t)first;         // (a multiple of 2 * STAGE: the XORs change no other bits)
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));                       // (formed here, not kept from pass to pass)
+    const int g = lane >> 4, i = lane & 15, row = 4 * (g >> 1) + (i >> 2);
+    const unsigned rows = (unsigned)(lane & 31) * (D * 2) + (unsigned)(((lane >> 5) ^ TL::swz(lane & 15)) << 4);
+    const unsigned cols = (unsigned)row * (D * 2) + (unsigned)(((2 * (g & 1) + ((i & 3) >> 1)) ^ TL::swz(row)) << 4) + 8u * (i & 1);
+#pragma unroll
+    for (int k = 0; k < D / 16; ++k) r[k] = base + (rows ^ (unsigned)(k * 32));
+#pragma unroll
+    for (int k = 0; k < D / 32; ++k) {
+      lo[k] = base + (cols ^ (unsigned)(k * 64));
+      hi[k] = base + (cols ^ (16u * TL::FLIP8) ^ (unsigned)(k * 64));
+    }
+  }
+  __device__ __forceinline__ void flip() {
+#pragma unroll
+    for (int k = 0; k < D / 16; ++k) { r[k] ^= STAGE; asm volatile("" : "+v"(r[k])); }
+#pragma unroll
+    for (int k = 0; k < D / 32; ++k) { lo[k] ^= STAGE; hi[k] ^= STAGE; asm volatile("" : "+v"(lo[k]), "+v"(hi[k])); }
+  }
+  // rows [rb, rb + 32) of tile A (0) or B (1), contraction over d in [16 k, 16 k + 16)
+  __device__ __forceinline__ bf16x8 rows(int tile, int rb, int k) const {
+    return *(const LDS_AS bf16x8*)(uintptr_t)(r[k] + (unsigned)(tile * TILE_BYTES + rb * (D * 2)));
+  }
+  // d in [32 k, 32 k + 32), contraction over the 16 rows from tb on
+  __device__ __forceinline__ bf16x8 cols(int tile, int k, int tb) const {
+    const unsigned at = (unsigned)(tile * TILE_BYTES + tb * (D * 2));
+    union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+    u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(uintptr_t)(lo[k] + at));
+    u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(uintptr_t)(hi[k] + at + 8u * (D * 2)));
+    return u.v;
+  }
+};
+
 // fragment of 32 rows of a row-major [*, ld] matrix straight from global memory (rows = MFMA rows)
 template <int D>
 __device__ void load_row_frags(const bf16* __restrict__ g, int64_t ld, int row0, int nrows, bf16x8 (&f)[D / 16], int d) {
@@ -212,17 +272,46 @@ __device__ void store_transposed_unrotated(const f32x16 (&acc)[D / 32], bf16* __
     }
 }
 
+// f(0), f(1), .. f(N - 1) with the index as a type: products and what runs between them, unrolled whatever their number
+template <typename F, int... I> __device__ __forceinline__ void static_steps_of(F& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void static_steps(F f) { static_steps_of(f, std::make_integer_sequence<int, N>{}); }
+// place AT of PLACES over which the work on 16 elements is spread
+template <int AT, int PLACES, typename F> __device__ __forceinline__ void spread(F f) {
+  if constexpr (AT >= 0 && AT < PLACES) {
+#pragma unroll
+    for (int e = AT * 16 / PLACES; e < (AT + 1) * 16 / PLACES; ++e) f(e);
+  }
+}
+
+// Wavefronts per SIMD, that is blocks per compute unit, that the four-wavefront kernels are compiled for: as many as their registers allow without a
+// spill.
+template <int D> constexpr int kFwdWaves = D == 128 ? 2 : 4;
+template <int D> constexpr int kDqWaves = D == 32 ? 4 : D == 64 ? 3 : 2;
+template <int D> constexpr int kDkvWaves = D == 32 ? 3 : 2;
+
+// How the four-wavefront kernels (forward, dQ, and dK / dV of heads up to 64) run a tile.  What bounds them is three units in about equal measure: the
+// matrix core, the vector unit (an exponential takes as long as half a 32x32x16 product) and waits for LDS and for one another.  A wavefront's products of a
+// tile are one straight line, pinned product by product: fragments are asked for kAhead products early, and the exponentials of one block of 32
+// scores go, a few after each product, between the products that do not need them.  Masking is a branch around a few selects (two copies of
+// the whole tile, one masked, keep the accumulators in different registers: 64 moves and 130 spills), the tiles a wavefront has no work in are
+// a loop of their own for the same reason, and fragment addresses are FragAddr's.  Eight wavefronts in step, their products and exponentials in phases of
+// their own -> this form, us alone: forward 6 x 1024 tokens, 25 heads of 64, causal 45 -> 35; 2 x 1024, 8 heads of 128 26.5 -> 22.9; 8 x 512, 16 of 64 16.5 ->
+// 15.5; backward 157 -> 104, 8 x 512, 16 of 64 54.7 -> 44.5, 16 x 197, 16 of 64 35.9 -> 29.0, 8 x 257, 16 of 104 60.1 -> 49.3, 2048, 80 of 32, causal 142 ->
+// 112, 4 x 2048, 16 of 128, causal 286 -> 269 (dK / dV of 128, bound by LDS reads, did not gain by it and keeps its form).
+
 // ------------------------------------------------------------------------------------ forward
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(kThreads, 2)
-attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale) {
+__global__ void __launch_bounds__(kThreads, kFwdWaves<D>)
+attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale, TileOrder order) {
   typedef Tile<D> TL;
+  constexpr int NP = D / 16, DT = D / 32, N = 4 * NP, kAhead = CAUSAL && D == 64 ? 2 : 3;      // (a third fragment ahead would spill a register there)
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Ks = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto Vs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
 
-  const BlockCoords blk = block_coords();
+  const BlockCoords blk = ordered_coords(order, A);
+  if (blk.y < 0) return;
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: tests on a wavefront's rows become real branches
@@ -232,112 +321,112 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
   const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
   const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
-  // Under a causal mask the work of a query tile grows with its index, and a launch has about as many blocks as the
-  // chip has slots, so nothing would even the load out: each block takes tile x and then tile ntq-1-x, whose key
-  // ranges add up to the same length for every x.
   const int ntq = (S + 127) / 128;
-  for (int pass = 0; pass < (CAUSAL ? 2 : 1); ++pass) {
-  const int qt = pass == 0 ? blk.x : ntq - 1 - blk.x;
+  for (int pass = 0; pass < (CAUSAL && order.kind == kPaired ? 2 : 1); ++pass) {
+  const int qt = pass == 0 && (order.kind == kPaired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;
   if (pass == 1 && qt == blk.x) break;   // odd tile count: the middle tile is its own partner
   const int q0 = qt * 128 + wave * 32;             // this wavefront's 32 query rows
   const int q = q0 + (lane & 31);
-
-  bf16x8 qf[D / 16];
-  load_row_frags<D>(base, ld, q0, S, qf, d);
-
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
 
   const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
   const int ntiles = (kv_end + TILE - 1) / TILE;
   TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
   TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
+  bf16x8 qf[NP];
+  load_row_frags<D>(base, ld, q0, S, qf, d);
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
   __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
   __syncthreads();
 
-  for (int kt = 0; kt < ntiles; ++kt) {
-    const int cur = kt & 1, t0 = kt * TILE;
-    if (kt + 1 < ntiles) {
-      TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, t0 + TILE, Ks(cur ^ 1), d);
-      TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, t0 + TILE, Vs(cur ^ 1), d);
-    }
-    if (q0 < S && (!CAUSAL || t0 <= q0 + 31)) {          // (a wavefront whose queries all lie past the end only stages)
-      // All K fragments of the tile are read before the first MFMA needs one, and the two 32-key blocks accumulate
-      // in turn, so neither an LDS round trip nor a dependent accumulator sits between consecutive MFMAs.
-      bf16x8 kfr[2][D / 16];
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) kfr[tb][kk] = TL::frag_rows(Ks(cur), tb * 32, kk * 16);
-      f32x16 s[2];
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s[tb][e] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-          s[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[tb][kk], qf[kk], s[tb], 0, 0, 0);
-      // Only tiles that touch the diagonal or the ragged end need per-element masking (wave-uniform test).
-      if ((CAUSAL && t0 + TILE - 1 > q0) || t0 + TILE > S) {
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int t = t0 + tb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-            if (t >= S || (CAUSAL && t > q)) s[tb][e] = -INFINITY;
-          }
-      }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[tb][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;          // scores enter the exponent as s*c2 (c2 > 0)
-      // Running maximum, in the log2 domain.  It is only raised when some row of the wavefront would otherwise see
-      // an exponent above 8 (probabilities up to 2^8 are harmless in fp32 / bf16 and cancel in the final division);
-      // raising it costs a pass over the output accumulators, and after the first tiles it is rarely needed.
-      if (__any(mx > m_run + 8.0f)) {
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-        l_run *= alpha;
-        m_run = m_new;
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
-      }
-      const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-      float psum = 0.f;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[tb][e], c2, neg_m));
-          s[tb][e] = p;
-          psum += p;
-        }
-      l_run += psum;
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          bf16x8 vfr[D / 32];
-#pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt) vfr[dt] = TL::frag_cols(Vs(cur), dt * 32, tb * 32 + 16 * jj);
-          const bf16x8 pf = pack8(s[tb], 8 * jj);
-#pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt)
-            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[dt], pf, o[dt], 0, 0, 0);
-        }
-    }
+  FragAddr<D> at(smem);
+  auto stage_after = [&](int kt) {
+    if (kt + 1 >= ntiles) return;
+    TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * TILE, Ks((kt + 1) & 1), d);
+    TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * TILE, Vs((kt + 1) & 1), d);
+  };
+  auto close = [&] {
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
+  };
+  const int mine = q0 >= S ? 0 : CAUSAL ? min(ntiles, (q0 + 31) / TILE + 1) : ntiles;
+  int kt = 0;
+  for (; kt < mine; ++kt) {
+    const int t0 = kt * TILE;
+    stage_after(kt);
+    const bool mask = (CAUSAL && t0 + 63 > q0) || t0 + 64 > S;
+    const int last = (CAUSAL ? min(q, S - 1) : S - 1) - t0 - 4 * h;
+    // S^T of the two blocks of 32 keys, then O^T += V^T P^T of each
+    auto fetch = [&](int i) -> bf16x8 {
+      const int seg = i / NP, j = i % NP;
+      if (seg < 2) return at.rows(0, seg * 32, j);
+      return at.cols(1, j % DT, (seg - 2) * 32 + 16 * (j / DT));
+    };
+    bf16x8 f[kAhead], pf[2][2];
+    f32x16 s[2], zero;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) f[i] = fetch(i);
+    __builtin_amdgcn_sched_barrier(0);
+    float psum = 0.f;
+    float neg_m = 0.f;
+    auto prob = [&](int b, int e) {
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][e], c2, neg_m));
+      s[b][e] = p;
+      psum += p;
+    };
+    static_steps<N>([&](auto step) {
+      constexpr int i = decltype(step)::value, seg = i / NP, j = i % NP;
+      if constexpr (seg < 2) s[seg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], qf[j], j == 0 ? zero : s[seg], 0, 0, 0);
+      else o[j % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], pf[seg - 2][j / DT], o[j % DT], 0, 0, 0);
+      if constexpr (i + kAhead < N) f[i % kAhead] = fetch(i + kAhead);
+      if constexpr (i == 2 * NP - 1) {
+        if (mask) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[b][e] = b * 32 + 8 * (e >> 2) + (e & 3) <= last ? s[b][e] : -INFINITY;
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[b][e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;          // scores enter the exponent as s*c2 (c2 > 0)
+        // Running maximum, in the log2 domain.  It is only raised when some row of the wavefront would otherwise see
+        // an exponent above 8 (probabilities up to 2^8 are harmless in fp32 / bf16 and cancel in the final division);
+        // raising it costs a pass over the output accumulators, and after the first tiles it is rarely needed.
+        if (__any(mx > m_run + 8.0f)) {
+          const float m_new = fmaxf(m_run, mx);
+          const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+          l_run *= alpha;
+          m_run = m_new;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
+        }
+        neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) prob(0, e);
+        pf[0][0] = pack8(s[0], 0); pf[0][1] = pack8(s[0], 8);
+      }
+      spread<i - 2 * NP, NP>([&](int e) { prob(1, e); });
+      if constexpr (i == 3 * NP - 1) { pf[1][0] = pack8(s[1], 0); pf[1][1] = pack8(s[1], 8); }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    l_run += psum;
+    at.flip();
+    close();
+  }
+  for (; kt < ntiles; ++kt) {
+    stage_after(kt);
+    close();
   }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = 1.0f / l_tot;
@@ -347,21 +436,14 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
 }
 
 // ------------------------------------------------------------------------------------ forward, 8 wavefronts
-// The same computation with two wavefronts per SIMD: 512 threads stage 128 keys per step, wavefronts 0-3 take the
+// The same computation for launches of few blocks (heads of 64 or less, causal): 512 threads stage 128 keys per step, wavefronts 0-3 take the
 // first 64 of them and wavefronts 4-7 the second 64, for the same four blocks of 32 queries.  Each half keeps its own
 // running maximum, sum and output; at the end the second half hands them over through LDS and the first half merges
 // (o = o0 2^(m0-m) + o1 2^(m1-m), likewise the sums).  While one wavefront of a SIMD runs its softmax on the vector
 // unit the other's MFMAs keep the matrix core busy.
 constexpr int kThreads8 = 512;
-// Wavefronts per SIMD the eight-wavefront kernels are compiled for.  A head of 64 or less is bound by the softmax arithmetic (about
-// 40 clocks of the vector unit per score against 8 to 16 of the matrix core) and by waits; within 128 registers two blocks share a
-// compute unit and cover each other's (32 heads of 64, 2 x 2048 tokens, causal: forward 59 -> 51 us).  The backward keeps too much at
-// 64 (within 128 registers it spills: 173 -> 359 us); at 128 the accumulators alone rule it out.
-template <int D> constexpr int kFwdWaves = D == 128 ? 2 : 4;
-template <int D> constexpr int kBwdWaves = D == 32 ? 4 : 2;
-
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(kThreads8, kFwdWaves<D>)
+__global__ void __launch_bounds__(kThreads8, 4)
 attn_fwd8_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __restrict__ lse, int S, int H, int A, float scale, int paired) {
   typedef Tile<D, 128, kThreads8> TL;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -746,47 +828,84 @@ attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float*
   }
 }
 
+// One wavefront's share of a key tile in the dQ kernel: 32 queries by 64 keys, as two blocks of 32 keys.
+template <int D>
+__device__ __forceinline__ void dq_tile(const FragAddr<D>& at, const bf16x8 (&qf)[D / 16], const bf16x8 (&dof)[D / 16], f32x16 (&dq)[D / 32],
+                                        float c2, float lse2, float dv, bool mask, int last) {
+  constexpr int NP = D / 16, N = 6 * NP, kAhead = 3, DT = D / 32;
+  auto fetch = [&](int i) -> bf16x8 {
+    const int seg = i / NP, j = i % NP;
+    if (seg < 4) return at.rows(seg & 1, seg / 2 * 32, j);
+    return at.cols(0, j % DT, (seg - 4) * 32 + 16 * (j / DT));
+  };
+  bf16x8 f[kAhead], df[2][2];
+  f32x16 s[2], dp[2], zero;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) f[i] = fetch(i);
+  __builtin_amdgcn_sched_barrier(0);
+  auto prob = [&](f32x16& s, int e) { s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c2, -lse2)); };
+  auto hide = [&](f32x16& s, int tb) {
+    if (mask) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = tb * 32 + 8 * (e >> 2) + (e & 3) <= last ? s[e] : 0.f;
+    }
+  };
+  static_steps<N>([&](auto step) {
+    constexpr int i = decltype(step)::value, seg = i / NP, j = i % NP;
+    if constexpr (seg == 0 || seg == 2) s[seg / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], qf[j], j == 0 ? zero : s[seg / 2], 0, 0, 0);
+    else if constexpr (seg == 1 || seg == 3) dp[seg / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], dof[j], j == 0 ? zero : dp[seg / 2], 0, 0, 0);
+    else dq[j % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], df[seg - 4][j / DT], dq[j % DT], 0, 0, 0);
+    if constexpr (i + kAhead < N) f[i % kAhead] = fetch(i + kAhead);
+    spread<i - NP - 1, NP>([&](int e) { prob(s[0], e); });
+    spread<i - 2 * NP - 1, NP>([&](int e) { s[0][e] *= dp[0][e] - dv; });
+    if constexpr (i == 3 * NP) { hide(s[0], 0); df[0][0] = pack8(s[0], 0); df[0][1] = pack8(s[0], 8); }
+    spread<i - 3 * NP - 1, NP>([&](int e) { prob(s[1], e); });
+    spread<i - 4 * NP - 1, NP - 1>([&](int e) { s[1][e] *= dp[1][e] - dv; });
+    if constexpr (i == 5 * NP - 1) { hide(s[1], 1); df[1][0] = pack8(s[1], 0); df[1][1] = pack8(s[1], 8); }
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
 // ------------------------------------------------------------------------------------ dQ
-// A block owns 128 queries (causal: tile x, then its mirror tile) and walks the keys they see in stages of 128.  Eight
-// wavefronts, as in the forward kernel: wavefront w takes the 32 queries of block w & 3 and the 64 keys of half w >> 2
-// of every stage; each half accumulates its own dQ and the second hands it over through LDS at the end of the pass.
+// A block of four wavefronts owns 128 queries, 32 a wavefront, and walks the keys they see in tiles of 64.  (Eight wavefronts that split
+// 128 keys, one block per compute unit, move in step between barriers: all multiply, then all run their exponentials.  Blocks that do not
+// share a barrier drift apart.)
 // The products are taken transposed (S^T = K Q^T, dP^T = V dO^T), so that a lane's 16 values belong to one query and
 // its statistics are two scalars, and dS^T is at once the operand of dQ^T += K^T dS^T.
 template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads8, kBwdWaves<D>)
+__global__ void __launch_bounds__(kThreads, kDqWaves<D>)
 attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
                float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
-               const float* __restrict__ rot, int paired) {
-  typedef Tile<D, 128, kThreads8> TL;
+               const float* __restrict__ rot, TileOrder order) {
+  typedef Tile<D> TL;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Ks = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto Vs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
 
-  const BlockCoords blk = block_coords();
+  const BlockCoords blk = ordered_coords(order, A);
+  if (blk.y < 0) return;
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: tests on a wavefront's rows become real branches
   const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int qsub = wave & 3, kh = wave >> 2;        // block of 32 queries, half of the staged keys
   const int64_t ld = 3 * (int64_t)H;
   const bf16* base = qkv + (int64_t)n * S * ld + a * d;
   const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
   const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
   const int ntq = (S + 127) / 128;                 // causal, paired: query tiles x and ntq-1-x in turn (equal work per block)
-  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
-  const int qt = pass == 0 && (paired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
+  for (int pass = 0; pass < (CAUSAL && order.kind == kPaired ? 2 : 1); ++pass) {
+  const int qt = pass == 0 && (order.kind == kPaired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
   if (pass == 1 && qt == blk.x) break;
-  const int q0 = qt * 128 + qsub * 32;
+  const int q0 = qt * 128 + wave * 32;
   const int q = q0 + (lane & 31);
 
   bf16x8 qf[D / 16], dof[D / 16];
   load_row_frags<D>(dO + (int64_t)n * S * H + a * d, H, q0, S, dof, d);
   const int64_t stat = ((int64_t)n * A + a) * S + q;
-  // dvec = rowsum(dO * O) of this lane's query, formed here (dO's row is in registers) and left for the dK/dV kernel, which runs next.  First of
-  // all, before the query's row takes registers too.  Both kernels -> this one, inside a layer's backward: 2 x 2048 tokens, 32 heads of 128,
-  // rotary 157.5 + 12.7 -> 166.7 us; 4 x 2048, 16 of 128 148.2 + 13.9 -> 160.1; 2 x 1024, 25 of 64 29.0 + 6.3 -> 30.5.
   float dv = 0.f;
   {
     bf16x8 of[D / 16];
@@ -799,7 +918,7 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
   }
   load_row_frags<D>(base, ld, q0, S, qf, d);
   const float lse2 = (q < S) ? lse[stat] * kLog2e : 0.f;
-  if (kh == 0 && h == 0 && q < S) dvec[stat] = dv;
+  if (h == 0 && q < S) dvec[stat] = dv;
 
   f32x16 dq[D / 32];
 #pragma unroll
@@ -808,80 +927,39 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
     for (int e = 0; e < 16; ++e) dq[dt][e] = 0.f;
 
   const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
-  const int ntiles = (kv_end + 127) / 128;
+  const int ntiles = (kv_end + TILE - 1) / TILE;
   TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
   TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
   __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
   __syncthreads();
 
-  for (int kt = 0; kt < ntiles; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < ntiles) {                             // the next stage flies meanwhile
-      TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * 128, Ks(cur ^ 1), d);
-      TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * 128, Vs(cur ^ 1), d);
-    }
-    const int t0 = kt * 128 + kh * 64;                 // this wavefront's 64 keys
-    const lds_bf16* Kt = Ks(cur) + kh * 64 * TL::LD;
-    const lds_bf16* Vt = Vs(cur) + kh * 64 * TL::LD;
-    if (t0 < S && q0 < S && (!CAUSAL || t0 <= q0 + 31)) {      // (a wavefront whose queries or keys all lie past the end only stages)
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        f32x16 s, dp;       // S^T and dP^T accumulate in turn: no dependent accumulator between consecutive MFMAs
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_rows(Kt, tb * 32, kk * 16), qf[kk], s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_rows(Vt, tb * 32, kk * 16), dof[kk], dp, 0, 0, 0);
-        }
-        // (the dQ products of the first key block share a basic block with the second block's scores)
-        if (tb == 0) lds_ahead_schedule<D / 8, 1>();
-        else lds_ahead_schedule<D / 16, 2, D / 8, 1>();
-        const int tb0 = t0 + tb * 32;
-        if ((CAUSAL && tb0 + 31 > q0) || tb0 + 32 > S) {      // block touches the diagonal or the ragged end (wave-uniform)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int t = tb0 + 8 * (e >> 2) + 4 * h + (e & 3);
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c2, -lse2));
-            if (t >= S || (CAUSAL && t > q)) p = 0.f;
-            s[e] = p * (dp[e] - dv);              // dS^T
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c2, -lse2)) * (dp[e] - dv);
-        }
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const bf16x8 df = pack8(s, 8 * jj);
-#pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt)
-            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_cols(Kt, dt * 32, tb * 32 + 16 * jj), df, dq[dt], 0, 0, 0);
-        }
-        if (tb == 1) lds_ahead_schedule<D / 16, 2>();
-      }
-    }
+  FragAddr<D> at(smem);
+  auto stage_after = [&](int kt) {                     // the next stage flies meanwhile
+    if (kt + 1 >= ntiles) return;
+    TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, (kt + 1) * TILE, Ks((kt + 1) & 1), d);
+    TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, (kt + 1) * TILE, Vs((kt + 1) & 1), d);
+  };
+  auto close = [&] {
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
+  };
+  // (the tiles whose keys the wavefront's queries see, then those it only helps to stage; one loop with the question inside copies the sums
+  // from register to register every time)
+  const int mine = q0 >= S ? 0 : CAUSAL ? min(ntiles, (q0 + 31) / TILE + 1) : ntiles;
+  int kt = 0;
+  for (; kt < mine; ++kt) {
+    const int t0 = kt * TILE;
+    stage_after(kt);
+    dq_tile<D>(at, qf, dof, dq, c2, lse2, dv, (CAUSAL && t0 + 63 > q0) || t0 + 64 > S, (CAUSAL ? min(q, S - 1) : S - 1) - t0 - 4 * h);
+    at.flip();
+    close();
   }
-  // the second half's sums go through LDS ([query block][value][lane], lanes contiguous) and the first half stores
-  constexpr int NV = D / 32 * 16;
-  LDS_AS float* mrg = (LDS_AS float*)smem_raw + qsub * NV * 64 + lane;
-  if (kh == 1) {
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mrg[(dt * 16 + e) * 64] = dq[dt][e];
+  for (; kt < ntiles; ++kt) {
+    stage_after(kt);
+    close();
   }
-  __syncthreads();
-  if (kh == 0) {
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) dq[dt][e] += mrg[(dt * 16 + e) * 64];
-    if (ROT) store_transposed_unrotated<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, rot, d);
-    else store_transposed<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, d);
-  }
-  __syncthreads();     // the merge area is staged over again by the next pass
+  if (ROT) store_transposed_unrotated<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, rot, d);
+  else store_transposed<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, d);
   }   // pass
 }
 
@@ -895,7 +973,7 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
 // kernel past 256 registers, where the accumulators move to the second register file and every score has to be copied
 // back for the vector unit.  Query and dO tiles are double-buffered.
 template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads8, kBwdWaves<D>)
+__global__ void __launch_bounds__(kThreads8, 2)
 attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
                 const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
                 const float* __restrict__ rot, int paired) {
@@ -1052,35 +1130,205 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
   }   // pass
 }
 
-// Causal launches: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute unit of their own at
-// once: then the launch lasts as long as the longest tile, not as the longest and the shortest (8 heads of 80, 700 tokens, 48 tiles: forward 22 ->
-// 15 us, backward 61 -> 44).  Beyond that single tiles, longest first, lose (25 heads of 64, 2 x 1024 tokens, 400 tiles: backward 56 paired, 78).
-inline bool pair_tiles(int nt, int A, int m) { return (int64_t)nt * A * m > 256; }
+// ------------------------------------------------------------------------------------ dK, dV, heads of 64 or less
+// Four wavefronts: a block owns 128 keys, each wavefront 32 of them, whose rows stay in its registers (at these widths they fit), and walks the
+// query tiles of 64 that see them, as two blocks of 32 queries.
+template <int D, bool CAUSAL, bool ROT>
+__global__ void __launch_bounds__(kThreads, kDkvWaves<D>)
+attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
+                       const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+                       const float* __restrict__ rot, TileOrder order) {
+  typedef Tile<D> TL;
+  constexpr int NP = D / 16, DT = D / 32, N = 8 * NP, kAhead = 3;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  lds_bf16* smem = (lds_bf16*)smem_raw;
+  auto Qs = [&](int st) { return smem + st * 2 * TL::ELEMS; };
+  auto dOs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
+  LDS_AS float* stats = (LDS_AS float*)(smem + 4 * TL::ELEMS);      // [2 buffers][-lse / scale | -dvec][64]
 
+  const BlockCoords blk = ordered_coords(order, A);
+  if (blk.y < 0) return;
+  const int a = blk.y, n = blk.z;
+  const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: tests on a wavefront's rows become real branches
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int64_t ld = 3 * (int64_t)H;
+  const bf16* base = qkv + (int64_t)n * S * ld + a * d;
+  const i32x4 rs_qkv = make_rsrc_words(qkv + (int64_t)n * S * ld, (unsigned)(S * ld * 2));
+  const i32x4 rs_do = make_rsrc_words(dO + (int64_t)n * S * H, (unsigned)((int64_t)S * H * 2));
+  const unsigned col_bytes = (unsigned)(a * d * 2);
+  const float* lse_base = lse + ((int64_t)n * A + a) * S;
+  const float* dv_base = dvec + ((int64_t)n * A + a) * S;
+  const float c2 = scale * kLog2e, per_scale = -1.0f / scale;
+  const int ntk = (S + 127) / 128;                 // causal, paired: key tiles x and ntk-1-x in turn (early key tiles see the most queries)
+  for (int pass = 0; pass < (CAUSAL && order.kind == kPaired ? 2 : 1); ++pass) {
+  const int tt = pass == 0 ? blk.x : ntk - 1 - blk.x;
+  if (pass == 1 && tt == blk.x) break;
+  const int t0 = tt * 128 + wave * 32;             // this wavefront's 32 keys
+  const int t = t0 + (lane & 31);
+
+  const int first = CAUSAL ? (tt * 128) / TILE : 0;    // first query tile that can see these keys
+  const int ntiles = (S + TILE - 1) / TILE;
+  float rstat = 0.f;                                   // threads 0..63: of lse, 64..127: of dvec
+  auto load_stats = [&](int row0) {
+    rstat = 0.f;
+    if (threadIdx.x < 128) {
+      const int r = row0 + (threadIdx.x & 63);
+      if (r < S) rstat = threadIdx.x < 64 ? lse_base[r] * per_scale : -dv_base[r];
+    }
+  };
+  TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, first * TILE, Qs(0), d);
+  TL::stage(rs_do, col_bytes, (unsigned)H * 2, first * TILE, dOs(0), d);
+  bf16x8 kf[NP], vf[NP];
+  load_row_frags<D>(base + H, ld, t0, S, kf, d);
+  load_row_frags<D>(base + 2 * H, ld, t0, S, vf, d);
+  load_stats(first * TILE);
+  if (threadIdx.x < 128) stats[threadIdx.x] = rstat;
+
+  f32x16 dk[DT], dvv[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dvv[dt][e] = 0.f; }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
+  __syncthreads();
+
+  FragAddr<D> at(smem);
+  auto stage_after = [&](int it) {                     // the next tile flies into the other stage meanwhile
+    if (it + 1 >= ntiles) return;
+    const int nxt = (it + 1 - first) & 1;
+    TL::stage(rs_qkv, col_bytes, (unsigned)ld * 2, (it + 1) * TILE, Qs(nxt), d);
+    TL::stage(rs_do, col_bytes, (unsigned)H * 2, (it + 1) * TILE, dOs(nxt), d);
+    load_stats((it + 1) * TILE);
+  };
+  auto close = [&](int it) {
+    if (it + 1 < ntiles && threadIdx.x < 128) stats[((it + 1 - first) & 1) * 128 + threadIdx.x] = rstat;
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+    __syncthreads();
+  };
+  // (the tiles before the first whose queries see the wavefront's keys it only helps to stage; likewise all of them if its keys lie past the end)
+  const int mine = t0 >= S ? ntiles : CAUSAL ? max(first, t0 / TILE) : first;
+  int it = first;
+  for (; it < mine; ++it) {
+    stage_after(it);
+    at.flip();
+    close(it);
+  }
+  for (; it < ntiles; ++it) {
+    const int qb0 = it * TILE;
+    stage_after(it);
+    {
+      const LDS_AS float* st = stats + ((it - first) & 1) * 128 + 4 * h;
+      // the products: S and dP of the first block and of the second, then dV and dK of each
+      auto fetch = [&](int i) -> bf16x8 {
+        const int seg = i / NP, j = i % NP;
+        if (seg < 4) return at.rows(seg & 1, seg / 2 * 32, j);
+        return at.cols(1 - (seg & 1), j % DT, (seg - 4) / 2 * 32 + 16 * (j / DT));
+      };
+      f32x16 s[2], dp[2];
+      auto start = [&](f32x16& acc, int at) {           // a row's statistic is where its sums start
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4 v = *reinterpret_cast<const LDS_AS f32x4*>(st + at + 8 * j);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[4 * j + i] = v[i];
+        }
+      };
+      bf16x8 f[kAhead], pf[2][2], df[2][2];
+      start(s[0], 0);
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) f[i] = fetch(i);
+      start(dp[0], 64);
+      __builtin_amdgcn_sched_barrier(0);
+      const int seen = t - qb0 - 4 * h;                 // query rows from here on see the key
+      auto hide = [&](f32x16& p, int b) {
+        if (CAUSAL && t0 + 31 > qb0 + b * 32) {         // (the block touches the diagonal: wave-uniform)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) p[e] = b * 32 + 8 * (e >> 2) + (e & 3) >= seen ? p[e] : 0.f;
+        }
+      };
+      static_steps<N>([&](auto step) {
+        constexpr int i = decltype(step)::value, seg = i / NP, j = i % NP;
+        if constexpr (seg == 0 || seg == 2) s[seg / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], kf[j], s[seg / 2], 0, 0, 0);
+        else if constexpr (seg == 1 || seg == 3) dp[seg / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], vf[j], dp[seg / 2], 0, 0, 0);
+        else if constexpr (seg == 4 || seg == 6) dvv[j % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], pf[(seg - 4) / 2][j / DT], dvv[j % DT], 0, 0, 0);
+        else dk[j % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], df[(seg - 4) / 2][j / DT], dk[j % DT], 0, 0, 0);
+        if constexpr (i + kAhead < N) f[i % kAhead] = fetch(i + kAhead);
+        if constexpr (i == NP) start(s[1], 32);
+        if constexpr (i == 2 * NP) start(dp[1], 96);
+        // P = exp2(c2 (S - lse / scale)) and dS = P (dP - dvec)
+        spread<i - NP - 1, NP>([&](int e) { s[0][e] = __builtin_amdgcn_exp2f(s[0][e] * c2); });
+        if constexpr (i == 2 * NP) hide(s[0], 0);
+        spread<i - 2 * NP - 1, NP - 1>([&](int e) { dp[0][e] *= s[0][e]; });
+        if constexpr (i == 3 * NP - 1) {
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) { pf[0][jj] = pack8(s[0], 8 * jj); df[0][jj] = pack8(dp[0], 8 * jj); }
+        }
+        spread<i - 3 * NP, NP>([&](int e) { s[1][e] = __builtin_amdgcn_exp2f(s[1][e] * c2); });
+        if constexpr (i == 4 * NP - 1) hide(s[1], 1);
+        spread<i - 4 * NP - 1, NP - 1>([&](int e) { dp[1][e] *= s[1][e]; });
+        if constexpr (i == 5 * NP - 1) {
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) { pf[1][jj] = pack8(s[1], 8 * jj); df[1][jj] = pack8(dp[1], 8 * jj); }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    at.flip();
+    close(it);
+  }
+  bf16* out = dqkv + (int64_t)n * S * ld + a * d;
+  store_transposed<D>(dvv, out + 2 * H, ld, t, S, 1.0f, d);
+  if (ROT) store_transposed_unrotated<D>(dk, out + H, ld, t, S, scale, rot, d);
+  else store_transposed<D>(dk, out + H, ld, t, S, scale, d);
+  }   // pass
+}
+
+// Causal launches of the eight-wavefront kernels: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute
+// unit of their own at once: then the launch lasts as long as the longest tile, not as the longest and the shortest (8 heads of 80, 700 tokens, 48
+// tiles: forward 22 -> 15 us, backward 61 -> 44).  Beyond that single tiles, longest first, lose (4 x 2048 tokens, 16 heads of 128).
+inline bool pair_tiles(int nt, int A, int m) { return (int64_t)nt * A * m > 256; }
+// grid and order of a four-wavefront kernel (by_head: whether that order is worth it for the kernel)
+inline dim3 tile_order(bool causal, bool by_head, int nt, int A, int m, TileOrder* order) {
+  const int64_t heads = (int64_t)A * m, per = (heads + 7) / 8;
+  *order = {causal && pair_tiles(nt, A, m) ? kPaired : kSingle, 0, (int)heads};
+  if (order->kind == kPaired && by_head && (heads % 8 == 0 || heads >= 64) && 8 * per * nt < (int64_t)1 << 31) {
+    *order = {kByHead, (int)per, (int)heads};
+    return dim3((unsigned)(8 * per * nt));
+  }
+  return dim3(order->kind == kPaired ? (nt + 1) / 2 : nt, A, m);
+}
+
+// Forward.  Causal heads of 128: two groups that take turns.  Causal narrower heads: where a sample has at most 64 tiles of queries, eight wavefronts,
+// which split the keys between them and so halve the chain that such a launch consists of (1024 tokens, 8 heads of 64, one sample 14.3 us, with four
+// wavefronts 16.7; 128 tokens, 16 heads, 64 samples 20.7 and 18.6); the samples do not count, so that a sample's result does not depend on
+// how many a launch takes.  Otherwise four wavefronts.
 template <int D, bool CAUSAL>
 int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hipStream_t s) {
   const int nt = (S + 127) / 128;
   const float scale = 1.0f / sqrtf((float)(H / A));
   if constexpr (CAUSAL) {
-    // eight wavefronts, the staged keys split between two groups; at D = 128 the two groups take turns on the matrix core and the
-    // vector unit
-    const bool paired = pair_tiles(nt, A, m);
-    dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
-    const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16 + 2) * 64 * sizeof(float);
-    const size_t lds = staging > merge ? staging : merge;
-    constexpr auto kern = [] { if constexpr (D == 128) return attn_fwd_turns_kernel<D, CAUSAL>; else return attn_fwd8_kernel<D, CAUSAL>; }();
-    int rc = reserve_lds<kern>("attention", lds);
-    if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, scale, paired);
-  } else {
-    // uniform tiles: two independent four-wavefront blocks per compute unit run out of phase with each other
-    // (measured 12 % faster than the eight-wavefront form, whose wavefronts move in step between barriers)
-    dim3 grid(nt, A, m);
-    const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);
+    if (D == 128 || (int64_t)A * nt <= 64) {
+      const bool paired = pair_tiles(nt, A, m);
+      dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
+      const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16 + 2) * 64 * sizeof(float);
+      const size_t lds = staging > merge ? staging : merge;
+      constexpr auto kern = [] { if constexpr (D == 128) return attn_fwd_turns_kernel<D, CAUSAL>; else return attn_fwd8_kernel<D, CAUSAL>; }();
+      int rc = reserve_lds<kern>("attention", lds);
+      if (rc != CEPHALO_OK) return rc;
+      kern<<<grid, kThreads8, lds, s>>>(qkv, O, lse, S, H, A, scale, paired);
+      CEPHALO_CHECK_LAUNCH("attn_fwd_mfma");
+      return CEPHALO_OK;
+    }
+  }
+  if constexpr (!CAUSAL || D <= 64) {
+    TileOrder order;
+    const dim3 grid = tile_order(CAUSAL, true, nt, A, m, &order);
+    const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);      // two stages of 64 keys and values
     constexpr auto kern = attn_fwd_kernel<D, CAUSAL>;
     int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads, lds, s>>>(qkv, O, lse, S, H, A, scale);
+    kern<<<grid, kThreads, lds, s>>>(qkv, O, lse, S, H, A, scale, order);
   }
   CEPHALO_CHECK_LAUNCH("attn_fwd_mfma");
   return CEPHALO_OK;
@@ -1091,18 +1339,22 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
             int m, int S, int H, int A, const float* rot, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)(H / A));
   const int nt = (S + 127) / 128;
-  const bool paired = CAUSAL && pair_tiles(nt, A, m);
-  dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
+  TileOrder order;
+  const dim3 grid = tile_order(CAUSAL, D <= 64, nt, A, m, &order);
   {
-    // two stages of 128 keys and values or, at the end, the merge of the halves
-    const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16) * 64 * sizeof(float);
-    const size_t lds = staging > merge ? staging : merge;
+    const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);      // two stages of 64 keys and values
     constexpr auto kern = attn_dq_kernel<D, CAUSAL, ROT>;
     int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads8, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
+    kern<<<grid, kThreads, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, order);
   }
-  {
+  if constexpr (D <= 64) {
+    const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * 128 * sizeof(float);      // two stages of Q and dO and of the row statistics
+    constexpr auto kern = attn_dkv_narrow_kernel<D, CAUSAL, ROT>;
+    int rc = reserve_lds<kern>("attention", lds);
+    if (rc != CEPHALO_OK) return rc;
+    kern<<<grid, kThreads, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot, order);
+  } else {
     // staging (2 stages of Q and dO, the keys, the values, the row statistics) or, at the end, the merge of the halves
     const size_t staging = (4 * (size_t)Tile<D>::ELEMS + 2 * (size_t)Tile<D, 128>::ELEMS) * sizeof(bf16) + 2 * 128 * sizeof(float);
     const size_t merge = (size_t)4 * (D / 32 * 16 * 2) * 64 * sizeof(float);
@@ -1110,7 +1362,7 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
     constexpr auto kern = attn_dkv_kernel<D, CAUSAL, ROT>;
     int rc = reserve_lds<kern>("attention", lds);
     if (rc != CEPHALO_OK) return rc;
-    kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot, paired);
+    kern<<<grid, kThreads8, lds, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, scale, rot, order.kind == kPaired);
   }
   CEPHALO_CHECK_LAUNCH("attn_bwd_mfma");
   return CEPHALO_OK;

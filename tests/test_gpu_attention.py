@@ -82,3 +82,34 @@ def test_attention_fwd_bwd(bf16, m, S, A, d, causal):
         e = rel_errors(got[:, sl], dqkv_ref[:, sl])
         print(name, e, flush=True)
         assert e[0] < tol_max and e[1] < tol_mean, name
+
+
+@pytest.mark.parametrize("m,S,A,d", [
+    (20, 300, 5, 64),       # 100 heads, 300 tiles: each XCD's longest first
+    (8, 520, 13, 32),       # the same with heads of 32, the last XCD with fewer heads
+    (4, 1100, 9, 64),       # 36 heads, 324 tiles: in pairs, an odd number of tiles
+    (5, 700, 9, 128),       # pairs, heads of 128
+    (64, 64, 8, 64),        # one tile a head
+])
+def test_causal_samples_do_not_depend_on_the_launch(m, S, A, d):
+    """The order of the tiles follows from the launch's size; a sample's results are the same bits as by itself."""
+    print("attention order", m, S, A, d, flush=True)
+    H = A * d
+    g = torch.Generator(device="cuda").manual_seed(S)
+    qkv = torch.randn(m * S, 3 * H, device="cuda", generator=g).to(torch.bfloat16)
+    dO = torch.randn(m * S, H, device="cuda", generator=g).to(torch.bfloat16)
+    desc = C.layer_desc(H, A, 4 * H, S, True, C.BF16)
+
+    def run(qkv, dO, m):
+        O, dqkv = torch.full_like(dO, float("nan")), torch.full_like(qkv, float("nan"))
+        lse, dvec = (torch.full((m, A, S), float("nan"), device="cuda") for _ in range(2))
+        C.cephalo_op_attention_fwd(desc, qkv, O, lse, m)
+        C.cephalo_op_attention_bwd(desc, qkv, O, dO, lse, dvec, dqkv, m)
+        return O, lse, dqkv
+
+    O, lse, dqkv = run(qkv, dO, m)
+    assert not any(torch.isnan(t).any() for t in (O, lse, dqkv))
+    for n in range(m):
+        rows = slice(n * S, (n + 1) * S)
+        o1, l1, g1 = run(qkv[rows].contiguous(), dO[rows].contiguous(), 1)
+        assert torch.equal(o1, O[rows]) and torch.equal(l1[0], lse[n]) and torch.equal(g1, dqkv[rows]), n
