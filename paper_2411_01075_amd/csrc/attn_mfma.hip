@@ -16,7 +16,6 @@
 #include <utility>
 #include "kernels.h"
 #include "reserve_lds.h"
-#include <cstdlib>
 
 namespace cephalo {
 namespace {
@@ -125,12 +124,14 @@ template <int D, int ROWS = TILE, int THREADS = kThreads> struct Tile {
 // tile pays the full memory latency.  Give each XCD a contiguous run of the (pair, head, sample) order instead, so the
 // blocks of a head sit behind one L2: the first to ask for a tile brings it in, the others hit.
 struct BlockCoords { int x, y, z; };
-__device__ __forceinline__ BlockCoords block_coords() {
-  const int gx = gridDim.x, gy = gridDim.y, n = gx * gy * gridDim.z;
-  int l = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+__device__ __forceinline__ BlockCoords block_coords(int l, int gx, int gy, int n) {      // (block l of n, gx tiles by gy heads by samples)
   l = (l & 7) * (n >> 3) + min(l & 7, n & 7) + (l >> 3);      // (the first n % 8 runs are one longer)
   // (the divisions run on the vector unit; readfirstlane tells the compiler that the results are uniform)
   return {__builtin_amdgcn_readfirstlane(l % gx), __builtin_amdgcn_readfirstlane((l / gx) % gy), __builtin_amdgcn_readfirstlane(l / (gx * gy))};
+}
+__device__ __forceinline__ BlockCoords block_coords() {
+  const int gx = gridDim.x, gy = gridDim.y;
+  return block_coords(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx, gy, gx * gy * gridDim.z);
 }
 
 // The order in which a causal launch of the four-wavefront kernels takes its tiles (the work of a tile grows with the keys its queries see):
@@ -828,6 +829,19 @@ attn_fwd_turns_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float*
   }
 }
 
+// rowsum(dO * O) of this lane's row (row0 + lane % 32), dO's row at hand
+template <int D>
+__device__ __forceinline__ float row_dot(const bf16* __restrict__ O, int64_t ld, int row0, int nrows, const bf16x8 (&dof)[D / 16], int d) {
+  bf16x8 of[D / 16];
+  load_row_frags<D>(O, ld, row0, nrows, of, d);
+  float dv = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dv = __builtin_fmaf((float)of[kk][e], (float)dof[kk][e], dv);
+  return dv + __shfl_xor(dv, 32, 64);
+}
+
 // One wavefront's share of a key tile in the dQ kernel: 32 queries by 64 keys, as two blocks of 32 keys.
 template <int D>
 __device__ __forceinline__ void dq_tile(const FragAddr<D>& at, const bf16x8 (&qf)[D / 16], const bf16x8 (&dof)[D / 16], f32x16 (&dq)[D / 32],
@@ -875,18 +889,15 @@ __device__ __forceinline__ void dq_tile(const FragAddr<D>& at, const bf16x8 (&qf
 // The products are taken transposed (S^T = K Q^T, dP^T = V dO^T), so that a lane's 16 values belong to one query and
 // its statistics are two scalars, and dS^T is at once the operand of dQ^T += K^T dS^T.
 template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads, kDqWaves<D>)
-attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
-               float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
-               const float* __restrict__ rot, TileOrder order) {
+__device__ __forceinline__ void dq_block(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
+                                         float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+                                         const float* __restrict__ rot, const BlockCoords& blk, bool paired) {
   typedef Tile<D> TL;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Ks = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto Vs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
 
-  const BlockCoords blk = ordered_coords(order, A);
-  if (blk.y < 0) return;
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: tests on a wavefront's rows become real branches
@@ -897,8 +908,8 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
   const unsigned k_bytes = (unsigned)((H + a * d) * 2), v_bytes = (unsigned)((2 * H + a * d) * 2);
   const float c2 = scale * kLog2e;
   const int ntq = (S + 127) / 128;                 // causal, paired: query tiles x and ntq-1-x in turn (equal work per block)
-  for (int pass = 0; pass < (CAUSAL && order.kind == kPaired ? 2 : 1); ++pass) {
-  const int qt = pass == 0 && (order.kind == kPaired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
+  const int qt = pass == 0 && (paired || !CAUSAL) ? blk.x : ntq - 1 - blk.x;      // (not paired: the longest first)
   if (pass == 1 && qt == blk.x) break;
   const int q0 = qt * 128 + wave * 32;
   const int q = q0 + (lane & 31);
@@ -906,16 +917,7 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
   bf16x8 qf[D / 16], dof[D / 16];
   load_row_frags<D>(dO + (int64_t)n * S * H + a * d, H, q0, S, dof, d);
   const int64_t stat = ((int64_t)n * A + a) * S + q;
-  float dv = 0.f;
-  {
-    bf16x8 of[D / 16];
-    load_row_frags<D>(O + (int64_t)n * S * H + a * d, H, q0, S, of, d);
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dv += (float)of[kk][e] * (float)dof[kk][e];
-    dv += __shfl_xor(dv, 32, 64);
-  }
+  const float dv = row_dot<D>(O + (int64_t)n * S * H + a * d, H, q0, S, dof, d);
   load_row_frags<D>(base, ld, q0, S, qf, d);
   const float lse2 = (q < S) ? lse[stat] * kLog2e : 0.f;
   if (h == 0 && q < S) dvec[stat] = dv;
@@ -961,6 +963,15 @@ attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const b
   if (ROT) store_transposed_unrotated<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, rot, d);
   else store_transposed<D>(dq, dqkv + (int64_t)n * S * ld + a * d, ld, q, S, scale, d);
   }   // pass
+}
+template <int D, bool CAUSAL, bool ROT>
+__global__ void __launch_bounds__(kThreads, kDqWaves<D>)
+attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
+               float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+               const float* __restrict__ rot, TileOrder order) {
+  const BlockCoords blk = ordered_coords(order, A);
+  if (blk.y < 0) return;
+  dq_block<D, CAUSAL, ROT>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
 }
 
 // ------------------------------------------------------------------------------------ dK, dV
@@ -1133,21 +1144,19 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
 // ------------------------------------------------------------------------------------ dK, dV, heads of 64 or less
 // Four wavefronts: a block owns 128 keys, each wavefront 32 of them, whose rows stay in its registers (at these widths they fit), and walks the
 // query tiles of 64 that see them, as two blocks of 32 queries.
-template <int D, bool CAUSAL, bool ROT>
-__global__ void __launch_bounds__(kThreads, kDkvWaves<D>)
-attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
-                       const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
-                       const float* __restrict__ rot, TileOrder order) {
+// OWN: the rows' statistics are formed here, all of them at the start and from O (dvec is not read), for a launch that runs beside the dQ blocks.
+template <int D, bool CAUSAL, bool ROT, bool OWN>
+__device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
+                                          const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+                                          const float* __restrict__ rot, const BlockCoords& blk, bool paired) {
   typedef Tile<D> TL;
   constexpr int NP = D / 16, DT = D / 32, N = 8 * NP, kAhead = 3;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Qs = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto dOs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
-  LDS_AS float* stats = (LDS_AS float*)(smem + 4 * TL::ELEMS);      // [2 buffers][-lse / scale | -dvec][64]
+  LDS_AS float* stats = (LDS_AS float*)(smem + 4 * TL::ELEMS);      // [2 buffers][-lse / scale | -dvec][64], OWN: [-lse / scale | -dvec][all rows]
 
-  const BlockCoords blk = ordered_coords(order, A);
-  if (blk.y < 0) return;
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: tests on a wavefront's rows become real branches
@@ -1161,7 +1170,7 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
   const float* dv_base = dvec + ((int64_t)n * A + a) * S;
   const float c2 = scale * kLog2e, per_scale = -1.0f / scale;
   const int ntk = (S + 127) / 128;                 // causal, paired: key tiles x and ntk-1-x in turn (early key tiles see the most queries)
-  for (int pass = 0; pass < (CAUSAL && order.kind == kPaired ? 2 : 1); ++pass) {
+  for (int pass = 0; pass < (CAUSAL && paired ? 2 : 1); ++pass) {
   const int tt = pass == 0 ? blk.x : ntk - 1 - blk.x;
   if (pass == 1 && tt == blk.x) break;
   const int t0 = tt * 128 + wave * 32;             // this wavefront's 32 keys
@@ -1171,6 +1180,7 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
   const int ntiles = (S + TILE - 1) / TILE;
   float rstat = 0.f;                                   // threads 0..63: of lse, 64..127: of dvec
   auto load_stats = [&](int row0) {
+    if (OWN) return;
     rstat = 0.f;
     if (threadIdx.x < 128) {
       const int r = row0 + (threadIdx.x & 63);
@@ -1182,8 +1192,18 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
   bf16x8 kf[NP], vf[NP];
   load_row_frags<D>(base + H, ld, t0, S, kf, d);
   load_row_frags<D>(base + 2 * H, ld, t0, S, vf, d);
+  const int all = ntiles * TILE;
+  if (OWN) {
+    for (int r0 = first * TILE + wave * 32; r0 < all; r0 += 128) {
+      const int r = r0 + (lane & 31);
+      bf16x8 dof[NP];
+      load_row_frags<D>(dO + (int64_t)n * S * H + a * d, H, r0, S, dof, d);
+      const float dv = row_dot<D>(O + (int64_t)n * S * H + a * d, H, r0, S, dof, d), l = r < S ? lse_base[r] * per_scale : 0.f;
+      if (h == 0) { stats[r] = l; stats[all + r] = -dv; }
+    }
+  }
   load_stats(first * TILE);
-  if (threadIdx.x < 128) stats[threadIdx.x] = rstat;
+  if (!OWN && threadIdx.x < 128) stats[threadIdx.x] = rstat;
 
   f32x16 dk[DT], dvv[DT];
 #pragma unroll
@@ -1202,7 +1222,7 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
     load_stats((it + 1) * TILE);
   };
   auto close = [&](int it) {
-    if (it + 1 < ntiles && threadIdx.x < 128) stats[((it + 1 - first) & 1) * 128 + threadIdx.x] = rstat;
+    if (!OWN && it + 1 < ntiles && threadIdx.x < 128) stats[((it + 1 - first) & 1) * 128 + threadIdx.x] = rstat;
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
     __syncthreads();
   };
@@ -1218,7 +1238,8 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
     const int qb0 = it * TILE;
     stage_after(it);
     {
-      const LDS_AS float* st = stats + ((it - first) & 1) * 128 + 4 * h;
+      const LDS_AS float* st = stats + (OWN ? qb0 : ((it - first) & 1) * 128) + 4 * h;
+      const int dvecs = OWN ? all : 64;
       // the products: S and dP of the first block and of the second, then dV and dK of each
       auto fetch = [&](int i) -> bf16x8 {
         const int seg = i / NP, j = i % NP;
@@ -1238,7 +1259,7 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
       start(s[0], 0);
 #pragma unroll
       for (int i = 0; i < kAhead; ++i) f[i] = fetch(i);
-      start(dp[0], 64);
+      start(dp[0], dvecs);
       __builtin_amdgcn_sched_barrier(0);
       const int seen = t - qb0 - 4 * h;                 // query rows from here on see the key
       auto hide = [&](f32x16& p, int b) {
@@ -1255,7 +1276,7 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
         else dk[j % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i % kAhead], df[(seg - 4) / 2][j / DT], dk[j % DT], 0, 0, 0);
         if constexpr (i + kAhead < N) f[i % kAhead] = fetch(i + kAhead);
         if constexpr (i == NP) start(s[1], 32);
-        if constexpr (i == 2 * NP) start(dp[1], 96);
+        if constexpr (i == 2 * NP) start(dp[1], dvecs + 32);
         // P = exp2(c2 (S - lse / scale)) and dS = P (dP - dvec)
         spread<i - NP - 1, NP>([&](int e) { s[0][e] = __builtin_amdgcn_exp2f(s[0][e] * c2); });
         if constexpr (i == 2 * NP) hide(s[0], 0);
@@ -1282,6 +1303,29 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
   if (ROT) store_transposed_unrotated<D>(dk, out + H, ld, t, S, scale, rot, d);
   else store_transposed<D>(dk, out + H, ld, t, S, scale, d);
   }   // pass
+}
+template <int D, bool CAUSAL, bool ROT>
+__global__ void __launch_bounds__(kThreads, kDkvWaves<D>)
+attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
+                       const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
+                       const float* __restrict__ rot, TileOrder order) {
+  const BlockCoords blk = ordered_coords(order, A);
+  if (blk.y < 0) return;
+  dkv_block<D, CAUSAL, ROT, false>(qkv, nullptr, dO, lse, dvec, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
+}
+
+// The whole backward of narrow heads in one launch, where two would not fill the chip: the dK / dV blocks first (they are the longer ones), then the dQ
+// blocks, side by side instead of one after the other.  The statistics that the dK / dV kernel otherwise takes from the dQ kernel it forms itself,
+// in the same order of additions, so that the choice does not show in the results.  Two launches -> one, us: 2 x 128 tokens, 4 heads of 64 15.0 -> 9.1;
+// 2 x 512, 8 of 64 26.6 -> 18.5; 8 x 512, 8 of 64 29.2 -> 23.7; 1024, 8 of 64 41.7 -> 30.0; 16 x 197, 16 of 64, no mask 30.2 -> 28.7 (1024 blocks, as far as it
+// gains; under a mask up to 512, beyond which the tiles are taken in pairs or by head).
+template <int D, bool CAUSAL, bool ROT>
+__global__ void __launch_bounds__(kThreads, 2)
+attn_bwd_small_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
+                      float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, int m, float scale, const float* __restrict__ rot) {
+  const int tiles = (S + 127) / 128, blocks = tiles * A * m;
+  if ((int)blockIdx.x < blocks) dkv_block<D, CAUSAL, ROT, true>(qkv, O, dO, lse, nullptr, dqkv, S, H, A, scale, rot, block_coords(blockIdx.x, tiles, A, blocks), false);
+  else dq_block<D, CAUSAL, ROT>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, block_coords((int)blockIdx.x - blocks, tiles, A, blocks), false);
 }
 
 // Causal launches of the eight-wavefront kernels: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute
@@ -1339,6 +1383,18 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
             int m, int S, int H, int A, const float* rot, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)(H / A));
   const int nt = (S + 127) / 128;
+  if constexpr (D <= 64) {
+    const int64_t blocks = 2 * (int64_t)nt * A * m;
+    if (S <= 2048 && blocks <= (CAUSAL ? 512 : 1024)) {
+      const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * (size_t)((S + TILE - 1) / TILE * TILE) * sizeof(float);
+      constexpr auto kern = attn_bwd_small_kernel<D, CAUSAL, ROT>;
+      int rc = reserve_lds<kern>("attention", 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * 2048 * sizeof(float));
+      if (rc != CEPHALO_OK) return rc;
+      kern<<<(int)blocks, kThreads, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, m, scale, rot);
+      CEPHALO_CHECK_LAUNCH("attn_bwd_mfma");
+      return CEPHALO_OK;
+    }
+  }
   TileOrder order;
   const dim3 grid = tile_order(CAUSAL, D <= 64, nt, A, m, &order);
   {

@@ -113,3 +113,36 @@ def test_causal_samples_do_not_depend_on_the_launch(m, S, A, d):
         rows = slice(n * S, (n + 1) * S)
         o1, l1, g1 = run(qkv[rows].contiguous(), dO[rows].contiguous(), 1)
         assert torch.equal(o1, O[rows]) and torch.equal(l1[0], lse[n]) and torch.equal(g1, dqkv[rows]), n
+
+
+@pytest.mark.parametrize("S,A,d,causal", [
+    (40, 8, 64, True),          # under one tile
+    (64, 6, 32, False),
+    (197, 12, 64, False),
+    (333, 10, 64, True),
+    (640, 5, 24, True),
+    (2048, 2, 64, False),       # the longest sample whose statistics the one launch holds
+    (2048, 1, 32, True),
+    (2049, 2, 64, False),       # beyond it: always two launches
+])
+def test_backward_in_one_launch_or_two(S, A, d, causal):
+    """Up to 512 blocks under a mask, 1024 without, the backward of narrow heads is one launch; a sample's results are the same bits on both sides."""
+    print("attention backward launches", S, A, d, causal, flush=True)
+    H, limit, each = A * d, 512 if causal else 1024, 2 * A * ((S + 127) // 128)
+    below = max(1, limit // each)                                        # samples of the last launch in one, the first in two
+    m = below + 1
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    qkv = torch.randn(m * S, 3 * H, device="cuda", generator=g).to(torch.bfloat16)
+    dO = torch.randn(m * S, H, device="cuda", generator=g).to(torch.bfloat16)
+    desc = C.layer_desc(H, A, 4 * H, S, causal, C.BF16)
+    O, lse = torch.empty_like(dO), torch.empty(m, A, S, device="cuda")
+    C.cephalo_op_attention_fwd(desc, qkv, O, lse, m)
+
+    def backward(n):
+        dqkv, dvec = torch.full((n * S, 3 * H), float("nan"), dtype=torch.bfloat16, device="cuda"), torch.empty(n, A, S, device="cuda")
+        C.cephalo_op_attention_bwd(desc, qkv[:n * S], O[:n * S], dO[:n * S], lse[:n], dvec, dqkv, n)
+        return dqkv
+
+    many, most, one = backward(m), backward(below), backward(1)
+    assert not torch.isnan(many).any()
+    assert torch.equal(most, many[:below * S]) and torch.equal(one, many[:S])
