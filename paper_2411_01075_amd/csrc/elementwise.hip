@@ -351,14 +351,13 @@ reduce_jobs_kernel(ReduceBatch b, float scale, int accumulate) {
 // the former kernel: 8192 x 10240 fp32 57.3 (55.8) and, for its reduction in one stage, 100000 x 256 fp32 25.8 (25.1).
 constexpr int kColsumRowsPerChunk = 64;
 template <typename T, bool LOWP, int ROWS>
-__global__ void __launch_bounds__(kThreads)
-colsum_kernel(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restrict__ partials, int rows, int N, int runs) {
+__device__ __forceinline__ void colsum_block(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restrict__ partials, int rows, int N, int runs, int block, int total) {
   constexpr int VN = Vec<T>::N;
   typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
   __shared__ float red[kWaves][64][VN + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col_blocks = (N / VN + 63) / 64, total = gridDim.x, xcd = blockIdx.x & 7;
-  const int at = runs ? xcd * (total >> 3) + min(xcd, total & 7) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int col_blocks = (N / VN + 63) / 64, xcd = block & 7;
+  const int at = runs ? xcd * (total >> 3) + min(xcd, total & 7) + (block >> 3) : block;
   const int chunk = at / col_blocks, col = (at % col_blocks * 64 + lane) * VN;
   const int r0 = chunk * ROWS + wave;
   const bool in = col < N;
@@ -395,21 +394,26 @@ colsum_kernel(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restri
   }
 }
 
+template <typename T, bool LOWP, int ROWS>
+__global__ void __launch_bounds__(kThreads)
+colsum_kernel(const T* __restrict__ dY, bf16* __restrict__ lowp, float* __restrict__ partials, int rows, int N, int runs) {
+  colsum_block<T, LOWP, ROWS>(dY, lowp, partials, rows, N, runs, blockIdx.x, gridDim.x);
+}
+
 // 64x64 tiles transposed through LDS: 16-byte global reads along the input rows, 16-byte global
 // writes along the output rows; the LDS tile is padded so that the column walk is conflict-free.
 // out has row pitch `pitch` >= rows; its columns [rows, pitch) are written with zeros.
 // Up to kMaxTransposes matrices in one launch (a layer's four weights: 4.6 us each at width 1024, most of it the launch).
 struct TransposeBatch { int n; int first[kMaxTransposes + 1]; TransposeJob job[kMaxTransposes]; };
-__global__ void __launch_bounds__(kThreads)
-transpose_bf16_kernel(TransposeBatch b) {
+__device__ __forceinline__ void transpose_block(const TransposeBatch& b, int block) {
   __shared__ bf16 tile[64][64 + 2];
   typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
   int q = 0;
-  while (q + 1 < b.n && (int)blockIdx.x >= b.first[q + 1]) ++q;
+  while (q + 1 < b.n && block >= b.first[q + 1]) ++q;
   const bf16* __restrict__ in = b.job[q].in;
   bf16* __restrict__ out = b.job[q].out;
   const int rows = b.job[q].rows, cols = b.job[q].cols, pitch = b.job[q].pitch;
-  const int tile_cols = (cols + 63) / 64, at = (int)blockIdx.x - b.first[q];
+  const int tile_cols = (cols + 63) / 64, at = block - b.first[q];
   const int r0 = at / tile_cols * 64, c0 = at % tile_cols * 64;
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
@@ -432,6 +436,17 @@ transpose_bf16_kernel(TransposeBatch b) {
       *reinterpret_cast<bf16x8*>(out + (int64_t)(c0 + c) * pitch + r0 + r) = val;
     }
   }
+}
+
+__global__ void __launch_bounds__(kThreads) transpose_bf16_kernel(TransposeBatch b) { transpose_block(b, blockIdx.x); }
+
+// What a layer's backward needs before its first product: the transposed weights and, of a gradient that the caller hands over, its copy and column
+// sums.  Neither reads the other, and for small layers a launch costs more than its work (a layer of width 256 on 256 tokens: 92.4 us with two launches,
+// 90.1 with one; from width 1024 on no difference).
+constexpr int kCastColsumRows = 32;
+__global__ void __launch_bounds__(kThreads) prepare_backward_kernel(TransposeBatch b, CastColsum c, int sums) {
+  if ((int)blockIdx.x < sums) colsum_block<float, true, kCastColsumRows>(c.x, c.lowp, c.partials, c.rows, c.N, 0, blockIdx.x, sums);
+  else transpose_block(b, (int)blockIdx.x - sums);
 }
 
 template <typename T> int maxv_for(int H) {
@@ -528,17 +543,9 @@ int launch_colsum(const T* dY, float* partials, size_t partial_bytes, float* g, 
 }
 
 // (half the rows per block of the plain column sum: the launch has only N / 256 blocks per chunk)
-constexpr int kCastColsumRows = 32;
 int cast_colsum_chunks(int rows) { return (rows + kCastColsumRows - 1) / kCastColsumRows; }
-int launch_cast_colsum(const float* x, bf16* lowp, float* partials, size_t partial_bytes, int rows, int N, hipStream_t s) {
-  const int nchunks = cast_colsum_chunks(rows);
-  if (partial_bytes < (size_t)nchunks * N * sizeof(float)) return fail(CEPHALO_EWORKSPACE, "cast_colsum: partial buffer too small");
-  colsum_kernel<float, true, kCastColsumRows><<<(unsigned)((int64_t)nchunks * ((N / 4 + 63) / 64)), kThreads, 0, s>>>(x, lowp, partials, rows, N, 0);
-  CEPHALO_CHECK_LAUNCH("cast_colsum");
-  return CEPHALO_OK;
-}
 
-int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s) {
+int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s, const CastColsum* beside) {
   if (n <= 0 || n > kMaxTransposes) return fail(CEPHALO_EINVAL, "transpose: %d matrices in one launch", n);
   TransposeBatch b = {};
   b.n = n;
@@ -548,6 +555,14 @@ int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s) {
     if (t.pitch % 8 != 0 || t.pitch < t.rows || t.cols % 8 != 0)
       return fail(CEPHALO_EINVAL, "transpose: %d x %d into pitch %d: columns and pitch must be multiples of 8", t.rows, t.cols, t.pitch);
     b.first[i + 1] = b.first[i] + ((t.cols + 63) / 64) * ((t.pitch + 63) / 64);
+  }
+  if (beside) {
+    const int chunks = cast_colsum_chunks(beside->rows);
+    if (beside->partial_bytes < (size_t)chunks * beside->N * sizeof(float)) return fail(CEPHALO_EWORKSPACE, "cast_colsum: partial buffer too small");
+    const int sums = chunks * ((beside->N / 4 + 63) / 64);
+    prepare_backward_kernel<<<(unsigned)(sums + b.first[n]), kThreads, 0, s>>>(b, *beside, sums);
+    CEPHALO_CHECK_LAUNCH("prepare_backward");
+    return CEPHALO_OK;
   }
   transpose_bf16_kernel<<<b.first[n], kThreads, 0, s>>>(b);
   CEPHALO_CHECK_LAUNCH("transpose");

@@ -231,7 +231,7 @@ int launch_colsum(const T* dY, float* partials, size_t partial_bytes, float* g, 
                   int accumulate, int rows, int N, hipStream_t s);
 size_t colsum_partial_bytes(int rows, int N);
 // lowp = bf16(x) for x [rows, N] fp32 and, on the way, the column sums of x in cast_colsum_chunks(rows) partial rows
-int launch_cast_colsum(const float* x, bf16* lowp, float* partials, size_t partial_bytes, int rows, int N, hipStream_t s);
+struct CastColsum { const float* x; bf16* lowp; float* partials; size_t partial_bytes; int rows, N; };
 int cast_colsum_chunks(int rows);
 
 // dst[i] = bf16(src[i]), i in [0, n)
@@ -241,7 +241,7 @@ int launch_cast_bf16(bf16* dst, const float* src, int64_t n, hipStream_t s);
 // columns [rows, pitch) are zero-filled; cols and the pitch are multiples of 8
 struct TransposeJob { const bf16* in; bf16* out; int rows, cols, pitch; };
 constexpr int kMaxTransposes = 4;
-int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s);      // several such matrices in one launch
+int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s, const CastColsum* beside = nullptr);      // several such matrices, and a copy with sums, in one launch
 
 // ---------------------------------------------------------------------------------------
 // Attention on the packed projection qkv [m*S, 3H] (Q | K | V column blocks, head a in

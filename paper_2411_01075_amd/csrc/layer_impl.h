@@ -464,21 +464,7 @@ template <> inline const float* lowp_of<float>(const float* f, const float*) { r
 template <> inline const bf16* lowp_of<bf16>(const float*, const bf16* l) { return l; }
 template <typename T> T* lowp_out(T* l) { return std::is_same<T, float>::value ? nullptr : l; }   // nothing extra to write in fp32 mode
 
-// The caller's dy [tokens, H], handed over in fp32: its copy in T (when T is not float) and, for a layer with biases, partial rows of
-// its column sums, in `sums` for the parameter pass.
 struct DySums { const float* part; int chunks; };
-template <typename T> int take_dy(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<T>& w, DySums* sums, hipStream_t s);
-template <> inline int take_dy<float>(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<float>&, DySums* sums, hipStream_t) {
-  *sums = {is_llama(d) ? nullptr : dy, is_llama(d) ? 0 : tokens};          // (a row is a partial sum of one token)
-  return CEPHALO_OK;
-}
-template <> inline int take_dy<bf16>(const cephalo_layer_desc& d, const float* dy, int tokens, const Work<bf16>& w, DySums* sums, hipStream_t s) {
-  *sums = {nullptr, 0};
-  if (is_llama(d)) return launch_cast_bf16(w.dyl, dy, (int64_t)tokens * d.hidden, s);
-  TRY(launch_cast_colsum(dy, w.dyl, w.col_part, w.col_part_bytes, tokens, d.hidden, s));
-  *sums = {w.col_part, cast_colsum_chunks(tokens)};
-  return CEPHALO_OK;
-}
 
 // Input-gradient contraction dX = dY W of the linear layer whose weight sits at flat offset `off`.  In bf16 mode it
 // reads the transposed copy made by prepare_dgrad_weights (so both MFMA operands come from 16-byte LDS reads, the
@@ -491,14 +477,26 @@ template <> inline GemmArgs<bf16> dgrad_args<bf16>(const bf16* dY, const bf16*, 
   return linear_dgrad_wt<bf16>(dY, wT + off, Tn, N, K);
 }
 // Once per layer and step (the weights do not change between micro-batches): W^T of the four projections.
-template <typename T> int prepare_dgrad_weights(const cephalo_layer_desc& d, const T* P, T* wT, hipStream_t s);
-template <> inline int prepare_dgrad_weights<float>(const cephalo_layer_desc&, const float*, float*, hipStream_t) { return CEPHALO_OK; }
-template <> inline int prepare_dgrad_weights<bf16>(const cephalo_layer_desc& d, const bf16* P, bf16* wT, hipStream_t s) {
+template <typename T> int prepare_dgrad_weights(const cephalo_layer_desc& d, const T* P, T* wT, hipStream_t s, const CastColsum* beside = nullptr);
+template <> inline int prepare_dgrad_weights<float>(const cephalo_layer_desc&, const float*, float*, hipStream_t, const CastColsum*) { return CEPHALO_OK; }
+template <> inline int prepare_dgrad_weights<bf16>(const cephalo_layer_desc& d, const bf16* P, bf16* wT, hipStream_t s, const CastColsum* beside) {
   const ParamOffsets o = param_offsets(d);
   const int H = d.hidden, F = d.mlp;
   const TransposeJob jobs[] = {{P + o.w_qkv, wT + o.w_qkv, 3 * H, H, 0}, {P + o.w_o, wT + o.w_o, H, H, 0},
                                {P + o.w_fc1, wT + o.w_fc1, (int)ff1_width(d), H, 0}, {P + o.w_fc2, wT + o.w_fc2, H, F, 0}};
-  return launch_transposes(jobs, 4, s);
+  return launch_transposes(jobs, 4, s, beside);
+}
+// The same for a caller who hands over dy [tokens, H], in fp32: in the same launch its copy in T (when T is not float) and, for a layer with biases,
+// partial rows of its column sums, in `sums` for the parameter pass.
+template <typename T> int prepare_backward(const cephalo_layer_desc& d, const T* P, const float* dy, int tokens, const Work<T>& w, DySums* sums, hipStream_t s);
+template <> inline int prepare_backward<float>(const cephalo_layer_desc& d, const float*, const float* dy, int tokens, const Work<float>&, DySums* sums, hipStream_t) {
+  *sums = {is_llama(d) ? nullptr : dy, is_llama(d) ? 0 : tokens};          // (a row is a partial sum of one token)
+  return CEPHALO_OK;
+}
+template <> inline int prepare_backward<bf16>(const cephalo_layer_desc& d, const bf16* P, const float* dy, int tokens, const Work<bf16>& w, DySums* sums, hipStream_t s) {
+  const CastColsum c = {dy, w.dyl, w.col_part, w.col_part_bytes, tokens, d.hidden};
+  *sums = {is_llama(d) ? nullptr : w.col_part, is_llama(d) ? 0 : cast_colsum_chunks(tokens)};
+  return prepare_dgrad_weights<bf16>(d, P, w.wT, s, &c);
 }
 
 // ---- backward, data path of one run of `samples` samples in micro-batches of m: dx and the dY operands (dz, dx1, dqkv) of the weight gradients ----
@@ -567,7 +565,7 @@ int layer_bwd_data_t(const cephalo_layer_desc& d, const T* P, const float* x, co
 // happens inside the fp32 MFMA accumulators and each gradient element is written exactly once.  Bias gradients of the
 // two residual-stream projections are column sums of the fp32 gradients of the stream: of dx1 (out-projection), which
 // the backward of the second LayerNorm has summed block by block as it wrote it, and of dy (second feed-forward
-// projection), whose partial rows take_dy has left in dy_sums.  A caller whose dy was the dx of the layer above (a stack)
+// projection), whose partial rows prepare_backward has left in dy_sums.  A caller whose dy was the dx of the layer above (a stack)
 // passes none and gives that layer `b_fc2_below` instead: where the sums of its dx go, with the same scale / acc.
 //
 // The sums of partial rows are collected and added in one launch: with a second stream the norms' ones at once, beside
@@ -718,9 +716,8 @@ int run_bwd(const cephalo_layer_desc& d, const void* P, const float* x, const fl
   const Saved<T> sv = saved_at<T>(save, L, d, 0);
   const Work<T> w = work_at<T>(scratch, W, d, 0, 0, m, at<char>(scratch, W.pool), m);
   DySums dy_sums;
-  TRY(take_dy<T>(d, dy, m * d.seq, w, &dy_sums, s));
+  TRY(prepare_backward<T>(d, static_cast<const T*>(P), dy, m * d.seq, w, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w.dyl);
-  TRY(prepare_dgrad_weights<T>(d, static_cast<const T*>(P), w.wT, s));
   TRY(layer_bwd_data_t<T>(d, static_cast<const T*>(P), x, dy, dyl, dx, (T*)nullptr, m, m, sv, w, s));
   return layer_bwd_params_t<T>(d, dy_sums, dyl, m * d.seq, ln_bwd_blocks(m * d.seq), sv, w, G, scale, acc, s);
 }
@@ -781,9 +778,8 @@ int run_share(const cephalo_layer_desc& d, const void* Pv, const float* x, float
   struct JCloser { Streams& j; bool done = false; ~JCloser() { if (!done) (void)j.close(); } } jcloser{J};   // early exits still join
   const Work<T> w0 = work_at<T>(scratch, W, d, 0, 0, m, pool.base, m);
   DySums dy_sums;
-  TRY(take_dy<T>(d, dy, b * d.seq, w0, &dy_sums, s));
+  TRY(prepare_backward<T>(d, P, dy, b * d.seq, w0, &dy_sums, s));
   const T* dyl = lowp_of<T>(dy, w0.dyl);
-  TRY(prepare_dgrad_weights<T>(d, P, w0.wT, s));
   TRY(make_rotary<T>(d, saved_at<T>(save, L, d, 0), s));
   J.fork();
   {

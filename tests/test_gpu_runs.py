@@ -83,3 +83,14 @@ def test_stack_forms_agree_bit_for_bit(kind, S, m, l, V):
         assert torch.equal(loss, got[0][0]) and torch.equal(G, got[0][1])
     # one micro-batch instead of l: the norms' partial sums differ where a micro-batch is no multiple of 8 rows, in the order of fp32 additions
     assert torch.equal(got[4][0], got[0][0]) and float((got[4][1] - got[0][1]).norm() / got[0][1].norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("S,m,l,hidden", [(1, 1, 1, 64), (31, 1, 1, 72), (33, 1, 2, 264), (64, 2, 3, 512)])      # (rows around the 32 of a chunk, columns around the 256 of a block)
+def test_bias_gradient_is_the_column_sum_of_dy(S, m, l, hidden):
+    """The launch that transposes the weights also copies dy and sums its columns."""
+    print(S, m, l, hidden, flush=True)
+    desc = C.layer_desc(hidden, hidden // 8, 4 * hidden, S, True, C.BF16, 1e-5, C.LAYER_GPT)
+    _, _, dy, _, _, G = _share(desc, m * l, m)
+    rows, got = dy.reshape(-1, hidden).double(), G[-hidden:].double()        # (the last tensor: the second feed-forward projection's bias)
+    bound = rows.shape[0] * 2.0 ** -24 * rows.abs().sum(0) * 0.5             # one rounding of at most the sum of magnitudes per addition
+    assert bool(((got - 0.5 * rows.sum(0)).abs() <= bound).all())
