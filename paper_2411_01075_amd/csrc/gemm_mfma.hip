@@ -4,8 +4,8 @@
 //   forward          Y  = X W^T        both k-contiguous
 //   input gradient   dX = dY (W^T)^T   both k-contiguous (the layer keeps a transposed copy of its weights)
 //   weight gradient  dW = dY^T X       tokens are k: both row-contiguous, read as they lie
-// Two main loops share the staging, the matrix instruction and the epilogues: gemm_mfma_tile for the large tiles (256 x 256 and
-// 256 x 192: as many products per byte as the accumulators allow) and gemm_ring_tile for the small ones, down to 64 x 64, where the
+// Two main loops share the staging, the matrix instruction and the epilogues: gemm_mfma_tile for the large tiles (256 x 256, 256 x 192
+// and 256 x 160: as many products per byte as the accumulators allow) and gemm_ring_tile for the small ones, down to 64 x 64, where the
 // output has few tiles.  Tile and number of pieces are chosen per launch by estimated time (kTiles, kGradTiles below).
 //
 // Matrix instruction: v_mfma_f32_16x16x32_bf16.  On this chip a stream of 16x16x32 products sustains an eighth
@@ -69,16 +69,20 @@ __device__ __forceinline__ unsigned operand_bytes(int rows, int64_t rs, int64_t 
   return (unsigned)(2 * (KFAST ? (int64_t)rows * rs : (int64_t)(K - 1) * cs + (rows + 7) / 8 * 8));
 }
 
-// One operand's tile: ROWS matrix rows (m or n) by BK k-values, ROWS*BK*2 bytes of LDS, unpadded.
+// Rows that a tile of `rows` takes in LDS: NW wavefronts load 1 KiB (8 rows of a slab) each at a time.
+constexpr int lds_rows(int rows, int nw) { return (rows + 8 * nw - 1) / (8 * nw) * (8 * nw); }
+
+// One operand's tile: ROWS matrix rows (m or n) by BK k-values, ROWS*BK*2 bytes of LDS, unpadded.  Where the wavefronts cannot share ROWS evenly
+// (160 among 8), the tile's place in LDS is as long as their loads, and those past ROWS read nothing.
 template <int ROWS, bool KFAST, int NW>
 struct OperandTile {
-  static constexpr int BYTES = ROWS * BK * 2;
+  static constexpr int BYTES = lds_rows(ROWS, NW) * BK * 2;
   static constexpr int INSTR = BYTES / 1024;            // direct-to-LDS load instructions per tile (1 KiB each)
   static constexpr int PER_WAVE = INSTR / NW;           // NW wavefronts share the loads
   static constexpr int PITCH = KFAST ? BK * 2 : ROWS * 2;   // bytes per LDS row
   static constexpr int CHUNKS = PITCH / 16;                 // 16-byte chunks per LDS row
   static_assert(INSTR % NW == 0, "tile must split evenly over the wavefronts");
-  static_assert(KFAST || ROWS >= 128, "row-contiguous tiles need at least 128 rows");
+  static_assert(KFAST || (ROWS >= 128 && BYTES == ROWS * BK * 2), "row-contiguous tiles need at least 128 rows, and whole loads");
 
   // LDS row / chunk slot that lane `lane` of load instruction `j` of this wavefront fills, and the
   // (un-swizzled) chunk of the tile that belongs there
@@ -99,7 +103,7 @@ struct OperandTile {
       slot(j, line, chunk);
       if (KFAST) {      // line = tile row, chunk = 8 k-values
         const int64_t e = (int64_t)(row0 + line) * rs + chunk * 8;
-        off[j] = (row0 + line < nrows) ? (unsigned)(e * 2) : kOob;
+        off[j] = ((BYTES == ROWS * PITCH || line < ROWS) && row0 + line < nrows) ? (unsigned)(e * 2) : kOob;
       } else {          // line = k, chunk = 8 rows
         const int64_t e = (int64_t)line * cs + row0 + chunk * 8;
         off[j] = (row0 + chunk * 8 < nrows) ? (unsigned)(e * 2) : kOob;
@@ -941,9 +945,10 @@ int launch_cfg(const GemmArgs<bf16>& a, hipStream_t s) {
   // The L2 prefetch pays where both operands are read token-major (the weight gradients: +3..5 % on c5's shapes); the
   // k-contiguous kernels lose 1..6 % with it, so they run without.
   constexpr int PF = (!AK && !BKF) ? 2 : 0;
-  // a third buffer for A where it fits beside two whole stages (the 256 x 256 and 256 x 192 tiles)
-  constexpr bool A3 = NS == 2 && PF == 0 && (size_t)(3 * BM + 2 * BN) * BK * 2 <= 160 * 1024;
-  constexpr size_t stages = A3 ? (size_t)(3 * BM + 2 * BN) * BK * 2 : (size_t)NS * (BM + BN) * BK * 2 + (PF > 0 ? 256 : 0);    // + the prefetches' scratch line
+  // a third buffer for A where it fits beside two whole stages (the tiles of 256 x 256 to 256 x 160)
+  constexpr int RN = lds_rows(BN, WGM * WGN);
+  constexpr bool A3 = NS == 2 && PF == 0 && (size_t)(3 * BM + 2 * RN) * BK * 2 <= 160 * 1024;
+  constexpr size_t stages = A3 ? (size_t)(3 * BM + 2 * RN) * BK * 2 : (size_t)NS * (BM + RN) * BK * 2 + (PF > 0 ? 256 : 0);    // + the prefetches' scratch line
   constexpr size_t staging = (size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4;
   static_assert(stages <= 160 * 1024, "the stages must fit in LDS");
   const size_t lds = std::max<size_t>(stages, EPI == EPI_GRAD ? 0 : staging);
@@ -967,9 +972,11 @@ thread_local int side_by_side = 1;     // kernels the caller runs at once (GemmS
 // Examples (us, former choice -> this one): 1024 x 1024 x 4096 48.0 (128 x 128, four wavefronts) -> 19.3 (64 x 64); 2048 x 1600 x 6400
 // 73.6 (the same) -> 44.0 (128 x 128); 2048 x 2560 x 10240 134.5 (256 x 128) -> 114.1 (128 x 192); two at a time 4096 x 2048 x 8192 195
 // (256 x 256) as before.  The products do not depend on the choice: every tile adds those of an output in the same order.
+// The tile of 256 x 160 is there for widths such as 1600 = 10 x 160 and for what its number of blocks fits better: 6144 x 1600 x 6400 103.8 us
+// (256 x 192) -> 95.6, 2048 x 10240 x 2560 99 -> 90, 2056 x 8192 x 1664 59.9 -> 56.1; of 39 measured shapes its estimate loses 0.03 % against the fastest tile.
 struct TileCost { int bm, bn, blocks; double alone, one, more, fixed; };
 constexpr TileCost kTiles[] = {
-  {256, 256, 1, 0.56, 1.09, 1.16, 6.7}, {256, 192, 1, 0.46, 0.83, 0.85, 8.3}, {256, 128, 1, 0.39, 0.68, 0.80, 5.3}, {128, 192, 1, 0.42, 0.53, 0.62, 6.0},
+  {256, 256, 1, 0.56, 1.09, 1.16, 6.7}, {256, 192, 1, 0.46, 0.83, 0.85, 8.3}, {256, 160, 1, 0.42, 0.70, 0.73, 8.0}, {256, 128, 1, 0.39, 0.68, 0.80, 5.3}, {128, 192, 1, 0.42, 0.53, 0.62, 6.0},
   {128, 128, 1, 0.38, 0.41, 0.47, 4.1}, {128, 64, 2, 0.36, 0.32, 0.31, 4.3},  {64, 64, 2, 0.30, 0.21, 0.195, 3.3},
 };
 // splits: pieces the contraction is cut into, one block each
@@ -1008,10 +1015,11 @@ int launch_rows(const GemmArgs<bf16>& a, hipStream_t s) {
   switch (best_tile(a.M, a.N, a.K, side_by_side, &us)) {
     case 0: return launch_cfg<256, 256, 4, 2, true, true, EPI>(a, s);
     case 1: return launch_cfg<256, 192, 4, 2, true, true, EPI>(a, s);
-    case 2: return launch_ring<256, 128, 4, 2, EPI, 3>(a, s);
-    case 3: return launch_ring<128, 192, 2, 4, EPI, 3>(a, s);
-    case 4: return launch_ring<128, 128, 4, 2, EPI, 4>(a, s);
-    case 5: return launch_ring<128, 64, 4, 2, EPI, 3>(a, s);
+    case 2: return launch_cfg<256, 160, 4, 2, true, true, EPI>(a, s);
+    case 3: return launch_ring<256, 128, 4, 2, EPI, 3>(a, s);
+    case 4: return launch_ring<128, 192, 2, 4, EPI, 3>(a, s);
+    case 5: return launch_ring<128, 128, 4, 2, EPI, 4>(a, s);
+    case 6: return launch_ring<128, 64, 4, 2, EPI, 3>(a, s);
     default: return launch_ring<64, 64, 2, 2, EPI, 5>(a, s);
   }
 }

@@ -80,6 +80,13 @@ def test_gemm_tiles_give_the_same_bits(M, N, K):
     assert (np.abs(first["resid"].double().cpu().numpy() - ref) <= bound + 3 * 2.0 ** -24 * (np.abs(acc) + np.abs(ref) + 4)).all()
 
 
+# with 40 to 256 kernels side by side these take the tile of 256 x 160, whose place in LDS is 192 rows long: one column block whole and one ragged,
+# two, five; one row block, one and a row, three
+@pytest.mark.parametrize("M,N,K", [(256, 160, 264), (257, 304, 520), (700, 312, 264), (500, 808, 520)])
+def test_gemm_tile_of_160_columns(M, N, K):
+    test_gemm_tiles_give_the_same_bits(M, N, K)
+
+
 @pytest.mark.parametrize("rows", [1, 7, 64, 65, 200, 4099])
 @pytest.mark.parametrize("N", [8, 72, 264, 1032])
 @pytest.mark.parametrize("bf16", [False, True])
