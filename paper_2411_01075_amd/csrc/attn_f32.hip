@@ -206,15 +206,26 @@ attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ O, float*
   }
 }
 
+// o[r] . do[r] of row r = r0 + l % 16, in every lane of the column; dof: those rows of dO
+template <int P, bool VEC>
+__device__ __forceinline__ float row_dot(const float* __restrict__ O, int64_t ld, int r0, int rows, int d, const f32x4 (&dof)[P]) {
+  f32x4 of[P];
+  load_rows<P, VEC>(O, ld, r0, rows, d, of);
+  float v = 0.f;
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v = fmaf(of[i][e], dof[i][e], v);
+  return groups_sum(v);
+}
+
 // dQ[s] = scale * sum_t dZ[s,t] K[t],  dZ = P (dP - dvec[s]),  dP[s,t] = dO[s] . V[t];  dvec[s] = dO[s] . O[s] on the way
 template <int P, bool VEC>
-__global__ void __launch_bounds__(64 * kWaves)
-attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ lse,
-                   float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal) {
-  __shared__ f32x4 red[(kWaves - 1) * P * 64];
+__device__ __forceinline__ void dq_block(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ lse,
+                                         float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal, int block, f32x4* red) {
   const int a = blockIdx.y, n = blockIdx.z, d = H / A;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4;
-  const int q0 = blockIdx.x * 16, q = q0 + (lane & 15);
+  const int q0 = block * 16, q = q0 + (lane & 15);
   const float scale = 1.0f / sqrtf((float)d);
   const int64_t ld = 3 * (int64_t)H, stat = ((int64_t)n * A + a) * S;
   const float* base = qkv + (int64_t)n * S * ld + a * d;
@@ -222,16 +233,7 @@ attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ O, c
   f32x4 qf[P], dof[P], dq[P];
   load_rows<P, VEC>(base, ld, q0, S, d, qf);
   load_rows<P, VEC>(dO + orow, H, q0, S, d, dof);
-  float dv = 0.f;
-  {
-    f32x4 of[P];
-    load_rows<P, VEC>(O + orow, H, q0, S, d, of);
-#pragma unroll
-    for (int i = 0; i < P; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dv += of[i][e] * dof[i][e];
-    dv = groups_sum(dv);
-  }
+  const float dv = row_dot<P, VEC>(O + orow, H, q0, S, d, dof);
   if (wave == 0 && g == 0 && q < S) dvec[stat + q] = dv;
   const float l = lse[stat + min(q, S - 1)];
 #pragma unroll
@@ -256,15 +258,13 @@ attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ O, c
   if (wave == 0) store_columns<P>(dqkv + (int64_t)n * S * ld + a * d, ld, q, S, d, dq, scale);
 }
 
-// dV[t] = sum_s P[s,t] dO[s],  dK[t] = scale * sum_s dZ[s,t] Q[s]
-template <int P, bool VEC>
-__global__ void __launch_bounds__(64 * kWaves)
-attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ dO, const float* __restrict__ lse,
-                    const float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal) {
-  __shared__ f32x4 red[(kWaves - 1) * P * 64];
+// dV[t] = sum_s P[s,t] dO[s],  dK[t] = scale * sum_s dZ[s,t] Q[s].  OWN: forms dvec of the queries it meets itself, as the dQ blocks do.
+template <int P, bool VEC, bool OWN>
+__device__ __forceinline__ void dkv_block(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ lse,
+                                          const float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal, int block, f32x4* red) {
   const int a = blockIdx.y, n = blockIdx.z, d = H / A;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4;
-  const int t0 = blockIdx.x * 16, t = t0 + (lane & 15);
+  const int t0 = block * 16, t = t0 + (lane & 15);
   const float scale = 1.0f / sqrtf((float)d);
   const int64_t ld = 3 * (int64_t)H, stat = ((int64_t)n * A + a) * S;
   const float* base = qkv + (int64_t)n * S * ld + a * d;
@@ -285,7 +285,12 @@ attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ dO,
     for (int i = 0; i < 4; ++i) {
       const int q = min(q0 + 4 * g + i, S - 1);
       l[i] = lse[stat + q];
-      dv[i] = dvec[stat + q];
+      if (!OWN) dv[i] = dvec[stat + q];
+    }
+    if (OWN) {
+      const float own = row_dot<P, VEC>(O + (int64_t)n * S * H + a * d, H, q0, S, d, dof);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dv[i] = __shfl(own, 4 * g + i, 64);
     }
     const f32x4 s = dot_rows<P>(qf, kf), dp = dot_rows<P>(dof, vf);      // rows: queries q0 + 4 g + i, column: key t
     f32x4 p, dz;
@@ -309,6 +314,33 @@ attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ dO,
   if (wave == 0) store_columns<P>(out + 2 * H, ld, t, S, d, dvv, 1.0f);
   merge_sums<P>(dk, red);
   if (wave == 0) store_columns<P>(out + H, ld, t, S, d, dk, scale);
+}
+
+template <int P, bool VEC>
+__global__ void __launch_bounds__(64 * kWaves)
+attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ lse,
+                   float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal) {
+  __shared__ f32x4 red[(kWaves - 1) * P * 64];
+  dq_block<P, VEC>(qkv, O, dO, lse, dvec, dqkv, S, H, A, causal, blockIdx.x, red);
+}
+template <int P, bool VEC>
+__global__ void __launch_bounds__(64 * kWaves)
+attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ dO, const float* __restrict__ lse,
+                    const float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal) {
+  __shared__ f32x4 red[(kWaves - 1) * P * 64];
+  dkv_block<P, VEC, false>(qkv, nullptr, dO, lse, dvec, dqkv, S, H, A, causal, blockIdx.x, red);
+}
+// Both in one launch where they fit on the chip side by side: up to 512 blocks (256 for heads wider than 64, whose blocks have a compute unit each); the
+// results are the same bits either way.  Two launches -> one, us: 2 x 128 tokens, 4 heads of 64 24.4 -> 14.3; 4 x 128, 8 heads, no mask (512 blocks) 26.6 -> 21.2;
+// 2 x 512, 4 heads (512) 72.4 -> 57.1.  Beyond: 1024 blocks 178 -> 181, 2048 65.5 -> 75.6; heads of 128, 1024 blocks 259 -> 295.
+template <int P, bool VEC>
+__global__ void __launch_bounds__(64 * kWaves)
+attn_f32_bwd_kernel(const float* __restrict__ qkv, const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ lse,
+                    float* __restrict__ dvec, float* __restrict__ dqkv, int S, int H, int A, int causal) {
+  __shared__ f32x4 red[(kWaves - 1) * P * 64];
+  const int tiles = (S + 15) / 16, b = blockIdx.x;
+  if (b < tiles) dkv_block<P, VEC, true>(qkv, O, dO, lse, nullptr, dqkv, S, H, A, causal, b, red);
+  else dq_block<P, VEC>(qkv, O, dO, lse, dvec, dqkv, S, H, A, causal, causal ? 2 * tiles - 1 - b : b - tiles, red);      // (the longest first)
 }
 
 int check_f32(int S, int H, int A) {
@@ -340,6 +372,14 @@ int launch_attn_bwd_f32(const float* qkv, const float* O, const float* dO, const
   if (const int rc = check_f32(S, H, A); rc != CEPHALO_OK) return rc;
   const bool vec = (H / A) % 4 == 0 && aligned16(qkv) && aligned16(O) && aligned16(dO);
   dim3 grid((S + 15) / 16, A, m);
+  if (2 * (int64_t)grid.x * A * m <= (H / A <= 64 ? 512 : 256)) {
+    grid.x *= 2;
+#define CALL(P, V) attn_f32_bwd_kernel<P, V><<<grid, 64 * kWaves, 0, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, causal);
+    ATTN_F32_FORMS(CALL)
+#undef CALL
+    CEPHALO_CHECK_LAUNCH("attn_bwd");
+    return CEPHALO_OK;
+  }
 #define CALL(P, V)                                                                                                \
   attn_f32_dq_kernel<P, V><<<grid, 64 * kWaves, 0, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, causal);            \
   attn_f32_dkv_kernel<P, V><<<grid, 64 * kWaves, 0, s>>>(qkv, dO, lse, dvec, dqkv, S, H, A, causal);

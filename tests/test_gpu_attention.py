@@ -146,3 +146,27 @@ def test_backward_in_one_launch_or_two(S, A, d, causal):
     many, most, one = backward(m), backward(below), backward(1)
     assert not torch.isnan(many).any()
     assert torch.equal(most, many[:below * S]) and torch.equal(one, many[:S])
+
+
+@pytest.mark.parametrize("S,A,d,causal", [(1, 4, 64, True), (37, 3, 24, True), (130, 4, 64, False), (200, 2, 30, True), (260, 2, 128, True), (100, 3, 100, False)])
+def test_fp32_backward_in_one_launch_or_two(S, A, d, causal):
+    """Up to 512 blocks (256 for heads wider than 64) the fp32 backward is one launch; a sample's results are the same bits on both sides."""
+    print("fp32 attention backward launches", S, A, d, causal, flush=True)
+    H, limit, each = A * d, 512 if d <= 64 else 256, 2 * A * ((S + 15) // 16)
+    below = limit // each
+    m = below + 1
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    qkv, dO = torch.randn(m * S, 3 * H, device="cuda", generator=g), torch.randn(m * S, H, device="cuda", generator=g)
+    desc = C.layer_desc(H, A, 4 * H, S, causal, C.F32)
+    O, lse = torch.empty_like(dO), torch.empty(m, A, S, device="cuda")
+    C.cephalo_op_attention_fwd(desc, qkv, O, lse, m)
+
+    def backward(n):
+        dqkv, dvec = torch.full((n * S, 3 * H), float("nan"), device="cuda"), torch.full((n, A, S), float("nan"), device="cuda")
+        C.cephalo_op_attention_bwd(desc, qkv[:n * S], O[:n * S], dO[:n * S], lse[:n], dvec, dqkv, n)
+        return dqkv, dvec
+
+    many, most, one = backward(m), backward(below), backward(1)
+    assert not any(torch.isnan(t).any() for t in many)
+    for t, (rows, n) in ((most, (below * S, below)), (one, (S, 1))):
+        assert torch.equal(t[0], many[0][:rows]) and torch.equal(t[1], many[1][:n])
