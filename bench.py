@@ -75,7 +75,7 @@ def main():
     ap.add_argument("--checkpoint", action="store_true",
                     help="stacks only: layer-boundary activation checkpointing with recomputation in the backward (one extra forward)")
     ap.add_argument("--single-stream", action="store_true",
-                    help="one micro-batch at a time on one stream (the default runs two micro-batches side by side on two streams)")
+                    help="everything on one stream (the default keeps two runs of micro-batches in flight on two streams)")
     ap.add_argument("--legs-only", action="store_true",
                     help="skip the timed steps and run only the per-kernel legs (for a profile in which each GEMM kernel's line holds "
                          "the legs' launches and nothing else); `value` is then null")
@@ -247,7 +247,7 @@ def main():
             torch.cuda.empty_cache()
         bt = torch.bfloat16
         # The GEMM kernels of the step, each launched through the C ABI with the shapes, operand layouts and epilogues
-        # the step uses.  Forward and input-gradient GEMMs run per micro-batch on T tokens (the input gradients read
+        # the step uses.  Forward and input-gradient GEMMs are timed on one micro-batch of T tokens; the step takes one or more a launch (the input gradients read
         # the per-layer transposed weights, so they are the same contraction as the forward); the weight gradient
         # runs once per linear layer over all b*S tokens (token-minor copy of one operand + GEMM + split reduction).
         L = cfg.layers
