@@ -110,12 +110,13 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
   const int stride = gridDim.x * TEAMS;
   int row = blockIdx.x * TEAMS + __builtin_amdgcn_readfirstlane((int)threadIdx.x / THREADS);
   float a[MAXG][VN];
-  // rows are read and written through descriptors of one row each: groups past its end come as zeros and are not stored, without a branch
+  // Rows are read and written through descriptors of one row each: groups past its end come as zeros and are not stored, without a branch.  The whole
+  // offset is in the vector register, the one that the descriptor's range check covers (a scalar offset is added past the check).
   auto row_of = [&](const void* base, int row, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(base) + (int64_t)row * ld * bytes), 0, ld * bytes, 0x00020000); };
   auto fetch = [&](int j, __amdgpu_buffer_rsrc_t from) {
 #pragma unroll
     for (int q = 0; q < VN / 4; ++q) {
-      const f32x4 r = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, t * (VN * 4) + 16 * q, j * (THREADS * VN * 4), 0));
+      const f32x4 r = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, t * (VN * 4) + 16 * q + j * (THREADS * VN * 4), 0, 0));
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[j][4 * q + i] = r[i];
     }
@@ -177,8 +178,8 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
       typename Vec<T>::raw v;
 #pragma unroll
       for (int i = 0; i < VN; ++i) v[i] = (T)o[i];
-      // (the whole offset in the vector register: after a store with a scalar offset the compiler lets the next instruction overwrite the
-      // data, and now and then the store then wrote the new value)
+      // (after a store with a scalar offset the compiler also lets the next instruction overwrite the data, and now and then the store then wrote
+      // the new value)
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), to, t * 16 + j * (THREADS * 16), 0, 2);
       if (next >= 0) fetch(j, from);
     }

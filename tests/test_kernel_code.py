@@ -18,3 +18,12 @@ def test_norm_backward_reads_the_statistics_through_the_scalar_unit(form):
 def test_no_register_is_spilled(kernel):
     for name, k in kernel_code.kernels(kernel).items():
         assert k[".vgpr_spill_count"] == 0, (name, k[".vgpr_spill_count"])
+
+
+def test_no_buffer_access_has_a_scalar_offset():
+    """A buffer's range check covers the offset in the vector register and the immediate one.  The kernels rely on it for rows and columns past the end."""
+    for name in kernel_code.kernels(""):
+        for i in kernel_code.instructions(name):
+            words = i.replace(",", " ").split()
+            if words[0].startswith("buffer_") and "offen" in words:
+                assert words[words.index("offen") - 1] == "0", (name, i)
