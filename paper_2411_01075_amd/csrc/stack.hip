@@ -121,8 +121,8 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
       for (int i = 0; i < 4; ++i) a[j][4 * q + i] = r[i];
     }
   };
-  constexpr float kLog2e = 1.44269504088896340736f;
-  auto exp2_ = [](float x) { return __builtin_amdgcn_exp2f(x); };
+  // (the difference first, then the factor: the product of a large logit and log2(e) would be rounded, or overflow, before its reference is taken off)
+  auto exp_ = [](float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f); };
   auto finish = [&](int row, int next) {                // next < 0: none
     const int tgt = clamp_id(targets[row], V);
     const float at_tgt = logits[(int64_t)row * ld + tgt];
@@ -137,15 +137,15 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
       float m = mx;
 #pragma unroll
       for (int i = 0; i < VN; ++i) m = fmaxf(m, a[j][i]);
-      const float ref = m == -INFINITY ? 0.f : m * kLog2e;      // (nothing but -inf so far: every exponential is 0)
-      sum *= exp2_(__builtin_fmaf(mx, kLog2e, -ref));
+      const float ref = m == -INFINITY ? 0.f : m;               // (nothing but -inf so far: every exponential is 0)
+      sum *= exp_(mx - ref);
 #pragma unroll
-      for (int i = 0; i < VN; ++i) { a[j][i] = exp2_(__builtin_fmaf(a[j][i], kLog2e, -ref)); sum += a[j][i]; }
+      for (int i = 0; i < VN; ++i) { a[j][i] = exp_(a[j][i] - ref); sum += a[j][i]; }
       mx = m;
-      top[j] = m * kLog2e;
+      top[j] = m;
     }
     float bmx = wave_max(mx);
-    sum = wave_sum(sum * exp2_((mx - (bmx == -INFINITY ? 0.f : bmx)) * kLog2e));
+    sum = wave_sum(sum * exp_(mx - (bmx == -INFINITY ? 0.f : bmx)));
     if (NW > 1) {
       float (&r)[2][NW] = red[(row / stride) & 1];      // (the slots alternate: a second barrier is not needed)
       if (lane == 0) { r[0][wave] = bmx; r[1][wave] = sum; }
@@ -155,15 +155,15 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
       for (int w = 1; w < NW; ++w) bmx = fmaxf(bmx, r[0][w]);
       sum = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) sum += r[1][w] * exp2_((r[0][w] - bmx) * kLog2e);
+      for (int w = 0; w < NW; ++w) sum += r[1][w] * exp_(r[0][w] - bmx);
     }
-    if (t == 0) loss[row] = bmx + __logf(sum) - at_tgt;
-    const float scale = coef / sum, bmx2 = bmx * kLog2e;
+    if (t == 0) loss[row] = bmx - at_tgt + __logf(sum);
+    const float scale = coef / sum;
     const __amdgpu_buffer_rsrc_t to = row_of(dlogits, row, sizeof(T)), from = row_of(logits, max(next, 0), 4);
 #pragma unroll
     for (int j = 0; j < MAXG; ++j) {
       const int c0 = (t + THREADS * j) * VN, first = (wave * 64 + THREADS * j) * VN;
-      const float f = scale * exp2_(top[j] - bmx2);
+      const float f = scale * exp_(top[j] - bmx);
       float o[VN];
 #pragma unroll
       for (int i = 0; i < VN; ++i) o[i] = a[j][i] * f;

@@ -39,3 +39,34 @@ def test_cross_entropy_rows(rows, V, ld, dtype):
     # (half a unit: 2^-9 of a bf16 value); at the target 1 is taken off, which leaves the probability's own error
     err, p = (d[:, :V].double() - want).abs(), torch.exp(z - lse[:, None]) * 0.25
     assert bool((err <= want.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -22) + p * 2.0 ** -16 + 1e-38).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,V,ld", [(9, 1031, 1088), (70, 8191, 8192), (70, 16380, 16384), (261, 50257, 50304), (3, 65537, 65600)])
+@pytest.mark.parametrize("offset", [3000.0, -3000.0])
+def test_cross_entropy_of_large_logits_and_masks(rows, V, ld, dtype, offset):
+    """The result depends on differences of logits only, however large they are; a mask may be the type's lowest value."""
+    print("cross entropy", rows, V, ld, dtype, offset, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    x = torch.randn(rows, ld, device="cuda", generator=g) * 3 + offset
+    lowest = torch.finfo(torch.float32).min
+    x[0, : V // 2] = lowest                                       # half of a row, its first groups wholly; every other column; every column but one
+    x[1, ::2] = lowest
+    x[2, : V - 1] = lowest
+    tgt = torch.randint(V // 2, V, (rows,), device="cuda", generator=g, dtype=torch.int32)
+    tgt[1], tgt[2] = V // 2 * 2 - 1, V - 1
+    d = torch.full((rows, ld), float("nan"), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    loss = torch.full((rows,), float("nan"), device="cuda")
+    C.cephalo_op_cross_entropy(C.BF16 if dtype == "bf16" else C.F32, x, ld, tgt, d, loss, rows, V, 0.25)
+    z = x[:, :V].double()
+    z = z - z.max(-1, keepdim=True).values
+    lse = torch.logsumexp(z, -1)
+    at = torch.arange(rows, device="cuda")
+    # the two-pass form of the widest rows rounds the whole logsumexp: half a unit of 4096
+    assert float((loss.double() - (lse - z[at, tgt.long()])).abs().max()) <= (1e-5 if ld <= 65536 else 2.0 ** -12)
+    want = torch.exp(z - lse[:, None]) * 0.25
+    p = want.clone()
+    want[at, tgt.long()] -= 0.25
+    # as above; and the two-pass form's rounded logsumexp in every exponent
+    err, own = (d[:, :V].double() - want).abs(), 2.0 ** -16 if ld <= 65536 else 2.0 ** -12
+    assert bool((err <= want.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -22) + p * own + 1e-38).all())
