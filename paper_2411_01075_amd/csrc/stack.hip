@@ -96,7 +96,7 @@ cross_entropy_kernel(const float* __restrict__ logits, T* __restrict__ dlogits, 
 // seen so far (kept per group: the factor that turns them into probabilities follows when the row's maximum and sum are known, which is the only
 // time the block waits for itself), and as a group of the gradient is written its registers take the same group of the block's next row.  The gradient is
 // stored past the caches (as ordinary stores 463 us).  bf16, a block per row with two exponentials a value -> this, us: 8192 rows of 50257 515 -> 453 (5.5
-// TB/s), 4096 x 50257 272 -> 229, 512 x 50257 35.4 -> 24.8, 2400 x 8000 25.3 -> 18.6, 8192 x 2000 42.6 -> 16.3; 8192 x 16000 138 and 140.
+// TB/s), 4096 x 50257 272 -> 229, 512 x 50257 35.4 -> 24.8, 2400 x 8000 25.3 -> 18.6, 8192 x 2000 42.6 -> 16.3; 8192 x 16000 140 and 140, 8192 x 12000 107 -> 106.
 template <typename T, int THREADS, int MAXG>
 __global__ void __launch_bounds__(THREADS < 256 ? 256 : THREADS)
 cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogits, const int* __restrict__ targets,
@@ -191,25 +191,29 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
   finish(row, -1);
 }
 
-// Threads of a row: the fewest of 64, 256 and 1024 that hold it in half of the registers (32 values each), or, from 1024 on, in 64 values (a
-// thread of such a block has 128 registers).  Blocks: as many as the chip holds at once, each with its share of the rows.
+// Threads of a row: the fewest of 64, 256, 512 and 1024 that hold it in 32 values each, in registers of which a compute unit has room for 16 wavefronts
+// (256 threads with 64 values, bf16, us: 8192 x 8200 71 against 66 with 512, 8192 x 12000 107 and 106, 8192 x 16000 141 and 140).  Wider rows are held by
+// 1024 threads in 56 values and past 57344 columns in 64: with the last eight, which a row of 50257 does not fill, 8192 x 50257 takes 453 instead of 451,
+// 512 x 50257 25.8 instead of 25.0, in fp32 33.8 instead of 32.2.  Blocks: one row or run of rows each, as many as the chip holds at once or, of the
+// smaller blocks, a few times that.
 template <typename T>
 void launch_cross_entropy(const float* logits, T* dlogits, const int* targets, float* loss, int rows, int V, int ld, float coef, hipStream_t s) {
   const int ng = ld / Vec<T>::N;
   constexpr int kMost = 64 / Vec<T>::N;
   auto go = [&](auto threads, auto groups) {
     constexpr int THREADS = decltype(threads)::value, MAXG = decltype(groups)::value, TEAMS = THREADS < 256 ? 256 / THREADS : 1;
-    const int blocks = std::min((rows + TEAMS - 1) / TEAMS, THREADS == 1024 ? 256 : MAXG == kMost / 2 ? 1024 : 768);
+    const int blocks = std::min((rows + TEAMS - 1) / TEAMS, THREADS == 1024 ? 256 : 1024);
     cross_entropy_row_kernel<T, THREADS, MAXG><<<blocks, THREADS * TEAMS, 0, s>>>(logits, dlogits, targets, loss, rows, V, ld, coef);
   };
   typedef std::integral_constant<int, kMost / 2> Half;
   typedef std::integral_constant<int, 64> Wave;
   typedef std::integral_constant<int, 256> Narrow;
+  typedef std::integral_constant<int, 512> Middle;
   typedef std::integral_constant<int, 1024> Wide;
   auto count = [&](int threads) { return (ng + threads - 1) / threads; };
   if (count(64) <= kMost / 2) go(Wave(), Half());
   else if (count(256) <= kMost / 2) go(Narrow(), Half());
-  else if (count(256) <= kMost) go(Narrow(), std::integral_constant<int, kMost>());
+  else if (count(512) <= kMost / 2) go(Middle(), Half());
   else if (count(1024) <= kMost / 2) go(Wide(), Half());
   else if (count(1024) <= kMost - kMost / 8) go(Wide(), std::integral_constant<int, kMost - kMost / 8>());
   else if (count(1024) <= kMost) go(Wide(), std::integral_constant<int, kMost>());
