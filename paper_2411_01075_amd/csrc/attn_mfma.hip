@@ -129,26 +129,27 @@ __device__ __forceinline__ BlockCoords block_coords(int l, int gx, int gy, int n
   // (the divisions run on the vector unit; readfirstlane tells the compiler that the results are uniform)
   return {__builtin_amdgcn_readfirstlane(l % gx), __builtin_amdgcn_readfirstlane((l / gx) % gy), __builtin_amdgcn_readfirstlane(l / (gx * gy))};
 }
+__device__ __forceinline__ int block_index() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 __device__ __forceinline__ BlockCoords block_coords() {
   const int gx = gridDim.x, gy = gridDim.y;
-  return block_coords(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx, gy, gx * gy * gridDim.z);
+  return block_coords(block_index(), gx, gy, gx * gy * gridDim.z);
 }
 
 // The order in which a causal launch of the four-wavefront kernels takes its tiles (the work of a tile grows with the keys its queries see):
 //   kSingle  one tile per block, the longest of a head first
 //   kPaired  a block takes a tile and then its mirror image, so that every block does the same work
-//   kByHead  one tile per block; each XCD has `per` heads and takes the longest tiles of all of them first (grid 8 * per * tiles; the last XCDs
-//            have fewer heads, y < 0: nothing to do)
+//   kByHead  one tile per block; each XCD has an eighth of the heads (some one more than others: y < 0, nothing to do) and takes the longest tiles of
+//            all of them first (grid 8 * heads of an XCD * tiles)
 // With several blocks on a compute unit pairs leave it idle at the end (600 pairs are 2.3 per compute unit); single tiles, the longest first, even
-// out.  6 x 1024 tokens, 25 heads of 64, kPaired -> kByHead, us: forward 42.5 -> 36.3, dQ 52 -> 46, dK/dV 75 -> 61; 2048 tokens, 80 heads of
-// 32: 48.1 -> 42.3, and 124 -> 112 for the two.  Below 64 heads that are no multiple of 8 the XCDs' shares differ too much (3 x 777 tokens, 12 heads of
-// 80: backward 48.7 -> 50.5).
-struct TileOrder { int kind, per, heads; };
+// out.  6 x 1024 tokens, 25 heads of 64, kPaired -> kByHead, us: forward 41.2 -> 35.5, backward 123 -> 102; 2048 tokens, 80 heads of 32: 50.0 -> 42.2
+// and 122 -> 109; 4096 tokens, 50 heads of 64: backward 464 -> 411.
+struct TileOrder { int kind, tiles, heads, blocks; };      // tiles: of a head, or pairs of them; blocks: of the whole order
 enum { kSingle = 0, kPaired = 1, kByHead = 2 };
-__device__ __forceinline__ BlockCoords ordered_coords(const TileOrder& order, int A) {
-  if (order.kind != kByHead) return block_coords();
-  const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3, head = xcd * order.per + i % order.per;
-  return {__builtin_amdgcn_readfirstlane(i / order.per), __builtin_amdgcn_readfirstlane(head < order.heads ? head % A : -1), __builtin_amdgcn_readfirstlane(head / A)};
+__device__ __forceinline__ BlockCoords ordered_coords(const TileOrder& order, int A, int l) {
+  if (order.kind != kByHead) return block_coords(l, order.tiles, A, order.blocks);
+  const int xcd = l & 7, i = l >> 3, per = (order.heads + 7) >> 3, at = i % per;
+  const int first = (int)((int64_t)xcd * order.heads >> 3), count = (int)((int64_t)(xcd + 1) * order.heads >> 3) - first, head = first + at;
+  return {__builtin_amdgcn_readfirstlane(i / per), __builtin_amdgcn_readfirstlane(at < count ? head % A : -1), __builtin_amdgcn_readfirstlane(head / A)};
 }
 
 // The LDS addresses of one lane's fragment reads (Tile::frag_rows / frag_cols) for two double-buffered tiles A and B that lie [A | B][A | B]: a register
@@ -315,7 +316,7 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
   auto Ks = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto Vs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
 
-  const BlockCoords blk = ordered_coords(order, A);
+  const BlockCoords blk = ordered_coords(order, A, block_index());
   if (blk.y < 0) return;
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
@@ -335,10 +336,10 @@ attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O, float* __res
 
   const int kv_end = CAUSAL ? min(S, qt * 128 + 128) : S;
   const int ntiles = (kv_end + TILE - 1) / TILE;
+  bf16x8 qf[NP];
+  load_row_frags<D>(base, ld, q0, S, qf, d);      // (before the staging: 16 x 197 tokens, 16 heads of 64 9.6 us, after it 10.3)
   TL::stage(rs_qkv, k_bytes, (unsigned)ld * 2, 0, Ks(0), d);
   TL::stage(rs_qkv, v_bytes, (unsigned)ld * 2, 0, Vs(0), d);
-  bf16x8 qf[NP];
-  load_row_frags<D>(base, ld, q0, S, qf, d);
   __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
   __syncthreads();
 
@@ -998,7 +999,7 @@ __global__ void __launch_bounds__(kThreads, kDqWaves<D>)
 attn_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
                float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
                const float* __restrict__ rot, TileOrder order) {
-  const BlockCoords blk = ordered_coords(order, A);
+  const BlockCoords blk = ordered_coords(order, A, block_index());
   if (blk.y < 0) return;
   dq_block<D, CAUSAL, ROT>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
 }
@@ -1338,7 +1339,7 @@ __global__ void __launch_bounds__(kThreads, kDkvWaves<D>)
 attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const float* __restrict__ lse,
                        const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
                        const float* __restrict__ rot, TileOrder order) {
-  const BlockCoords blk = ordered_coords(order, A);
+  const BlockCoords blk = ordered_coords(order, A, block_index());
   if (blk.y < 0) return;
   dkv_block<D, CAUSAL, ROT, false>(qkv, nullptr, dO, lse, dvec, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
 }
@@ -1361,27 +1362,31 @@ attn_bwd_small_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, 
 // unit of their own at once: then the launch lasts as long as the longest tile, not as the longest and the shortest (8 heads of 80, 700 tokens, 48
 // tiles: forward 22 -> 15 us, backward 61 -> 44).  Beyond that single tiles, longest first, lose (4 x 2048 tokens, 16 heads of 128).
 inline bool pair_tiles(int nt, int A, int m) { return (int64_t)nt * A * m > 256; }
-// grid and order of a four-wavefront kernel (by_head: whether that order is worth it for the kernel)
-inline dim3 tile_order(bool causal, bool by_head, int nt, int A, int m, TileOrder* order) {
+// a four-wavefront kernel's tiles in a given order, and the grid that goes with it.  By head only where no XCD has half as much again as it would at
+// equal shares: 18 heads of 8192 tokens (three heads on an XCD, 2.25 at equal shares) 634 us by head, 674 in pairs; 9 heads (two, 1.1) 412 and 408.
+inline dim3 tile_order(int kind, int nt, int A, int m, TileOrder* order) {
   const int64_t heads = (int64_t)A * m, per = (heads + 7) / 8;
-  *order = {causal && pair_tiles(nt, A, m) ? kPaired : kSingle, 0, (int)heads};
-  if (order->kind == kPaired && by_head && (heads % 8 == 0 || heads >= 64) && 8 * per * nt < (int64_t)1 << 31) {
-    *order = {kByHead, (int)per, (int)heads};
-    return dim3((unsigned)(8 * per * nt));
-  }
-  return dim3(order->kind == kPaired ? (nt + 1) / 2 : nt, A, m);
+  if (kind == kByHead && (2 * 8 * per > 3 * heads || 8 * per * nt >= (int64_t)1 << 31)) kind = kPaired;
+  const int tiles = kind == kPaired ? (nt + 1) / 2 : nt;
+  *order = {kind, tiles, (int)heads, (int)(kind == kByHead ? 8 * per * nt : heads * tiles)};
+  return kind == kByHead ? dim3(order->blocks) : dim3(tiles, A, m);
 }
 
-// Forward.  Causal heads of 128: two groups that take turns.  Causal narrower heads: where a sample has at most 64 tiles of queries, eight wavefronts,
-// which split the keys between them and so halve the chain that such a launch consists of (1024 tokens, 8 heads of 64, one sample 14.3 us, with four
-// wavefronts 16.7; 128 tokens, 16 heads, 64 samples 20.7 and 18.6); the samples do not count, so that a sample's result does not depend on
-// how many a launch takes.  Otherwise four wavefronts.
+// Forward.  Causal heads of 128: two groups that take turns.  Causal narrower heads: eight wavefronts, which split the keys between them and so
+// halve the chain of a tile, where the launch consists of such chains, four where it has tiles enough to fill the chip with blocks of less; both give the
+// same bits.  Us with eight and with four, heads of 64: 256 tiles of 1024 tokens 15.2 and 18.0, of 4096 42.6 and 55.7; 320 of 1024 19.6 and 18.7; 512 of
+// 2048 28.8 and 32.7, 528 44.7 and 35.3 (eight: 256 pairs have a compute unit each, 257 do not); 640 of 4096 77.2 and 69.4, 1024 87.5 and 89.3, 1280 124
+// and 108; 9 heads of 8192 141 and 151 (too few heads for four wavefronts' order), 18 227 and 221.
+inline bool eight_wavefronts(int nt, int A, int m) {
+  const int64_t tiles = (int64_t)nt * A * m;
+  return tiles <= 256 || (nt > 8 && (tiles <= 512 || (int64_t)A * m < 16)) || (nt > 24 && tiles > 768 && tiles <= 1024);
+}
 template <int D, bool CAUSAL>
 int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hipStream_t s) {
   const int nt = (S + 127) / 128;
   const float scale = 1.0f / sqrtf((float)(H / A));
   if constexpr (CAUSAL) {
-    if (D == 128 || (int64_t)A * nt <= 64) {
+    if (D == 128 || eight_wavefronts(nt, A, m)) {
       const bool paired = pair_tiles(nt, A, m);
       dim3 grid(paired ? (nt + 1) / 2 : nt, A, m);
       const size_t staging = 4 * (size_t)Tile<D, 128, kThreads8>::ELEMS * sizeof(bf16), merge = (size_t)4 * (D / 32 * 16 + 2) * 64 * sizeof(float);
@@ -1396,7 +1401,7 @@ int fwd_cfg(const bf16* qkv, bf16* O, float* lse, int m, int S, int H, int A, hi
   }
   if constexpr (!CAUSAL || D <= 64) {
     TileOrder order;
-    const dim3 grid = tile_order(CAUSAL, true, nt, A, m, &order);
+    const dim3 grid = tile_order(CAUSAL ? kByHead : kSingle, nt, A, m, &order);
     const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);      // two stages of 64 keys and values
     constexpr auto kern = attn_fwd_kernel<D, CAUSAL>;
     int rc = reserve_lds<kern>("attention", lds);
@@ -1425,7 +1430,9 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
     }
   }
   TileOrder order;
-  const dim3 grid = tile_order(CAUSAL, D <= 64, nt, A, m, &order);
+  const int64_t heads = (int64_t)A * m;
+  const bool by_head = D <= 64 && (heads % 8 == 0 || heads >= 64);
+  const dim3 grid = tile_order(!CAUSAL || !pair_tiles(nt, A, m) ? kSingle : by_head ? kByHead : kPaired, nt, A, m, &order);
   {
     const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);      // two stages of 64 keys and values
     constexpr auto kern = attn_dq_kernel<D, CAUSAL, ROT>;

@@ -134,9 +134,12 @@ def test_probabilities_are_rounded_relative_to_the_maximum_of_their_half(S, A, d
 
 
 @pytest.mark.parametrize("m,S,A,d", [
-    (20, 300, 5, 64),       # 100 heads, 300 tiles: each XCD's longest first
-    (8, 520, 13, 32),       # the same with heads of 32, the last XCD with fewer heads
-    (4, 1100, 9, 64),       # 36 heads, 324 tiles: in pairs, an odd number of tiles
+    (20, 300, 5, 64),       # 100 heads, 300 tiles: forward with four wavefronts, by head, some XCDs with one head more
+    (8, 520, 13, 32),       # 520 tiles, 13 heads an XCD
+    (6, 700, 15, 64),       # 540 tiles, 90 heads: some XCDs with one head more
+    (4, 1100, 9, 64),       # 324 tiles of long samples: forward with eight wavefronts, in pairs, an odd number of tiles
+    (4, 4200, 5, 32),       # 660 tiles of 20 heads
+    (3, 4200, 3, 64),       # 297 tiles of 9 heads: not by head
     (5, 700, 9, 128),       # pairs, heads of 128
     (64, 64, 8, 64),        # one tile a head
 ])
