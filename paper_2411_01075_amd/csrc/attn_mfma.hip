@@ -1174,7 +1174,8 @@ attn_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO, const
 // ------------------------------------------------------------------------------------ dK, dV, heads of 64 or less
 // Four wavefronts: a block owns 128 keys, each wavefront 32 of them, whose rows stay in its registers (at these widths they fit), and walks the
 // query tiles of 64 that see them, as two blocks of 32 queries.
-// OWN: the rows' statistics are formed here, all of them at the start and from O (dvec is not read), for a launch that runs beside the dQ blocks.
+// OWN: the rows' statistics are formed here, kStatRows of them at a time and from O (dvec is not read), for a launch that runs beside the dQ blocks.
+constexpr int kStatRows = 2048;
 template <int D, bool CAUSAL, bool ROT, bool OWN>
 __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
                                           const float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale,
@@ -1185,7 +1186,7 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
   lds_bf16* smem = (lds_bf16*)smem_raw;
   auto Qs = [&](int st) { return smem + st * 2 * TL::ELEMS; };
   auto dOs = [&](int st) { return smem + st * 2 * TL::ELEMS + TL::ELEMS; };
-  LDS_AS float* stats = (LDS_AS float*)(smem + 4 * TL::ELEMS);      // [2 buffers][-lse / scale | -dvec][64], OWN: [-lse / scale | -dvec][all rows]
+  LDS_AS float* stats = (LDS_AS float*)(smem + 4 * TL::ELEMS);      // [2 buffers][-lse / scale | -dvec][64], OWN: [-lse / scale | -dvec][kStatRows]
 
   const int a = blk.y, n = blk.z;
   const int d = H / A;        // the head's own width: D, or less (a multiple of 8) with the tiles' further columns held at zero
@@ -1222,16 +1223,15 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
   bf16x8 kf[NP], vf[NP];
   load_row_frags<D>(base + H, ld, t0, S, kf, d);
   load_row_frags<D>(base + 2 * H, ld, t0, S, vf, d);
-  const int all = ntiles * TILE;
-  if (OWN) {
-    for (int r0 = first * TILE + wave * 32; r0 < all; r0 += 128) {
-      const int r = r0 + (lane & 31);
+  auto own_stats = [&](int row0, int end) {
+    for (int r0 = row0 + wave * 32; r0 < end; r0 += 128) {
+      const int r = r0 + (lane & 31), at = r % kStatRows;
       bf16x8 dof[NP];
       load_row_frags<D>(dO + (int64_t)n * S * H + a * d, H, r0, S, dof, d);
       const float dv = row_dot<D>(O + (int64_t)n * S * H + a * d, H, r0, S, dof, d), l = r < S ? lse_base[r] * per_scale : 0.f;
-      if (h == 0) { stats[r] = l; stats[all + r] = -dv; }
+      if (h == 0) { stats[at] = l; stats[kStatRows + at] = -dv; }
     }
-  }
+  };
   load_stats(first * TILE);
   if (!OWN && threadIdx.x < 128) stats[threadIdx.x] = rstat;
 
@@ -1240,9 +1240,6 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dvv[dt][e] = 0.f; }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
-  __syncthreads();
-
   FragAddr<D> at(smem);
   auto stage_after = [&](int it) {                     // the next tile flies into the other stage meanwhile
     if (it + 1 >= ntiles) return;
@@ -1259,17 +1256,22 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
   // (the tiles before the first whose queries see the wavefront's keys it only helps to stage; likewise all of them if its keys lie past the end)
   const int mine = t0 >= S ? ntiles : CAUSAL ? max(first, t0 / TILE) : first;
   int it = first;
-  for (; it < mine; ++it) {
+  do {
+  const int upto = OWN ? min(ntiles, (it / (kStatRows / TILE) + 1) * (kStatRows / TILE)) : ntiles;
+  if (OWN) own_stats(it * TILE, upto * TILE);          // (those of the tiles before have been read: every tile ends with a barrier)
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wavefront's rows have landed
+  __syncthreads();
+  for (; it < min(mine, upto); ++it) {
     stage_after(it);
     at.flip();
     close(it);
   }
-  for (; it < ntiles; ++it) {
+  for (; it < upto; ++it) {
     const int qb0 = it * TILE;
     stage_after(it);
     {
-      const LDS_AS float* st = stats + (OWN ? qb0 : ((it - first) & 1) * 128) + 4 * h;
-      const int dvecs = OWN ? all : 64;
+      const LDS_AS float* st = stats + (OWN ? qb0 % kStatRows : ((it - first) & 1) * 128) + 4 * h;
+      constexpr int dvecs = OWN ? kStatRows : 64;
       // the products: S and dP of the first block and of the second, then dV and dK of each
       auto fetch = [&](int i) -> bf16x8 {
         const int seg = i / NP, j = i % NP;
@@ -1328,6 +1330,7 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
     at.flip();
     close(it);
   }
+  } while (OWN && it < ntiles);
   bf16* out = dqkv + (int64_t)n * S * ld + a * d;
   store_transposed<D>(dvv, out + 2 * H, ld, t, S, 1.0f, d);
   if (ROT) store_transposed_unrotated<D>(dk, out + H, ld, t, S, scale, rot, d);
@@ -1346,16 +1349,20 @@ attn_dkv_narrow_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO
 
 // The whole backward of narrow heads in one launch, where two would not fill the chip: the dK / dV blocks first (they are the longer ones), then the dQ
 // blocks, side by side instead of one after the other.  The statistics that the dK / dV kernel otherwise takes from the dQ kernel it forms itself,
-// in the same order of additions, so that the choice does not show in the results.  Two launches -> one, us: 2 x 128 tokens, 4 heads of 64 15.0 -> 9.1;
-// 2 x 512, 8 of 64 26.6 -> 18.5; 8 x 512, 8 of 64 29.2 -> 23.7; 1024, 8 of 64 41.7 -> 30.0; 16 x 197, 16 of 64, no mask 30.2 -> 28.7 (1024 blocks, as far as it
-// gains; under a mask up to 512, beyond which the tiles are taken in pairs or by head).
+// in the same order of additions, so that the choice does not show in the results.  Two launches -> one, heads of 64, us: 2 x 128 tokens, 4 heads 15.0 -> 9.1;
+// 1024, 8 heads 41.7 -> 30.7; 4096, 8 132 -> 113.  Without a mask up to 512 tiles of short samples (16 x 197 tokens, 16 heads 29.7 -> 27.7) and 384 of
+// longer ones (384 of 2048 112 -> 114, heads of 32 77 -> 66; 448 117 -> 137 and 80 -> 85).  Under a mask up to 512 tiles; from 257 on, of up to 16 tiles a head, by head (50 heads of 1024 tokens: two launches in
+// pairs 57.6, by head 49.8, one by head 43.1, in pairs 45.2), of longer ones in pairs (16 heads of 4096: 158, 159, 148, 141).  Beyond, two launches win (64
+// heads of 2048 142 and 161).
 template <int D, bool CAUSAL, bool ROT>
 __global__ void __launch_bounds__(kThreads, 2)
 attn_bwd_small_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ O, const bf16* __restrict__ dO, const float* __restrict__ lse,
-                      float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, int m, float scale, const float* __restrict__ rot) {
-  const int tiles = (S + 127) / 128, blocks = tiles * A * m;
-  if ((int)blockIdx.x < blocks) dkv_block<D, CAUSAL, ROT, true>(qkv, O, dO, lse, nullptr, dqkv, S, H, A, scale, rot, block_coords(blockIdx.x, tiles, A, blocks), false);
-  else dq_block<D, CAUSAL, ROT>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, block_coords((int)blockIdx.x - blocks, tiles, A, blocks), false);
+                      float* __restrict__ dvec, bf16* __restrict__ dqkv, int S, int H, int A, float scale, const float* __restrict__ rot, TileOrder order) {
+  const bool second = (int)blockIdx.x >= order.blocks;
+  const BlockCoords blk = ordered_coords(order, A, (int)blockIdx.x - (second ? order.blocks : 0));
+  if (blk.y < 0) return;
+  if (!second) dkv_block<D, CAUSAL, ROT, true>(qkv, O, dO, lse, nullptr, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
+  else dq_block<D, CAUSAL, ROT>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, blk, order.kind == kPaired);
 }
 
 // Causal launches of the eight-wavefront kernels: a block takes a tile and its mirror image (equal work per block) unless all tiles find a compute
@@ -1418,21 +1425,23 @@ int bwd_cfg(const bf16* qkv, const bf16* O, const bf16* dO, const float* lse, fl
   const float scale = 1.0f / sqrtf((float)(H / A));
   const int nt = (S + 127) / 128;
   if constexpr (D <= 64) {
-    const int64_t blocks = 2 * (int64_t)nt * A * m;
-    if (S <= 2048 && blocks <= (CAUSAL ? 512 : 1024)) {
-      const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * (size_t)((S + TILE - 1) / TILE * TILE) * sizeof(float);
+    const int64_t tiles = (int64_t)nt * A * m;
+    if (tiles <= (CAUSAL || nt <= 4 ? 512 : 384)) {
+      TileOrder order;
+      (void)tile_order(!CAUSAL || tiles <= 256 ? kSingle : nt <= 16 ? kByHead : kPaired, nt, A, m, &order);
+      const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * kStatRows * sizeof(float);
       constexpr auto kern = attn_bwd_small_kernel<D, CAUSAL, ROT>;
-      int rc = reserve_lds<kern>("attention", 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16) + 2 * 2048 * sizeof(float));
+      int rc = reserve_lds<kern>("attention", lds);
       if (rc != CEPHALO_OK) return rc;
-      kern<<<(int)blocks, kThreads, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, m, scale, rot);
+      kern<<<2 * order.blocks, kThreads, lds, s>>>(qkv, O, dO, lse, dvec, dqkv, S, H, A, scale, rot, order);
       CEPHALO_CHECK_LAUNCH("attn_bwd_mfma");
       return CEPHALO_OK;
     }
   }
   TileOrder order;
-  const int64_t heads = (int64_t)A * m;
-  const bool by_head = D <= 64 && (heads % 8 == 0 || heads >= 64);
-  const dim3 grid = tile_order(!CAUSAL || !pair_tiles(nt, A, m) ? kSingle : by_head ? kByHead : kPaired, nt, A, m, &order);
+  // (heads of 128, whose dK / dV blocks have a compute unit each: dQ in pairs and by head, us of the whole backward: 12 heads of 4096 tokens 215 and 222, 64 of
+  // 2048 268 and 268, 320 of 512 175 and 181, but 18 of 4096 408 and 396)
+  const dim3 grid = tile_order(!CAUSAL ? kSingle : D <= 64 ? kByHead : pair_tiles(nt, A, m) ? kPaired : kSingle, nt, A, m, &order);
   {
     const size_t lds = 4 * (size_t)Tile<D>::ELEMS * sizeof(bf16);      // two stages of 64 keys and values
     constexpr auto kern = attn_dq_kernel<D, CAUSAL, ROT>;

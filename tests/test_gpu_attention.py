@@ -134,12 +134,14 @@ def test_probabilities_are_rounded_relative_to_the_maximum_of_their_half(S, A, d
 
 
 @pytest.mark.parametrize("m,S,A,d", [
-    (20, 300, 5, 64),       # 100 heads, 300 tiles: forward with four wavefronts, by head, some XCDs with one head more
-    (8, 520, 13, 32),       # 520 tiles, 13 heads an XCD
-    (6, 700, 15, 64),       # 540 tiles, 90 heads: some XCDs with one head more
+    (20, 300, 5, 64),       # 100 heads, 300 tiles: forward with four wavefronts, by head, some XCDs with one head more; backward in one launch by head
+    (8, 520, 13, 32),       # 520 tiles, 13 heads an XCD: two launches by head
+    (6, 700, 15, 64),       # 540 tiles, 90 heads: two launches by head, some XCDs with one head more
     (4, 1100, 9, 64),       # 324 tiles of long samples: forward with eight wavefronts, in pairs, an odd number of tiles
+    (9, 2100, 3, 64),       # 459 tiles: backward in one launch in pairs, the statistics in two windows
+    (1, 2100, 3, 32),       # 51 tiles: single ones, in two windows
     (4, 4200, 5, 32),       # 660 tiles of 20 heads
-    (3, 4200, 3, 64),       # 297 tiles of 9 heads: not by head
+    (3, 4200, 3, 64),       # 297 tiles of 9 heads: no by head
     (5, 700, 9, 128),       # pairs, heads of 128
     (64, 64, 8, 64),        # one tile a head
 ])
@@ -173,14 +175,16 @@ def test_causal_samples_do_not_depend_on_the_launch(m, S, A, d):
     (197, 12, 64, False),
     (333, 10, 64, True),
     (640, 5, 24, True),
-    (2048, 2, 64, False),       # the longest sample whose statistics the one launch holds
+    (640, 5, 64, False),
+    (2048, 2, 64, False),       # the longest sample whose statistics the one launch holds at once
     (2048, 1, 32, True),
-    (2049, 2, 64, False),       # beyond it: always two launches
+    (2049, 2, 64, False),       # one row beyond it
+    (4160, 1, 64, True),        # three windows of statistics
 ])
 def test_backward_in_one_launch_or_two(S, A, d, causal):
-    """Up to 512 blocks under a mask, 1024 without, the backward of narrow heads is one launch; a sample's results are the same bits on both sides."""
+    """Up to 512 tiles, or 384 of more than four a head without a mask, the backward of narrow heads is one launch; a sample's results are the same bits on both sides."""
     print("attention backward launches", S, A, d, causal, flush=True)
-    H, limit, each = A * d, 512 if causal else 1024, 2 * A * ((S + 127) // 128)
+    H, limit, each = A * d, 512 if causal or S <= 512 else 384, A * ((S + 127) // 128)
     below = max(1, limit // each)                                        # samples of the last launch in one, the first in two
     m = below + 1
     g = torch.Generator(device="cuda").manual_seed(S + d)
