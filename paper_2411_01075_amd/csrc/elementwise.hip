@@ -384,6 +384,7 @@ __device__ __forceinline__ void colsum_block(const T* __restrict__ dY, bf16* __r
       if (ok) *reinterpret_cast<bf16x4*>(lowp + (int64_t)r * N + col) = q;
     }
   }
+  if (LOWP && !partials) return;                           // (the copy alone)
 #pragma unroll
   for (int i = 0; i < VN; ++i) red[wave][lane][i] = acc[i];
   __syncthreads();
@@ -558,7 +559,7 @@ int launch_transposes(const TransposeJob* jobs, int n, hipStream_t s, const Cast
   }
   if (beside) {
     const int chunks = cast_colsum_chunks(beside->rows);
-    if (beside->partial_bytes < (size_t)chunks * beside->N * sizeof(float)) return fail(CEPHALO_EWORKSPACE, "cast_colsum: partial buffer too small");
+    if (beside->partials && beside->partial_bytes < (size_t)chunks * beside->N * sizeof(float)) return fail(CEPHALO_EWORKSPACE, "cast_colsum: partial buffer too small");
     const int sums = chunks * ((beside->N / 4 + 63) / 64);
     prepare_backward_kernel<<<(unsigned)(sums + b.first[n]), kThreads, 0, s>>>(b, *beside, sums);
     CEPHALO_CHECK_LAUNCH("prepare_backward");

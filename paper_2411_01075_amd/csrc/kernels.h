@@ -230,12 +230,9 @@ template <typename T>
 int launch_colsum(const T* dY, float* partials, size_t partial_bytes, float* g, float scale,
                   int accumulate, int rows, int N, hipStream_t s);
 size_t colsum_partial_bytes(int rows, int N);
-// lowp = bf16(x) for x [rows, N] fp32 and, on the way, the column sums of x in cast_colsum_chunks(rows) partial rows
+// lowp = bf16(x) for x [rows, N] fp32 and, on the way, unless partials is null, the column sums of x in cast_colsum_chunks(rows) partial rows
 struct CastColsum { const float* x; bf16* lowp; float* partials; size_t partial_bytes; int rows, N; };
 int cast_colsum_chunks(int rows);
-
-// dst[i] = bf16(src[i]), i in [0, n)
-int launch_cast_bf16(bf16* dst, const float* src, int64_t n, hipStream_t s);
 
 // out[c][r] = in[r][c] for a row-major bf16 matrix [rows, cols]; out has row pitch `pitch` (0: rows) and its
 // columns [rows, pitch) are zero-filled; cols and the pitch are multiples of 8

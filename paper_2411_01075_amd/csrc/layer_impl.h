@@ -494,8 +494,9 @@ template <> inline int prepare_backward<float>(const cephalo_layer_desc& d, cons
   return CEPHALO_OK;
 }
 template <> inline int prepare_backward<bf16>(const cephalo_layer_desc& d, const bf16* P, const float* dy, int tokens, const Work<bf16>& w, DySums* sums, hipStream_t s) {
-  const CastColsum c = {dy, w.dyl, w.col_part, w.col_part_bytes, tokens, d.hidden};
-  *sums = {is_llama(d) ? nullptr : w.col_part, is_llama(d) ? 0 : cast_colsum_chunks(tokens)};
+  float* const partials = is_llama(d) ? nullptr : w.col_part;
+  const CastColsum c = {dy, w.dyl, partials, w.col_part_bytes, tokens, d.hidden};
+  *sums = {partials, partials ? cast_colsum_chunks(tokens) : 0};
   return prepare_dgrad_weights<bf16>(d, P, w.wT, s, &c);
 }
 

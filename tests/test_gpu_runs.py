@@ -94,3 +94,20 @@ def test_bias_gradient_is_the_column_sum_of_dy(S, m, l, hidden):
     rows, got = dy.reshape(-1, hidden).double(), G[-hidden:].double()        # (the last tensor: the second feed-forward projection's bias)
     bound = rows.shape[0] * 2.0 ** -24 * rows.abs().sum(0) * 0.5             # one rounding of at most the sum of magnitudes per addition
     assert bool(((got - 0.5 * rows.sum(0)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("kind", [C.LAYER_GPT, C.LAYER_LLAMA], ids=["gpt", "llama"])
+@pytest.mark.parametrize("S,hidden", [(31, 72), (200, 264)])
+def test_column_sums_of_dy_only_where_there_is_a_bias(kind, S, hidden):
+    """The partial sums are the scratch area's last region.  A layer without biases leaves it alone."""
+    print(kind, S, hidden, flush=True)
+    desc = C.layer_desc(hidden, hidden // 8, 4 * hidden, S, True, C.BF16, 1e-5, kind)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, dy = (torch.randn(1, S, hidden, device="cuda", generator=g) for _ in range(2))
+    flat, y, dx = _flat(C.cephalo_layer_param_count(desc), desc.dtype), torch.empty_like(x), torch.empty_like(x)
+    save, scratch = (_bytes(n) for n in C.cephalo_layer_workspace_bytes(desc, 1))
+    C.cephalo_layer_fwd(desc, flat, x, y, 1, save, scratch)
+    C.cephalo_layer_bwd(desc, flat, x, dy, dx, 1, save, torch.empty(flat.numel(), device="cuda"), 1.0, False, scratch)
+    widest = (8 if kind == C.LAYER_LLAMA else 4) * hidden                 # of 3 * hidden and the feed-forward's first outputs
+    region = scratch[-((S + 63) // 64 * widest * 4 + 255) // 256 * 256:]
+    assert bool((region == 255).all()) == (kind == C.LAYER_LLAMA)
