@@ -519,7 +519,7 @@ int check_stack(const cephalo_stack_desc* d) {
 }
 
 struct StackLayout {
-  size_t xs, saves, save_each, scratch, dxa, dxb, dxal, dxbl, uf, meanf, rstdf, duf, logits, dlogits, wteT, loss, lnf_part, keys, embed_part, logits_bytes, total;
+  size_t xs, saves, save_each, scratch, dxa, dxb, dxal, dxbl, uf, meanf, rstdf, logits, dlogits, wteT, loss, lnf_part, keys, embed_part, logits_bytes, total;
   int ldv;            // padded pitch of the logits
   size_t lnf_rows;
 };
@@ -536,7 +536,6 @@ StackLayout stack_layout(const cephalo_stack_desc& d, int b, int m) {
   // layer-boundary activations, the fp32 residual stream: all of them, or (offload) two micro-batches coming in from the
   // host and two going out
   L.xs = take(d.offload ? 4 * Tm * H * 4 : (size_t)(d.layers + 1) * n * H * 4);
-  if (d.checkpoint) take((d.interleave ? 2 : 1) * Tm * H * 4);         // (not used any more; what is reported and refused stays what it was)
   L.save_each = align_up(save_layout(ld, b).total);
   L.saves = take((size_t)(d.checkpoint ? 1 : d.layers) * L.save_each);   // checkpointing: one layer's internals at a time
   L.scratch = take(scratch_layout(ld, m, b, d.interleave ? 2 : 1).total);
@@ -545,7 +544,6 @@ StackLayout stack_layout(const cephalo_stack_desc& d, int b, int m) {
   L.dxa = take(n * H * 4); L.dxb = take(d.offload == 2 ? 4 * Tm * H * 4 : n * H * 4);
   L.dxal = es == 4 ? L.dxa : take(n * H * es); L.dxbl = es == 4 ? L.dxb : take(n * H * es);   // and its copy in the activation type
   L.uf = take(n * H * es); L.meanf = take(n * 4); L.rstdf = take(n * 4);
-  L.duf = take((d.interleave ? 2 : 1) * Tm * H * 4);
   L.logits_bytes = (d.interleave ? 2 : 1) * Tm * (size_t)L.ldv * 4;   // one micro-batch of fp32 logits, reused (interleave: one per stream)
   L.logits = take(L.logits_bytes);
   L.dlogits = take(n * (size_t)L.ldv * es);       // their gradient for the whole share (an operand of the weight gradient)
@@ -724,16 +722,16 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
       X.out_done(li + 1, j);
     }
   }
-  // ---- head: final LN, tied logits (fp32, one micro-batch at a time), cross-entropy and its gradient, back to the last layer's output
-  T* uf = at<T>(ws, L.uf); T* dlogits = at<T>(ws, L.dlogits); float* duf = at<float>(ws, L.duf);
+  // ---- head: final norm, fp32 logits of as many of a run's micro-batches as there is room for, cross-entropy and its gradient, back to the last layer's output
+  T* uf = at<T>(ws, L.uf); T* dlogits = at<T>(ws, L.dlogits);
   float* meanf = at<float>(ws, L.meanf); float* rstdf = at<float>(ws, L.rstdf);
   float* lnf_g = at<float>(ws, L.lnf_part); float* lnf_b = lnf_g + L.lnf_rows * H; float* lnf_s = lnf_b + L.lnf_rows * H;
   float* dx_cur = at<float>(ws, L.dxa); float* dx_nxt = at<float>(ws, L.dxb);
   T* dxl_cur = at<T>(ws, L.dxal); T* dxl_nxt = at<T>(ws, L.dxbl);
   const float coef = scale / (float)n;
   const int nb = ln_bwd_blocks(Tm);
-  // The fp32 logits and the gradient of the final norm's output: a run's micro-batches together where there is room, the logits in the work area
-  // of the layers' backward (not in use yet) if it is the larger, the gradient in the buffer of the next layer's; otherwise one after the other.
+  // The logits lie in the work area of the layers' backward (not in use yet) if it is larger than their own; the gradient of the final norm's output where
+  // the last layer's backward will leave that of its input.
   const size_t mb_logits = (size_t)Tm * L.ldv * sizeof(float);
   const bool roomy = WL.total > L.logits_bytes && !d.offload;
   char* const lg_area = roomy ? at<char>(ws, L.scratch) : at<char>(ws, L.logits);
@@ -748,7 +746,7 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
     const size_t t0 = (size_t)j * Tm;
     hipStream_t sj = st[q.lane];
     float* logits_q = reinterpret_cast<float*>(lg_area + q.lane * lg_lane);
-    float* duf_q = d.offload ? duf : dx_nxt + t0 * H;
+    float* duf_q = (Gx.offload ? at<float>(ws, L.dxa) : dx_nxt) + t0 * H;      // (offload = 2: the buffer that layer 0 fills at the end)
     const float* xL = X.in(NL, j, l);
     X.prefetch(NL, j + 1, l);
     TRY(launch_ln_fwd<T>(xL, P + o_lnf, rms ? (const T*)nullptr : P + o_lnf + H, uf + t0 * H, meanf + t0, rstdf + t0, Tr, H, ld.ln_eps, sj, rms));

@@ -113,3 +113,12 @@ def test_host_validation_of_slices_and_shares():
     s_share, w_share = C.cephalo_share_workspace_bytes(d, 4, 2)
     s_mb, w_mb = C.cephalo_layer_workspace_bytes(d, 2)
     assert s_share <= 2 * s_mb and w_share >= w_mb
+
+
+def test_stack_work_area_holds_no_more_than_is_used():
+    """Checkpointing itself needs no memory (the recomputed output is not formed), and a second stream needs a second pool and a second micro-batch of logits only."""
+    layer = C.layer_desc(256, 4, 1024, 64, True, C.BF16)
+    size = lambda layers, checkpoint, interleave: C.cephalo_stack_workspace_bytes(C.StackDesc(layer, layers, 1024, checkpoint, 0, interleave), 8, 2)
+    assert size(1, 1, 0) == size(1, 0, 0) and size(1, 1, 1) == size(1, 0, 1)
+    tokens = 2 * 64
+    assert size(3, 0, 1) - size(3, 0, 0) == tokens * (2 * 256 * 4 + 256 * 2 + 4 * 4 + 1024 * 4)
