@@ -118,6 +118,11 @@ int cephalo_layer_workspace_bytes(const cephalo_layer_desc* desc, int32_t micro_
 int cephalo_share_workspace_bytes(const cephalo_layer_desc* desc, int32_t batch_share, int32_t micro_batch,
                                   size_t* save_bytes_total, size_t* scratch_bytes);
 
+/* How the share calls below run the micro-batches: on how many streams (2 only with two_streams = 1, the interleaved call), and in how
+ * many launches of several micro-batches each on the first of them.  Host pointers out; nothing is launched. */
+int cephalo_share_runs(const cephalo_layer_desc* desc, int32_t batch_share, int32_t micro_batch, int32_t two_streams,
+                       int32_t* streams, int32_t* runs_per_stream);
+
 /* Forward of one layer on one micro-batch of m samples (Sec. 3.2; the step timed as T_f(m)
  * in Sec. 3.3).
  *   flat_param  device, [P] in the compute dtype (fp32, or the bf16 copy of the fp32 master)
@@ -254,6 +259,10 @@ int cephalo_op_linear_wgrad_bias(int32_t dtype, const void* dY, const void* X, i
                                  float* G, float* gb, float scale, int32_t accumulate, void* workspace,
                                  size_t workspace_bytes, void* stream);
 
+/* The tile (rows and columns of C a block) that a bf16 product C [M,N] with both operands k-contiguous takes where `kernels` of them run side by
+ * side.  The result does not depend on it.  Host pointers out; nothing is launched. */
+int cephalo_gemm_rows_tile(int32_t M, int32_t N, int32_t K, int32_t kernels, int32_t* tile_rows, int32_t* tile_columns);
+
 /* Up to four bf16 weight gradients over the same T tokens in one launch, as a layer's backward runs its projections' where
  * that is faster: G[i] [N[i],K[i]] and, where gb[i] is not NULL, gb[i] [N[i]] as in cephalo_op_linear_wgrad_bias.  Every product
  * is one piece.  tile: 0 is 256 x 256, 1 is 256 x 128, 2 is 128 x 128 with four stages, 3 is 128 x 128 with two; G does not depend on
@@ -377,6 +386,9 @@ int cephalo_stack_param_offsets(const cephalo_stack_desc* desc, int64_t* offsets
  * Host pointer out.  Without offload the area begins with the layer-boundary activations, fp32 [layers+1][b*S][H]:
  * entry 0 is the embedding output, entry i the output of layer i-1; they are valid after cephalo_stack_step returns. */
 int cephalo_stack_workspace_bytes(const cephalo_stack_desc* desc, int32_t batch_share, int32_t micro_batch, size_t* bytes);
+
+/* As cephalo_share_runs, for a step of the stack (2 streams only for a desc with interleave = 1). */
+int cephalo_stack_runs(const cephalo_stack_desc* desc, int32_t batch_share, int32_t micro_batch, int32_t* streams, int32_t* runs_per_stream);
 
 /* Where three things lie in that work area once a step has returned, as byte offsets written to host array
  * offsets[3], so that a layer of a full-size stack can be checked on its own (Sec. 3.2's layered order: the backward

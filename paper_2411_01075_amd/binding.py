@@ -96,6 +96,9 @@ SIGNATURES = {
     "cephalo_op_linear_wgrad": (ctypes.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _f32, _i32, _vp, _sz, _vp]),
     "cephalo_op_linear_wgrad_bias_workspace": (_sz, [_i32, _i32, _i32, _i32]),
     "cephalo_op_linear_wgrad_bias": (ctypes.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _f32, _i32, _vp, _sz, _vp]),
+    "cephalo_share_runs": (ctypes.c_int, [_dp, _i32, _i32, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
+    "cephalo_stack_runs": (ctypes.c_int, [ctypes.POINTER(StackDesc), _i32, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
+    "cephalo_gemm_rows_tile": (ctypes.c_int, [_i32, _i32, _i32, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
     "cephalo_wgrad_group_tile": (ctypes.c_int, [_i32, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32), ctypes.POINTER(_i32), ctypes.POINTER(_i32),
                                                 ctypes.POINTER(_i32)]),
     "cephalo_op_linear_wgrad_group_workspace": (_sz, [_i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
@@ -339,6 +342,25 @@ def _ints(values):
 
 def _ptrs(tensors):
     return (_vp * len(tensors))(*[_ptr(t) for t in tensors])
+
+
+def cephalo_share_runs(desc, batch_share, micro_batch, two_streams):
+    """(streams, runs of micro-batches on the first of them)"""
+    a, b = _i32(0), _i32(0)
+    _check(lib().cephalo_share_runs(ctypes.byref(desc), batch_share, micro_batch, int(two_streams), ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
+
+
+def cephalo_stack_runs(sdesc, batch_share, micro_batch):
+    a, b = _i32(0), _i32(0)
+    _check(lib().cephalo_stack_runs(ctypes.byref(sdesc), batch_share, micro_batch, ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
+
+
+def cephalo_gemm_rows_tile(M, N, K, kernels=1):
+    a, b = _i32(0), _i32(0)
+    _check(lib().cephalo_gemm_rows_tile(M, N, K, kernels, ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
 
 
 def cephalo_wgrad_group_tile(T, N, K, bias):

@@ -1140,6 +1140,11 @@ double gemm_rows_us(int M, int N, int K, int kernels) {
   (void)best_tile(M, N, K, kernels, &us);
   return us;
 }
+void gemm_rows_tile(int M, int N, int K, int kernels, int* bm, int* bn) {
+  double us;
+  const TileCost& t = kTiles[best_tile(M, N, K, kernels, &us)];
+  *bm = t.bm; *bn = t.bn;
+}
 
 int gemm_grad_splits_most(int M, int N, int K) {
   const double tiles = (double)((M + 255) / 256) * ((N + 255) / 256);

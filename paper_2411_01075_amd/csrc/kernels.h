@@ -168,6 +168,7 @@ int gemm_grad_splits_most(int M, int N, int K);
 
 // Estimated time in us of a k-contiguous bf16 product (a projection's forward or input gradient) with `kernels` of them side by side.
 double gemm_rows_us(int M, int N, int K, int kernels);
+void gemm_rows_tile(int M, int N, int K, int kernels, int* bm, int* bn);     // and the tile it takes
 
 template <typename T> int launch_gemm_simple(const GemmArgs<T>& a, hipStream_t s);   // (bf16 only)
 int launch_gemm_f32(const GemmArgs<float>& a, hipStream_t s);  // fp32 operands and arithmetic, any strides

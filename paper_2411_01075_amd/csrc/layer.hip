@@ -42,6 +42,17 @@ extern "C" int cephalo_share_workspace_bytes(const cephalo_layer_desc* desc, int
   return CEPHALO_OK;
 }
 
+extern "C" int cephalo_share_runs(const cephalo_layer_desc* desc, int32_t batch_share, int32_t micro_batch, int32_t two_streams,
+                                  int32_t* streams, int32_t* runs_per_stream) {
+  TRY(check_desc(desc));
+  if (micro_batch <= 0 || batch_share <= 0 || batch_share % micro_batch != 0)
+    return fail(CEPHALO_EINVAL, "share_runs: batch share b = %d is not a positive multiple of micro-batch size m = %d", batch_share, micro_batch);
+  if (!streams || !runs_per_stream) return fail(CEPHALO_EINVAL, "share_runs: null output");
+  const Runs r = plan_runs(*desc, micro_batch, batch_share / micro_batch, two_streams != 0, scratch_layout(*desc, micro_batch, batch_share, 2).pool_bytes);
+  *streams = r.lanes; *runs_per_stream = r.n;
+  return CEPHALO_OK;
+}
+
 extern "C" int cephalo_layer_fwd(const cephalo_layer_desc* desc, const void* flat_param,
                                  const void* x, void* y, int32_t micro_batch,
                                  void* save, size_t save_bytes,

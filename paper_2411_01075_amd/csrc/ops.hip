@@ -154,6 +154,13 @@ int group_jobs(const char* who, int count, int T, const int32_t* N, const int32_
 }
 }  // namespace
 
+extern "C" int cephalo_gemm_rows_tile(int32_t M, int32_t N, int32_t K, int32_t kernels, int32_t* tile_rows, int32_t* tile_columns) {
+  if (M <= 0 || N <= 0 || K <= 0 || kernels <= 0) return fail(CEPHALO_EINVAL, "gemm_rows_tile: sizes %d x %d x %d and the number of kernels must be positive", M, N, K);
+  if (!tile_rows || !tile_columns) return fail(CEPHALO_EINVAL, "gemm_rows_tile: null output");
+  gemm_rows_tile(M, N, K, kernels, tile_rows, tile_columns);
+  return CEPHALO_OK;
+}
+
 extern "C" int cephalo_wgrad_group_tile(int32_t count, int32_t T, const int32_t* N, const int32_t* K, const int32_t* bias, int32_t* tile,
                                         int32_t* pieces) {
   GradJob<bf16> jobs[kMaxGradGroup];

@@ -632,6 +632,11 @@ struct Boundary {
   }
 };
 
+// The runs of a stack's micro-batches (the logits' area is free while the layers run backward, and usually the larger pool)
+Runs stack_runs(const cephalo_stack_desc& d, const StackLayout& L, const ScratchLayout& WL, int m, int l) {
+  return plan_runs(d.layer, m, l, d.interleave != 0, d.offload ? 0 : std::max(WL.pool_bytes, L.logits_bytes));
+}
+
 template <typename T>
 int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const int* targets, int b, int m,
               float* G, float scale, float* loss_out, void* ws, float* host_area, hipStream_t s, hipStream_t copy_in, hipStream_t copy_out,
@@ -653,10 +658,9 @@ int run_stack(const cephalo_stack_desc& d, const void* Pv, const int* ids, const
   // matrix-core kernels of the other and GEMMs with few output tiles share the compute units.  A run's whole
   // chain through the layers stays on its stream; the streams meet where the share is handled as one (weight
   // gradients, shared weight transposes, the embeddings), through fork / join events.
-  // (the logits' area is free while the layers run backward, and usually the larger pool)
   Pool pool = {at<char>(scratch, WL.pool), WL.pool_bytes};
   if (L.logits_bytes > pool.bytes) pool = {at<char>(ws, L.logits), L.logits_bytes};
-  const Runs runs = plan_runs(ld, m, l, d.interleave != 0, d.offload ? 0 : pool.bytes);
+  const Runs runs = stack_runs(d, L, WL, m, l);
   if (runs.lanes == 1) side = nullptr;
   const int nst = runs.lanes;
   hipStream_t st[2] = {s, side ? side : s};
@@ -878,6 +882,17 @@ extern "C" int cephalo_stack_workspace_bytes(const cephalo_stack_desc* d, int32_
                 batch_share, micro_batch);
   if (!bytes) return fail(CEPHALO_EINVAL, "stack_workspace_bytes: null output");
   *bytes = stack_layout(*d, batch_share, micro_batch).total;
+  return CEPHALO_OK;
+}
+
+extern "C" int cephalo_stack_runs(const cephalo_stack_desc* d, int32_t batch_share, int32_t micro_batch, int32_t* streams, int32_t* runs_per_stream) {
+  TRY(check_stack(d));
+  if (micro_batch <= 0 || batch_share <= 0 || batch_share % micro_batch != 0)
+    return fail(CEPHALO_EINVAL, "stack_runs: batch share b = %d is not a positive multiple of micro-batch size m = %d", batch_share, micro_batch);
+  if (!streams || !runs_per_stream) return fail(CEPHALO_EINVAL, "stack_runs: null output");
+  const Runs r = stack_runs(*d, stack_layout(*d, batch_share, micro_batch), scratch_layout(d->layer, micro_batch, batch_share, d->interleave ? 2 : 1),
+                            micro_batch, batch_share / micro_batch);
+  *streams = r.lanes; *runs_per_stream = r.n;
   return CEPHALO_OK;
 }
 

@@ -40,6 +40,9 @@ def test_fp32_gemm_edges(M, N, K, pad, layout):
     assert (np.abs(out.double().cpu().numpy() - 2 * ref) <= 3 * bound + 2.0 ** -23 * np.abs(ref)).all()
 
 
+SIDE_BY_SIDE = (1, 2, 3, 5, 8, 16, 40, 128, 256)
+
+
 # rows, columns, contraction: every tile of the k-contiguous products (64 x 64 up to 256 x 256) with ragged edges; a contraction shorter
 # than a slab of 64, of one slab, of an odd number of slabs, and one with a remainder
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (65, 72, 64), (130, 200, 72), (257, 264, 320), (300, 1032, 456), (1000, 1544, 192), (2050, 2056, 136), (1550, 400, 136),
@@ -57,7 +60,7 @@ def test_gemm_tiles_give_the_same_bits(M, N, K):
     first = {}
     before = C.binding.cephalo_gemm_side_by_side(1)
     try:
-        for kernels in (1, 2, 3, 5, 8, 16, 40, 128, 256):
+        for kernels in SIDE_BY_SIDE:
             C.binding.cephalo_gemm_side_by_side(kernels)
             out = torch.full((M, N), float("nan"), device="cuda")
             C.cephalo_op_gemm(C.BF16, X, K, 1, W, K, 1, M, N, K, C.EPI_NONE_F32, C=out)
@@ -80,10 +83,11 @@ def test_gemm_tiles_give_the_same_bits(M, N, K):
     assert (np.abs(first["resid"].double().cpu().numpy() - ref) <= bound + 3 * 2.0 ** -24 * (np.abs(acc) + np.abs(ref) + 4)).all()
 
 
-# with 40 to 256 kernels side by side these take the tile of 256 x 160, whose place in LDS is 192 rows long: one column block whole and one ragged,
+# with so many kernels side by side these take the tile of 256 x 160, whose place in LDS is 192 rows long: one column block whole and one ragged,
 # two, five; one row block, one and a row, three
 @pytest.mark.parametrize("M,N,K", [(256, 160, 264), (257, 304, 520), (700, 312, 264), (500, 808, 520)])
 def test_gemm_tile_of_160_columns(M, N, K):
+    assert (256, 160) in {C.cephalo_gemm_rows_tile(M, N, K, kernels) for kernels in SIDE_BY_SIDE}
     test_gemm_tiles_give_the_same_bits(M, N, K)
 
 

@@ -80,11 +80,11 @@ def test_per_microbatch_calls_match_share_call(case):
 
 
 @pytest.mark.parametrize("case", ["f32_ragged", "f32_noncausal", "bf16_c2_small", "bf16_c3_small", "bf16_vitl", "bf16_vitg"])     # (f32_noncausal, bf16_vitg: a single micro-batch)
-def test_two_micro_batches_in_flight_give_identical_results(case):
-    """The share call with micro-batches alternating between two streams: every micro-batch's kernels and every
-    reduction keep their order, so y, dx and the gradient are bit-identical to the one-stream call (an odd number of
-    micro-batches included).  Twice, the second time over work areas holding the first run's values."""
+def test_interleaved_call_of_small_shares_gives_identical_results(case):
+    """The interleaved call runs shares of this size on the compute stream alone (both streams: test_gpu_runs.py); y, dx and the
+    gradient are bit-identical to the one-stream call.  Twice, the second time over work areas holding the first run's values."""
     cfg = CASES[case]
+    assert C.cephalo_share_runs(C.desc_from_config(cfg), cfg.batch_share, cfg.micro_batch, True)[0] == 1
     tensors = draw_layer_params(cfg, perturbed=True)
     x, dy = draw_activations(cfg)
     a = Hn.gpu_share_step(cfg, tensors, x, dy, grad_scale=0.75)
@@ -150,20 +150,18 @@ def test_device_argument_errors_launch_nothing():
     torch.cuda.synchronize()
 
 
-def test_share_step_replays_from_a_hip_graph():
+@pytest.mark.parametrize("streams,H,A,F,S,m,l", [(1, 256, 4, 1024, 128, 2, 3), (2, 64, 1, 256, 512, 3, 12)], ids=["one_stream", "two_streams"])
+def test_share_step_replays_from_a_hip_graph(streams, H, A, F, S, m, l):
     """The library only enqueues kernels and stream-ordering events on the caller's streams, so a caller may capture a
     step, two-stream form included, into a HIP graph.  Replays (with eager work and synchronisations in between, output
     buffers cleared each time) must reproduce the eager results bit for bit."""
-    cfg = CASES["bf16_c2_small"]
-    desc = C.desc_from_config(cfg)
+    desc, b = C.layer_desc(H, A, F, S, True, C.BF16), m * l
+    assert C.cephalo_share_runs(desc, b, m, True)[0] == streams
     P = C.cephalo_layer_param_count(desc)
-    flat32 = torch.from_numpy(C.flatten_layer_params(desc, draw_layer_params(cfg, perturbed=True))).cuda()
-    flat = torch.empty(P, dtype=torch.bfloat16, device="cuda")
-    C.cephalo_cast_bf16(flat, flat32)
-    x_h, dy_h = draw_activations(cfg)
-    x, dy = torch.from_numpy(x_h).cuda(), torch.from_numpy(dy_h).cuda()
+    g = torch.Generator(device="cuda").manual_seed(9)
+    flat = (torch.randn(P, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    x, dy = (torch.randn(b, S, H, device="cuda", generator=g) for _ in range(2))
     y, dx, G = torch.empty_like(x), torch.empty_like(x), torch.zeros(P, device="cuda")
-    b, m = cfg.batch_share, cfg.micro_batch
     sb, cb = C.cephalo_share_workspace_bytes(desc, b, m)
     save, scratch = torch.empty(sb, dtype=torch.uint8, device="cuda"), torch.empty(cb, dtype=torch.uint8, device="cuda")
     side = torch.cuda.Stream()

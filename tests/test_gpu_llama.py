@@ -92,7 +92,7 @@ def test_llama_is_reproducible():
     a = run_gpu(cfg, params, x, dy, 1.0, True)
     b = run_gpu(cfg, params, x, dy, 1.0, True)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
-    for case in ("bf16_mini", "bf16_d128"):        # two micro-batches in flight on two streams: the same bits
+    for case in ("bf16_mini", "bf16_d128"):        # the interleaved call, on one stream at this size: the same bits
         cfg = CASES[case]
         params = draw_layer_params(cfg, perturbed=True)
         x, dy = draw_activations(cfg)
@@ -194,7 +194,7 @@ def test_llama_stack_checkpointing_offload_and_interleave_are_bit_identical():
     b = run_stack_gpu(cfg, params, ids, tgt, 1.25, checkpoint=True)
     c = run_stack_gpu(cfg, params, ids, tgt, 1.25, checkpoint=True, offload=True)
     assert a[0] == b[0] == c[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[1], c[1])
-    d = run_stack_gpu(cfg, params, ids, tgt, 1.25, interleave=True)              # two micro-batches in flight on two streams
+    d = run_stack_gpu(cfg, params, ids, tgt, 1.25, interleave=True)              # (on one stream at this size)
     e = run_stack_gpu(cfg, params, ids, tgt, 1.25, checkpoint=True, interleave=True)
     assert a[0] == d[0] == e[0] and np.array_equal(a[1], d[1]) and np.array_equal(a[1], e[1])
 

@@ -51,25 +51,28 @@ def test_share_is_its_micro_batches_bit_for_bit(kind, dtype, S, m, l):
     assert float((G - Gm).norm() / Gm.norm()) <= 1e-5
 
 
+@pytest.mark.parametrize("kind,dtype", [("gpt", "bf16"), ("llama", "bf16"), ("gpt", "f32"), ("llama", "f32")])
 @pytest.mark.parametrize("S,m,l", [(512, 3, 12), (509, 3, 11), (512, 2, 9)])             # (more than 16384 tokens: both streams; odd counts; 9216 tokens that the pool does not take at once)
-def test_two_streams_take_a_large_share_to_the_same_bits(S, m, l):
-    print(S, m, l, flush=True)
-    desc = C.layer_desc(64, 1, 256, S, True, C.BF16, 1e-5, C.LAYER_GPT)
+def test_two_streams_take_a_large_share_to_the_same_bits(S, m, l, kind, dtype):
+    print(S, m, l, kind, dtype, flush=True)
+    desc = C.layer_desc(64, 1, 256, S, True, C.F32 if dtype == "f32" else C.BF16, 1e-5, C.LAYER_LLAMA if kind == "llama" else C.LAYER_GPT)
+    assert C.cephalo_share_runs(desc, m * l, m, True)[0] == 2 and C.cephalo_share_runs(desc, m * l, m, False)[0] == 1
     one, two = _share(desc, m * l, m), _share(desc, m * l, m, side=True)
     assert all(torch.equal(a, b) for a, b in zip(one, two))
 
 
-@pytest.mark.parametrize("kind", [C.LAYER_GPT, C.LAYER_LLAMA], ids=["gpt", "llama"])
-@pytest.mark.parametrize("S,m,l,V", [(37, 1, 5, 77), (512, 3, 12, 1031), (64, 2, 4, 30011)])      # (small logits; two streams; one micro-batch of logits at a time)
-def test_stack_forms_agree_bit_for_bit(kind, S, m, l, V):
-    print(kind, S, m, l, V, flush=True)
-    layer = C.layer_desc(64, 2, 256, S, True, C.BF16, 1e-5, kind)
+@pytest.mark.parametrize("kind,dtype", [(C.LAYER_GPT, C.BF16), (C.LAYER_LLAMA, C.BF16), (C.LAYER_GPT, C.F32)], ids=["gpt", "llama", "gpt_f32"])
+@pytest.mark.parametrize("S,m,l,V,streams", [(37, 1, 5, 77, 1), (512, 3, 12, 1031, 2), (64, 2, 4, 30011, 1)])      # (small logits; two streams; one micro-batch of logits at a time)
+def test_stack_forms_agree_bit_for_bit(kind, dtype, S, m, l, V, streams):
+    print(kind, dtype, S, m, l, V, flush=True)
+    layer = C.layer_desc(64, 2, 256, S, True, dtype, 1e-5, kind)
     g = torch.Generator(device="cuda").manual_seed(3)
     ids, tgt = (torch.randint(0, V, (m * l, S), device="cuda", generator=g, dtype=torch.int32) for _ in range(2))
     got = []
     for checkpoint, interleave, mb in ((0, 0, m), (0, 1, m), (1, 0, m), (1, 1, m), (0, 0, m * l)):
         sd = C.StackDesc(layer, 2, V, checkpoint, 0, interleave)
-        flat = _flat(C.cephalo_stack_param_count(sd), C.BF16)
+        assert C.cephalo_stack_runs(sd, m * l, mb)[0] == (streams if interleave else 1)
+        flat = _flat(C.cephalo_stack_param_count(sd), dtype)
         G, loss = torch.full((flat.numel(),), float("nan"), device="cuda"), torch.full((1,), float("nan"), device="cuda")
         ws = _bytes(C.cephalo_stack_workspace_bytes(sd, m * l, mb))
         if interleave:

@@ -209,11 +209,10 @@ def test_boundary_activations_offloaded_to_host_give_identical_results(case):
 
 @pytest.mark.parametrize("case", ["bf16_mini", "bf16_mini_m1", "f32_tiny", "bf16_deep6"])
 @pytest.mark.parametrize("checkpoint", [False, True])
-def test_two_micro_batches_in_flight_give_identical_results(case, checkpoint):
-    """Micro-batches alternating between two streams (the layered order of Sec. 3.2 leaves the micro-batches of a layer
-    independent of each other): each micro-batch's own kernels run in the same order and every reduction keeps its
-    order, so the loss and every gradient element are bit-identical to the one-stream run; so are the layer-boundary
-    activations left in the work area.  Twice, the second time over a work area that holds the first run's values."""
+def test_interleaved_step_of_small_shares_gives_identical_results(case, checkpoint):
+    """The interleaved form of the step, which runs shares of this size on the compute stream alone (both streams: test_gpu_runs.py):
+    the loss and every gradient element are bit-identical to the plain run; so are the layer-boundary activations left in the work area.
+    Twice, the second time over a work area that holds the first run's values."""
     cfg = CASES[case]
     params = draw_stack_params(cfg, perturbed=True)
     ids, tgt = draw_token_ids(cfg)
