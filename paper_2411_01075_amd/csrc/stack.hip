@@ -110,13 +110,18 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
   const int stride = gridDim.x * TEAMS;
   int row = blockIdx.x * TEAMS + __builtin_amdgcn_readfirstlane((int)threadIdx.x / THREADS);
   float a[MAXG][VN];
-  // Rows are read and written through descriptors of one row each: groups past its end come as zeros and are not stored, without a branch.  The whole
-  // offset is in the vector register, the one that the descriptor's range check covers (a scalar offset is added past the check).
-  auto row_of = [&](const void* base, int row, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(base) + (int64_t)row * ld * bytes), 0, ld * bytes, 0x00020000); };
-  auto fetch = [&](int j, __amdgpu_buffer_rsrc_t from) {
+  // A row is read and written through descriptors of what is left of it from the threads' group j on: groups past its end come as zeros and are not
+  // stored, without a branch.  A thread's offset is in the vector register, the one that the descriptor's range check covers (a scalar offset is
+  // added past the check), and the same for every group (with an offset for each the widest form spills two registers).
+  auto rest_of = [&](const void* base, int row, int bytes, int j) {
+    const int at = j * THREADS * VN * bytes;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(base) + (int64_t)row * ld * bytes + at), 0, max(ld * bytes - at, 0), 0x00020000);
+  };
+  auto fetch = [&](int j, int row) {
+    const __amdgpu_buffer_rsrc_t from = rest_of(logits, row, 4, j);
 #pragma unroll
     for (int q = 0; q < VN / 4; ++q) {
-      const f32x4 r = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, t * (VN * 4) + 16 * q + j * (THREADS * VN * 4), 0, 0));
+      const f32x4 r = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, t * (VN * 4) + 16 * q, 0, 0));
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[j][4 * q + i] = r[i];
     }
@@ -159,7 +164,6 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
     }
     if (t == 0) loss[row] = bmx - at_tgt + __logf(sum);
     const float scale = coef / sum;
-    const __amdgpu_buffer_rsrc_t to = row_of(dlogits, row, sizeof(T)), from = row_of(logits, max(next, 0), 4);
 #pragma unroll
     for (int j = 0; j < MAXG; ++j) {
       const int c0 = (t + THREADS * j) * VN, first = (wave * 64 + THREADS * j) * VN;
@@ -180,13 +184,13 @@ cross_entropy_row_kernel(const float* __restrict__ logits, T* __restrict__ dlogi
       for (int i = 0; i < VN; ++i) v[i] = (T)o[i];
       // (after a store with a scalar offset the compiler also lets the next instruction overwrite the data, and now and then the store then wrote
       // the new value)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), to, t * 16 + j * (THREADS * 16), 0, 2);
-      if (next >= 0) fetch(j, from);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), rest_of(dlogits, row, sizeof(T), j), t * 16, 0, 2);
+      if (next >= 0) fetch(j, next);
     }
   };
   if (row >= rows) return;      // (a whole block, or wavefronts of a block that meets no barrier)
 #pragma unroll
-  for (int j = 0; j < MAXG; ++j) fetch(j, row_of(logits, row, 4));
+  for (int j = 0; j < MAXG; ++j) fetch(j, row);
   for (; row + stride < rows; row += stride) finish(row, row + stride);
   finish(row, -1);
 }

@@ -14,7 +14,8 @@ def test_norm_backward_reads_the_statistics_through_the_scalar_unit(form):
         assert not [i for i in code if i.split()[0] in ("global_load_dword", "flat_load_dword", "buffer_load_dword")], name
 
 
-@pytest.mark.parametrize("kernel", ["attn_dq_kernelILi", "attn_fwd8_kernelILi", "attn_fwd_kernelILi", "ln_bwd_kernel", "gemm_mfma_kernel", "gemm_ring_kernel", "grad_group_kernel"])
+@pytest.mark.parametrize("kernel", ["attn_dq_kernelILi", "attn_fwd8_kernelILi", "attn_fwd_kernelILi", "attn_dkv_narrow_kernelILi", "attn_bwd_small_kernelILi", "attn_f32_bwd_kernelILi", "cross_entropy_row_kernelI",
+                                    "ln_bwd_kernel", "gemm_mfma_kernel", "gemm_ring_kernel", "grad_group_kernel"])
 def test_no_register_is_spilled(kernel):
     for name, k in kernel_code.kernels(kernel).items():
         assert k[".vgpr_spill_count"] == 0, (name, k[".vgpr_spill_count"])
