@@ -160,7 +160,9 @@ template <int D> struct FragAddr {
   static constexpr unsigned TILE_BYTES = TL::ELEMS * 2, STAGE = 2 * TILE_BYTES;
   unsigned r[D / 16], lo[D / 32], hi[D / 32];
   __device__ __forceinline__ explicit FragAddr(const lds_bf16* first) {
-    const unsigned base = (unsigned)(uintptr_t)first;         // (a multiple of 2 * STAGE: the XORs change no other bits)
+    // The XORs need a multiple of 2 * STAGE.  The tiles are the first of the dynamic LDS, which begins at 0 as long as the kernel has no static LDS: a test
+    // of the compiled kernels sees to that.
+    const unsigned base = (unsigned)(uintptr_t)first;
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));                       // (formed here, not kept from pass to pass)
     const int g = lane >> 4, i = lane & 15, row = 4 * (g >> 1) + (i >> 2);

@@ -28,3 +28,10 @@ def test_no_buffer_access_has_a_scalar_offset():
             words = i.replace(",", " ").split()
             if words[0].startswith("buffer_") and "offen" in words:
                 assert words[words.index("offen") - 1] == "0", (name, i)
+
+
+@pytest.mark.parametrize("kernel", ["attn_fwd_kernelILi", "attn_dq_kernelILi", "attn_dkv_narrow_kernelILi", "attn_bwd_small_kernelILi"])
+def test_staged_tiles_begin_at_the_start_of_lds(kernel):
+    """These kernels turn from one buffer to the other by an XOR of the address, so their dynamic LDS has to begin at 0: no static LDS before it."""
+    for name, k in kernel_code.kernels(kernel).items():
+        assert k[".group_segment_fixed_size"] == 0, name
