@@ -303,8 +303,8 @@ template <int D> constexpr int kDkvWaves = D == 32 ? 3 : 2;
 // 15.5; backward 157 -> 104, 8 x 512, 16 of 64 54.7 -> 44.5, 16 x 197, 16 of 64 35.9 -> 29.0, 8 x 257, 16 of 104 60.1 -> 49.3, 2048, 80 of 32, causal 142 ->
 // 112, 4 x 2048, 16 of 128, causal 286 -> 269 (dK / dV of 128, bound by LDS reads, did not gain by it and keeps its form).
 
-// The sums of the two halves of a sample's keys, each relative to its own maximum, brought to a common one.  (Written out, so that it is rounded alike
-// wherever it stands.)
+// The sums of the two halves of a sample's keys, each relative to its own maximum, brought to a common one: rounded as the compiler rounds it in the
+// eight-wavefront kernel (where, written like this, it would spill two registers); a test compares the bits of the two.
 __device__ __forceinline__ float merged(float first, float a0, float second, float a1) { return __builtin_fmaf(first, a0, second * a1); }
 
 // ------------------------------------------------------------------------------------ forward

@@ -339,7 +339,9 @@ Work<T> work_at(void* base, const ScratchLayout& W, const cephalo_layer_desc& d,
 // micro-batches: 500 us side by side, 689 in turns, 490 in one run on one stream).  So the side stream is used for shares of more than 16384 tokens (24
 // layers of width 2048, 6 micro-batches of 4096: 192.7 ms against 196.0 on one stream) and where the pool does not take the share in one run (6 of
 // 2048 tokens, width 768: 937 us against 1040); below that the two are within 5 % of each other, and small shares lose to the events alone (4 x 128
-// tokens of width 256: 135 us, 105 without).
+// tokens of width 256: 135 us, 105 without).  The line knows tokens only; what it may cost is small: 15 shares of 8192 to 24576 tokens, widths 512 to 4096, take
+// between 0.70 of the time of single micro-batches on two streams that do overlap (16 x 512 tokens of width 512: 677 -> 477 us) and 1.002 of it (16384
+// tokens of width 2048: 5069 -> 5081).
 struct Run { int first, count, lane; };       // micro-batches [first, first + count), on stream `lane`
 struct Runs {
   int lanes, per_lane[2], n;                  // micro-batches and runs of a stream (the second's may be one run fewer)

@@ -62,7 +62,7 @@ def gpu_share_step(cfg, tensors, x, dy, grad_scale=1.0, via_share_call=True, int
         save_b, scr_b = C.cephalo_share_workspace_bytes(desc, b, m)
         save = torch.empty(save_b, dtype=torch.uint8, device="cuda")
         scratch = torch.empty(scr_b, dtype=torch.uint8, device="cuda")
-        if interleave:      # two micro-batches in flight on two streams; the call joins them into the current stream
+        if interleave:      # with a second stream; the call joins it into the current one
             C.cephalo_share_layer_step_interleaved(desc, flat, xd, yd, dyd, dxd, b, m, save, G, grad_scale, scratch, torch.cuda.Stream())
             torch.cuda.current_stream().synchronize()
         else:

@@ -110,7 +110,7 @@ def over_tol(e):
 
 @pytest.mark.parametrize("interleave", [True, False], ids=["two_streams", "one_stream"])
 def test_c5_stack_full_size_layer_by_layer(interleave):
-    """The whole c5 step at full size, in the form bench.py times (two micro-batches in flight) and in the one-stream
+    """The whole c5 step at full size, in the form bench.py times (on two streams) and in the one-stream
     form.  The oracle cannot run 24 layers x 12 samples in a test, so layers are checked on their own against it:
     forward: the GPU's input of layer i (a layer-boundary activation kept at the head of the workspace) goes through
     the oracle's layer and is compared with the GPU's input of layer i+1, for one sample of three layers;
@@ -204,7 +204,7 @@ OWN_SIZE = {"c2": {}, "c3": {}, "c4": dict(n_micro=1), "c5_layer": dict(layers=1
 def test_workload_at_its_own_size_against_oracle_and_rounded_chain(name):
     """c2 (H 1024, S 512, 4 x 2 samples, non-causal), c3 (H 1600, 25 heads, S 1024, 3 x 2), c4 (H 4096, S 2048, one
     micro-batch of 1) and one layer of c5 (H 2048, S 2048, one micro-batch of 2): the whole share through the share call
-    in the form bench.py times (two micro-batches in flight where there are two), every output and every gradient
+    in the form bench.py times (with a second stream where there are two micro-batches), every output and every gradient
     tensor, at the stated tolerance with nothing scaled.
     Two references.  (i) The oracle: parameters rounded to bf16, then fp64 with no further rounding.  (ii) The control
     of tests/rounded_chain.py: the same formulas with the bf16 mode's stored tensors rounded where they are stored.
